@@ -1055,49 +1055,30 @@ __device__ __forceinline__ void signsum_tile(const double *__restrict__ X, int i
 // tstart[b] = first tile of problem b; problem b has ceil(mj / 64) x
 // ceil(m / 64) tiles with mj = ncand when cand is given (problem 0 only),
 // else m.  DZ[pair_off + j m + k] = (D_jk, Zr_jk).
-// split > 1 (one problem, a candidate list): block g sums tile g / split over
-// the rows of part g % split into part[(g % split) ncand m + jj m + k] (jj
-// the candidate's index); k_signsum_parts adds the parts.
+// split > 1: block g sums tile g / split over the rows of part g % split
+// (whole LDS stages) into part[(g % split) per + e], e the pair's place in DZ
+// (with a candidate list jj m + k, jj the candidate's index);
+// k_zero_segments adds the parts in order and writes DZ.
+// One block takes about 2 us per 16-row stage when it has a CU to itself
+// (load latency and the FP64 matrix rate), so a matrix of few columns, whose
+// tiles leave most of the CUs idle, is bound by the length of its row loop:
+// 1003 x 517 (81 tiles) 123 us, 20011 x 151 (9 tiles) 2344 us in one part.
 __global__ void __launch_bounds__(256)
 k_signsum_batch(const ProbDesc *__restrict__ P, const int *__restrict__ tstart, int B,
                 const int *__restrict__ cand, int ncand, double2 *__restrict__ DZ,
-                const int *__restrict__ gate, int gate_on, int split, double2 *__restrict__ part) {
+                const int *__restrict__ gate, int gate_on, int split, double2 *__restrict__ part, long long per) {
   if (gate && *gate != gate_on) return;
-  if (split > 1) {
-    const ProbDesc d = P[0];
-    const int tile = blockIdx.x / split, sp = blockIdx.x % split;
-    const int tk_count = (d.m + SS_TILE - 1) / SS_TILE;
-    const int rows = (d.n + split - 1) / split;
-    const int ilo = min(d.n, sp * rows), ihi = min(d.n, ilo + rows);
-    signsum_tile(d.X, ilo, ihi, d.m, d.ld, cand, ncand, (tile / tk_count) * SS_TILE, (tile % tk_count) * SS_TILE,
-                 part + (long long)sp * ncand * d.m, true);
-    return;
-  }
-  const int g = blockIdx.x;
+  const int g = blockIdx.x / split, sp = blockIdx.x % split;
   const int b = find_owner(tstart, B, g);
   const ProbDesc d = P[b];
   const int mj = cand ? ncand : d.m;
   const int tk_count = (d.m + SS_TILE - 1) / SS_TILE;
   const int tloc = g - tstart[b];
-  signsum_tile(d.X, 0, d.n, d.m, d.ld, cand, mj, (tloc / tk_count) * SS_TILE, (tloc % tk_count) * SS_TILE,
-               DZ + d.pair_off, false);
-}
-
-// DZ[cand[jj] m + k] = the parts' sums added in part order (one problem)
-__global__ void __launch_bounds__(256)
-k_signsum_parts(const double2 *__restrict__ part, int split, const int *__restrict__ cand, int ncand, int m,
-                double2 *__restrict__ DZ, const int *__restrict__ gate, int gate_on) {
-  if (gate && *gate != gate_on) return;
-  const long long per = (long long)ncand * m;
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < per; e += (long long)gridDim.x * blockDim.x) {
-    double2 acc = part[e];
-    for (int sp = 1; sp < split; ++sp) {
-      const double2 x = part[(long long)sp * per + e];
-      acc.x = acc.x + x.x;
-      acc.y = acc.y + x.y;
-    }
-    DZ[(long long)cand[e / m] * m + e % m] = acc;
-  }
+  const int rows = ((d.n + split - 1) / split + SS_ROWS - 1) / SS_ROWS * SS_ROWS;
+  const int ilo = min(d.n, sp * rows), ihi = min(d.n, ilo + rows);
+  double2 *out = split > 1 ? part + sp * per + (cand ? 0 : d.pair_off) : DZ + d.pair_off;
+  signsum_tile(d.X, ilo, ihi, d.m, d.ld, cand, mj, (tloc / tk_count) * SS_TILE, (tloc % tk_count) * SS_TILE, out,
+               split > 1);
 }
 
 // ---------------------------------------------------------------- segments
@@ -1371,9 +1352,10 @@ __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInf
 __global__ void __launch_bounds__(256)
 k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, int total_words,
                 const double *__restrict__ lam_all, const ColInfo *__restrict__ ci,
-                const double2 *__restrict__ DZ, double *__restrict__ V, double *__restrict__ E,
+                double2 *__restrict__ DZ, double *__restrict__ V, double *__restrict__ E,
                 int *__restrict__ R, unsigned long long *__restrict__ mask, const int *__restrict__ cand,
-                const int *__restrict__ gate, int gate_on) {
+                const int *__restrict__ gate, int gate_on, int split, const double2 *__restrict__ part,
+                long long per) {
   const int w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (w >= total_words) return;
   if (gate && *gate != gate_on) return;
@@ -1385,9 +1367,22 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
   const int j = cand ? cand[jj] : jj;
   bool skip = false;
   if (k < d.m && k != j) {
+    const long long pair = d.pair_off + (long long)j * d.m + k;
+    double2 dz;
+    if (split > 1) {
+      const double2 *pp = part + (cand ? (long long)jj * d.m + k : pair);
+      dz = pp[0];
+      for (int sp = 1; sp < split; ++sp) {
+        const double2 x = pp[sp * per];
+        dz.x = dz.x + x.x;
+        dz.y = dz.y + x.y;
+      }
+      DZ[pair] = dz;
+    } else {
+      dz = DZ[pair];
+    }
     const ColInfo cj = ci[d.col_off + j], ck = ci[d.col_off + k];
     if (!cj.flags && !ck.flags) {
-      const double2 dz = DZ[d.pair_off + (long long)j * d.m + k];
       const bool unc = sign_sums_unsure(cj, ck, dz);
       const double *lam = lam_all + d.lam_off;
       skip = true;

@@ -298,7 +298,8 @@ static int check_problem(const l1line_problem &p) {
 //   data: ColInfo, segflags, V, E, R, Z, zflag
 struct BatchLayout {
   int B, nitems, ksplit, nmax, Lmax;
-  int ss_split, ss_ncand, ss_m;   // sign sums of a candidate list: row parts, candidates, m
+  int ss_split;               // row parts of the sign sums
+  long long ss_per;           // pairs per part
   int xstart[SEG_XCDS + 1];   // explicit items: XCD x owns [xstart[x], xstart[x + 1])
   long long total_cols, total_z, total_out, total_ws, total_lam, total_pairs, total_tiles, total_words;
   size_t o_desc, o_colstart, o_zstart, o_ostart, o_tstart, o_wstart, o_lam, o_items, o_counter, o_xstart,
@@ -323,7 +324,7 @@ static void layout_sizes(BatchLayout &Ly) {
   Ly.o_ci = take(sizeof(ColInfo) * Ly.total_cols);
   Ly.o_segflags = take(sizeof(int) * Ly.total_cols);
   Ly.o_DZ = take(2 * sizeof(double) * Ly.total_pairs);
-  Ly.o_DZp = take(Ly.ss_split > 1 ? 2 * sizeof(double) * Ly.ss_split * (size_t)Ly.ss_ncand * Ly.ss_m : 0);
+  Ly.o_DZp = take(Ly.ss_split > 1 ? 2 * sizeof(double) * Ly.ss_split * (size_t)Ly.ss_per : 0);
   Ly.o_mask = take(sizeof(unsigned long long) * Ly.total_words);
   Ly.o_V = take(sizeof(double) * Ly.total_ws);
   Ly.o_E = take(sizeof(double) * Ly.total_ws);
@@ -375,9 +376,10 @@ struct BatchPtrs {
 };
 
 // Sizes, work items and workspace layout of a batch call (no allocation for
-// B == 1: its items are implicit).
+// B == 1: its items are implicit).  max_bytes: the workspace the caller has.
 static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, const TuneParams &tp,
-                      const RunOpts &ro, BatchLayout &Ly, std::vector<WorkItem> &items) {
+                      const RunOpts &ro, BatchLayout &Ly, std::vector<WorkItem> &items,
+                      size_t max_bytes = ~(size_t)0) {
   memset(&Ly, 0, sizeof Ly);
   Ly.B = (int)B;
   Ly.nmax = 1;
@@ -463,18 +465,22 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
     Ly.ksplit = 0;
     Ly.nitems = (int)items.size();
   }
-  // a candidate list leaves few sign-sum tiles (32 columns j: one row of
-  // tiles): their rows are cut into parts, summed apart and then added, so
-  // that every compute unit gets work (parts of at least 512 rows)
-  if (B == 1 && ro.cand) {
-    const long long want = 2ll * ctx->num_cu;
-    long long sp = std::min<long long>(16, (want + Ly.total_tiles - 1) / std::max(1ll, Ly.total_tiles));
-    sp = std::min<long long>(sp, std::max<long long>(1, probs[0].n / 512));
-    Ly.ss_split = (int)std::max<long long>(1, sp);
-    Ly.ss_ncand = ro.ncand;
-    Ly.ss_m = (int)probs[0].m;
-  }
+  // few sign-sum tiles (a narrow matrix, a candidate list): their rows are cut
+  // into parts, summed apart and then added, so that every compute unit gets
+  // two workgroups; parts of at least 64 rows (four LDS stages), at most 32 of
+  // them (each costs 16 bytes per pair written and read again).  From 2 tiles
+  // per CU on one part is the faster form.  Never past the caller's limit on
+  // the workspace.
+  const long long want = 2ll * ctx->num_cu;
+  long long sp = (want + Ly.total_tiles - 1) / std::max(1ll, Ly.total_tiles);
+  sp = std::min<long long>({sp, 32, Ly.nmax / 64});
+  Ly.ss_split = (int)std::max<long long>(1, sp);
+  Ly.ss_per = (B == 1 && ro.cand) ? (long long)ro.ncand * probs[0].m : Ly.total_pairs;
   layout_sizes(Ly);
+  while (Ly.bytes > max_bytes && Ly.ss_split > 1) {
+    Ly.ss_split /= 2;
+    layout_sizes(Ly);
+  }
   return L1LINE_OK;
 }
 
@@ -564,7 +570,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   int *dsegflags = (int *)(d + Ly.o_segflags);
   double *dV = (double *)(d + Ly.o_V), *dE = (double *)(d + Ly.o_E), *dZ = (double *)(d + Ly.o_Z);
   int *dR = (int *)(d + Ly.o_R), *dzflag = (int *)(d + Ly.o_zflag);
-  double2 *dDZ = (double2 *)(d + Ly.o_DZ);
+  double2 *dDZ = (double2 *)(d + Ly.o_DZ), *dDZp = (double2 *)(d + Ly.o_DZp);
   unsigned long long *dmask = (unsigned long long *)(d + Ly.o_mask);
   if (outp) *outp = BatchPtrs{dV, dR, dci};
   l1line_ctx pc = prof ? ctx : nullptr;
@@ -617,21 +623,16 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   }
   {
     ProfScope ps(pc, ls, "signsum");
-    const int split = Ly.ss_split > 1 ? Ly.ss_split : 1;
-    double2 *dDZp = (double2 *)(d + Ly.o_DZp);
-    hipLaunchKernelGGL(k_signsum_batch, dim3((unsigned)(Ly.total_tiles * split)), dim3(256), 0, ls, dP, dtile,
-                       (int)B, (B == 1) ? ro.cand : nullptr, ro.ncand, dDZ, ro.gate, ro.gate_on, split, dDZp);
-    if (split > 1)
-      hipLaunchKernelGGL(k_signsum_parts,
-                         dim3((unsigned)std::min<long long>(1024, ((long long)Ly.ss_ncand * Ly.ss_m + 255) / 256)),
-                         dim3(256), 0, ls, (const double2 *)dDZp, split, ro.cand, Ly.ss_ncand, Ly.ss_m, dDZ, ro.gate,
-                         ro.gate_on);
+    hipLaunchKernelGGL(k_signsum_batch, dim3((unsigned)(Ly.total_tiles * Ly.ss_split)), dim3(256), 0, ls, dP, dtile,
+                       (int)B, (B == 1) ? ro.cand : nullptr, ro.ncand, dDZ, ro.gate, ro.gate_on, Ly.ss_split, dDZp,
+                       Ly.ss_per);
   }
   {
     ProfScope ps(pc, ls, "zero_seg");
     hipLaunchKernelGGL(k_zero_segments, dim3((unsigned)((Ly.total_words + 3) / 4)), dim3(256), 0, ls, dP, dwst,
                        (int)B, (int)Ly.total_words, dlam, dci, dDZ, dV, dE, dR, dmask,
-                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on);
+                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, Ly.ss_split, (const double2 *)dDZp,
+                       Ly.ss_per);
   }
   if (t0) HIP_TRY(hipEventRecord(t0, ls));
   {
@@ -1133,7 +1134,7 @@ static int fit_noalloc_impl(l1line_ctx ctx, const double *X, int64_t n, int64_t 
   BatchLayout Ly;
   std::vector<WorkItem> items;        // stays empty: one problem's items are implicit
   const TuneParams tp = tune_for(ctx, &p, 1);
-  st = plan_batch(ctx, &p, 1, tp, kNoOpts, Ly, items);
+  st = plan_batch(ctx, &p, 1, tp, kNoOpts, Ly, items, NOALLOC_BYTES);
   if (st) return st;
   if (Ly.bytes > NOALLOC_BYTES || !items.empty()) return L1LINE_ESIZE;
   const MetaCursor c0 = {0, 0, 0, 0, 0, 0, 0, 0};

@@ -1,0 +1,87 @@
+"""GPU parity, bit for bit, at the sizes where a launch changes its shape or a
+kernel its branch: edges of tiles and row slots, remainders, the smallest and
+largest of a range.  The reference is the CPU oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2402_16712_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2402_16712_amd import binding as B
+    c = B.Context(0)
+    yield c
+    c.close()
+
+
+def _host(out):
+    import torch
+    torch.cuda.synchronize()
+    return {k: (v.cpu().numpy() if v is not None else None) for k, v in out.items()}
+
+
+def _fit_equal(g, r, tag):
+    assert int(g["status"][0]) == 0, (tag, g["status"])
+    assert int(g["j"][0]) == r["j"], tag
+    assert g["v"].tobytes() == r["v"].tobytes(), (tag, np.argwhere(g["v"] != r["v"])[:5])
+    assert np.array_equal(g["row"], r["row"]), tag
+    assert g["z_all"].tobytes() == r["z_all"].tobytes(), tag
+
+
+def _path_equal(g, r, tag):
+    assert int(g["status"][0]) == 0, (tag, g["status"])
+    assert np.array_equal(g["J"], r["J"]), tag
+    assert g["V"].tobytes() == r["V"].tobytes(), (tag, np.argwhere(g["V"] != r["V"])[:5])
+    assert np.array_equal(g["ROW"], r["ROW"]), tag
+    assert g["ZALL"].tobytes() == r["ZALL"].tobytes(), tag
+
+
+def _data(seed, n, m, kind):
+    if kind == "counts":
+        return wl.random_small(seed, n, m, integer=True, zero_frac=0.3, span=4)
+    if kind == "dense":
+        return wl.accuracy_matrix(n, m, seed)[0]
+    return wl.rank_one_matrix(n, m, max(1, m // 10), n // 10, 20.0, 0.01, (11, seed, n, m))
+
+
+# row parts of the sign sums: one part, a last part of one row, an empty last
+# part, the most parts, more than one tile each way
+@pytest.mark.parametrize("n,m", [(63, 5), (129, 30), (1040, 64), (2049, 65), (2311, 7), (1025, 130)])
+@pytest.mark.parametrize("kind", ["sparse", "counts"])
+def test_sign_sum_row_parts(ctx, n, m, kind):
+    from paper_2402_16712_amd import binding as B
+    print(f"case parts {n}x{m} {kind}", flush=True)
+    sys.stdout.flush()
+    X = _data(n, n, m, kind)
+    big = wl.max_column_mass(X)
+    Xd = B.device_matrix(X)
+    _fit_equal(_host(ctx.fit(Xd, 0.05 * big)), O.fit(X, 0.05 * big), (n, m, kind))
+    lams = np.array([0.0, 0.01 * big, 0.3 * big])
+    r = O.fit_path(X, lams)
+    _path_equal(_host(ctx.fit_path(Xd, lams)), r, (n, m, kind))
+    # a batch whose other problem is shorter than one part
+    Y = _data(n + 1, 17, 9, kind)
+    got = ctx.fit_batch([(Xd, lams), (B.device_matrix(Y), lams)])
+    _path_equal(_host(got[0]), r, (n, m, kind, "batch"))
+    _path_equal(_host(got[1]), O.fit_path(Y, lams), (n, m, kind, "batch"))
+
+
+# the no-alloc workspace leaves room for all, some and none of the row parts
+@pytest.mark.parametrize("m", [200, 700, 960])
+def test_noalloc_row_parts(ctx, m):
+    from paper_2402_16712_amd import binding as B
+    print(f"case noalloc {m}", flush=True)
+    X = _data(m, 700, m, "sparse")
+    Xd, lam = B.device_matrix(X), 0.05 * wl.max_column_mass(X)
+    a, b = _host(ctx.fit_noalloc(Xd, lam)), _host(ctx.fit(Xd, lam))
+    for key in a:
+        assert a[key].tobytes() == b[key].tobytes(), (m, key)
