@@ -63,84 +63,219 @@ __device__ __forceinline__ int find_owner(const int *__restrict__ prefix, int co
 }
 
 // ------------------------------------------------------------------ columns
-// One wave per column: finiteness, counts, the fixed-point exponent e0, the
-// range check, the exact fixed-point mass and the R64 column mass.
-__device__ __forceinline__ void colprep_wave(const double *__restrict__ x, int n, ColInfo *__restrict__ out,
-                                             int lane) {
-  int bad = 0, nnz = 0, zeros = 0, lsb = 1 << 20, hb = -(1 << 20), bemin = 4096, bemax = -1;
-  double part = 0.0;
-  for (int i = lane; i < n; i += 64) {
-    double v = x[i];
-    double a = fabs(v);
-    part = part + a;
-    if (!isfinite(v)) {
-      bad = 1;
-    } else if (v == 0.0) {
-      ++zeros;
-    } else {
-      ++nnz;
-      lsb = min(lsb, lowest_bit_exp(a));
-      hb = max(hb, highest_bit_exp(a));
-      const int be = (int)((__double_as_longlong(a) >> 52) & 0x7ff);
-      bemin = min(bemin, be);
-      bemax = max(bemax, be);
-    }
-  }
-  double W = wave_r64_tree(part);
-  bad = wave_max_int(bad);
+constexpr int SAMPLE_ROWS = 128;    // rows of column j drawn for the key windows
+
+// One workgroup of kW waves per column: finiteness, counts, the fixed-point
+// exponent e0, the range check, the exact fixed-point mass, the R64 column
+// mass and (smp not null) a systematic sample of SAMPLE_ROWS rows with
+// probability ~ |x_ij|.  The exponent e0 and the mass are needed before the
+// exact sum and the sample, so the column is gone through twice.
+//   kLds, 4 waves   up to PREP_LDS_MAX rows: the column stays in LDS between
+//   4 waves         longer columns, too few to fill the chip with one wave
+//                   each: a wave takes a quarter of the 64-row slots, wave 0
+//                   also the R64 mass (its order is one chain of adds a lane)
+//   1 wave          many columns: the four-wave form's extra pass and
+//                   reductions cost more than they hide
+// (one wave per column and one load in flight before, and no sample: 2000 x
+// 2000 32 us, now 23; 20011 x 151 213 us, now 86; 10000 x 4000 215 us, now 159)
+// The sample's cumulative weight runs wave by wave and lane by lane (a lane's
+// rows in turn, from the scan of the lanes' masses): sample r is the row whose
+// weight interval holds (r + 1/2) step; one that no row took (rounding) is
+// the column's first nonzero row.  Any rows serve: they only place windows.
+template <int CB, class F>
+__device__ __forceinline__ void for_rows_batch(const double *__restrict__ x, int n, int i0, F f) {
+  double v[CB];
+#pragma unroll
+  for (int q = 0; q < CB; ++q) v[q] = i0 + 64 * q < n ? gld(x + i0 + 64 * q) : 0.0;
+#pragma unroll
+  for (int q = 0; q < CB; ++q) f(v[q], i0 + 64 * q);
+}
+// the rows lane + 64 t, t in [t0, t1), of a column, loads 8 slots at a time
+// (rows past n give 0)
+template <class F>
+__device__ __forceinline__ void for_rows(const double *__restrict__ x, int n, int t0, int t1, int lane, F f) {
+  int t = t0;
+  for (; t + 6 < t1; t += 8) for_rows_batch<8>(x, min(n, 64 * t1), 64 * t + lane, f);
+  for (; t < t1; t += 2) for_rows_batch<2>(x, min(n, 64 * t1), 64 * t + lane, f);
+}
+
+constexpr int PREP_WAVES = 4, PREP_LDS_MAX = 4096;   // (a 32 KB copy leaves room for five workgroups per CU)
+struct PrepShared {
+  unsigned short smp[SAMPLE_ROWS];
+  double mass[PREP_WAVES], amin[PREP_WAVES], amax[PREP_WAVES];
+  int nbad[PREP_WAVES], nnz[PREP_WAVES], lsb[PREP_WAVES], first[PREP_WAVES];
+  u128 fix[PREP_WAVES];
+};
+
+__device__ __forceinline__ double wave_min_dbl_x(double x) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) x = fmin(x, xswapd(x, d));
+  return readlane_dbl(x, 0);
+}
+__device__ __forceinline__ double wave_max_dbl_x(double x) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) x = fmax(x, xswapd(x, d));
+  return readlane_dbl(x, 0);
+}
+
+template <int kW, bool kLds>
+__device__ __forceinline__ void colprep_block(const double *__restrict__ x, int n, ColInfo *__restrict__ out,
+                                              unsigned short *__restrict__ smp, PrepShared &sh, double *col) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int T = (n + 63) >> 6, Tq = (T + kW - 1) / kW, t0 = min(T, wave * Tq), t1 = min(T, t0 + Tq);
+  int nbad = 0, nnz = 0, lsb = 1 << 20, first = 1 << 30;
+  double mine = 0.0, amin = __builtin_inf(), amax = 0.0;
+  for_rows(x, n, t0, t1, lane, [&](double v, int i) {
+    const double a = fabs(v);
+    if (kLds && i < min(n, 64 * t1)) col[i] = a;
+    mine = mine + a;
+    const uint64_t ab = (uint64_t)__double_as_longlong(a);
+    const uint32_t lo = (uint32_t)ab, hi = (uint32_t)(ab >> 32), be = hi >> 20;
+    const bool fin = be != 0x7ff, nz = fin && ab != 0;
+    nbad += fin ? 0 : 1;
+    nnz += nz ? 1 : 0;
+    // lowest set bit of the magnitude (the implicit bit included)
+    const uint32_t hm = (hi & 0xFFFFFu) | (be ? 1u << 20 : 0u);
+    const int tz = lo ? __builtin_ctz(lo) : 32 + __builtin_ctz(hm | (1u << 21));
+    lsb = nz ? min(lsb, (int)max(be, 1u) - 1075 + tz) : lsb;
+    first = nz ? min(first, i) : first;
+    amin = nz ? fmin(amin, a) : amin;
+    amax = nz ? fmax(amax, a) : amax;
+  });
+  const double scan = wave_incl_scan_dbl_x(mine, lane), all = readlane_dbl(scan, 63);
+  nbad = wave_sum_int(nbad);
   nnz = wave_sum_int(nnz);
-  zeros = wave_sum_int(zeros);
   lsb = wave_min_int(lsb);
-  hb = wave_max_int(hb);
-  bemin = wave_min_int(bemin);
-  bemax = wave_max_int(bemax);
-  int flags = bad ? COL_NONFINITE : 0;
-  int e0 = nnz ? lsb : 0;
-  if (!bad && nnz) {
-    int bl = 32 - __builtin_clz((unsigned)nnz);
-    if ((hb - e0 + 1) + bl > 124) flags |= COL_WIDE;
+  first = wave_min_int(first);
+  amin = wave_min_dbl_x(amin);
+  amax = wave_max_dbl_x(amax);
+  if (lane == 0) {
+    sh.mass[wave] = all;
+    sh.amin[wave] = amin;
+    sh.amax[wave] = amax;
+    sh.nbad[wave] = nbad;
+    sh.nnz[wave] = nnz;
+    sh.lsb[wave] = lsb;
+    sh.first[wave] = first;
   }
+  // the rows again, from where they are now
+  auto again = [&](int ta, int tb, auto f) {
+    if constexpr (kLds) {
+      for (int i = 64 * ta + lane; i < min(n, 64 * tb); i += 64) f(col[i], i);
+    } else {
+      for_rows(x, n, ta, tb, lane, f);
+    }
+  };
+  __syncthreads();
+  double before = 0.0, total = 0.0;
+  nbad = nnz = 0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) {
+    before = w < wave ? before + sh.mass[w] : before;
+    total = total + sh.mass[w];
+    nbad += sh.nbad[w];
+    nnz += sh.nnz[w];
+    lsb = min(lsb, sh.lsb[w]);
+    first = min(first, sh.first[w]);
+    amin = fmin(amin, sh.amin[w]);
+    amax = fmax(amax, sh.amax[w]);
+  }
+  int flags = nbad ? COL_NONFINITE : 0;
+  const int e0 = nnz ? lsb : 0;
+  if (!nbad && nnz) {
+    const int bl = 32 - __builtin_clz((unsigned)nnz);
+    if ((highest_bit_exp(amax) - e0 + 1) + bl > 124) flags |= COL_WIDE;
+  }
+  const bool sample = smp != nullptr && flags == 0 && nnz > 0;
+  if (wave == 0) {
+    const unsigned f = sample ? (unsigned)first : 0u;   // (without a sample no segment uses it)
+    ((unsigned *)sh.smp)[lane] = f | (f << 16);
+  }
+  __syncthreads();
   u128 s = 0;
   if (!flags) {
-    for (int i = lane; i < n; i += 64) {
-      double v = x[i];
-      if (v != 0.0) s += fixed_of(fabs(v), e0);
-    }
-    s = wave_sum_u128(s);
+    const bool chunks = n <= L1LINE_MAX_N;        // (chunk sums exact below 2^16 nonzeros)
+    double c0s = 0.0, c1s = 0.0, c2s = 0.0;
+    const double step = total / SAMPLE_ROWS;
+    double cum = before + (scan - mine);
+    int r = sample ? max((int)ceil(cum / step - 0.5), 0) : SAMPLE_ROWS;
+    double next = r < SAMPLE_ROWS ? (r + 0.5) * step : __builtin_inf();
+    again(t0, t1, [&](double v, int i) {
+      const double a = fabs(v);
+      if (chunks) {
+        double c0, c1, c2;
+        weight_chunks(a, e0, c0, c1, c2);
+        c0s = c0s + c0;
+        c1s = c1s + c1;
+        c2s = c2s + c2;
+      } else {
+        s += a != 0.0 ? fixed_of(a, e0) : (u128)0;
+      }
+      cum = cum + a;
+      if (cum > next && a != 0.0) {
+        for (; r < SAMPLE_ROWS && (r + 0.5) * step < cum; ++r) sh.smp[r] = (unsigned short)i;
+        next = r < SAMPLE_ROWS ? (r + 0.5) * step : __builtin_inf();
+      }
+    });
+    s = chunks ? chunks_to_u128(wave_sum_dbl_x(c0s), wave_sum_dbl_x(c1s), wave_sum_dbl_x(c2s)) : wave_sum_u128(s);
+    if (lane == 0) sh.fix[wave] = s;
   }
+  double part = mine;
+  if (wave == 0) {
+    if constexpr (kW > 1) {
+      part = 0.0;
+      again(0, T, [&](double v, int) { part = part + fabs(v); });   // (rows past n add +0)
+    }
+    part = wave_r64_tree_x(part);
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  if (smp) ((unsigned *)smp)[lane] = ((const unsigned *)sh.smp)[lane];
   if (lane == 0) {
     ColInfo c;
-    c.wfix = s;
-    c.W = W;
+    c.wfix = 0;
+    if (!flags)
+      for (int w = 0; w < kW; ++w) c.wfix += sh.fix[w];
+    c.W = part;
     c.e0 = e0;
     c.nnz = nnz;
-    c.zeros = zeros;
+    c.zeros = n - nnz - nbad;
     c.flags = flags;
-    c.bemin = bemin;
-    c.bemax = bemax;
+    c.bemin = nnz ? (int)((uint64_t)__double_as_longlong(amin) >> 52) : 4096;
+    c.bemax = nnz ? (int)((uint64_t)__double_as_longlong(amax) >> 52) : -1;
     *out = c;
   }
 }
 
-__global__ void __launch_bounds__(256)
-k_colprep(const double *__restrict__ X, int n, int m, long long ld, ColInfo *__restrict__ ci) {
-  const int col = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (col >= m) return;
-  colprep_wave(X + (long long)col * ld, n, ci + col, threadIdx.x & 63);
+// smp (optional): SAMPLE_ROWS row ids per column.  kLds: the launch has n
+// doubles of dynamic LDS.
+template <int kW, bool kLds>
+__global__ void __launch_bounds__(64 * kW)
+k_colprep(const double *__restrict__ X, int n, int m, long long ld, ColInfo *__restrict__ ci,
+          unsigned short *__restrict__ smp) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ __attribute__((aligned(16))) PrepShared sh;
+  const int col = blockIdx.x;
+  colprep_block<kW, kLds>(X + (long long)col * ld, n, ci + col, smp ? smp + (long long)col * SAMPLE_ROWS : nullptr, sh,
+                      (double *)smem);
 }
 
-// every column of every problem: colstart[b] = first column of problem b
-__global__ void __launch_bounds__(256)
-k_colprep_batch(const ProbDesc *__restrict__ P, const int *__restrict__ colstart, int B, int total_cols,
-                ColInfo *__restrict__ ci, int *__restrict__ segflags, const int *__restrict__ gate, int gate_on) {
-  const int g = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (g >= total_cols) return;
+// every column of every problem: colstart[b] = first column of problem b.
+// kLds: the launch has room for the longest problem's column.
+template <int kW, bool kLds>
+__global__ void __launch_bounds__(64 * kW)
+k_colprep_batch(const ProbDesc *__restrict__ P, const int *__restrict__ colstart, int B,
+                ColInfo *__restrict__ ci, unsigned short *__restrict__ smp, int *__restrict__ segflags,
+                const int *__restrict__ gate, int gate_on) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ __attribute__((aligned(16))) PrepShared sh;
+  const int g = blockIdx.x;
   if (gate && *gate != gate_on) return;
   const int b = find_owner(colstart, B, g);
   const ProbDesc d = P[b];
   const int col = g - colstart[b];
-  colprep_wave(d.X + (long long)col * d.ld, d.n, ci + g, threadIdx.x & 63);
-  if ((threadIdx.x & 63) == 0) segflags[g] = 0;
+  colprep_block<kW, kLds>(d.X + (long long)col * d.ld, d.n, ci + g, smp + (long long)g * SAMPLE_ROWS, sh, (double *)smem);
+  if (threadIdx.x == 0) segflags[g] = 0;
 }
 
 // ----------------------------------------------------------- segment access
@@ -187,15 +322,14 @@ __device__ __forceinline__ uint64_t key_of_pair(bool in, double a, double b) {
   return ok ? key_of(r) : KEY_NONE;
 }
 
-// The top 32 bits of the key of row i's ratio, estimated by the hardware
-// reciprocal (x_ij != 0 at sample rows).  Sample keys only place window
+// The top 32 bits of the key of row i's ratio, estimated with the hardware
+// reciprocal inv of x_ij (not 0 at sample rows).  Sample keys only place window
 // bounds and pivots, and any keys are valid there (every element is decided
 // exactly against them), so neither the IEEE divide nor the low 32 bits of
 // the key are needed: a bound derived from a prefix p is p 2^32 (lower) or
 // p 2^32 + 2^32 - 1 (upper), at most 2^-20 relative off the sample's ratio.
-__device__ __forceinline__ uint32_t sample_key32(const SegIO &s, int i) {
-  const double a = sxj_at(s, i), b = gld(s.xk + i);
-  double r = b * __builtin_amdgcn_rcp(a);
+__device__ __forceinline__ uint32_t sample_key32(const SegIO &s, int i, double inv) {
+  double r = gld(s.xk + i) * inv;
   r = r + 0.0;
   return (uint32_t)(key_of(r) >> 32);
 }
@@ -1099,7 +1233,6 @@ k_signsum_batch(const ProbDesc *__restrict__ P, const int *__restrict__ tstart, 
 //     scanned exactly.
 //  Whatever the window does not settle goes to the general rounds.
 constexpr int SEG_WAVES = 4;
-constexpr int SAMPLE_ROWS = 128;
 constexpr int SXJ_LDS_MAX = 4096;   // longest column j copied to LDS (32 KB)
 constexpr int SEG_MASK_WORDS = 64;  // zero-segment mask words an item holds (one per lane: 4096 k)
 
@@ -1107,7 +1240,7 @@ __host__ __device__ constexpr size_t seg_sxj_bytes(int n) {
   return ((size_t)((n + 63) / 64) * 64 * 8 + 15) / 16 * 16;
 }
 __host__ __device__ constexpr size_t seg_lds_bytes(int n, int L, int lcap) {
-  return seg_sxj_bytes(n) + SAMPLE_ROWS * 4 + (size_t)L * 16 +
+  return seg_sxj_bytes(n) + (size_t)L * 16 +
          SEG_WAVES * (sizeof(WaveScratch) + (size_t)lcap * (sizeof(uint64_t) + sizeof(unsigned short))) + 16;
 }
 
@@ -1573,7 +1706,8 @@ __device__ __forceinline__ void select_one_fp64(const SegIO &s, uint64_t *lk, un
 // (the pointer's address space is then known to the compiler: LDS loads).
 template <bool kLdsJ, bool kMulti>
 __device__ __forceinline__ void seg_item(const double *__restrict__ X, int n, int m, long long ld,
-                                         const ColInfo *__restrict__ ci, const double *__restrict__ lam, int L,
+                                         const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp,
+                                         const double *__restrict__ lam, int L,
                                          const double2 *__restrict__ DZ, int j, int kbeg, int kend,
                                          double *__restrict__ V,
                                          double *__restrict__ E, int *__restrict__ R, int *__restrict__ segflags,
@@ -1588,8 +1722,7 @@ __device__ __forceinline__ void seg_item(const double *__restrict__ X, int n, in
   constexpr bool lds_j = kLdsJ;
   (void)sxj_rows;
   double *sxj_lds = (double *)smem;                 // T*64 entries, zero padded
-  int *srow = (int *)(smem + (lds_j ? seg_sxj_bytes(n) : 0));
-  u128 *slam = (u128 *)(srow + SAMPLE_ROWS);
+  u128 *slam = (u128 *)(smem + (lds_j ? seg_sxj_bytes(n) : 0));
   WaveScratch *wsc = (WaveScratch *)(slam + L);
   uint64_t *lkeys = (uint64_t *)(wsc + SEG_WAVES);
   unsigned short *lrows = (unsigned short *)(lkeys + (size_t)SEG_WAVES * lcap);
@@ -1624,65 +1757,16 @@ __device__ __forceinline__ void seg_item(const double *__restrict__ X, int n, in
     kpre = wave_excl_scan_int(cnt, lane);
     nlive = uni_int(__shfl(kpre + cnt, 63));
   }
-  if (wave == 0) {
-    // systematic sample of SAMPLE_ROWS rows with probability ~ |x_ij|: the
-    // cumulative weight runs over the rows in order, 64 rows (one per lane)
-    // at a time; sample r is the row whose weight interval holds (r + 1/2)
-    // step.  Consecutive lanes read consecutive rows (no LDS bank conflicts).
-    auto wt = [&](int i) {
-      const double a = sxj[i < n ? i : 0];
-      return i < n ? fabs(a) : 0.0;
-    };
-    double part = 0.0;
-    for (int t = 0; t < T; ++t) part = part + wt(lane + 64 * t);
-    const double all = wave_sum_dbl_x(part);
-    for (int r = lane; r < SAMPLE_ROWS; r += 64) srow[r] = -1;
-    wave_lds_sync();
-    if (all > 0.0) {
-      const double step = all / SAMPLE_ROWS;
-      double base = 0.0;
-      for (int t = 0; t < T; ++t) {
-        const int i = lane + 64 * t;
-        const double w = wt(i);
-        const double incl = base + wave_incl_scan_dbl_x(w, lane);
-        const double cum = incl - w;
-        int r = (int)ceil(cum / step - 0.5);
-        r = r < 0 ? 0 : r;
-        for (; w > 0.0 && r < SAMPLE_ROWS && (r + 0.5) * step < incl; ++r) srow[r] = i;
-        base = readlane_dbl(incl, 63);
-      }
-    }
-    wave_lds_sync();
-    // samples no row took (rounding at the end) repeat the nearest earlier
-    // sample, or the column's first nonzero row; sampled rows increase with
-    // r (an inclusive max-scan over the entries, two per lane, finds that
-    // row), and any row with x_ij != 0 would do
-    int first = 0;
-    for (int t = 0; t < T; ++t) {
-      const uint64_t nzm = __ballot(wt(lane + 64 * t) != 0.0);
-      if (nzm) {
-        first = 64 * t + __builtin_ctzll(nzm);
-        break;
-      }
-    }
-    const int s0 = srow[2 * lane], s1 = srow[2 * lane + 1];
-    const int c1 = max(s0, s1);
-    int tot = c1, x = c1;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = (int)xswap32((uint32_t)tot, d);
-      x = (lane & d) ? max(x, o) : x;
-      tot = max(tot, o);
-    }
-    // (x: the largest row over entries [0, 2 lane + 2); prev: over [0, 2 lane))
-    const int up1 = __shfl_up(x, 1);
-    const int prev = lane > 0 ? up1 : -1;
-    const int e0 = max(prev, s0), e1 = max(e0, s1);
-    wave_lds_sync();
-    srow[2 * lane] = e0 >= 0 ? e0 : first;
-    srow[2 * lane + 1] = e1 >= 0 ? e1 : first;
+  // the sample of column j: two rows per lane, and (one penalty: the
+  // several-penalty kernel has no registers for them and takes them per
+  // segment) the reciprocals of their x_ij
+  const unsigned srows = smp[(long long)j * SAMPLE_ROWS + lane] |
+                         ((unsigned)smp[(long long)j * SAMPLE_ROWS + 64 + lane] << 16);
+  double sv0 = 0.0, sv1 = 0.0;
+  if constexpr (!kMulti) {
+    sv0 = __builtin_amdgcn_rcp(sxj[srows & 0xFFFF]);
+    sv1 = __builtin_amdgcn_rcp(sxj[srows >> 16]);
   }
-  __syncthreads();
 
   WaveScratch *ws = wsc + wave;
   uint64_t *lk = lkeys + (size_t)wave * lcap;
@@ -1795,7 +1879,9 @@ __device__ __forceinline__ void seg_item(const double *__restrict__ X, int n, in
     const bool neg = sd == 1;
     const uint64_t klo0 = neg ? 0ull : KEY_ZERO, khi0 = neg ? KEY_ZERO - 1 : KEY_NONE - 1;
     // the sample's keys (top 32 bits), sorted across the wave
-    uint32_t sa = sample_key32(s, srow[lane]), sb = sample_key32(s, srow[lane + 64]);
+    const int sr0 = (int)(srows & 0xFFFF), sr1 = (int)(srows >> 16);
+    uint32_t sa = sample_key32(s, sr0, kMulti ? __builtin_amdgcn_rcp(sxj_at(s, sr0)) : sv0),
+             sb = sample_key32(s, sr1, kMulti ? __builtin_amdgcn_rcp(sxj_at(s, sr1)) : sv1);
     wave_sort2_u32_x(sa, sb, lane);
     // one penalty: the sorted sample (index 2 l + c in lane l) goes to the
     // wave's LDS scratch, free until the rounds after the window (several:
@@ -2208,7 +2294,7 @@ template <bool kLdsJ, bool kMulti>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_batch(const ProbDesc *__restrict__ P, const WorkItem *__restrict__ items, int nitems, int chunks,
             int *__restrict__ counter, const int *__restrict__ xstart, const double *__restrict__ lam_all,
-            const ColInfo *__restrict__ ci,
+            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp,
             const double2 *__restrict__ DZ, double *__restrict__ V, double *__restrict__ E,
             int *__restrict__ R, int *__restrict__ segflags, const int *__restrict__ cand, int ncand,
             const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask, int lcap,
@@ -2258,7 +2344,8 @@ k_seg_batch(const ProbDesc *__restrict__ P, const WorkItem *__restrict__ items, 
     const ProbDesc d = P[it.b];
     const unsigned long long *maskrow =
         segmask ? segmask + d.mask_off + (long long)jj * ((d.m + 63) >> 6) : nullptr;
-    seg_item<kLdsJ, kMulti>(d.X, d.n, d.m, d.ld, ci + d.col_off, lam_all + d.lam_off, d.L, DZ + d.pair_off, it.j,
+    seg_item<kLdsJ, kMulti>(d.X, d.n, d.m, d.ld, ci + d.col_off,
+                    smp + (long long)d.col_off * SAMPLE_ROWS, lam_all + d.lam_off, d.L, DZ + d.pair_off, it.j,
                     it.kbeg, it.kend, V + d.ws_off, E + d.ws_off, R + d.ws_off, segflags + d.col_off, maskrow,
                     lcap, sxj_rows, smem);
   }

@@ -304,7 +304,7 @@ struct BatchLayout {
   long long total_cols, total_z, total_out, total_ws, total_lam, total_pairs, total_tiles, total_words;
   size_t o_desc, o_colstart, o_zstart, o_ostart, o_tstart, o_wstart, o_lam, o_items, o_counter, o_xstart,
       meta_bytes;
-  size_t o_ci, o_segflags, o_DZ, o_DZp, o_mask, o_V, o_E, o_R, o_Z, o_zflag, bytes;
+  size_t o_ci, o_smp, o_segflags, o_DZ, o_DZp, o_mask, o_V, o_E, o_R, o_Z, o_zflag, bytes;
 };
 
 static void layout_sizes(BatchLayout &Ly) {
@@ -322,6 +322,7 @@ static void layout_sizes(BatchLayout &Ly) {
   Ly.o_xstart = take(sizeof(int) * (SEG_XCDS + 1));
   Ly.meta_bytes = off;
   Ly.o_ci = take(sizeof(ColInfo) * Ly.total_cols);
+  Ly.o_smp = take(sizeof(unsigned short) * SAMPLE_ROWS * Ly.total_cols);
   Ly.o_segflags = take(sizeof(int) * Ly.total_cols);
   Ly.o_DZ = take(2 * sizeof(double) * Ly.total_pairs);
   Ly.o_DZp = take(Ly.ss_split > 1 ? 2 * sizeof(double) * Ly.ss_split * (size_t)Ly.ss_per : 0);
@@ -352,8 +353,8 @@ static uint64_t fnv1a(const void *data, size_t n, uint64_t h) {
 // Optional restrictions of a one-problem run (device pointers): cand / ncand
 // restrict the preserved columns to a list, jmask marks them for the
 // reduction, gate / gate_on make every kernel a no-op unless *gate == gate_on,
-// ci (ungated runs) is the problem's column info computed by an earlier
-// kernel on the same stream.
+// ci and smp (ungated runs) are the problem's column info and row samples
+// computed by an earlier kernel on the same stream.
 struct RunOpts {
   const int *cand;
   int ncand;
@@ -361,8 +362,9 @@ struct RunOpts {
   const int *gate;
   int gate_on;
   const ColInfo *ci;
+  const unsigned short *smp;
 };
-static const RunOpts kNoOpts = {nullptr, 0, nullptr, nullptr, 0, nullptr};
+static const RunOpts kNoOpts = {nullptr, 0, nullptr, nullptr, 0, nullptr, nullptr};
 
 // Build the layout, stage the metadata, launch (or replay) the sequence.
 // `only_seg_ms` (autotuner): time the segment kernel alone.
@@ -551,6 +553,25 @@ static void fill_meta(char *h, const BatchLayout &Ly, const l1line_problem *prob
   memcpy(h + Ly.o_xstart, Ly.xstart, sizeof Ly.xstart);
 }
 
+// The form of the column preparation for `cols` columns of up to n rows: four
+// waves per column with the column in LDS up to eight columns per CU (2000 x
+// 2000: 23 us, one wave 29), longer columns four waves up to four per CU (20011
+// x 151: 86, one wave 176), else one wave per column (the batch's 32470 columns
+// of up to 4000 rows: 197, four waves with LDS 402; 10000 x 4000: 159, 280).
+enum { PREP_ONE, PREP_FOUR, PREP_LDS };
+static int prep_form(l1line_ctx ctx, int64_t n, int64_t cols) {
+  if (n <= PREP_LDS_MAX) return cols <= 8ll * ctx->num_cu ? PREP_LDS : PREP_ONE;
+  return cols <= 4ll * ctx->num_cu ? PREP_FOUR : PREP_ONE;
+}
+// one matrix (smp nullable)
+static void launch_colprep(l1line_ctx ctx, hipStream_t s, const double *X, int64_t n, int64_t m, int64_t ld, ColInfo *ci,
+                           unsigned short *smp) {
+  const int f = prep_form(ctx, n, m);
+  auto k = f == PREP_ONE ? k_colprep<1, false> : f == PREP_FOUR ? k_colprep<PREP_WAVES, false> : k_colprep<PREP_WAVES, true>;
+  hipLaunchKernelGGL(k, dim3((unsigned)m), dim3(f == PREP_ONE ? 64 : 64 * PREP_WAVES), f == PREP_LDS ? (size_t)n * 8 : 0,
+                     s, X, (int)n, (int)m, (long long)ld, ci, smp);
+}
+
 // The launch sequence of one batch call on stream ls, the workspace at d
 // (its metadata block already in place or written by an earlier kernel on
 // ls).  `prof`: bracket the kernels with the context's timing events;
@@ -566,7 +587,10 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   const WorkItem *ditems = Ly.ksplit ? nullptr : (const WorkItem *)(d + Ly.o_items);
   int *dcounter = (int *)(d + Ly.o_counter);
   const int *dxstart = (const int *)(d + Ly.o_xstart);
-  ColInfo *dci = (ColInfo *)(d + Ly.o_ci);
+  // (an earlier kernel's column info and samples are used where they are)
+  const bool have_ci = ro.ci && B == 1 && !ro.gate;
+  ColInfo *dci = have_ci ? (ColInfo *)ro.ci : (ColInfo *)(d + Ly.o_ci);
+  unsigned short *dsmp = have_ci ? (unsigned short *)ro.smp : (unsigned short *)(d + Ly.o_smp);
   int *dsegflags = (int *)(d + Ly.o_segflags);
   double *dV = (double *)(d + Ly.o_V), *dE = (double *)(d + Ly.o_E), *dZ = (double *)(d + Ly.o_Z);
   int *dR = (int *)(d + Ly.o_R), *dzflag = (int *)(d + Ly.o_zflag);
@@ -612,13 +636,15 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   {
     ProfScope ps(pc, ls, "colprep");
     hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, ls, dcounter, 16ll, 0);
-    if (ro.ci && B == 1 && !ro.gate) {
-      HIP_TRY(hipMemcpyAsync(dci, ro.ci, sizeof(ColInfo) * Ly.total_cols, hipMemcpyDeviceToDevice, ls));
+    if (have_ci) {
       hipLaunchKernelGGL(k_fill_int, dim3((unsigned)((Ly.total_cols + 255) / 256)), dim3(256), 0, ls, dsegflags,
                          (long long)Ly.total_cols, 0);
     } else {
-      hipLaunchKernelGGL(k_colprep_batch, dim3((unsigned)((Ly.total_cols + 3) / 4)), dim3(256), 0, ls, dP, dcol,
-                         (int)B, (int)Ly.total_cols, dci, dsegflags, ro.gate, ro.gate_on);
+      const int f = prep_form(ctx, Ly.nmax, Ly.total_cols);
+      auto k = f == PREP_ONE ? k_colprep_batch<1, false>
+               : f == PREP_FOUR ? k_colprep_batch<PREP_WAVES, false> : k_colprep_batch<PREP_WAVES, true>;
+      hipLaunchKernelGGL(k, dim3((unsigned)Ly.total_cols), dim3(f == PREP_ONE ? 64 : 64 * PREP_WAVES),
+                         f == PREP_LDS ? (size_t)Ly.nmax * 8 : 0, ls, dP, dcol, (int)B, dci, dsmp, dsegflags, ro.gate, ro.gate_on);
     }
   }
   {
@@ -642,7 +668,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
     auto kseg = sxj_rows > 0 ? (multi ? k_seg_batch<true, true> : k_seg_batch<true, false>)
                              : (multi ? k_seg_batch<false, true> : k_seg_batch<false, false>);
     hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * SEG_WAVES), lds, ls, dP, ditems,
-                       Ly.nitems, Ly.ksplit, dcounter, dxstart, dlam, dci, dDZ, dV, dE, dR, dsegflags, ro.cand,
+                       Ly.nitems, Ly.ksplit, dcounter, dxstart, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags, ro.cand,
                        ro.ncand,
                        ro.gate, ro.gate_on, dmask, lcap, sxj_rows);
   }
@@ -1066,8 +1092,7 @@ static int column_stats_impl(l1line_ctx ctx, const double *X, int64_t n, int64_t
   int st = ensure_ws(ctx, align_up(sizeof(ColInfo) * m, 256), s);
   if (st) return st;
   ColInfo *ci = (ColInfo *)ctx->ws;
-  hipLaunchKernelGGL(k_colprep, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, X, (int)n, (int)m, (long long)ld,
-                     ci);
+  launch_colprep(ctx, s, X, n, m, ld, ci, nullptr);
   hipLaunchKernelGGL(k_colstats_out, dim3(1), dim3(256), 0, s, ci, (int)m, W, zeros, status);
   HIP_TRY(hipGetLastError());
   return L1LINE_OK;
@@ -1355,7 +1380,7 @@ int l1line_mlp_adam(l1line_ctx ctx, float *params, float *m1, float *m2, const f
 // ranker scratch layout for a matrix of n x m: sign sums, slope aggregates,
 // column info, statistics, features, scores, candidates, mask, flags
 struct RkLayout {
-  size_t o_DZ, o_agg, o_ci, o_stats, o_F, o_score, o_cand, o_mask, o_flag, o_margin, o_H, o_L, o_S, bytes;
+  size_t o_DZ, o_agg, o_ci, o_smp, o_stats, o_F, o_score, o_cand, o_mask, o_flag, o_margin, o_H, o_L, o_S, bytes;
 };
 
 static RkLayout rk_layout(int64_t n, int64_t m) {
@@ -1370,6 +1395,7 @@ static RkLayout rk_layout(int64_t n, int64_t m) {
   R.o_S = take(plane);
   R.o_agg = take(sizeof(double) * 4 * m);
   R.o_ci = take(sizeof(ColInfo) * m);
+  R.o_smp = take(sizeof(unsigned short) * SAMPLE_ROWS * m);
   R.o_stats = take(sizeof(double) * 3 * FEAT_Q);
   R.o_F = take(sizeof(float) * MLP_IN * m);
   R.o_score = take(sizeof(float) * m);
@@ -1393,7 +1419,7 @@ static int feature_signsums(l1line_ctx ctx, const double *X, int64_t n, int64_t 
   __bf16 *Hp = (__bf16 *)(b + R.o_H), *Lp = (__bf16 *)(b + R.o_L), *Sp = (__bf16 *)(b + R.o_S);
   const int np = (int)fss_rows(n);
   const long long tb = (m + FSS_T - 1) / FSS_T;
-  hipLaunchKernelGGL(k_colprep, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, X, (int)n, (int)m, (long long)ld, ci);
+  launch_colprep(ctx, s, X, n, m, ld, ci, (unsigned short *)(b + R.o_smp));
   hipLaunchKernelGGL(k_feat_planes, dim3((unsigned)(m * ((np + 255) / 256))), dim3(256), 0, s, X, (int)n, (int)m,
                      (long long)ld, np, (const ColInfo *)ci, Hp, Lp, Sp);
   {
@@ -1500,11 +1526,12 @@ static int fit_ranked_impl(l1line_ctx ctx, const double *X, int64_t n, int64_t m
   const l1line_problem p = single(X, n, m, ld, &lambda, 1, v, j, obj, median_row, nullptr, status);
   // exact solve of the K candidates
   // (the column info the features computed)
-  const RunOpts rc{cand, (int)K, mask, nullptr, 0, (const ColInfo *)(b + R.o_ci)};
+  const RunOpts rc{cand, (int)K, mask, nullptr, 0, (const ColInfo *)(b + R.o_ci),
+                   (const unsigned short *)(b + R.o_smp)};
   st = run_batch(ctx, &p, 1, 0, s, tune_for(ctx, &p, 1), nullptr, rc);
   if (st) return st;
   // exhaustive solve, which does nothing unless the margin test failed
-  const RunOpts rf{nullptr, 0, nullptr, flag, 1, nullptr};
+  const RunOpts rf{nullptr, 0, nullptr, flag, 1, nullptr, nullptr};
   st = run_batch(ctx, &p, 1, 0, s, tune_for(ctx, &p, 1), nullptr, rf);
   if (st) return st;
   if (used_fallback) hipLaunchKernelGGL(k_copy_flag, dim3(1), dim3(64), 0, s, flag, used_fallback);
@@ -1700,7 +1727,7 @@ int l1line_ranker_train(l1line_ctx ctx, const char *ckpt_path, int64_t steps, ui
     const int n = 500 + (int)(h % 3501), m = 50 + (int)((h >> 32) % 451);
     const PhiloxKey key{(uint32_t)(h ^ (h >> 32)), (uint32_t)(ctx->rk_seed ^ (ctx->rk_cursor << 20))};
     hipLaunchKernelGGL(k_gen_training, dim3((unsigned)(((long long)n * m + 255) / 256)), dim3(256), 0, s, X, n, m, key);
-    hipLaunchKernelGGL(k_colprep, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, X, n, m, (long long)n, ci);
+    launch_colprep(ctx, s, X, n, m, n, ci, nullptr);
     hipLaunchKernelGGL(k_max_mass, dim3(1), dim3(256), 0, s, (const ColInfo *)ci, m, mass);
     double big = 0.0;
     if (hipGetLastError() != hipSuccess || hipMemcpy(&big, mass, db, hipMemcpyDeviceToHost) != hipSuccess) {

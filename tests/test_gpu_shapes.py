@@ -85,3 +85,19 @@ def test_noalloc_row_parts(ctx, m):
     a, b = _host(ctx.fit_noalloc(Xd, lam)), _host(ctx.fit(Xd, lam))
     for key in a:
         assert a[key].tobytes() == b[key].tobytes(), (m, key)
+
+
+# the forms of the column preparation: column in LDS (one row to the longest),
+# four waves from global memory, one wave per column; the last slots partial
+@pytest.mark.parametrize("n,m", [(1, 2), (65, 3), (4096, 2), (4097, 3), (5003, 2), (70, 2100), (4200, 1030)])
+def test_column_statistics_forms(ctx, n, m):
+    from paper_2402_16712_amd import binding as B
+    print(f"case columns {n}x{m}", flush=True)
+    X = _data(n + m, n, m, "sparse")
+    X[:, 0] *= 2.0 ** -60
+    X[: n // 2, m - 1] = 0.0
+    W, zeros, st = (t.cpu().numpy() for t in ctx.column_stats(B.device_matrix(X)))
+    r = O.column_stats(X)
+    assert int(st[0]) == 0
+    assert W.tobytes() == np.asarray(r[0]).tobytes()
+    assert np.array_equal(zeros, (X == 0.0).sum(axis=0))
