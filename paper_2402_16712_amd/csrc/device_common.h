@@ -372,12 +372,26 @@ __device__ __forceinline__ double wave_sum_dbl_x(double x) {
   return __longlong_as_double((long long)uni_u64((uint64_t)__double_as_longlong(x)));
 }
 
-// R64 tree (p[l] = p[l] + p[l + d] for d = 32..1, the result in lane 0): for
-// l < d the partner l ^ d is l + d, so lane 0 adds the same values in the
-// same order as wave_r64_tree.
+// R64 tree (p[l] = p[l] + p[l + d] for d = 32..1, the result in lane 0): at
+// level d the lanes below d need lane l + d, so one swap or row shift per word
+// does (the other lanes' sums are not used).
+__device__ __forceinline__ uint32_t xdown32(uint32_t x, int d) {
+  const int v = (int)x;
+  switch (d) {
+    case 1: return (uint32_t)__builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+    case 2: return (uint32_t)__builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+    case 4: return (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0xF, false);  // row_shl:4
+    case 8: return (uint32_t)__builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, false);  // row_ror:8
+    case 16: return __builtin_amdgcn_permlane16_swap(x, x, false, false)[1];
+    default: return __builtin_amdgcn_permlane32_swap(x, x, false, false)[1];
+  }
+}
 __device__ __forceinline__ double wave_r64_tree_x(double p) {
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) p = p + xswapd(p, d);
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint64_t b = (uint64_t)__double_as_longlong(p);
+    p = p + __longlong_as_double((long long)(((uint64_t)xdown32((uint32_t)(b >> 32), d) << 32) | xdown32((uint32_t)b, d)));
+  }
   return p;
 }
 
@@ -450,4 +464,63 @@ __device__ __forceinline__ void wave_sort_key_row_x(uint64_t &key, int &row, int
       row = take ? orow : row;
     }
   }
+}
+
+// ------------------------------------------------------- DPP scans and sums
+// Inclusive scans over the 64 lanes in row shifts (1, 2, 4, 8 within a row of
+// 16 lanes) and the two row broadcasts: lanes without a source add 0.  Every
+// lane must be active; lane 63 holds the total.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp0(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRowMask, 0xF, true);
+}
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ double dpp0d(double x) {
+  const uint64_t b = (uint64_t)__double_as_longlong(x);
+  return __longlong_as_double((long long)(((uint64_t)dpp0<kCtrl, kRowMask>((uint32_t)(b >> 32)) << 32) |
+                                          dpp0<kCtrl, kRowMask>((uint32_t)b)));
+}
+__device__ __forceinline__ int wave_scan_int(int x) {
+  x += (int)dpp0<0x111, 0xF>((uint32_t)x);
+  x += (int)dpp0<0x112, 0xF>((uint32_t)x);
+  x += (int)dpp0<0x114, 0xF>((uint32_t)x);
+  x += (int)dpp0<0x118, 0xF>((uint32_t)x);
+  x += (int)dpp0<0x142, 0xA>((uint32_t)x);
+  x += (int)dpp0<0x143, 0xC>((uint32_t)x);
+  return x;
+}
+// (each result takes at most six rounded adds)
+__device__ __forceinline__ double wave_scan_dbl(double x) {
+  x = x + dpp0d<0x111, 0xF>(x);
+  x = x + dpp0d<0x112, 0xF>(x);
+  x = x + dpp0d<0x114, 0xF>(x);
+  x = x + dpp0d<0x118, 0xF>(x);
+  x = x + dpp0d<0x142, 0xA>(x);
+  x = x + dpp0d<0x143, 0xC>(x);
+  return x;
+}
+__device__ __forceinline__ double wave_total_dbl(double x) { return readlane_dbl(wave_scan_dbl(x), 63); }
+
+// minimum and maximum of an int over the wave (uniform results)
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int dpp_or(int none, int x) {
+  return __builtin_amdgcn_update_dpp(none, x, kCtrl, kRowMask, 0xF, false);
+}
+__device__ __forceinline__ int wave_min_int_x(int x) {
+  constexpr int NONE = 0x7fffffff;
+  x = min(x, dpp_or<0x111, 0xF>(NONE, x));
+  x = min(x, dpp_or<0x112, 0xF>(NONE, x));
+  x = min(x, dpp_or<0x114, 0xF>(NONE, x));
+  x = min(x, dpp_or<0x118, 0xF>(NONE, x));
+  x = min(x, dpp_or<0x142, 0xA>(NONE, x));
+  x = min(x, dpp_or<0x143, 0xC>(NONE, x));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ int wave_max_int_x(int x) { return -wave_min_int_x(-x); }
+
+__device__ __forceinline__ uint32_t hi32(double x) { return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32); }
+// a, its sign flipped where d's sign bit is set
+__device__ __forceinline__ double flip_sign(double a, double d) {
+  const uint64_t b = (uint64_t)__double_as_longlong(a);
+  return __longlong_as_double((long long)(((uint64_t)((uint32_t)(b >> 32) ^ (hi32(d) & 0x80000000u)) << 32) | (uint32_t)b));
 }

@@ -348,11 +348,9 @@ __device__ __forceinline__ void take_sample(bool c, int pri, uint64_t key, int t
   bt = better ? t : bt;
 }
 
-// Per-wave LDS area: the elements (key, row) that fall in the key window of
-// the exact pass, and a 64-entry compaction buffer.
-// Per-wave LDS: the <= 64 final candidates of the selection rounds, and the
-// window list (keys and rows, capacity chosen per launch: WIN_CAP for single
-// penalties, PATH_CAP for paths when the LDS allows).
+// Per-wave LDS of the exact kernel: the <= 64 final candidates of the
+// selection rounds, and the window list (keys and rows; WIN_CAP for single
+// penalties, PATH_CAP for several).
 constexpr int WIN_CAP = 512;
 constexpr int PATH_CAP = 1024;
 // (the LDS sort pads a list to the next power of two, which must stay
@@ -369,11 +367,9 @@ struct WaveScratch {
   int bcnt, steps;
 };
 
-// Element sources of the exact selection: every row of the column (ratio
-// recomputed), or the window list in LDS.  Slot t of lane l is element
-// l + 64 t; both enumerate their elements in increasing row order.
-// sbase / cbase: weight and count of the elements below every listed one
-// (the selection's sums and counts are over all elements of the segment).
+// Element source of the exact selection: every row of the column, the ratio
+// recomputed.  Slot t of lane l is element l + 64 t (increasing row order).
+// sbase / cbase: weight and count of elements below them.
 struct ColSrc {
   const SegIO &s;
   u128 sbase;
@@ -382,22 +378,6 @@ struct ColSrc {
   __device__ __forceinline__ void at(int t, uint64_t &key, int &row) const {
     row = s.lane + 64 * t;
     key = seg_key(s, row);
-  }
-};
-
-struct ListSrc {
-  const SegIO &s;
-  u128 sbase;
-  int cbase;
-  const uint64_t *keys;
-  const unsigned short *rows;
-  int nlist;
-  __device__ __forceinline__ int slots() const { return (nlist + 63) >> 6; }
-  __device__ __forceinline__ void at(int t, uint64_t &key, int &row) const {
-    const int e = s.lane + 64 * t;
-    const bool in = e < nlist;
-    key = in ? keys[e] : KEY_NONE;
-    row = in ? (int)rows[e] : 0;
   }
 };
 
@@ -631,97 +611,45 @@ __device__ __forceinline__ void wave_list_sums(const SegIO &s, const uint64_t *l
 // element below the list), reaches its tau.  A binary search over the lanes'
 // inclusive sums finds the owning lane, a walk over its entries the element.
 // hit = false when tau lies outside (Slo, Slo + weight of the list].
-// The weight below the list is known to lie in [SloA, SloB]; the search runs
-// at SloA, and amb is set where the answer at SloB could differ: the hit
-// status, or an earlier entry reaching tau (the entries before the found one
-// weigh run_prev - SloA; at SloB the found entry is still the first iff
-// run_prev + (SloB - SloA) < tau; it still reaches tau since SloB >= SloA).
 __device__ __forceinline__ void wave_resolve(const SegIO &s, const uint64_t *lk, const unsigned short *lr, int E,
-                                             u128 SloA, u128 SloB, u128 tot, u128 incl, bool active, u128 tau,
-                                             uint64_t &okey, int &orow, bool &hit, bool &amb) {
+                                             u128 Slo, u128 tot, u128 incl, bool active, u128 tau,
+                                             uint64_t &okey, int &orow, bool &hit) {
   const u128 wall = readlane_u128(incl, 63);
-  const bool inwin = active && tau > SloA && tau <= SloA + wall;
-  const bool inwinB = active && tau > SloB && tau <= SloB + wall;
+  const bool inwin = active && tau > Slo && tau <= Slo + wall;
   int lo = 0, hi = 63;
 #pragma unroll
   for (int it = 0; it < 6; ++it) {
     const int mid = (lo + hi) >> 1;
     const u128 im = shfl_u128(incl, mid);
-    if (SloA + im >= tau) hi = mid;
+    if (Slo + im >= tau) hi = mid;
     else lo = mid + 1;
   }
   const u128 totc = shfl_u128(tot, lo), inclc = shfl_u128(incl, lo);
   hit = false;
-  amb = inwin != inwinB;
   if (inwin) {
-    u128 run = SloA + inclc - totc;
+    u128 run = Slo + inclc - totc;
     for (int q = 0; q < E; ++q) {
       const int e = E * lo + q;
       const uint64_t key = lk[e];
       const bool valid = key != KEY_NONE;
-      const u128 before = run;
       run += seg_weight(s, valid ? (int)lr[e] : 0, valid);
       if (valid && run >= tau) {
         okey = key;
         orow = (int)lr[e];
         hit = true;
-        amb = amb || !(before + (SloB - SloA) < tau);
         break;
       }
     }
   }
 }
 
-// Resolution of one target tau, the same on every lane: the entry's owner is
-// the first lane whose inclusive sum, counted from Slo, reaches tau (one
-// ballot), and a walk over that lane's E entries finds the entry.  The exact
-// weight below the list is known to lie in [SloA, SloB]; amb = the answer is
-// not the same at both ends (then nothing is reported).
-__device__ __forceinline__ void wave_resolve_one(const SegIO &s, const uint64_t *lk, const unsigned short *lr,
-                                                 int E, u128 SloA, u128 SloB, u128 tot, u128 incl, u128 tau,
-                                                 uint64_t &okey, int &orow, bool &hit, bool &amb) {
-  auto find = [&](u128 Slo, uint64_t &k, int &r) -> bool {
-    const uint64_t owner = __ballot(Slo + incl >= tau);
-    if (!(tau > Slo) || owner == 0) return false;
-    const int lo = __builtin_ctzll(owner);
-    u128 run = Slo + readlane_u128(incl, lo) - readlane_u128(tot, lo);
-    for (int q = 0; q < E; ++q) {
-      const int e = E * lo + q;
-      const uint64_t key = lk[e];
-      const bool valid = key != KEY_NONE;
-      run += seg_weight(s, valid ? (int)lr[e] : 0, valid);
-      if (valid && run >= tau) {
-        k = key;
-        r = (int)lr[e];
-        return true;
-      }
-    }
-    return false;
-  };
-  uint64_t k2 = KEY_NONE;
-  int r2 = -1;
-  hit = find(SloA, k2, r2);
-  amb = false;
-  if (SloB != SloA) {
-    uint64_t k3 = KEY_NONE;
-    int r3 = -1;
-    const bool h3 = find(SloB, k3, r3);
-    amb = h3 != hit || k3 != k2 || r3 != r2;
-  }
-  okey = k2;
-  orow = r2;
-}
-
-// e_jk = R64 over i of |x_ik - fl(v x_ij)| (result in lane 0).  kPad: rows
-// past n are read as 0 instead of masked (the single-penalty kernels; the
-// several-penalty ones keep the masked loop, which spills less there)
-template <bool kPad>
+// e_jk = R64 over i of |x_ik - fl(v x_ij)| (result in lane 0).
 __device__ __forceinline__ double wave_residual(const SegIO &s, double v) {
   // column k in batches of RB loads issued back to back (the sum is still
   // taken slot by slot in increasing order)
   constexpr int RB = 8;
   double p = 0.0;
-  if (kPad && __builtin_isfinite(v)) {
+  if (__builtin_isfinite(v)) {
     // rows past n read 0 from both columns and add |0 - v 0| = +0, which
     // leaves the lane's partial as it is: no per-row masks or clamps
     const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, s.n), rj = col_rsrc(s.lds ? s.xk : s.sxj, s.n);
@@ -768,164 +696,6 @@ __device__ __forceinline__ double wave_residual(const SegIO &s, double v) {
   return wave_r64_tree_x(p);
 }
 
-// G residuals in one pass over the rows (the same sums as wave_residual,
-// G at a time); e[r] is the wave's R64 sum for v[r].
-template <int G>
-__device__ __forceinline__ void wave_residual_multi(const SegIO &s, const double *v, double *e) {
-  double p[G];
-#pragma unroll
-  for (int r = 0; r < G; ++r) p[r] = 0.0;
-  bool fin = true;
-#pragma unroll
-  for (int r = 0; r < G; ++r) fin = fin && __builtin_isfinite(v[r]);
-  if (fin) {
-    // rows past n read 0 from both columns and add |0 - v 0| = +0; the
-    // rows in batches of RB slots, every load of a batch issued before the
-    // first is used (the sums still run slot by slot in increasing order)
-    const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, s.n), rj = col_rsrc(s.lds ? s.xk : s.sxj, s.n);
-    constexpr int RB = 4;
-    // batch t0's loads are issued while batch t0 - RB is scored
-    auto load_batch = [&](int t0, double *av, double *bv) {
-      if (t0 + RB <= s.T) {
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-          const int i = s.lane + 64 * (t0 + q);
-          av[q] = sxj_pad(s, rj, i);
-          bv[q] = col_ld(rk, i * 8);
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-          // (slots past T, of the last batch: 0 from both columns)
-          const bool in = t0 + q < s.T;
-          const int i = s.lane + 64 * (t0 + q);
-          av[q] = in ? sxj_pad(s, rj, i) : 0.0;
-          bv[q] = in ? col_ld(rk, i * 8) : 0.0;
-        }
-      }
-    };
-    double an[RB], bn[RB];
-    load_batch(0, an, bn);
-    for (int t0 = 0; t0 < s.T; t0 += RB) {
-      double av[RB], bv[RB];
-#pragma unroll
-      for (int q = 0; q < RB; ++q) {
-        av[q] = an[q];
-        bv[q] = bn[q];
-      }
-      if (t0 + RB < s.T) load_batch(t0 + RB, an, bn);
-#pragma unroll
-      for (int q = 0; q < RB; ++q) {
-#pragma unroll
-        for (int r = 0; r < G; ++r) {
-          const double prod = v[r] * av[q];
-          const double d = bv[q] - prod;
-          p[r] = p[r] + fabs(d);
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < G; ++r) e[r] = readlane_dbl(wave_r64_tree_x(p[r]), 0);
-    return;
-  }
-  const int l0 = s.lane < s.n ? s.lane : 0;
-  double an = sxj_at(s, l0), bn = gld(s.xk + l0);
-  for (int t = 0; t < s.T; ++t) {
-    const int i = s.lane + 64 * t;
-    const bool in = i < s.n;
-    const double a = an, b = bn;
-    if (t + 1 < s.T) {
-      const int i2 = i + 64 < s.n ? i + 64 : 0;
-      an = sxj_at(s, i2);
-      bn = gld(s.xk + i2);
-    }
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const double prod = v[r] * a;
-      const double d = b - prod;
-      p[r] = p[r] + (in ? fabs(d) : 0.0);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < G; ++r) e[r] = readlane_dbl(wave_r64_tree_x(p[r]), 0);
-}
-
-// The next RJ residual jobs of mask jm (lanes whose target needs its own
-// e_jk; v_l: the lane's ratio): one pass over the rows scores them all, and
-// each job's lane receives its e in e_l.  Clears the jobs taken from jm.
-template <int RJ>
-__device__ __forceinline__ void run_jobs(const SegIO &s, uint64_t &jm, double v_l, int lane, double &e_l) {
-  int jl[RJ];
-  double jv[RJ], je[RJ];
-#pragma unroll
-  for (int r = 0; r < RJ; ++r) {
-    jl[r] = jm ? __builtin_ctzll(jm) : -1;
-    jm &= jm ? jm - 1 : 0;
-    jv[r] = jl[r] >= 0 ? readlane_dbl(v_l, jl[r]) : 0.0;
-  }
-  wave_residual_multi<RJ>(s, jv, je);
-#pragma unroll
-  for (int r = 0; r < RJ; ++r)
-    if (lane == jl[r]) e_l = je[r];
-}
-
-// Bitonic sort of 128 keys held two per lane (element 2*lane + r), ascending.
-__device__ __forceinline__ void wave_sort2(uint64_t &a, uint64_t &b, int lane) {
-#pragma unroll
-  for (int size = 2; size <= 128; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const bool up = ((2 * lane) & size) == 0;
-      if (stride == 1) {
-        const uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
-        a = up ? lo : hi;
-        b = up ? hi : lo;
-      } else {
-        const int ls = stride >> 1;
-        const uint64_t oa = shfl_xor_u64(a, ls), ob = shfl_xor_u64(b, ls);
-        const bool keep_min = (((2 * lane) & stride) == 0) == up;
-        a = keep_min ? (oa < a ? oa : a) : (oa > a ? oa : a);
-        b = keep_min ? (ob < b ? ob : b) : (ob > b ? ob : b);
-      }
-    }
-  }
-}
-
-// Bitonic sort of 128 (key, row) pairs held two per lane (element
-// 2 lane + r), ascending in (key, row).
-__device__ __forceinline__ void wave_sort2_kr(uint64_t &ka, int &ra, uint64_t &kb, int &rb, int lane) {
-#pragma unroll
-  for (int size = 2; size <= 128; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const bool up = ((2 * lane) & size) == 0;
-      if (stride == 1) {
-        const bool sw = (kb < ka || (kb == ka && rb < ra)) == up;
-        const uint64_t tk = ka;
-        const int tr = ra;
-        ka = sw ? kb : ka;
-        ra = sw ? rb : ra;
-        kb = sw ? tk : kb;
-        rb = sw ? tr : rb;
-      } else {
-        const int ls = stride >> 1;
-        const bool keep_min = (((2 * lane) & stride) == 0) == up;
-        const uint64_t oka = shfl_xor_u64(ka, ls), okb = shfl_xor_u64(kb, ls);
-        const int ora = __shfl_xor(ra, ls), orb = __shfl_xor(rb, ls);
-        const bool la = oka < ka || (oka == ka && ora < ra), lb = okb < kb || (okb == kb && orb < rb);
-        if (la == keep_min) {
-          ka = oka;
-          ra = ora;
-        }
-        if (lb == keep_min) {
-          kb = okb;
-          rb = orb;
-        }
-      }
-    }
-  }
-}
-
 // Bitonic sort of 128 32-bit keys held two per lane (element 2 lane + r),
 // ascending, through VALU lane exchanges.
 __device__ __forceinline__ void wave_sort2_u32_x(uint32_t &a, uint32_t &b, int lane) {
@@ -949,28 +719,8 @@ __device__ __forceinline__ void wave_sort2_u32_x(uint32_t &a, uint32_t &b, int l
   }
 }
 
-// wave_sort2 and wave_sort2_kr through VALU lane exchanges (same networks)
-__device__ __forceinline__ void wave_sort2_x(uint64_t &a, uint64_t &b, int lane) {
-#pragma unroll
-  for (int size = 2; size <= 128; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const bool up = ((2 * lane) & size) == 0;
-      if (stride == 1) {
-        const uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
-        a = up ? lo : hi;
-        b = up ? hi : lo;
-      } else {
-        const int ls = stride >> 1;
-        const uint64_t oa = xswap64(a, ls), ob = xswap64(b, ls);
-        const bool keep_min = (((2 * lane) & stride) == 0) == up;
-        a = keep_min ? (oa < a ? oa : a) : (oa > a ? oa : a);
-        b = keep_min ? (ob < b ? ob : b) : (ob > b ? ob : b);
-      }
-    }
-  }
-}
-
+// Bitonic sort of 128 (key, row) pairs held two per lane (element
+// 2 lane + r), ascending in (key, row).
 __device__ __forceinline__ void wave_sort2_kr_x(uint64_t &ka, int &ra, uint64_t &kb, int &rb, int lane) {
 #pragma unroll
   for (int size = 2; size <= 128; size <<= 1) {
@@ -1216,22 +966,20 @@ k_signsum_batch(const ProbDesc *__restrict__ P, const int *__restrict__ tstart, 
 }
 
 // ---------------------------------------------------------------- segments
-// Workgroup = (preserved column j, one part of the k range); its waves take
-// the next k from an LDS counter.  For every (j, k) and lambda_t it writes
-//   V[(t m + j) m + k] = v_k,  E[...] = e_jk,  R[...] = median row (-1 for 0).
-//
-// Per segment:
-//  1. the sign sums D_jk, Zr_jk (k_signsum_batch) decide, with a rigorous
+// For every (j, k) and lambda_t:  V[(t m + j) m + k] = v_k,  E[...] = e_jk,
+// R[...] = median row (-1 for 0).
+//  1. The sign sums D_jk, Zr_jk (k_signsum_batch) decide, with a rigorous
 //     error margin, whether 0 minimises g_jk -- then v_k = 0 and e_jk is the
-//     R64 column mass of k (|x_ik - fl(0 x_ij)| = |x_ik|) -- or on which side
-//     of 0 the minimiser lies.  Otherwise an exact pass (128-bit sums)
-//     decides.
+//     R64 column mass of k (|x_ik - fl(0 x_ij)| = |x_ik|): k_zero_segments --
+//     or on which side of 0 the minimiser lies.
 //  2. The ratios of 128 rows drawn once per j with probability proportional
-//     to |x_ij| estimate where the weighted median lies: a key window.
-//  3. One exact pass sums the weight below the window and appends the
-//     window's elements (key, row) to an LDS list, which is sorted and
-//     scanned exactly.
-//  Whatever the window does not settle goes to the general rounds.
+//     to |x_ij| estimate where the weighted median lies: a window.  k_seg_fast
+//     (one penalty) and k_seg_path (several) list its rows in one pass without
+//     a division per row and select among them in FP64 with a rigorous margin.
+//     Workgroup = (preserved column j, one part of the k range); its waves take
+//     the next k from an LDS counter.
+//  3. What the margin does not settle is left to k_seg_rest: exact 128-bit
+//     sums and general rounds.
 constexpr int SEG_WAVES = 4;
 constexpr int SXJ_LDS_MAX = 4096;   // longest column j copied to LDS (32 KB)
 constexpr int SEG_MASK_WORDS = 64;  // zero-segment mask words an item holds (one per lane: 4096 k)
@@ -1239,177 +987,18 @@ constexpr int SEG_MASK_WORDS = 64;  // zero-segment mask words an item holds (on
 __host__ __device__ constexpr size_t seg_sxj_bytes(int n) {
   return ((size_t)((n + 63) / 64) * 64 * 8 + 15) / 16 * 16;
 }
-__host__ __device__ constexpr size_t seg_lds_bytes(int n, int L, int lcap) {
-  return seg_sxj_bytes(n) + (size_t)L * 16 +
-         SEG_WAVES * (sizeof(WaveScratch) + (size_t)lcap * (sizeof(uint64_t) + sizeof(unsigned short))) + 16;
+__host__ __device__ constexpr size_t rest_wave_bytes(int L, int lcap) {
+  return (size_t)L * 16 + sizeof(WaveScratch) + (size_t)lcap * (sizeof(uint64_t) + sizeof(unsigned short));
 }
 
 
-// ------------------------------------------------ division-free window pass
-// Fast form of the exact pass.  For a row with a = x_ij != 0 and b = x_ik the
-// ratio is q = b / a = u / |a| with u = b sgn(a) (exact), so q <= bound
-// exactly when u <= bound |a|.  Comparing u with fl(bound' |a|), bound' the
-// window bound moved outwards by 2^-49 of its magnitude, decides without a
-// division, and rigorously, whether fl(q) lies at or below the window (its
-// weight |a| joins an FP64 sum) or above it (dropped); rows inside the guard
-// band or the window are listed by row and get their exact key (one IEEE
-// divide each) in a second pass over the list, which keeps the window's
-// elements (key, row) in row order -- the list the exact pass builds.  Zero
-// bounds are sign tests: u < 0 is u <= -2^-1074 (the smallest subnormal).
-// Valid when every nonzero magnitude of columns j and k lies in
-// [2^-300, 2^300]: then q and the products stay normal.
+// The division-free path takes columns whose nonzero magnitudes all lie in
+// [2^-300, 2^300]: then the ratios and the products with a window bound stay
+// normal.
 constexpr int FAST_BEXP_LO = 1023 - 300, FAST_BEXP_HI = 1023 + 300;
 
 __device__ __forceinline__ bool fast_columns(const ColInfo &c) {
   return c.nnz == 0 || (c.bemin >= FAST_BEXP_LO && c.bemax <= FAST_BEXP_HI);
-}
-
-// thresholds: "at or below the window" = u <= fma(lo_g, |a|, c_lo), "above
-// the window" = u > fma(hi_g, |a|, c_hi)
-struct FastBounds {
-  double lo_g, c_lo, hi_g, c_hi;
-};
-__device__ __forceinline__ FastBounds fast_bounds(uint64_t plo, uint64_t phi) {
-  constexpr double TINY = 0x1p-1074;
-  FastBounds f{0.0, 0.0, 0.0, 0.0};
-  if (plo == 0) {
-    f.c_lo = -__builtin_inf();                      // nothing at or below
-  } else if (plo == KEY_ZERO - 1) {
-    f.c_lo = -TINY;                                  // every negative ratio
-  } else {
-    const double lo = ratio_of_key(plo);
-    f.lo_g = lo - fabs(lo) * 0x1p-49;
-  }
-  if (phi == KEY_NONE - 1) {
-    f.c_hi = __builtin_inf();                        // nothing above
-  } else if (phi == KEY_ZERO - 1) {
-    f.c_hi = -TINY;                                  // every ratio >= 0
-  } else {
-    const double hi = ratio_of_key(phi);
-    f.hi_g = hi + fabs(hi) * 0x1p-49;
-  }
-  return f;
-}
-
-// floor(x / 2^e0) for a finite x >= 0 below 2^(e0 + 127)
-__device__ __forceinline__ u128 fixed_floor(double x, int e0) {
-  return x > 0.0 ? fixed_of(x, e0) : (u128)0;
-}
-
-// The fast pass over the rows of segment (j, k) for the window (plo, phi]:
-// lk / lr receive the window's elements in row order (count nwin; nwin >
-// lcap reports an overflow, the list then unusable), and [SA, SB] brackets
-// the exact weight of the elements at or below the window (units 2^e0).
-template <class LdJ, class LdK>
-__device__ __forceinline__ void fast_window_pass(const SegIO &s, LdJ ldj, LdK ldk, uint64_t plo, uint64_t phi,
-                                                 uint64_t *lk, unsigned short *lr, int lcap, int &nwin, u128 &SA,
-                                                 u128 &SB) {
-  const FastBounds f = fast_bounds(plo, phi);
-  const int lane = s.lane, T = s.T;
-  double S = 0.0;
-  int nc = 0;
-  // rows in batches of FB slots, every load of a batch issued before the
-  // first is used (one slot at a time left the wave waiting on L2 latency)
-  constexpr int FB = 4;
-  // batch t0's loads are issued while batch t0 - FB is classified
-  auto load_batch = [&](int t0, double *av, double *bv) {
-    if (t0 + FB <= T) {
-      // a whole batch (every one at 2000 rows): no per-slot guard
-#pragma unroll
-      for (int r = 0; r < FB; ++r) {
-        const int i = lane + 64 * (t0 + r);
-        av[r] = ldj(i);
-        bv[r] = ldk(i);
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < FB; ++r) {
-        const int i = lane + 64 * (t0 + r);
-        const bool in = t0 + r < T;
-        av[r] = in ? ldj(i) : 0.0;
-        bv[r] = in ? ldk(i) : 0.0;
-      }
-    }
-  };
-  double an[FB], bn[FB];
-  load_batch(0, an, bn);
-  for (int t0 = 0; t0 < T; t0 += FB) {
-    double av[FB], bv[FB];
-#pragma unroll
-    for (int r = 0; r < FB; ++r) {
-      av[r] = an[r];
-      bv[r] = bn[r];
-    }
-    if (t0 + FB < T) load_batch(t0 + FB, an, bn);
-#pragma unroll
-    for (int r = 0; r < FB; ++r) {
-      const int i = lane + 64 * (t0 + r);
-      const double a = av[r], b = bv[r];
-      const double aa = fabs(a);
-      const double u =
-          __longlong_as_double(__double_as_longlong(b) ^ (__double_as_longlong(a) & (long long)KEY_ZERO));
-      const bool valid = a != 0.0;
-      const bool below = valid && u <= fma(f.lo_g, aa, f.c_lo);
-      const bool above = u > fma(f.hi_g, aa, f.c_hi);
-      S = fma(aa, below ? 1.0 : 0.0, S);
-      const bool cand = valid && !below && !above;
-      const uint64_t cm = __ballot(cand);
-      const int pos = nc + lanes_below(cm);
-      nc += __builtin_popcountll(cm);
-      if (cand && pos < lcap) lr[pos] = (unsigned short)i;
-    }
-  }
-  nc = uni_int(nc);
-  wave_lds_sync();
-  int nw = 0;
-  if (nc <= lcap) {
-    // exact keys of the listed rows, GB slots of gathers in flight; the
-    // window's elements are compacted to the front (an entry never moves
-    // above its own slot, and a batch is read before it is written)
-    constexpr int GB = 4;
-    for (int e0 = 0; e0 < nc; e0 += 64 * GB) {
-      int rows[GB];
-      double av[GB], bv[GB];
-#pragma unroll
-      for (int r = 0; r < GB; ++r) {
-        const int e = e0 + 64 * r + lane;
-        rows[r] = e < nc ? (int)lr[e] : -1;
-      }
-#pragma unroll
-      for (int r = 0; r < GB; ++r) {
-        const int row = rows[r] < 0 ? 0 : rows[r];
-        av[r] = sxj_at(s, row);
-        bv[r] = gld(s.xk + row);
-      }
-#pragma unroll
-      for (int r = 0; r < GB; ++r) {
-        const bool in = rows[r] >= 0;
-        const uint64_t key = key_of_pair(in, av[r], bv[r]);
-        const bool le = in && key <= plo;
-        const bool inw = in && key > plo && key <= phi;
-        S = fma(fabs(av[r]), le ? 1.0 : 0.0, S);
-        const uint64_t wm = __ballot(inw);
-        const int pos = nw + lanes_below(wm);
-        nw += __builtin_popcountll(wm);
-        if (inw) {
-          lk[pos] = key;
-          lr[pos] = (unsigned short)rows[r];
-        }
-      }
-    }
-    nw = uni_int(nw);
-  } else {
-    nw = nc;                                         // overflow
-  }
-  wave_lds_sync();
-  nwin = nw;
-  // FP64 sum of nonnegative terms: each lane adds at most T + ceil(nc / 64)
-  // terms in sequence, then six tree levels; the error is below
-  // (terms + 8) 2^-52 of the sum
-  const double St = wave_sum_dbl_x(S);
-  const double dlt = (double)(T + ((min(nc, lcap) + 63) >> 6) + 8) * 0x1p-52 * St;
-  SA = fixed_floor(St - dlt, s.e0);
-  SB = fixed_floor(St + dlt, s.e0) + 1;
 }
 
 // Probe point of a window (plo, phi] that holds more elements than the
@@ -1486,8 +1075,8 @@ __global__ void __launch_bounds__(256)
 k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, int total_words,
                 const double *__restrict__ lam_all, const ColInfo *__restrict__ ci,
                 double2 *__restrict__ DZ, double *__restrict__ V, double *__restrict__ E,
-                int *__restrict__ R, unsigned long long *__restrict__ mask, const int *__restrict__ cand,
-                const int *__restrict__ gate, int gate_on, int split, const double2 *__restrict__ part,
+                int *__restrict__ R, unsigned long long *__restrict__ mask, unsigned long long *__restrict__ todo,
+                const int *__restrict__ cand, const int *__restrict__ gate, int gate_on, int split, const double2 *__restrict__ part,
                 long long per) {
   const int w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (w >= total_words) return;
@@ -1531,7 +1120,10 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
     }
   }
   const unsigned long long bits = __ballot(skip);
-  if (lane == 0) mask[d.mask_off + wl] = bits;
+  if (lane == 0) {
+    mask[d.mask_off + wl] = bits;
+    todo[d.mask_off + wl] = 0ull;
+  }
 }
 
 // exact A (negative ratios), B (non-positive), counts, one sample per side
@@ -1565,789 +1157,1401 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
   return e;
 }
 
-// Selection of one target from the division-free pass's window list in
-// FP64.  The list holds the window's elements (row order, count nwin); the
-// exact weight below the window lies in [SA, SB] (units 2^e0); tau is the
-// target's threshold (same units): the answer is the first element, in
-// (key, row) order, at which the weight below the window plus the list's
-// prefix reaches tau -- what the exact selection finds.  Here the weights
-// |x_ij| are summed in FP64.  Every value compared is a sum of nonnegative
-// weights of column j or a difference of such sums, at most W_j, reached
-// through at most 40 roundings (list sums: 8 per lane and 6 tree levels;
-// 128-bit values converted with 3; the walk's running sum), so it lies
-// within 40 u W_j of its exact value (u = 2^-53).  A comparison whose
-// operands differ by more than tol = 2^-38 W_j (2^15 u W_j) therefore has
-// the exact comparison's outcome; a closer one sets amb, and the caller
-// redoes the segment with the exact pass.  Live segments have lambda < W_j,
-// so tau is at most W_j.  Lists over 128 elements are first cut at three
-// sample keys (piv, ascending) to the part that holds the target, as the
-// exact path does.
-__device__ __forceinline__ void select_one_fp64(const SegIO &s, uint64_t *lk, unsigned short *lr, int &nwin,
-                                                int lane, u128 SA, u128 SB, u128 tau, double Wd,
-                                                const uint64_t *piv, uint64_t &okey, int &orow, bool &hit,
-                                                bool &amb) {
-  const double tol = 0x1p-38 * Wd;
-  // tau - (weight below the list) at both ends of the interval, in the
-  // column's own units; 0 when tau is at or below it (exactly known)
-  auto real_of = [&](u128 x) { return ldexp(u128_to_double_approx(x), s.e0); };
-  double DA = tau > SA ? real_of(tau - SA) : 0.0, DB = tau > SB ? real_of(tau - SB) : 0.0;
-  bool und = false;
-  if (nwin > 128) {
-    const uint64_t p0 = piv[0], p1 = piv[1] < p0 ? p0 : piv[1], p2 = piv[2] < p1 ? p1 : piv[2];
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    for (int e = lane; e < nwin; e += 64) {
-      const uint64_t key = lk[e];
-      const double w = fabs(sxj_at(s, lr[e]));
-      a0 = a0 + (key < p0 ? w : 0.0);
-      a1 = a1 + (key < p1 ? w : 0.0);
-      a2 = a2 + (key < p2 ? w : 0.0);
-    }
-    a0 = wave_sum_dbl_x(a0);
-    a1 = wave_sum_dbl_x(a1);
-    a2 = wave_sum_dbl_x(a2);
-    // parts below the target: pivots p with (weight below p) < D
-    auto below = [&](double D) {
-      const double d0 = a0 - D, d1 = a1 - D, d2 = a2 - D;
-      und = und || fabs(d0) <= tol || fabs(d1) <= tol || fabs(d2) <= tol;
-      return (d0 < 0.0 ? 1 : 0) + (d1 < 0.0 ? 1 : 0) + (d2 < 0.0 ? 1 : 0);
-    };
-    const int c = below(DA), cB = below(DB);
-    if (und || c != cB) {
-      amb = true;
-      return;
-    }
-    const uint64_t plo2 = c == 0 ? 0 : (c == 1 ? p0 : (c == 2 ? p1 : p2)), phi2 = c == 0 ? p0 : (c == 1 ? p1 : p2);
-    const double base = c == 0 ? 0.0 : (c == 1 ? a0 : (c == 2 ? a1 : a2));
-    // (c > 0: base < D by more than tol at both ends, so both stay positive)
-    DA = DA - base;
-    DB = DB - base;
-    // stable in-place compaction: an element never moves above its own
-    // slot, so slots not yet read are never overwritten
-    int kept = 0;
-    for (int e0 = 0; e0 < nwin; e0 += 64) {
-      const int e = e0 + lane;
-      const bool in = e < nwin;
-      const uint64_t key = in ? lk[e] : 0;
-      const unsigned short row = in ? lr[e] : 0;
-      const bool keep = in && (c == 0 || key >= plo2) && (c == 3 || key < phi2);
-      const uint64_t km = __ballot(keep);
-      const int d = kept + lanes_below(km);
-      kept += __builtin_popcountll(km);
-      if (keep) {
-        lk[d] = key;
-        lr[d] = row;
-      }
-    }
-    nwin = uni_int(kept);
-    wave_lds_sync();
-  }
-  const int N = wave_sort_list(lk, lr, nwin, lane);
-  const int E = N >> 6;
-  // lane l owns the sorted entries [E l, E l + E)
-  double tot = 0.0;
-  for (int q = 0; q < E; ++q) {
-    const int e = E * lane + q;
-    const bool valid = lk[e] != KEY_NONE;
-    tot = tot + (valid ? fabs(sxj_at(s, lr[e])) : 0.0);
-  }
-  const double incl = wave_incl_scan_dbl_x(tot, lane);
-  // the search at the lower end of [SA, SB] (D = DA); the upper end (DB <=
-  // DA) is then checked by one comparison: the found entry stays the first
-  // to reach DB iff the weight before it is below DB, and a miss above the
-  // list stays one iff the list's total is below DB
-  auto find = [&](double D, uint64_t &k, int &r, double &prev) -> bool {
-    if (!(D > 0.0)) return false;                  // tau at or below the list
-    const double df = incl - D;
-    und = und || __ballot(fabs(df) <= tol) != 0;
-    const uint64_t owner = __ballot(df >= 0.0);
-    if (owner == 0) return false;                  // above the list
-    const int lo = __builtin_ctzll(owner);
-    double run = readlane_dbl(incl, lo) - readlane_dbl(tot, lo);
-    for (int q = 0; q < E; ++q) {
-      const int e = E * lo + q;
-      const uint64_t key = lk[e];
-      if (key == KEY_NONE) break;
-      prev = run;
-      run = run + fabs(sxj_at(s, lr[e]));
-      const double d = run - D;
-      und = und || fabs(d) <= tol;
-      if (d >= 0.0) {
-        k = key;
-        r = (int)lr[e];
-        return true;
-      }
-    }
-    und = true;                                    // (the owner's entries must reach D)
-    return false;
-  };
-  uint64_t kA = KEY_NONE;
-  int rA = -1;
-  double prevA = 0.0;
-  const bool hA = find(DA, kA, rA, prevA);
-  if (DB != DA) {
-    if (hA) {
-      // (DB > 0 is exactly known: DB = 0 means tau is at or below SB)
-      und = und || (DB > 0.0 && fabs(prevA - DB) <= tol);
-      amb = amb || !(DB > 0.0 && prevA - DB < 0.0);
-    } else if (DA > 0.0) {
-      const double d = readlane_dbl(incl, 63) - DB;
-      und = und || fabs(d) <= tol;
-      amb = amb || d >= 0.0;
-    }
-  }
-  amb = amb || und;
-  okey = kA;
-  orow = rA;
-  hit = hA;
-}
+// ------------------------------------------------- division-free segments
+// One segment (j, k) at one penalty by one wave, without a division per row
+// and without a sort.  With a = x_ij, b = x_ik the sign of the fused d =
+// fma(-t, a, b) is the exact sign of b - t a (a and b zero or in [2^-300,
+// 2^300], |t| zero-like 2^-700 or more: no underflow), so it says on which
+// side of t the ratio b / a lies: below where d and a differ in sign.
+//  window_pass  over the rows: T = sum of |a| sgn(b/a - lo) (a with its sign
+//               flipped by d's: no comparison, no select), which is W - 2 S
+//               for the weight S below lo; the rows between lo and hi are
+//               those where the two signs differ, one bit per row shifted
+//               into a word per lane (v_alignbit) and expanded to a list of
+//               rows once per 32 slots;
+//  select_listed  the listed rows' ratios (one IEEE divide each) go to 64
+//               bins of the window, whose weights (LDS adds) are scanned; the
+//               target's bin holds a few rows, ranked by counting.
+// The target, counted from lo, is D = (T + lambda) / 2 on the negative side and
+// (T - lambda) / 2 on the positive one (first prefix sum reaching D).  Sums
+// run in FP64: every value compared is a sum of nonnegative weights of
+// column j or a difference of such sums, at most W_j, off its exact value by
+// at most the terms a lane adds in turn plus 60 roundings of W_j (u = 2^-53),
+// less than 2^11 u W_j for 65535 rows.  A comparison whose operands differ by
+// more than tol = 2^-38 W_j (2^15 u W_j) therefore has the exact comparison's
+// outcome; closer ones, a selected ratio equal to lo or hi (a row whose
+// rounded ratio meets the bound may be on either side of it) and whatever
+// else is unsettled leave the segment to k_seg_rest, which is exact.
+constexpr int FAST_CAP = 512;       // rows a window may list
+constexpr double FAST_ZERO = 0x1p-700, FAST_OPEN = 0x1p700;   // next to 0, beyond every ratio
 
-// One work item, by the whole workgroup (every thread calls it).  ci, V, E,
-// R and segflags are this problem's slices.  kLdsJ: column j is copied to LDS
-// (the pointer's address space is then known to the compiler: LDS loads).
-template <bool kLdsJ, bool kMulti>
-__device__ __forceinline__ void seg_item(const double *__restrict__ X, int n, int m, long long ld,
-                                         const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp,
-                                         const double *__restrict__ lam, int L,
-                                         const double2 *__restrict__ DZ, int j, int kbeg, int kend,
-                                         double *__restrict__ V,
-                                         double *__restrict__ E, int *__restrict__ R, int *__restrict__ segflags,
-                                         const unsigned long long *__restrict__ maskrow, int lcap, int sxj_rows,
-                                         unsigned char *smem) {
-  const int T = (n + 63) >> 6;
-  // penalties: the single-penalty instantiation has exactly one (one group,
-  // one pass, trip counts the compiler sees)
-  const int Lg = kMulti ? L : 1;
-  // column j in LDS when the launch reserved room for it (n <= sxj_rows),
-  // else read from global memory (it stays in L2 across the item's k)
-  constexpr bool lds_j = kLdsJ;
-  (void)sxj_rows;
-  double *sxj_lds = (double *)smem;                 // T*64 entries, zero padded
-  u128 *slam = (u128 *)(smem + (lds_j ? seg_sxj_bytes(n) : 0));
-  WaveScratch *wsc = (WaveScratch *)(slam + L);
-  uint64_t *lkeys = (uint64_t *)(wsc + SEG_WAVES);
-  unsigned short *lrows = (unsigned short *)(lkeys + (size_t)SEG_WAVES * lcap);
-  int *knext = (int *)(lrows + (size_t)SEG_WAVES * lcap);
+struct FastScratch {
+  uint32_t list[FAST_CAP];          // row, then row | bin << 16
+  double bin[64];                   // bin weights, then the target bin's rows
+};
 
-  const ColInfo cj = ci[j];
-  const double *xjg = X + (long long)j * ld;
-  if constexpr (kLdsJ)
-    for (int i = threadIdx.x; i < T * 64; i += blockDim.x) sxj_lds[i] = i < n ? xjg[i] : 0.0;
-  const double *__restrict__ sxj = kLdsJ ? (const double *)sxj_lds : xjg;
-  for (int t = threadIdx.x; t < L; t += blockDim.x) slam[t] = lambda_fixed(lam[t], cj.e0);
-  if (threadIdx.x == 0) *knext = 0;
-  __syncthreads();
-
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // the item's live segments: k in [kbeg, kend) not settled by
-  // k_zero_segments.  Lane l holds word l of the item's mask inverted (bit b:
-  // segment 64 (w0 + l) + b is live) and the live count of the words below
-  // it; the waves claim live segments by their rank, so settled ones cost no
-  // claim.  Without the mask every segment of the range is live.
-  const int w0 = kbeg >> 6, nwords = kend > kbeg ? ((kend - 1) >> 6) - w0 + 1 : 0;
-  const bool use_mask = maskrow != nullptr && nwords <= SEG_MASK_WORDS;
-  uint64_t live = 0;
-  int kpre = 0, nlive = kend - kbeg;
-  if (use_mask) {
-    if (lane < nwords) {
-      const int lo = max(kbeg - 64 * (w0 + lane), 0), hi = min(kend - 64 * (w0 + lane), 64);
-      const uint64_t range = (hi == 64 ? ~0ull : (1ull << hi) - 1ull) & ~((1ull << lo) - 1ull);
-      live = ~maskrow[w0 + lane] & range;
-    }
-    const int cnt = __builtin_popcountll(live);
-    kpre = wave_excl_scan_int(cnt, lane);
-    nlive = uni_int(__shfl(kpre + cnt, 63));
-  }
-  // the sample of column j: two rows per lane, and (one penalty: the
-  // several-penalty kernel has no registers for them and takes them per
-  // segment) the reciprocals of their x_ij
-  const unsigned srows = smp[(long long)j * SAMPLE_ROWS + lane] |
-                         ((unsigned)smp[(long long)j * SAMPLE_ROWS + 64 + lane] << 16);
-  double sv0 = 0.0, sv1 = 0.0;
-  if constexpr (!kMulti) {
-    sv0 = __builtin_amdgcn_rcp(sxj[srows & 0xFFFF]);
-    sv1 = __builtin_amdgcn_rcp(sxj[srows >> 16]);
-  }
-
-  WaveScratch *ws = wsc + wave;
-  uint64_t *lk = lkeys + (size_t)wave * lcap;
-  unsigned short *lr = lrows + (size_t)wave * lcap;
-  const long long mm = (long long)m * m;
-  const double Wd = cj.W;
-  int Tp = 1;
-  while (Tp < T) Tp <<= 1;
-  int err = 0;
-
-  // claims are taken one segment ahead, so the counter's round trip overlaps
-  // the current segment (claims only grow: once one is past the live count,
-  // so is every later one)
-  int claim = 0;
-  if (lane == 0) claim = atomicAdd(knext, 1);
-  while (true) {
-    const int c = __builtin_amdgcn_readlane(claim, 0);
-    if (c >= nlive) break;
-    if (lane == 0) claim = atomicAdd(knext, 1);
-    int k = kbeg + c;
-    if (use_mask) {
-      // the c-th live segment: the last word whose live prefix is <= c, then
-      // the (c - prefix)-th set bit of that word
-      const int w = __builtin_popcountll(__ballot(lane < nwords && kpre <= c)) - 1;
-      const uint64_t lw = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(live >> 32), w) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)live, w);
-      const int r = c - __builtin_amdgcn_readlane(kpre, w);
-      k = 64 * (w0 + w) + __builtin_ctzll(__ballot(((lw >> lane) & 1ull) && lanes_below(lw) == r));
-    }
-    const long long base = (long long)j * m + k;
-    if (k == j || cj.flags) {
-      if (lane == 0) {
-        for (int t = 0; t < Lg; ++t) {
-          V[t * mm + base] = (k == j) ? 1.0 : __longlong_as_double(0x7ff8000000000000ll);
-          E[t * mm + base] = 0.0;
-          R[t * mm + base] = -1;
-        }
-      }
-      continue;
-    }
-    const ColInfo ck = ci[k];
-    const SegIO s{X + (long long)k * ld, sxj, n, T, Tp, cj.e0, lane, kLdsJ};
-    const double Wk = ck.W;
-    const bool fast_seg = fast_columns(cj) && fast_columns(ck);
-
-    // 1. sign sums.  |x_ik / x_ij| can underflow to 0 only if the exponent
-    // fields differ by more than 1000: the column ranges rule that out for the
-    // whole segment in the usual case, else the exact pass decides.
-    const double2 dz = DZ[(long long)j * m + k];
-    const bool unc = sign_sums_unsure(cj, ck, dz);
-
-    bool have_exact = false;
-    ExactSides ex;
-    const u128 W = cj.wfix;
-    // (a) the side of every penalty: v_k = 0, or the minimiser is negative
-    // (1) or positive (2).  A <= B makes the nonzero side the same for every
-    // penalty of the segment.
-    uint64_t nz0 = 0, nz1 = 0;                     // bit t: v_k != 0 at penalty t
-    int sd = 0;
-    if constexpr (kMulti) {
-      // one penalty per lane, in groups of 64
-      for (int g0 = 0; g0 < L; g0 += 64) {
-        const int t = g0 + lane;
-        const bool in = t < L;
-        int side = 0;
-        if (in) side = sign_sum_side(dz, lam[t], Wd, unc);
-        if (__ballot(side == 3)) {
-          if (!have_exact) {
-            ex = exact_sides(s);
-            have_exact = true;
-          }
-          if (side == 3) {
-            const u128 lamf = slam[t], WpL = W + lamf;
-            side = ((ex.A << 1) <= WpL && W <= (ex.B << 1) + lamf) ? 0 : ((ex.A << 1) > WpL ? 1 : 2);
-          }
-        }
-        const uint64_t nzm = __ballot(side != 0);
-        if (g0 == 0) nz0 = nzm;
-        else nz1 = nzm;
-        // every nonzero penalty has the same side (A <= B)
-        if (nzm) sd = __builtin_amdgcn_readlane(side, __builtin_ctzll(nzm));
+// The rows of a segment in batches of FB slots, the next batch's loads issued
+// while f(a, b) runs on the current one; rows past n give (0, 0).
+// f is called for the slots [t0, t1) in order, in multiples of FB.
+template <int FB, class LdJ, class LdK, class F>
+__device__ __forceinline__ void for_row_pairs(const SegIO &s, LdJ ldj, LdK ldk, int t0, int t1, F f) {
+  auto load = [&](int t, double *av, double *bv) {
+    if (t + FB <= s.T) {
+#pragma unroll
+      for (int r = 0; r < FB; ++r) {
+        av[r] = ldj(s.lane + 64 * (t + r));
+        bv[r] = ldk(s.lane + 64 * (t + r));
       }
     } else {
-      for (int t = 0; t < Lg; ++t) {
-        int side = sign_sum_side(dz, lam[t], Wd, unc);
-        if (side == 3) {
-          if (!have_exact) {
-            ex = exact_sides(s);
-            have_exact = true;
-          }
-          const u128 lamf = slam[t], WpL = W + lamf;
-          side = ((ex.A << 1) <= WpL && W <= (ex.B << 1) + lamf) ? 0 : ((ex.A << 1) > WpL ? 1 : 2);
-        }
-        if (side) {
-          sd = side;
-          if (t < 64) nz0 |= 1ull << t;
-          else nz1 |= 1ull << (t - 64);
+#pragma unroll
+      for (int r = 0; r < FB; ++r) {
+        const bool in = t + r < s.T;
+        av[r] = in ? ldj(s.lane + 64 * (t + r)) : 0.0;
+        bv[r] = in ? ldk(s.lane + 64 * (t + r)) : 0.0;
+      }
+    }
+  };
+  double an[FB], bn[FB];
+  load(t0, an, bn);
+  for (int t = t0; t < t1; t += FB) {
+    double av[FB], bv[FB];
+#pragma unroll
+    for (int r = 0; r < FB; ++r) {
+      av[r] = an[r];
+      bv[r] = bn[r];
+    }
+    if (t + FB < t1) load(t + FB, an, bn);
+#pragma unroll
+    for (int r = 0; r < FB; ++r) f(av[r], bv[r]);
+  }
+}
+
+template <class LdJ, class LdK>
+__device__ __forceinline__ void window_pass(const SegIO &s, LdJ ldj, LdK ldk, double lo, double hi, uint32_t *list,
+                                            int cap, double &Tsum, int &count) {
+  double S = 0.0;
+  int c = 0;
+  for (int t0 = 0; t0 < s.T; t0 += 32) {
+    uint32_t m = 0;
+    const int t1 = min(s.T, t0 + 32);
+    for_row_pairs<4>(s, ldj, ldk, t0, t1, [&](double a, double b) {
+      const double dl = fma(-lo, a, b), dh = fma(-hi, a, b);
+      S = S + flip_sign(a, dl);
+      m = __builtin_amdgcn_alignbit(m, hi32(dl) ^ hi32(dh), 31);
+    });
+    // slot t0 + i at bit 31 - i
+    m <<= 32 - ((t1 - t0 + 3) & ~3);
+    const int pc = __builtin_popcount(m), incl = wave_scan_int(pc);
+    const int tot = __builtin_amdgcn_readlane(incl, 63);
+    if (c + tot <= cap) {
+      int pos = c + incl - pc;
+      while (__ballot(m != 0)) {
+        if (m) {
+          const int i = __builtin_clz(m);
+          list[pos++] = (uint32_t)(s.lane + 64 * (t0 + i));
+          m ^= 0x80000000u >> i;
         }
       }
     }
-    if ((nz0 | nz1) == 0) {
-      // v_k = 0 at every penalty: e_jk = R64 sum of |x_ik|
-      for (int t = lane; t < Lg; t += 64) {
-        V[t * mm + base] = 0.0;
-        E[t * mm + base] = Wk;
-        R[t * mm + base] = -1;
+    c += tot;
+  }
+  wave_lds_sync();
+  Tsum = wave_total_dbl(S);
+  count = c;
+}
+
+// T at three bounds in one pass, nothing listed
+template <class LdJ, class LdK>
+__device__ __forceinline__ void probe_pass(const SegIO &s, LdJ ldj, LdK ldk, const double (&t)[3], double (&T)[3]) {
+  double S[3] = {0.0, 0.0, 0.0};
+  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) S[q] = S[q] + flip_sign(a, fma(-t[q], a, b));
+  });
+#pragma unroll
+  for (int q = 0; q < 3; ++q) T[q] = wave_total_dbl(S[q]);
+}
+
+enum : int { FAST_HIT, FAST_ABOVE, FAST_UNSURE };
+
+// The first listed row, in (ratio, row) order, whose prefix weight reaches D
+// (> tol): FAST_HIT with its ratio and row; FAST_ABOVE when the whole list
+// weighs less than D; FAST_UNSURE when it is too close to call.  [blo, bhi]:
+// the range the bins divide.  A target bin of more than 64 rows is divided
+// again: over the range of its ratios, or, where they are all the same (whole
+// numbers tie often), over the rows.
+__device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, int count, double blo, double bhi,
+                                             double D, double tol, double &v, int &row) {
+  const int lane = s.lane;
+  double scale = 64.0 / (bhi - blo);
+  scale = bhi > blo && scale < 0x1p1000 ? scale : 0.0;
+  const uint32_t OUT = 0xFFu << 16;               // a row outside the bin being divided
+  bool by_row = false;
+  for (int level = 0; level < 8; ++level) {
+    fs->bin[lane] = 0.0;
+    wave_lds_sync();
+    constexpr int GB = 4;
+    for (int e0 = 0; e0 < count; e0 += 64 * GB) {
+      uint32_t x[GB];
+      double av[GB], bv[GB];
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        const int e = e0 + 64 * q + lane;
+        x[q] = e < count ? fs->list[e] : OUT;
+      }
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        const int r = (int)(x[q] & 0xFFFFu);
+        av[q] = sxj_at(s, r);
+        bv[q] = gld(s.xk + r);
+      }
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        if (e0 + 64 * q >= count) break;
+        const double r = by_row ? (double)(x[q] & 0xFFFFu) : bv[q] / av[q];
+        const int bi = (int)min((uint32_t)fmax((r - blo) * scale, 0.0), 63u);
+        if (x[q] < OUT) {
+          fs->list[e0 + 64 * q + lane] = (x[q] & 0xFFFFu) | ((uint32_t)bi << 16);
+          unsafeAtomicAdd(&fs->bin[bi], fabs(av[q]));
+        }
+      }
+    }
+    wave_lds_sync();
+    const double w = fs->bin[lane], incl = wave_scan_dbl(w);
+    if (__ballot(fabs(incl - D) <= tol)) return FAST_UNSURE;
+    const uint64_t reach = __ballot(incl >= D);
+    if (reach == 0) return level == 0 ? FAST_ABOVE : FAST_UNSURE;
+    const int bt = __builtin_ctzll(reach);
+    D = D - (readlane_dbl(incl, bt) - readlane_dbl(w, bt));
+    // the target bin's rows, one per lane
+    uint32_t *cr = (uint32_t *)fs->bin;
+    int nc = 0;
+    wave_lds_sync();
+    for (int e0 = 0; e0 < count; e0 += 64) {
+      const int e = e0 + lane;
+      const uint32_t y = e < count ? fs->list[e] : OUT;
+      const bool in = (y >> 16) == (uint32_t)bt;
+      const uint64_t m = __ballot(in);
+      const int pos = nc + lanes_below(m);
+      nc += __builtin_popcountll(m);
+      if (in && pos < 64) cr[pos] = y & 0xFFFFu;
+    }
+    nc = uni_int(nc);
+    wave_lds_sync();
+    if (nc <= 64) {
+      const int myrow = lane < nc ? (int)cr[lane] : 0;
+      const double a = sxj_at(s, myrow), r = gld(s.xk + myrow) / a, wa = fabs(a);
+      double run = 0.0;
+      for (int i = 0; i < nc; ++i) {
+        const double ri = readlane_dbl(r, i), wi = readlane_dbl(wa, i);
+        const int rowi = __builtin_amdgcn_readlane(myrow, i);
+        run = run + ((ri < r || (ri == r && rowi <= myrow)) ? wi : 0.0);
+      }
+      const bool mine = lane < nc;
+      if (__ballot(mine && fabs(run - D) <= tol)) return FAST_UNSURE;
+      const uint64_t sel = __ballot(mine && run >= D && run - wa < D);
+      if (__builtin_popcountll(sel) != 1) return FAST_UNSURE;
+      const int l = __builtin_ctzll(sel);
+      v = readlane_dbl(r, l);
+      row = __builtin_amdgcn_readlane(myrow, l);
+      return FAST_HIT;
+    }
+    // too many: only the bin's rows stay, over the range of their ratios
+    double rmin = __builtin_inf(), rmax = -__builtin_inf();
+    for (int e = lane; e < count; e += 64) {
+      const uint32_t y = fs->list[e];
+      const int r = (int)(y & 0xFFFFu);
+      const bool in = (y >> 16) == (uint32_t)bt;
+      const double ra = by_row ? (double)r : gld(s.xk + r) / sxj_at(s, r);
+      rmin = in ? fmin(rmin, ra) : rmin;
+      rmax = in ? fmax(rmax, ra) : rmax;
+      if (!in) fs->list[e] = (uint32_t)r | OUT;
+    }
+    blo = wave_min_dbl_x(rmin);
+    bhi = wave_max_dbl_x(rmax);
+    if (!by_row && !(bhi > blo)) {
+      by_row = true;
+      blo = 0.0;
+      bhi = (double)s.n;
+    }
+    scale = 64.0 / (bhi - blo);
+    scale = scale < 0x1p1000 ? scale : 0.0;
+    wave_lds_sync();
+  }
+  return FAST_UNSURE;
+}
+
+// The minimiser of segment s at one penalty, on side neg; sa, sb: the sorted
+// sample (top 32 bits of the keys; index 2 l + c in lane l), c0 the target's
+// expected place in it.  false: unsettled.
+// The window starts WDELTA of the weight either side of the target's place
+// in the sample (which is off by about 0.044, one sigma); a target outside it
+// moves it on.  Windows whose samples promise more rows than the list holds
+// (from about 2500 rows) are first cut by probe passes at three sample keys,
+// two or three apart as the bracket shrinks, and inside one sample's gap
+// (from about 26000 rows) at quarters of its range.
+template <class LdJ, class LdK>
+__device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool neg, double lam, double Wd,
+                                         uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
+  constexpr double WDELTA = 0.08;
+  const double tol = 0x1p-38 * Wd;
+  // sample values with low bits no simple fraction has: a ratio equal to a
+  // bound cannot be settled here
+  auto value = [&](int ix) {
+    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1);
+    return ratio_of_key(((uint64_t)p << 32) | 0x9E3779B1u);
+  };
+  // samples on the target's side: [first, last)
+  const uint32_t kz = (uint32_t)(key_of(neg ? -FAST_ZERO : FAST_ZERO) >> 32);
+  const int nb = __builtin_popcountll(__ballot(sa < kz)) + __builtin_popcountll(__ballot(sb < kz));
+  const int lmin = neg ? -1 : nb - 1, rmax = neg ? nb : SAMPLE_ROWS;
+  auto bound = [&](int ix) {
+    return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix);
+  };
+  auto target = [&](double T) { return 0.5 * (neg ? T + lam : T - lam); };
+  double c = c0;
+  int il = max((int)floor(c - WDELTA * SAMPLE_ROWS) - 1, lmin), ir = min((int)ceil(c + WDELTA * SAMPLE_ROWS), rmax);
+  if (neg) il = max(min(il, rmax - 3), lmin);
+  else ir = min(max(ir, lmin + 3), rmax);
+  double lo = bound(il), hi = bound(ir);
+  double est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);   // rows the window may list
+  for (int it = 0; it < 12; ++it) {
+    if (est > 0.8 * FAST_CAP) {
+      // cut the bracket at three points
+      double t[3], T[3];
+      int ix[3];
+      const bool by_sample = ir - il >= 2;
+      if (by_sample) {
+        const int h = max(1, (ir - il + 2) / 6), mid = min(max((int)rint(c), il + 1), ir - 1);
+        ix[0] = max(mid - h, il + 1);
+        ix[1] = mid;
+        ix[2] = min(mid + h, ir - 1);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) t[q] = value(ix[q]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) t[q] = lo + (hi - lo) * (0.25 * (q + 1));
+      }
+      probe_pass(s, ldj, ldk, t, T);
+      double dl = 0.0, dr = 0.0;
+      bool hl = false, hr = false;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const double d = target(T[q]);
+        if (fabs(d) <= tol) return false;
+        if (d > 0.0) {
+          lo = t[q];
+          dl = d;
+          hl = true;
+          if (by_sample) il = ix[q];
+        }
+      }
+#pragma unroll
+      for (int q = 2; q >= 0; --q) {
+        const double d = target(T[q]);
+        if (d < 0.0) {
+          hi = t[q];
+          dr = d;
+          hr = true;
+          if (by_sample) ir = ix[q];
+        }
+      }
+      if (by_sample) {
+        const double per = Wd * (1.0 / SAMPLE_ROWS);
+        c = hl && hr ? il + (ir - il) * (dl / (dl - dr)) : hl ? il + dl / per : ir + dr / per;
+        est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);
+      } else {
+        est *= 0.25;
       }
       continue;
     }
-    const bool neg = sd == 1;
-    const uint64_t klo0 = neg ? 0ull : KEY_ZERO, khi0 = neg ? KEY_ZERO - 1 : KEY_NONE - 1;
-    // the sample's keys (top 32 bits), sorted across the wave
-    const int sr0 = (int)(srows & 0xFFFF), sr1 = (int)(srows >> 16);
-    uint32_t sa = sample_key32(s, sr0, kMulti ? __builtin_amdgcn_rcp(sxj_at(s, sr0)) : sv0),
-             sb = sample_key32(s, sr1, kMulti ? __builtin_amdgcn_rcp(sxj_at(s, sr1)) : sv1);
-    wave_sort2_u32_x(sa, sb, lane);
-    // one penalty: the sorted sample (index 2 l + c in lane l) goes to the
-    // wave's LDS scratch, free until the rounds after the window (several:
-    // the rounds between groups reuse that area, so it stays in registers)
-    if constexpr (!kMulti) {
-      ws->ckey[lane] = ((uint64_t)sb << 32) | sa;
+    double T;
+    int count;
+    window_pass(s, ldj, ldk, lo, hi, fs->list, FAST_CAP, T, count);
+    const double D = target(T);
+    if (fabs(D) <= tol) return false;
+    if (D < 0.0) {
+      // the target lies at or below lo
+      if (il <= lmin) return false;
+      hi = lo;
+      ir = il;
+      il = max(il - 12, lmin);
+      lo = bound(il);
+      c = 0.5 * (il + ir);
+      est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);
+      continue;
+    }
+    if (count > FAST_CAP) {
+      est = count;
+      continue;
+    }
+    const double blo = il <= lmin && neg ? value(0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1) : hi;
+    const int got = select_listed(s, fs, count, blo, bhi, D, tol, v, row);
+    if (got == FAST_HIT) return v > lo && v < hi;
+    if (got == FAST_UNSURE || ir >= rmax) return false;
+    il = ir;
+    lo = hi;
+    ir = min(ir + 12, rmax);
+    hi = bound(ir);
+    c = 0.5 * (il + ir);
+    est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);
+  }
+  return false;
+}
+
+// ------------------------------------------- several penalties, one segment
+// The same pass with one target per lane (penalties in groups of 64): a window
+// that holds every target's place in the sample is listed once, its rows are
+// sorted once and every lane finds its target by a search over the prefix
+// weights.  A window whose samples promise more rows than the list holds is
+// taken in parts from its lower end, each part's pass serving the targets that
+// lie in it (at 5918 rows and 43 penalties up to 43 passes, one per penalty,
+// before).
+//  The sort is of one 32-bit word per row: the place of its ratio in the
+// window in 23 to 26 bits (a monotone function of the ratio) and its index in
+// the list, 9 to 6 bits: one exchange, one comparison and one select per
+// stage.  Neighbours in the sorted order are then checked against their exact
+// ratios and rows; where two ratios share a word the segment is left to
+// k_seg_rest.
+// 2000 x 2000 with 64 penalties 52.2 -> 27.6 ms (and 5.3 in k_seg_rest), 128
+// uneven matrices with 16 100 -> 62 (and 3.1).
+struct PathScratch {
+  double val[FAST_CAP];             // ratios in list order, then prefix weights in sorted order
+  uint32_t list[FAST_CAP];          // rows in list order, then in sorted order
+};
+
+// lanes (as a 64-bit mask) that keep the larger word of a bitonic stage over
+// E words per lane: element E lane + q, partner lane ^ ls
+template <int E>
+constexpr uint64_t keep_max_mask(int size, int ls) {
+  uint64_t m = 0;
+  for (int l = 0; l < 64; ++l) {
+    const bool up = ((E * l) & size) == 0, lower = (l & ls) == 0;
+    if (up != lower) m |= 1ull << l;
+  }
+  return m;
+}
+__device__ __forceinline__ uint32_t pick(uint64_t keep_max, uint32_t x, uint32_t o) {
+  return ((o < x) != __builtin_amdgcn_inverse_ballot_w64(keep_max)) ? o : x;
+}
+// compare-exchange of x with lane ^ ls (equal words are interchangeable)
+__device__ __forceinline__ uint32_t cmpx_lane(uint32_t x, int ls, uint64_t keep_max) {
+  if (ls >= 16) {
+    // the swap leaves the pair's lower word in p[0] and its upper one in p[1]
+    // on both lanes
+    const auto p = ls == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                            : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return ((p[1] < p[0]) != __builtin_amdgcn_inverse_ballot_w64(keep_max)) ? p[1] : p[0];
+  }
+  return pick(keep_max, x, xswap32(x, ls));
+}
+
+// Bitonic sort of 64 E words, element E lane + q, ascending.
+template <int E>
+__device__ __forceinline__ void wave_sort_u32(uint32_t (&x)[E]) {
+#pragma unroll
+  for (int size = 2; size <= 64 * E; size <<= 1) {
+#pragma unroll
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      if (stride < E) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) {
+          if (q & stride) continue;
+          const uint32_t a = x[q], b = x[q | stride];
+          if (size < E) {
+            const bool up = (q & size) == 0;
+            x[q] = up ? min(a, b) : max(a, b);
+            x[q | stride] = up ? max(a, b) : min(a, b);
+            continue;
+          }
+          const uint64_t down = keep_max_mask<E>(size, 0);   // lanes whose block descends
+          const bool sw = (b < a) != __builtin_amdgcn_inverse_ballot_w64(down);
+          x[q] = sw ? b : a;
+          x[q | stride] = sw ? a : b;
+        }
+      } else {
+        const int ls = stride / E;
+        const uint64_t km = keep_max_mask<E>(size, ls);
+#pragma unroll
+        for (int q = 0; q < E; ++q) x[q] = cmpx_lane(x[q], ls, km);
+      }
+    }
+  }
+}
+
+// The listed rows in (ratio, row) order: ps->list the rows, ps->val the
+// inclusive prefix weights, 64 E entries (the last repeated past count).
+// [blo, bhi]: the range the words divide.  false: two ratios share a word.
+template <int E>
+__device__ __forceinline__ bool sort_listed(const SegIO &s, PathScratch *ps, int count, double blo, double bhi) {
+  constexpr int N = 64 * E, IB = E == 1 ? 6 : E == 2 ? 7 : E == 4 ? 8 : 9;
+  const int lane = s.lane;
+  double scale = (double)(1u << (32 - IB)) / (bhi - blo);
+  scale = bhi > blo && scale < 0x1p1000 ? scale : 0.0;
+  uint32_t x[E];
+  {
+    int rw[E];
+    double av[E], bv[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) rw[q] = 64 * q + lane < count ? (int)ps->list[64 * q + lane] : 0;
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      av[q] = sxj_at(s, rw[q]);
+      bv[q] = gld(s.xk + rw[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      const int e = 64 * q + lane;
+      const double r = bv[q] / av[q];
+      ps->val[e] = r;
+      const uint32_t w = min((uint32_t)fmax((r - blo) * scale, 0.0), (1u << (32 - IB)) - 1u);
+      x[q] = e < count ? (w << IB) | (uint32_t)e : ~0u;
+    }
+  }
+  wave_sort_u32<E>(x);
+  wave_lds_sync();
+  // the entries E lane + q: rows, ratios and the next lane's first pair
+  uint32_t rw[E + 1];
+  double r[E + 1], w[E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int id = E * lane + q < count ? (int)(x[q] & (N - 1)) : 0;
+    rw[q] = ps->list[id];
+    r[q] = ps->val[id];
+  }
+  {
+    const uint32_t nx = (uint32_t)__shfl_down((int)x[0], 1);
+    const int id = E * lane + E < count ? (int)(nx & (N - 1)) : 0;
+    rw[E] = ps->list[id];
+    r[E] = ps->val[id];
+  }
+  bool bad = false;
+#pragma unroll
+  for (int q = 0; q < E; ++q)
+    bad = bad || (E * lane + q + 1 < count && !(r[q] < r[q + 1] || (r[q] == r[q + 1] && rw[q] < rw[q + 1])));
+  if (__ballot(bad)) return false;
+  double tot = 0.0;
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const bool in = E * lane + q < count;
+    w[q] = in ? fabs(sxj_at(s, (int)rw[q])) : 0.0;
+    tot = tot + w[q];
+  }
+  double run = wave_scan_dbl(tot) - tot;
+  wave_lds_sync();
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    run = run + w[q];
+    ps->val[E * lane + q] = run;
+    ps->list[E * lane + q] = rw[q];
+  }
+  wave_lds_sync();
+  return true;
+}
+
+// The minimisers of segment s for the penalties of the lanes with act (lam the
+// lane's penalty, c its target's expected place in the sample sa, sb); v and
+// row on those lanes.  false: some target is unsettled.
+template <class LdJ, class LdK>
+__device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool neg, bool act, double lam, double Wd,
+                                          uint32_t sa, uint32_t sb, double c, PathScratch *ps, double &v, int &row) {
+  constexpr double WDELTA = 0.08;
+  const int lane = s.lane;
+  const double tol = 0x1p-38 * Wd;
+  auto value = [&](int ix) {
+    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1);
+    return ratio_of_key(((uint64_t)p << 32) | 0x9E3779B1u);
+  };
+  const uint32_t kz = (uint32_t)(key_of(neg ? -FAST_ZERO : FAST_ZERO) >> 32);
+  const int nb = __builtin_popcountll(__ballot(sa < kz)) + __builtin_popcountll(__ballot(sb < kz));
+  const int lmin = neg ? -1 : nb - 1, rmax = neg ? nb : SAMPLE_ROWS;
+  auto bound = [&](int ix) {
+    return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix);
+  };
+  const int cl = (int)floor(c - WDELTA * SAMPLE_ROWS) - 1, cr = (int)ceil(c + WDELTA * SAMPLE_ROWS);
+  const double per = (double)s.n * (1.0 / SAMPLE_ROWS);   // rows a sample stands for
+  const int step = max(1, (int)(0.8 * FAST_CAP / per));   // samples a window may span
+  uint64_t pend = __ballot(act), low = 0;
+  // [il, iend): what the pending targets' windows span
+  int il = max(min(wave_min_int_x(act ? cl : SAMPLE_ROWS), neg ? rmax - 3 : SAMPLE_ROWS), lmin);
+  int iend = min(max(wave_max_int_x(act ? cr : -1), neg ? -1 : lmin + 3), rmax);
+  double lo = bound(il);
+  int shrink = 0, start = il;
+  for (int it = 0; it < 160 && pend; ++it) {
+    // the next window: [lo, hi), hi at sample ir or (shrink) inside a gap
+    int ir = min(il + step, max(iend, il + 1));
+    ir = min(ir, rmax);
+    if (ir <= il) return false;
+    double hi = bound(ir);
+    if (shrink > 0) {
+      if ((ir - il) >> shrink) {
+        ir = il + ((ir - il) >> shrink);
+        hi = bound(ir);
+      } else {
+        if (shrink > 12 || il <= lmin || il + 1 >= rmax) return false;
+        hi = lo + (bound(il + 1) - lo) * ldexp(1.0, -2 * shrink);
+        ir = il;                                   // (the window ends inside the gap)
+      }
+    }
+    double T;
+    int count;
+    window_pass(s, ldj, ldk, lo, hi, ps->list, FAST_CAP, T, count);
+    if (count > FAST_CAP) {
+      ++shrink;
+      continue;
+    }
+    const bool mine = ((pend >> lane) & 1ull) != 0;
+    const double D = 0.5 * (neg ? T + lam : T - lam);
+    if (__ballot(mine && fabs(D) <= tol)) return false;
+    low |= __ballot(mine && D < 0.0);
+    pend &= ~low;
+    if (pend && count > 0) {
+      const double blo = il <= lmin && neg ? value(0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1) : hi;
+      const bool ok = count <= 64 ? sort_listed<1>(s, ps, count, blo, bhi)
+                      : count <= 128 ? sort_listed<2>(s, ps, count, blo, bhi)
+                      : count <= 256 ? sort_listed<4>(s, ps, count, blo, bhi)
+                                     : sort_listed<8>(s, ps, count, blo, bhi);
+      if (!ok) return false;
+      // first entry whose prefix weight reaches D
+      int p = 0;
+      for (int h = count <= 64 ? 32 : count <= 128 ? 64 : count <= 256 ? 128 : 256; h; h >>= 1)
+        if (ps->val[p + h - 1] < D) p += h;
+      const double at = ps->val[p], before = p > 0 ? ps->val[p - 1] : 0.0;
+      const bool here = mine && D > 0.0;
+      const bool hit = here && at >= D;
+      const int rr = (int)ps->list[p];
+      const double vv = gld(s.xk + rr) / sxj_at(s, rr);
+      if (__ballot(here && (fabs(at - D) <= tol || fabs(before - D) <= tol)) ||
+          __ballot(hit && !(vv > lo && vv < hi)))
+        return false;
+      if (hit) {
+        v = vv;
+        row = rr;
+      }
+      pend &= ~__ballot(hit);
       wave_lds_sync();
     }
-    // sample position ix as a lower or upper key bound
-    auto sample_lo = [&](int ix) {
-      if constexpr (!kMulti) return sample_key(ws->ckey, ix);
-      return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1)) << 32;
-    };
-    auto sample_hi = [&](int ix) { return sample_lo(ix) | 0xFFFFFFFFull; };
-    int prev_row = -2;
-    double prev_e = 0.0;
-    // penalties in groups of 64, lane l holding the target of penalty 64 g + l
-    for (int g = 0; 64 * g < Lg; ++g) {
-      const uint64_t nzg = g ? nz1 : nz0;
-      const int tl = 64 * g + lane;
-      const bool act = ((nzg >> lane) & 1ull) != 0;
-      // negative side: first S_p > (W + lambda)/2; positive: first S_p >= (W - lambda)/2
-      double q = 2.0;
-      if (act) {
-        const double lamt = lam[tl];
-        q = (neg ? 0.5 * (Wd + lamt) : 0.5 * (Wd - lamt)) / Wd;
+    shrink = 0;
+    lo = hi;
+    il = ir;
+    if (pend == 0 && low) {
+      // targets below the first window: from further down, up to it
+      if (start <= lmin) return false;
+      pend = low;
+      low = 0;
+      iend = start;
+      il = start = max(start - 13, lmin);
+      lo = bound(il);
+    } else if (pend) {
+      // (nothing is expected before the pending targets' windows)
+      const int nx = min(wave_min_int_x(((pend >> lane) & 1ull) ? cl : SAMPLE_ROWS), rmax - 1);
+      if (nx > il) {
+        il = nx;
+        lo = bound(il);
       }
-      // window bounds on the targets' weight fractions (positive doubles
-      // order as their bit patterns)
-      double qmin, qmax;
-      if constexpr (!kMulti) {
-        // one penalty: lane 0's target (no cross-lane reduction)
-        qmin = qmax = __longlong_as_double((long long)uni_u64((uint64_t)__double_as_longlong(fmax(q, 0.0))));
-      } else {
-        qmin = __longlong_as_double((long long)wave_min_u64_x((uint64_t)__double_as_longlong(fmax(q, 0.0))));
-        qmax = __longlong_as_double((long long)wave_max_u64_x((uint64_t)__double_as_longlong(act ? fmax(q, 0.0) : 0.0)));
-      }
-      uint64_t okey = KEY_NONE;
-      int orow = -1;
-      bool hit = false;
-      // the ratios of the weighted row sample bracket the targets: a key
-      // window; one exact pass lists the window's elements, one sort serves
-      // every penalty.  A window too wide for the list is retried per penalty.
-      for (int pass = 0; nzg && pass <= (kMulti ? 64 : 0); ++pass) {
-        double wlo = qmin, whi = qmax;
-        bool mine = act;
-        if (pass > 0) {
-          const int t = pass - 1;
-          if (!((nzg >> t) & 1ull) || __builtin_amdgcn_readlane((int)hit, t)) continue;
-          wlo = whi = readlane_dbl(q, t);
-          mine = lane == t;
-        }
-        constexpr double WDELTA = 0.08;
-        const int ilo = (int)floor((wlo - WDELTA) * SAMPLE_ROWS) - 1;
-        const int ihi = (int)ceil((whi + WDELTA) * SAMPLE_ROWS);
-        uint64_t plo = klo0, phi = khi0;
-        if (ilo >= 0 && ilo < SAMPLE_ROWS) {
-          const uint64_t v = sample_lo(ilo);
-          plo = v > plo ? v : plo;
-        }
-        if (ihi >= 0 && ihi < SAMPLE_ROWS) {
-          const uint64_t v = sample_hi(ihi);
-          phi = v < phi ? v : phi;
-        }
-        if (plo > khi0) plo = khi0;
-        if (phi < plo) phi = plo;
+      iend = max(iend, il + 12);
+    }
+  }
+  return pend == 0;
+}
 
-        const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, n), rj = col_rsrc(s.lds ? s.xk : s.sxj, n);
-        // columns read through the range-checked descriptor (0 past row n)
-        // or the zero-padded LDS copy: no clamps
-        auto ldjp = [&](int i) { return sxj_pad(s, rj, i); };
-        auto ldkp = [&](int i) { return col_ld(rk, i * 8); };
-        // the division-free pass first; the exact pass when the columns'
-        // ranges rule the fast one out, or when the weight below the window,
-        // known from it only within an interval, leaves the selection open
-        bool use_fast = fast_seg;
-        bool ovf = false;
-        bool probe = false;
-        ws->steps = 0;
-        while (true) {
-          int nwin = 0;
-          u128 SlwA, SlwB;
-          if (use_fast) {
-            fast_window_pass(s, ldjp, ldkp, plo, phi, lk, lr, lcap, nwin, SlwA, SlwB);
-          } else {
-            // exact pass: weight at or below the window; the window's
-            // elements go to the LDS list (in row order).  The weight below
-            // the window in three FP64 sums of 37-bit chunks (whole numbers
-            // below 2^53: every add is exact)
-            double c0s = 0.0, c1s = 0.0, c2s = 0.0;
-            // columns j and k are read one slot ahead so the loads overlap
-            // the divide; the weight reuses x_ij (one penalty: rows past n
-            // read 0, key NONE and no weight; several: clamped to row 0,
-            // which spills less there)
-            auto ldj = [&](int i) { return kMulti ? sxj_at(s, i < n ? i : 0) : ldjp(i); };
-            auto ldk = [&](int i) { return kMulti ? gld(s.xk + (i < n ? i : 0)) : ldkp(i); };
-            double anext = ldj(lane), bnext = ldk(lane);
-            for (int tt = 0; tt < T; ++tt) {
-              const int i = lane + 64 * tt;
-              const double a = anext, b = bnext;
-              if (tt + 1 < T) {
-                anext = ldj(i + 64);
-                bnext = ldk(i + 64);
-              }
-              const uint64_t key = key_of_pair(i < n, a, b);
-              const bool valid = key != KEY_NONE;
-              const bool le_lo = valid && key <= plo;
-              const bool inwin = valid && key > plo && key <= phi;
-              {
-                double c0, c1, c2;
-                weight_chunks(a, s.e0, c0, c1, c2);
-                // masked adds as fma with a 0/1 factor: the same exact sums
-                // (whole numbers below 2^53; c 0 adds +0), one op each
-                const double fl = le_lo ? 1.0 : 0.0;
-                c0s = fma(c0, fl, c0s);
-                c1s = fma(c1, fl, c1s);
-                c2s = fma(c2, fl, c2s);
-              }
-              const uint64_t wm = __ballot(inwin);
-              const int pos = nwin + lanes_below(wm);
-              nwin += __builtin_popcountll(wm);
-              if (inwin && pos < lcap) {
-                lk[pos] = key;
-                lr[pos] = (unsigned short)i;
-              }
+// ------------------------------------------------- segments left to the end
+// One segment by one wave with exact 128-bit sums and the general rounds:
+// what the division-free kernels leave (columns outside their range, sums too
+// close to call, ties, windows that missed).  Any number of penalties.
+//  1. the sign sums dz decide the side of every penalty, the exact pass
+//     where they cannot;
+//  2. a key window from the row sample is listed with the exact weight below
+//     it, sorted and scanned exactly;
+//  3. whatever the window does not settle goes to the general rounds.
+__device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, const ColInfo &ck,
+                                          const unsigned short *__restrict__ smp, const double *__restrict__ lam, int L,
+                                          double2 dz, const u128 *slam, WaveScratch *ws, uint64_t *lk,
+                                          unsigned short *lr, int lcap, double *__restrict__ V,
+                                          double *__restrict__ E, int *__restrict__ R, long long base, long long mm,
+                                          int &err) {
+  const int lane = s.lane, n = s.n, T = s.T;
+  const double Wd = cj.W;
+  const double Wk = ck.W;
+
+  // 1. sign sums.  |x_ik / x_ij| can underflow to 0 only if the exponent
+  // fields differ by more than 1000: the column ranges rule that out for the
+  // whole segment in the usual case, else the exact pass decides.
+    const bool unc = sign_sums_unsure(cj, ck, dz);
+
+  bool have_exact = false;
+  ExactSides ex;
+  const u128 W = cj.wfix;
+  // (a) the side of every penalty: v_k = 0, or the minimiser is negative
+  // (1) or positive (2).  A <= B makes the nonzero side the same for every
+  // penalty of the segment.
+  uint64_t nz0 = 0, nz1 = 0;                     // bit t: v_k != 0 at penalty t
+  int sd = 0;
+  // one penalty per lane, in groups of 64
+  for (int g0 = 0; g0 < L; g0 += 64) {
+    const int t = g0 + lane;
+    const bool in = t < L;
+    int side = 0;
+    if (in) side = sign_sum_side(dz, lam[t], Wd, unc);
+    if (__ballot(side == 3)) {
+      if (!have_exact) {
+        ex = exact_sides(s);
+        have_exact = true;
+      }
+      if (side == 3) {
+        const u128 lamf = slam[t], WpL = W + lamf;
+        side = ((ex.A << 1) <= WpL && W <= (ex.B << 1) + lamf) ? 0 : ((ex.A << 1) > WpL ? 1 : 2);
+      }
+    }
+    const uint64_t nzm = __ballot(side != 0);
+    if (g0 == 0) nz0 = nzm;
+    else nz1 = nzm;
+    // every nonzero penalty has the same side (A <= B)
+    if (nzm) sd = __builtin_amdgcn_readlane(side, __builtin_ctzll(nzm));
+  }
+  if ((nz0 | nz1) == 0) {
+    // v_k = 0 at every penalty: e_jk = R64 sum of |x_ik|
+    for (int t = lane; t < L; t += 64) {
+      V[t * mm + base] = 0.0;
+      E[t * mm + base] = Wk;
+      R[t * mm + base] = -1;
+    }
+    return;
+  }
+  const bool neg = sd == 1;
+  const uint64_t klo0 = neg ? 0ull : KEY_ZERO, khi0 = neg ? KEY_ZERO - 1 : KEY_NONE - 1;
+  // the sample's keys (top 32 bits), sorted across the wave
+  const int sr0 = smp[lane], sr1 = smp[64 + lane];
+  uint32_t sa = sample_key32(s, sr0, __builtin_amdgcn_rcp(sxj_at(s, sr0))),
+           sb = sample_key32(s, sr1, __builtin_amdgcn_rcp(sxj_at(s, sr1)));
+  wave_sort2_u32_x(sa, sb, lane);
+  // sample position ix as a lower or upper key bound
+  auto sample_lo = [&](int ix) { return sample_key(ws->ckey, ix); };
+  auto sample_hi = [&](int ix) { return sample_lo(ix) | 0xFFFFFFFFull; };
+  int prev_row = -2;
+  double prev_e = 0.0;
+  // penalties in groups of 64, lane l holding the target of penalty 64 g + l
+  for (int g = 0; 64 * g < L; ++g) {
+    const uint64_t nzg = g ? nz1 : nz0;
+    const int tl = 64 * g + lane;
+    const bool act = ((nzg >> lane) & 1ull) != 0;
+    // negative side: first S_p > (W + lambda)/2; positive: first S_p >= (W - lambda)/2
+    double q = 2.0;
+    if (act) {
+      const double lamt = lam[tl];
+      q = (neg ? 0.5 * (Wd + lamt) : 0.5 * (Wd - lamt)) / Wd;
+    }
+    // window bounds on the targets' weight fractions (positive doubles
+    // order as their bit patterns)
+    const double qmin = __longlong_as_double((long long)wave_min_u64_x((uint64_t)__double_as_longlong(fmax(q, 0.0))));
+    const double qmax =
+        __longlong_as_double((long long)wave_max_u64_x((uint64_t)__double_as_longlong(act ? fmax(q, 0.0) : 0.0)));
+    // the sorted sample (index 2 l + c in lane l) in the wave's LDS scratch,
+    // which the rounds of an earlier group may have used
+    ws->ckey[lane] = ((uint64_t)sb << 32) | sa;
+    wave_lds_sync();
+    uint64_t okey = KEY_NONE;
+    int orow = -1;
+    bool hit = false;
+    // the ratios of the weighted row sample bracket the targets: a key
+    // window; one exact pass lists the window's elements, one sort serves
+    // every penalty.  A window too wide for the list is retried per penalty.
+    for (int pass = 0; nzg && pass <= 64; ++pass) {
+      double wlo = qmin, whi = qmax;
+      bool mine = act;
+      if (pass > 0) {
+        const int t = pass - 1;
+        if (!((nzg >> t) & 1ull) || __builtin_amdgcn_readlane((int)hit, t)) continue;
+        wlo = whi = readlane_dbl(q, t);
+        mine = lane == t;
+      }
+      constexpr double WDELTA = 0.08;
+      const int ilo = (int)floor((wlo - WDELTA) * SAMPLE_ROWS) - 1;
+      const int ihi = (int)ceil((whi + WDELTA) * SAMPLE_ROWS);
+      uint64_t plo = klo0, phi = khi0;
+      if (ilo >= 0 && ilo < SAMPLE_ROWS) {
+        const uint64_t v = sample_lo(ilo);
+        plo = v > plo ? v : plo;
+      }
+      if (ihi >= 0 && ihi < SAMPLE_ROWS) {
+        const uint64_t v = sample_hi(ihi);
+        phi = v < phi ? v : phi;
+      }
+      if (plo > khi0) plo = khi0;
+      if (phi < plo) phi = plo;
+
+      bool ovf = false;
+      bool probe = false;
+      ws->steps = 0;
+      while (true) {
+        int nwin = 0;
+        u128 Slw;
+        {
+          // exact pass: weight at or below the window; the window's
+          // elements go to the LDS list (in row order).  The weight below
+          // the window in three FP64 sums of 37-bit chunks (whole numbers
+          // below 2^53: every add is exact)
+          double c0s = 0.0, c1s = 0.0, c2s = 0.0;
+          // columns j and k are read one slot ahead so the loads overlap
+          // the divide; the weight reuses x_ij
+          auto ldj = [&](int i) { return sxj_at(s, i < n ? i : 0); };
+          auto ldk = [&](int i) { return gld(s.xk + (i < n ? i : 0)); };
+          double anext = ldj(lane), bnext = ldk(lane);
+          for (int tt = 0; tt < T; ++tt) {
+            const int i = lane + 64 * tt;
+            const double a = anext, b = bnext;
+            if (tt + 1 < T) {
+              anext = ldj(i + 64);
+              bnext = ldk(i + 64);
             }
-            SlwA = SlwB = chunks_to_u128(wave_sum_dbl_x(c0s), wave_sum_dbl_x(c1s), wave_sum_dbl_x(c2s));
-            nwin = uni_int(nwin);
-            wave_lds_sync();
+            const uint64_t key = key_of_pair(i < n, a, b);
+            const bool valid = key != KEY_NONE;
+            const bool le_lo = valid && key <= plo;
+            const bool inwin = valid && key > plo && key <= phi;
+            {
+              double c0, c1, c2;
+              weight_chunks(a, s.e0, c0, c1, c2);
+              // masked adds as fma with a 0/1 factor: the same exact sums
+              // (whole numbers below 2^53; c 0 adds +0), one op each
+              const double fl = le_lo ? 1.0 : 0.0;
+              c0s = fma(c0, fl, c0s);
+              c1s = fma(c1, fl, c1s);
+              c2s = fma(c2, fl, c2s);
+            }
+            const uint64_t wm = __ballot(inwin);
+            const int pos = nwin + lanes_below(wm);
+            nwin += __builtin_popcountll(wm);
+            if (inwin && pos < lcap) {
+              lk[pos] = key;
+              lr[pos] = (unsigned short)i;
+            }
           }
-          const u128 lamf = act ? slam[tl] : (u128)0;
-          const u128 tau = neg ? ((W + lamf) >> 1) + 1 : (W - lamf + 1) >> 1;
-          if (!kMulti && use_fast && (probe || nwin > lcap)) {
-            // one target and division-free classes: a window too full for
-            // the list is bisected.  (blo, phi] holds the target and about
-            // bcnt elements; a probe pass over (plo, phi], plo inside it,
-            // gives the weight at or below plo, which names the half.
-            const uint64_t tm = __ballot(mine && !hit);
-            if (__builtin_popcountll(tm) == 1 && ws->steps < 12) {
-              const bool at_or_below = readlane_u128(tau, __builtin_ctzll(tm)) <= SlwA;
-              bool more = true;
-              if (!probe) {
-                // the window itself: the target at or below it is a miss
-                if (at_or_below) {
-                  ovf = true;
-                  break;
-                }
-                ws->blo = plo;
-                ws->bcnt = nwin;
-              } else if (at_or_below) {
-                // at or below the probe point: (blo, plo], not listed yet
-                ws->bcnt -= nwin;
-                phi = plo;
-                plo = ws->blo;
-              } else {
-                ws->blo = plo;
-                ws->bcnt = nwin;
-                more = nwin > lcap;
+          Slw = chunks_to_u128(wave_sum_dbl_x(c0s), wave_sum_dbl_x(c1s), wave_sum_dbl_x(c2s));
+          nwin = uni_int(nwin);
+          wave_lds_sync();
+        }
+        const u128 lamf = act ? slam[tl] : (u128)0;
+        const u128 tau = neg ? ((W + lamf) >> 1) + 1 : (W - lamf + 1) >> 1;
+        if (probe || nwin > lcap) {
+          // one target: a window too full for the list is bisected.  (blo,
+          // phi] holds the target and about bcnt elements; a probe pass
+          // over (plo, phi], plo inside it, gives the weight at or below
+          // plo, which names the half.
+          const uint64_t tm = __ballot(mine && !hit);
+          if (__builtin_popcountll(tm) == 1 && ws->steps < 12) {
+            const bool at_or_below = readlane_u128(tau, __builtin_ctzll(tm)) <= Slw;
+            bool more = true;
+            if (!probe) {
+              // the window itself: the target at or below it is a miss
+              if (at_or_below) {
+                ovf = true;
+                break;
               }
-              probe = false;
-              if (more) {
-                ws->steps += 1;
-                if (ws->bcnt <= lcap) continue;      // list (blo, phi] in one pass
-                uint64_t mid;
-                if (!window_midpoint(ws->ckey, plo, phi, mid)) {
-                  ovf = true;
-                  break;
-                }
-                plo = mid;
-                probe = true;
-                continue;
-              }
+              ws->blo = plo;
+              ws->bcnt = nwin;
+            } else if (at_or_below) {
+              // at or below the probe point: (blo, plo], not listed yet
+              ws->bcnt -= nwin;
+              phi = plo;
+              plo = ws->blo;
+            } else {
+              ws->blo = plo;
+              ws->bcnt = nwin;
+              more = nwin > lcap;
             }
             probe = false;
-          }
-          if (nwin > lcap) {
-            ovf = true;
-            break;
-          }
-          const bool want = mine && !hit;
-          const uint64_t wantm = __ballot(want);
-          u128 SloA = SlwA, SloB = SlwB;
-          bool amb = false;
-          if constexpr (!kMulti) {
-            if (use_fast) {
-              // one target after the division-free pass: the rest in FP64
-              // with rigorous margins (a close call is redone exactly)
-              uint64_t piv[3];
-#pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                int ix = (int)floor((wlo + 0.04 * (c - 1)) * SAMPLE_ROWS);
-                ix = ix < 0 ? 0 : (ix >= SAMPLE_ROWS ? SAMPLE_ROWS - 1 : ix);
-                piv[c] = sample_lo(ix);
+            if (more) {
+              ws->steps += 1;
+              if (ws->bcnt <= lcap) continue;      // list (blo, phi] in one pass
+              uint64_t mid;
+              if (!window_midpoint(ws->ckey, plo, phi, mid)) {
+                ovf = true;
+                break;
               }
-              uint64_t k2 = KEY_NONE;
-              int r2 = -1;
-              bool h2 = false;
-              if (wantm & 1ull)
-                select_one_fp64(s, lk, lr, nwin, lane, SlwA, SlwB, uni_u128(tau), Wd, piv, k2, r2, h2, amb);
-              if (!amb && h2 && lane == 0) {
-                okey = k2;
-                orow = r2;
-                hit = true;
-              }
-              wave_lds_sync();
-              if (!amb) break;
-              use_fast = false;
+              plo = mid;
+              probe = true;
               continue;
             }
           }
-          if (__builtin_popcountll(wantm) == 1 && nwin > 128) {
-            // one target: only the quarter of the window that holds it is
-            // sorted.  Three sample keys around the target split the list;
-            // the exact weights below them pick the part (a contiguous range
-            // of the sorted order), which is compacted to the list's front.
-            const u128 tau1 = uni_u128(shfl_u128(tau, __builtin_ctzll(wantm)));
-            uint64_t piv[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              int ix = (int)floor((wlo + 0.04 * (c - 1)) * SAMPLE_ROWS);
-              ix = ix < 0 ? 0 : (ix >= SAMPLE_ROWS ? SAMPLE_ROWS - 1 : ix);
-              piv[c] = sample_lo(ix);
-            }
-            piv[1] = piv[1] < piv[0] ? piv[0] : piv[1];
-            piv[2] = piv[2] < piv[1] ? piv[1] : piv[2];
-            u128 a0 = 0, a1 = 0, a2 = 0;
-            for (int e = lane; e < nwin; e += 64) {
-              const uint64_t key = lk[e];
-              const u128 w = fixed_of_col(sxj_at(s, lr[e]), s.e0);
-              a0 += key < piv[0] ? w : (u128)0;
-              a1 += key < piv[1] ? w : (u128)0;
-              a2 += key < piv[2] ? w : (u128)0;
-            }
-            a0 = wave_sum_u128_x(a0);
-            a1 = wave_sum_u128_x(a1);
-            a2 = wave_sum_u128_x(a2);
-            const int c = (SlwA + a0 < tau1 ? 1 : 0) + (SlwA + a1 < tau1 ? 1 : 0) + (SlwA + a2 < tau1 ? 1 : 0);
-            const int cB = (SlwB + a0 < tau1 ? 1 : 0) + (SlwB + a1 < tau1 ? 1 : 0) + (SlwB + a2 < tau1 ? 1 : 0);
-            if (c != cB) {
-              amb = true;
-            } else {
-              const uint64_t plo2 = c == 0 ? 0 : piv[c - 1], phi2 = c == 3 ? KEY_NONE : piv[c];
-              const u128 ac = c == 0 ? (u128)0 : (c == 1 ? a0 : (c == 2 ? a1 : a2));
-              SloA = SlwA + ac;
-              SloB = SlwB + ac;
-              // stable in-place compaction: an element never moves above its
-              // own slot, so slots not yet read are never overwritten
-              int kept = 0;
-              for (int e0 = 0; e0 < nwin; e0 += 64) {
-                const int e = e0 + lane;
-                const bool in = e < nwin;
-                const uint64_t key = in ? lk[e] : 0;
-                const unsigned short row = in ? lr[e] : 0;
-                const bool keep = in && (c == 0 || key >= plo2) && (c == 3 || key < phi2);
-                const uint64_t km = __ballot(keep);
-                const int d = kept + lanes_below(km);
-                kept += __builtin_popcountll(km);
-                if (keep) {
-                  lk[d] = key;
-                  lr[d] = row;
-                }
-              }
-              nwin = uni_int(kept);
-              wave_lds_sync();
-            }
-          }
-          if (!amb) {
-            const int N = wave_sort_list(lk, lr, nwin, lane);
-            u128 tot, incl;
-            wave_list_sums(s, lk, lr, N >> 6, tot, incl);
-            uint64_t k2 = KEY_NONE;
-            int r2 = -1;
-            bool h2 = false;
-            if constexpr (!kMulti) {
-              // one penalty: its target sits in lane 0
-              if (wantm & 1ull) wave_resolve_one(s, lk, lr, N >> 6, SloA, SloB, tot, incl, uni_u128(tau), k2, r2, h2, amb);
-              h2 = h2 && lane == 0;
-            } else {
-              // the answer must not depend on where in [SloA, SloB] the
-              // exact weight below the list lies
-              bool amb_l = false;
-              wave_resolve(s, lk, lr, N >> 6, SloA, SloB, tot, incl, want, tau, k2, r2, h2, amb_l);
-              amb = __ballot(want && amb_l) != 0;
-            }
-            if (!amb && h2) {
-              okey = k2;
-              orow = r2;
-              hit = true;
-            }
-          }
-          wave_lds_sync();
-          if (!amb) break;
-          use_fast = false;                          // redo the pass exactly
+          probe = false;
         }
-        if (ovf) {
-          // the list cannot hold the window: after the shared window, retry
-          // each penalty with its own; a single penalty goes to the rounds
-          if (pass == 0 && __builtin_popcountll(nzg) == 1) break;
-          continue;
-        }
-        // the shared window held: the targets it missed go to the rounds
-        if (pass == 0) break;
-      }
-
-      // targets the windows missed: rounds over the whole side
-      uint64_t left = __ballot(act && !hit);
-      while (left) {
-        const int t = __builtin_ctzll(left);
-        left &= left - 1;
-        if (!have_exact) {
-          ex = exact_sides(s);
-          have_exact = true;
-        }
-        const u128 lamf = slam[64 * g + t];
-        const u128 tau = neg ? ((W + lamf) >> 1) + 1 : (W - lamf + 1) >> 1;
-        uint64_t k2 = KEY_NONE;
-        int r2 = -1;
-        const ColSrc cs{s, (u128)0, 0};
-        wave_select_rounds(s, cs, klo0, khi0, neg ? (u128)0 : ex.B, neg ? ex.A : W, neg ? 0 : ex.N + ex.Z,
-                           neg ? ex.N : ex.NV, tau, ws, k2, r2, err);
-        if (lane == t) {
-          okey = k2;
-          orow = r2;
-        }
-      }
-
-      if constexpr (!kMulti) {
-        // one penalty (lane 0): the residual of its row, or the column mass
-        // of k where v_k = 0; values taken from lane 0 without shuffles
-        const int orw0 = __builtin_amdgcn_readfirstlane((nzg & 1ull) ? orow : -1);
-        const double v0 = orw0 >= 0 ? ratio_of_key(uni_u64(okey)) : 0.0;
-        const double e0 = orw0 >= 0 ? wave_residual<true>(s, v0) : Wk;   // (the sum in lane 0)
-        if (lane == 0) {
-          V[base] = v0;
-          E[base] = e0;
-          R[base] = orw0;
-        }
-        continue;
-      }
-      // residuals, reused while the selected row repeats: the group's targets
-      // whose row differs from the previous target's are the jobs, scored up
-      // to RJ at a time in one pass over the rows
-      const int tend = min(Lg, 64 * g + 64);
-      const int cnt = tend - 64 * g;
-      int orw_l = -1;
-      double v_l = 0.0;
-      if (lane < cnt && ((nzg >> lane) & 1ull)) {
-        orw_l = orow;
-        v_l = ratio_of_key(okey);
-      }
-      int prv = __shfl_up(orw_l, 1);
-      if (lane == 0) prv = prev_row;
-      const bool need = lane < cnt && orw_l >= 0 && orw_l != prv;
-      const uint64_t needm = __ballot(need);
-      double e_l = 0.0;
-      if (__builtin_popcountll(needm) == 1) {
-        const int jl = __builtin_ctzll(needm);
-        const double e1 = readlane_dbl(wave_residual<!kMulti>(s, readlane_dbl(v_l, jl)), 0);
-        if (lane == jl) e_l = e1;
-      } else if constexpr (kMulti) {
-        // (one penalty: at most one job)
-        uint64_t jm = needm;
-        while (jm) {
-          if (__builtin_popcountll(jm) > 4) run_jobs<8>(s, jm, v_l, lane, e_l);
-          else run_jobs<4>(s, jm, v_l, lane, e_l);
-        }
-      }
-      // each target takes the e of the last job at or before it (or the
-      // previous group's last e when its row continues from there)
-      double e_t;
-      if (orw_l < 0) {
-        e_t = Wk;                                    // R64 sum of |x_ik|
-      } else {
-        const uint64_t upto = needm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-        const double ej = __shfl(e_l, upto ? 63 - __builtin_clzll(upto) : 0);
-        e_t = upto ? ej : prev_e;
-      }
-      if (lane < cnt) {
-        const int t = 64 * g + lane;
-        V[t * mm + base] = orw_l >= 0 ? v_l : 0.0;
-        E[t * mm + base] = e_t;
-        R[t * mm + base] = orw_l;
-      }
-      prev_row = __builtin_amdgcn_readlane(orw_l, cnt - 1);
-      prev_e = readlane_dbl(e_t, cnt - 1);
-    }
-  }
-  if (err && lane == 0) atomicOr(segflags + j, err);
-  __syncthreads();   // the LDS is reused by the next item
-}
-
-// Persistent segment kernel: every workgroup pulls work items from the
-// counter of its XCD until none is left.  Explicit items (a batch) come in
-// one list per XCD, [xstart[x], xstart[x + 1]).  With items == nullptr the
-// items of problem 0 are
-// implicit and routed by XCD: its k range is cut into SEG_XCDS * chunks
-// equal parts, XCD x owns parts [x chunks, (x + 1) chunks) and enumerates
-// them part by part, every preserved column j (or cand[jj]) within a part, so
-// the columns k that the workgroups of one XCD stream stay in its L2.
-// Workgroups are dispatched to the XCDs round-robin (blockIdx mod 8); one
-// whose XCD has no item left takes items of the next XCDs (the routing only
-// affects where data is cached, never the results).  kLdsJ: every problem's
-// column j fits the launch's LDS copy (n <= sxj_rows), else all are read from
-// global memory.  nitems = items per XCD
-// (implicit) or in total (explicit).  gate (optional): the kernel does
-// nothing unless *gate == gate_on.
-constexpr int SEG_XCDS = 8;
-
-template <bool kLdsJ, bool kMulti>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-k_seg_batch(const ProbDesc *__restrict__ P, const WorkItem *__restrict__ items, int nitems, int chunks,
-            int *__restrict__ counter, const int *__restrict__ xstart, const double *__restrict__ lam_all,
-            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp,
-            const double2 *__restrict__ DZ, double *__restrict__ V, double *__restrict__ E,
-            int *__restrict__ R, int *__restrict__ segflags, const int *__restrict__ cand, int ncand,
-            const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask, int lcap,
-            int sxj_rows) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_item, s_tried;                  // s_tried: XCD partitions found empty
-  if (gate && *gate != gate_on) return;
-  if (threadIdx.x == 0) s_tried = 0;
-  while (true) {
-    if (threadIdx.x == 0) {
-      int q = -1;
-      const int home = blockIdx.x % SEG_XCDS;
-      for (int tried = s_tried; tried < SEG_XCDS; ++tried) {
-        const int x = (home + tried) % SEG_XCDS;
-        const int c = atomicAdd(counter + x, 1);
-        const int have = items ? xstart[x + 1] - xstart[x] : nitems;
-        if (c < have) {
-          q = items ? xstart[x] + c : x * nitems + c;
+        if (nwin > lcap) {
+          ovf = true;
           break;
         }
-        s_tried = tried + 1;
+        const bool want = mine && !hit;
+        const uint64_t wantm = __ballot(want);
+        u128 Slo = Slw;
+        if (__builtin_popcountll(wantm) == 1 && nwin > 128) {
+          // one target: only the quarter of the window that holds it is
+          // sorted.  Three sample keys around the target split the list;
+          // the exact weights below them pick the part (a contiguous range
+          // of the sorted order), which is compacted to the list's front.
+          const u128 tau1 = uni_u128(shfl_u128(tau, __builtin_ctzll(wantm)));
+          uint64_t piv[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            int ix = (int)floor((wlo + 0.04 * (c - 1)) * SAMPLE_ROWS);
+            ix = ix < 0 ? 0 : (ix >= SAMPLE_ROWS ? SAMPLE_ROWS - 1 : ix);
+            piv[c] = sample_lo(ix);
+          }
+          piv[1] = piv[1] < piv[0] ? piv[0] : piv[1];
+          piv[2] = piv[2] < piv[1] ? piv[1] : piv[2];
+          u128 a0 = 0, a1 = 0, a2 = 0;
+          for (int e = lane; e < nwin; e += 64) {
+            const uint64_t key = lk[e];
+            const u128 w = fixed_of_col(sxj_at(s, lr[e]), s.e0);
+            a0 += key < piv[0] ? w : (u128)0;
+            a1 += key < piv[1] ? w : (u128)0;
+            a2 += key < piv[2] ? w : (u128)0;
+          }
+          a0 = wave_sum_u128_x(a0);
+          a1 = wave_sum_u128_x(a1);
+          a2 = wave_sum_u128_x(a2);
+          const int c = (Slw + a0 < tau1 ? 1 : 0) + (Slw + a1 < tau1 ? 1 : 0) + (Slw + a2 < tau1 ? 1 : 0);
+          const uint64_t plo2 = c == 0 ? 0 : piv[c - 1], phi2 = c == 3 ? KEY_NONE : piv[c];
+          Slo = Slw + (c == 0 ? (u128)0 : (c == 1 ? a0 : (c == 2 ? a1 : a2)));
+          {
+            // stable in-place compaction: an element never moves above its
+            // own slot, so slots not yet read are never overwritten
+            int kept = 0;
+            for (int e0 = 0; e0 < nwin; e0 += 64) {
+              const int e = e0 + lane;
+              const bool in = e < nwin;
+              const uint64_t key = in ? lk[e] : 0;
+              const unsigned short row = in ? lr[e] : 0;
+              const bool keep = in && (c == 0 || key >= plo2) && (c == 3 || key < phi2);
+              const uint64_t km = __ballot(keep);
+              const int d = kept + lanes_below(km);
+              kept += __builtin_popcountll(km);
+              if (keep) {
+                lk[d] = key;
+                lr[d] = row;
+              }
+            }
+            nwin = uni_int(kept);
+            wave_lds_sync();
+          }
+        }
+        const int N = wave_sort_list(lk, lr, nwin, lane);
+        u128 tot, incl;
+        wave_list_sums(s, lk, lr, N >> 6, tot, incl);
+        uint64_t k2 = KEY_NONE;
+        int r2 = -1;
+        bool h2 = false;
+        wave_resolve(s, lk, lr, N >> 6, Slo, tot, incl, want, tau, k2, r2, h2);
+        if (h2) {
+          okey = k2;
+          orow = r2;
+          hit = true;
+        }
+        wave_lds_sync();
+        break;
       }
-      s_item = q;
+      if (ovf) {
+        // the list cannot hold the window: after the shared window, retry
+        // each penalty with its own; a single penalty goes to the rounds
+        if (pass == 0 && __builtin_popcountll(nzg) == 1) break;
+        continue;
+      }
+      // the shared window held: the targets it missed go to the rounds
+      if (pass == 0) break;
     }
-    __syncthreads();
-    const int q = uni_int(s_item);
-    __syncthreads();
-    if (q < 0) break;
-    WorkItem it;
-    int jj;                                        // row of the item's column in the mask
-    if (items) {
-      it = items[q];
-      jj = it.j;
+
+    // targets the windows missed: rounds over the whole side
+    uint64_t left = __ballot(act && !hit);
+    while (left) {
+      const int t = __builtin_ctzll(left);
+      left &= left - 1;
+      if (!have_exact) {
+        ex = exact_sides(s);
+        have_exact = true;
+      }
+      const u128 lamf = slam[64 * g + t];
+      const u128 tau = neg ? ((W + lamf) >> 1) + 1 : (W - lamf + 1) >> 1;
+      uint64_t k2 = KEY_NONE;
+      int r2 = -1;
+      const ColSrc cs{s, (u128)0, 0};
+      wave_select_rounds(s, cs, klo0, khi0, neg ? (u128)0 : ex.B, neg ? ex.A : W, neg ? 0 : ex.N + ex.Z,
+                         neg ? ex.N : ex.NV, tau, ws, k2, r2, err);
+      if (lane == t) {
+        okey = k2;
+        orow = r2;
+      }
+    }
+
+    // residuals, reused while the selected row repeats: the group's targets
+    // whose row differs from the previous target's are the jobs, scored up
+    // to RJ at a time in one pass over the rows
+    const int tend = min(L, 64 * g + 64);
+    const int cnt = tend - 64 * g;
+    int orw_l = -1;
+    double v_l = 0.0;
+    if (lane < cnt && ((nzg >> lane) & 1ull)) {
+      orw_l = orow;
+      v_l = ratio_of_key(okey);
+    }
+    int prv = __shfl_up(orw_l, 1);
+    if (lane == 0) prv = prev_row;
+    const bool need = lane < cnt && orw_l >= 0 && orw_l != prv;
+    const uint64_t needm = __ballot(need);
+    double e_l = 0.0;
+    for (uint64_t jm = needm; jm; jm &= jm - 1) {
+      const int jl = __builtin_ctzll(jm);
+      const double e1 = readlane_dbl(wave_residual(s, readlane_dbl(v_l, jl)), 0);
+      if (lane == jl) e_l = e1;
+    }
+    // each target takes the e of the last job at or before it (or the
+    // previous group's last e when its row continues from there)
+    double e_t;
+    if (orw_l < 0) {
+      e_t = Wk;                                    // R64 sum of |x_ik|
     } else {
-      const int m0 = P[0].m;
-      const int mj = cand ? ncand : m0;
-      const int x = q / nitems, c = q % nitems;
-      const int part = x * chunks + c / mj;
-      jj = c % mj;
-      const int kchunk = (m0 + SEG_XCDS * chunks - 1) / (SEG_XCDS * chunks);
-      it.b = 0;
-      it.j = cand ? cand[jj] : jj;
-      it.kbeg = min(m0, part * kchunk);
-      it.kend = min(m0, it.kbeg + kchunk);
-      if (it.kbeg >= it.kend) continue;            // an empty part of a narrow matrix
+      const uint64_t upto = needm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
+      const double ej = __shfl(e_l, upto ? 63 - __builtin_clzll(upto) : 0);
+      e_t = upto ? ej : prev_e;
     }
+    if (lane < cnt) {
+      const int t = 64 * g + lane;
+      V[t * mm + base] = orw_l >= 0 ? v_l : 0.0;
+      E[t * mm + base] = e_t;
+      R[t * mm + base] = orw_l;
+    }
+    prev_row = __builtin_amdgcn_readlane(orw_l, cnt - 1);
+    prev_e = readlane_dbl(e_t, cnt - 1);
+  }
+}
+
+// The words of todo that hold an unsettled segment (listed by the
+// division-free kernels: todo_list[0, *todo_count)), one wave per word taken
+// from *next.  The count is final: it belongs to earlier kernels.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, const double *__restrict__ lam_all,
+           const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
+           double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, int *__restrict__ segflags,
+           const int *__restrict__ cand, const int *__restrict__ gate, int gate_on,
+           const unsigned long long *__restrict__ todo, const int *__restrict__ todo_list,
+           const int *__restrict__ todo_count, int *__restrict__ next, int Lmax, int lcap) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (gate && *gate != gate_on) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  u128 *slam = (u128 *)(smem + wave * rest_wave_bytes(Lmax, lcap));
+  WaveScratch *ws = (WaveScratch *)(slam + Lmax);
+  uint64_t *lk = (uint64_t *)(ws + 1);
+  unsigned short *lr = (unsigned short *)(lk + lcap);
+  const int count = *todo_count;
+  while (true) {
+    int e = 0;
+    if (lane == 0) e = atomicAdd(next, 1);
+    e = uni_int(e);
+    if (e >= count) break;
+    const int w = uni_int(todo_list[e]);
+    const int b = find_owner(wstart, B, w);
+    const ProbDesc d = P[b];
+    const int wpr = (d.m + 63) >> 6, wl = w - wstart[b], jj = wl / wpr, k0 = (wl - jj * wpr) * 64;
+    const int j = cand ? cand[jj] : jj;
+    const ColInfo cj = ci[d.col_off + j];
+    const double *lam = lam_all + d.lam_off;
+    const int T = (d.n + 63) >> 6;
+    int Tp = 1, err = 0;
+    while (Tp < T) Tp <<= 1;
+    wave_lds_sync();
+    for (int t = lane; t < d.L; t += 64) slam[t] = lambda_fixed(lam[t], cj.e0);
+    wave_lds_sync();
+    for (uint64_t bits = todo[d.mask_off + wl]; bits; bits &= bits - 1) {
+      const int k = k0 + __builtin_ctzll(bits);
+      const SegIO s{d.X + (long long)k * d.ld, d.X + (long long)j * d.ld, d.n, T, Tp, cj.e0, lane, false};
+      seg_exact(s, cj, ci[d.col_off + k], smp + (long long)(d.col_off + j) * SAMPLE_ROWS, lam, d.L,
+                DZ[d.pair_off + (long long)j * d.m + k], slam, ws, lk, lr, lcap, V + d.ws_off, E + d.ws_off,
+                R + d.ws_off, (long long)j * d.m + k, (long long)d.m * d.m, err);
+    }
+    if (err && lane == 0) atomicOr(segflags + d.col_off + j, err);
+  }
+}
+
+// The items of the segment kernels.  Every workgroup pulls work items from
+// the counter of its XCD until none is left.  Explicit items (a batch) come in
+// one list per XCD, [xstart[x], xstart[x + 1]).  With items == nullptr the
+// items of problem 0 are implicit and routed by XCD: its k range is cut into
+// SEG_XCDS * chunks equal parts, XCD x owns parts [x chunks, (x + 1) chunks)
+// and enumerates them part by part, every preserved column j (or cand[jj])
+// within a part, so the columns k that the workgroups of one XCD stream stay
+// in its L2.  Workgroups are dispatched to the XCDs round-robin (blockIdx mod
+// 8); one whose XCD has no item left takes items of the next XCDs (the
+// routing only affects where data is cached, never the results).  nitems =
+// items per XCD (implicit) or in total (explicit).
+constexpr int SEG_XCDS = 8;
+struct ItemQueue {
+  const WorkItem *items;
+  int nitems, chunks;
+  int *counter;
+  const int *xstart;
+};
+
+// The next item of the workgroup (every thread calls it): false when none is
+// left.  jj: the item's row in the masks.
+__device__ __forceinline__ bool next_item(const ItemQueue &q, const ProbDesc *__restrict__ P,
+                                          const int *__restrict__ cand, int ncand, int *s_item, int *s_tried,
+                                          WorkItem &it, int &jj) {
+  while (true) {
+    if (threadIdx.x == 0) {
+      int g = -1;
+      const int home = blockIdx.x % SEG_XCDS;
+      for (int tried = *s_tried; tried < SEG_XCDS; ++tried) {
+        const int x = (home + tried) % SEG_XCDS;
+        const int c = atomicAdd(q.counter + x, 1);
+        const int have = q.items ? q.xstart[x + 1] - q.xstart[x] : q.nitems;
+        if (c < have) {
+          g = q.items ? q.xstart[x] + c : x * q.nitems + c;
+          break;
+        }
+        *s_tried = tried + 1;
+      }
+      *s_item = g;
+    }
+    __syncthreads();
+    const int g = uni_int(*s_item);
+    __syncthreads();
+    if (g < 0) return false;
+    if (q.items) {
+      it = q.items[g];
+      jj = it.j;
+      return true;
+    }
+    const int m0 = P[0].m, mj = cand ? ncand : m0;
+    const int x = g / q.nitems, c = g % q.nitems;
+    const int part = x * q.chunks + c / mj;
+    jj = c % mj;
+    const int kchunk = (m0 + SEG_XCDS * q.chunks - 1) / (SEG_XCDS * q.chunks);
+    it.b = 0;
+    it.j = cand ? cand[jj] : jj;
+    it.kbeg = min(m0, part * kchunk);
+    it.kend = min(m0, it.kbeg + kchunk);
+    if (it.kbeg < it.kend) return true;            // (else an empty part of a narrow matrix)
+  }
+}
+
+// The live segments of an item: k in [kbeg, kend) not settled by
+// k_zero_segments.  Lane l holds word l of the item's mask inverted (bit b:
+// segment 64 (w0 + l) + b is live) and the live count of the words below it;
+// the waves claim live segments by their rank, so settled ones cost no claim.
+// An item of more than SEG_MASK_WORDS words counts every segment as live.
+struct LiveSegs {
+  uint64_t live;
+  int kpre, nlive, w0, nwords, kbeg;
+  bool use_mask;
+  __device__ __forceinline__ LiveSegs(const unsigned long long *__restrict__ maskrow, int kbeg_, int kend, int lane) {
+    kbeg = kbeg_;
+    w0 = kbeg >> 6;
+    nwords = kend > kbeg ? ((kend - 1) >> 6) - w0 + 1 : 0;
+    use_mask = nwords <= SEG_MASK_WORDS;
+    live = 0;
+    kpre = 0;
+    nlive = kend - kbeg;
+    if (use_mask) {
+      if (lane < nwords) {
+        const int lo = max(kbeg - 64 * (w0 + lane), 0), hi = min(kend - 64 * (w0 + lane), 64);
+        const uint64_t range = (hi == 64 ? ~0ull : (1ull << hi) - 1ull) & ~((1ull << lo) - 1ull);
+        live = ~maskrow[w0 + lane] & range;
+      }
+      const int cnt = __builtin_popcountll(live), incl = wave_scan_int(cnt);
+      kpre = incl - cnt;
+      nlive = __builtin_amdgcn_readlane(incl, 63);
+    }
+  }
+  // the c-th live segment: the last word whose live prefix is <= c, then the
+  // (c - prefix)-th set bit of that word
+  __device__ __forceinline__ int at(int c, int lane) const {
+    if (!use_mask) return kbeg + c;
+    const int w = __builtin_popcountll(__ballot(lane < nwords && kpre <= c)) - 1;
+    const uint64_t lw = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(live >> 32), w) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)live, w);
+    const int r = c - __builtin_amdgcn_readlane(kpre, w);
+    return 64 * (w0 + w) + __builtin_ctzll(__ballot(((lw >> lane) & 1ull) && lanes_below(lw) == r));
+  }
+};
+
+// Where the division-free kernels leave what they cannot settle: a bit per
+// segment, and the words that have one listed once.
+struct TodoList {
+  unsigned long long *bits;
+  int *list, *count;
+};
+__device__ __forceinline__ void leave_segment(const TodoList &td, long long word, int bit) {
+  if (atomicOr(td.bits + word, 1ull << bit) == 0ull) td.list[atomicAdd(td.count, 1)] = (int)word;
+}
+
+// One penalty per problem: every live segment by the division-free path, one
+// wave per segment.  kLdsJ: every problem's column j fits the launch's LDS
+// copy (sxj_rows rows), else it is read from global memory (it stays in L2
+// across the item's k).  gate (optional): the kernel does nothing unless
+// *gate == gate_on.
+template <bool kLdsJ>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
+           const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
+           double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, const int *__restrict__ cand, int ncand,
+           const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask, TodoList td,
+           int sxj_rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int s_item, s_tried, knext;
+  if (gate && *gate != gate_on) return;
+  if (threadIdx.x == 0) s_tried = 0;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double *sxj_lds = (double *)smem;
+  FastScratch *fs = (FastScratch *)(smem + (kLdsJ ? seg_sxj_bytes(sxj_rows) : 0)) + wave;
+  WorkItem it;
+  int jj;
+  while (next_item(queue, P, cand, ncand, &s_item, &s_tried, it, jj)) {
     const ProbDesc d = P[it.b];
-    const unsigned long long *maskrow =
-        segmask ? segmask + d.mask_off + (long long)jj * ((d.m + 63) >> 6) : nullptr;
-    seg_item<kLdsJ, kMulti>(d.X, d.n, d.m, d.ld, ci + d.col_off,
-                    smp + (long long)d.col_off * SAMPLE_ROWS, lam_all + d.lam_off, d.L, DZ + d.pair_off, it.j,
-                    it.kbeg, it.kend, V + d.ws_off, E + d.ws_off, R + d.ws_off, segflags + d.col_off, maskrow,
-                    lcap, sxj_rows, smem);
+    const int n = d.n, m = d.m, T = (n + 63) >> 6, j = it.j;
+    const ColInfo *cis = ci + d.col_off;
+    const ColInfo cj = cis[j];
+    const double *xjg = d.X + (long long)j * d.ld;
+    if constexpr (kLdsJ)
+      for (int i = threadIdx.x; i < T * 64; i += blockDim.x) sxj_lds[i] = i < n ? xjg[i] : 0.0;
+    const double *__restrict__ sxj = kLdsJ ? (const double *)sxj_lds : xjg;
+    if (threadIdx.x == 0) knext = 0;
+    __syncthreads();
+    const long long word0 = d.mask_off + (long long)jj * ((m + 63) >> 6);
+    const LiveSegs segs(segmask + word0, it.kbeg, it.kend, lane);
+    // the sample of column j: two rows per lane, and the reciprocals of their
+    // x_ij (sample keys need neither an exact quotient nor one per segment)
+    const unsigned short *sm = smp + (long long)(d.col_off + j) * SAMPLE_ROWS;
+    const int sr0 = sm[lane], sr1 = sm[64 + lane];
+    const double sv0 = __builtin_amdgcn_rcp(sxj[sr0]), sv1 = __builtin_amdgcn_rcp(sxj[sr1]);
+    const double lam = lam_all[d.lam_off], Wd = cj.W;
+    // the targets' places in the sample
+    const double cneg = 0.5 * SAMPLE_ROWS * (Wd + lam) / Wd, cpos = 0.5 * SAMPLE_ROWS * (Wd - lam) / Wd;
+    const bool fast_j = !cj.flags && fast_columns(cj);
+    const double2 *DZj = DZ + d.pair_off + (long long)j * m;
+    // claims are taken one segment ahead, and the next segment's sign sums and
+    // sample are loaded before the current one's residual
+    int claim = 0;
+    if (lane == 0) claim = atomicAdd(&knext, 1);
+    int c = __builtin_amdgcn_readlane(claim, 0);
+    if (lane == 0) claim = atomicAdd(&knext, 1);
+    int k = c < segs.nlive ? segs.at(c, lane) : it.kbeg;
+    double2 dz = DZj[k];
+    double b0 = gld(d.X + (long long)k * d.ld + sr0), b1 = gld(d.X + (long long)k * d.ld + sr1);
+    while (c < segs.nlive) {
+      const SegIO s{d.X + (long long)k * d.ld, sxj, n, T, 0, cj.e0, lane, kLdsJ};
+      const ColInfo ck = cis[k];
+      double v = 0.0, e = ck.W;
+      int row = -1;
+      bool left = false;
+      if (k == j || cj.flags) {
+        v = k == j ? 1.0 : __longlong_as_double(0x7ff8000000000000ll);
+        e = 0.0;
+      } else {
+        const int side = sign_sum_side(dz, lam, Wd, sign_sums_unsure(cj, ck, dz));
+        left = side == 3 || (side != 0 && !(fast_j && fast_columns(ck)));
+        if (side != 0 && !left) {
+          const bool neg = side == 1;
+          uint32_t sx[2] = {(uint32_t)(key_of(b0 * sv0 + 0.0) >> 32), (uint32_t)(key_of(b1 * sv1 + 0.0) >> 32)};
+          wave_sort_u32<2>(sx);
+          const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, n), rj = col_rsrc(kLdsJ ? s.xk : s.sxj, n);
+          auto ldj = [&](int i) { return sxj_pad(s, rj, i); };
+          auto ldk = [&](int i) { return col_ld(rk, i * 8); };
+          left = !fast_one(s, ldj, ldk, neg, lam, Wd, sx[0], sx[1], neg ? cneg : cpos, fs, v, row);
+        }
+      }
+      const long long base = d.ws_off + (long long)j * m + k;
+      const int kc = k;
+      c = __builtin_amdgcn_readlane(claim, 0);
+      if (lane == 0) claim = atomicAdd(&knext, 1);
+      k = c < segs.nlive ? segs.at(c, lane) : it.kbeg;
+      dz = DZj[k];
+      b0 = gld(d.X + (long long)k * d.ld + sr0);
+      b1 = gld(d.X + (long long)k * d.ld + sr1);
+      if (left) {
+        if (lane == 0) leave_segment(td, word0 + (kc >> 6), kc & 63);
+        continue;
+      }
+      if (row >= 0) e = wave_residual(s, v);
+      if (lane == 0) {
+        V[base] = v;
+        E[base] = e;
+        R[base] = row;
+      }
+    }
+    __syncthreads();   // the LDS is reused by the next item
+  }
+}
+
+// RJ residuals in one pass over the rows (the sums of wave_residual, RJ at a
+// time); the lanes of the first RJ bits of jm (v_l: the lane's ratio) receive
+// theirs in e_l, and the bits are cleared.  The R64 trees are folded: at each
+// level two trees trade halves and go on as one, the lower one on the lower
+// lanes, so the adds and their pairing are those of RJ separate trees.
+__device__ __forceinline__ double fold32(double a, double b, bool wide) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  const auto l = wide ? __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false)
+                      : __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto h = wide ? __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false)
+                      : __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
+__device__ __forceinline__ double add_down(double p, int d) {
+  const uint64_t b = (uint64_t)__double_as_longlong(p);
+  return p + __longlong_as_double((long long)(((uint64_t)xdown32((uint32_t)(b >> 32), d) << 32) | xdown32((uint32_t)b, d)));
+}
+template <int RJ, class LdJ, class LdK>
+__device__ __forceinline__ void run_jobs(const SegIO &s, LdJ ldj, LdK ldk, uint64_t &jm, double v_l, double &e_l) {
+  const uint64_t all = jm;
+  double jv[RJ], p[RJ];
+#pragma unroll
+  for (int r = 0; r < RJ; ++r) {
+    jv[r] = jm ? readlane_dbl(v_l, __builtin_ctzll(jm)) : 0.0;
+    jm &= jm ? jm - 1 : 0;
+    p[r] = 0.0;
+  }
+  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
+#pragma unroll
+    for (int r = 0; r < RJ; ++r) {
+      const double prod = jv[r] * a;
+      const double d = b - prod;
+      p[r] = p[r] + fabs(d);
+    }
+  });
+  double x;
+  int src;                                         // where job i ends: its bits on lane bits 5, 4 (, 3)
+  const int i = lanes_below(all);
+  if constexpr (RJ > 4) {
+    auto at = [&](int r) { return r < RJ ? p[r] : 0.0; };
+    const double q0 = fold32(fold32(p[0], p[4], true), fold32(p[2], at(6), true), false);
+    const double q1 = fold32(fold32(p[1], at(5), true), fold32(p[3], at(7), true), false);
+    const bool up = (threadIdx.x & 8) != 0;
+    const double keep = up ? q1 : q0, send = up ? q0 : q1;
+    const uint64_t sb = (uint64_t)__double_as_longlong(send);
+    x = keep + __longlong_as_double((long long)(((uint64_t)xswap32((uint32_t)(sb >> 32), 8) << 32) | xswap32((uint32_t)sb, 8)));
+    src = ((i & 4) << 3) | ((i & 2) << 3) | ((i & 1) << 3);
+  } else if constexpr (RJ > 2) {
+    x = add_down(fold32(fold32(p[0], p[2], true), fold32(p[1], p[3], true), false), 8);
+    src = ((i & 2) << 4) | ((i & 1) << 4);
+  } else {
+    x = add_down(add_down(fold32(p[0], p[1], true), 16), 8);
+    src = (i & 1) << 5;
+  }
+  x = add_down(add_down(add_down(x, 4), 2), 1);
+  const double got = __shfl(x, src);
+  if (((all >> (threadIdx.x & 63)) & 1ull) && i < RJ) e_l = got;
+}
+
+// Several penalties per problem: every live segment, one wave per segment, a
+// penalty per lane in groups of 64.
+template <bool kLdsJ>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
+           const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
+           double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, const int *__restrict__ cand, int ncand,
+           const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask, TodoList td,
+           int sxj_rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int s_item, s_tried, knext;
+  if (gate && *gate != gate_on) return;
+  if (threadIdx.x == 0) s_tried = 0;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double *sxj_lds = (double *)smem;
+  PathScratch *ps = (PathScratch *)(smem + (kLdsJ ? seg_sxj_bytes(sxj_rows) : 0)) + wave;
+  WorkItem it;
+  int jj;
+  while (next_item(queue, P, cand, ncand, &s_item, &s_tried, it, jj)) {
+    const ProbDesc d = P[it.b];
+    const int n = d.n, m = d.m, L = d.L, T = (n + 63) >> 6, j = it.j;
+    const ColInfo *cis = ci + d.col_off;
+    const ColInfo cj = cis[j];
+    const double *xjg = d.X + (long long)j * d.ld;
+    if constexpr (kLdsJ)
+      for (int i = threadIdx.x; i < T * 64; i += blockDim.x) sxj_lds[i] = i < n ? xjg[i] : 0.0;
+    const double *__restrict__ sxj = kLdsJ ? (const double *)sxj_lds : xjg;
+    if (threadIdx.x == 0) knext = 0;
+    __syncthreads();
+    const long long word0 = d.mask_off + (long long)jj * ((m + 63) >> 6), mm = (long long)m * m;
+    const LiveSegs segs(segmask + word0, it.kbeg, it.kend, lane);
+    const unsigned short *sm = smp + (long long)(d.col_off + j) * SAMPLE_ROWS;
+    const int sr0 = sm[lane], sr1 = sm[64 + lane];
+    const double sv0 = __builtin_amdgcn_rcp(sxj[sr0]), sv1 = __builtin_amdgcn_rcp(sxj[sr1]);
+    const double *lams = lam_all + d.lam_off;
+    const double Wd = cj.W;
+    const bool fast_j = !cj.flags && fast_columns(cj);
+    const double2 *DZj = DZ + d.pair_off + (long long)j * m;
+    int claim = 0;
+    if (lane == 0) claim = atomicAdd(&knext, 1);
+    while (true) {
+      const int cq = __builtin_amdgcn_readlane(claim, 0);
+      if (cq >= segs.nlive) break;
+      if (lane == 0) claim = atomicAdd(&knext, 1);
+      const int k = segs.at(cq, lane);
+      const long long base = d.ws_off + (long long)j * m + k;
+      const SegIO s{d.X + (long long)k * d.ld, sxj, n, T, 0, cj.e0, lane, kLdsJ};
+      const ColInfo ck = cis[k];
+      const double2 dz = DZj[k];
+      const bool unc = sign_sums_unsure(cj, ck, dz), plain = k == j || cj.flags;
+      bool left = false, sorted = false;
+      uint32_t sa = 0, sb = 0;
+      int prev_row = -2;
+      double prev_e = 0.0;
+      const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, n), rj = col_rsrc(kLdsJ ? s.xk : s.sxj, n);
+      auto ldj = [&](int i) { return sxj_pad(s, rj, i); };
+      auto ldk = [&](int i) { return col_ld(rk, i * 8); };
+      for (int t0 = 0; t0 < L && !left; t0 += 64) {
+        const int t = t0 + lane;
+        const double lam = t < L ? lams[t] : 0.0;
+        double v = plain ? (k == j ? 1.0 : __longlong_as_double(0x7ff8000000000000ll)) : 0.0, e = plain ? 0.0 : ck.W;
+        int row = -1;
+        const int side = t < L && !plain ? sign_sum_side(dz, lam, Wd, unc) : 0;
+        const uint64_t nz = __ballot(side != 0);
+        left = __ballot(side == 3) != 0 || (nz && !(fast_j && fast_columns(ck)));
+        if (nz && !left) {
+          // (every penalty of a segment has the minimiser on the same side)
+          const bool neg = __builtin_amdgcn_readlane(side, __builtin_ctzll(nz)) == 1;
+          if (!sorted) {
+            uint32_t x[2] = {(uint32_t)(key_of(gld(s.xk + sr0) * sv0 + 0.0) >> 32),
+                             (uint32_t)(key_of(gld(s.xk + sr1) * sv1 + 0.0) >> 32)};
+            wave_sort_u32<2>(x);
+            sa = x[0];
+            sb = x[1];
+            sorted = true;
+          }
+          const double u = 0.5 * SAMPLE_ROWS * lam / Wd;
+          left = !fast_path(s, ldj, ldk, neg, side != 0, lam, Wd, sa, sb, 0.5 * SAMPLE_ROWS + (neg ? u : -u), ps, v, row);
+          if (!left) {
+            // residuals, reused while the selected row repeats: the targets whose
+            // row differs from the previous target's are the jobs
+            int prv = __shfl_up(row, 1);
+            if (lane == 0) prv = prev_row;
+            const uint64_t needm = __ballot(row >= 0 && row != prv);
+            uint64_t jm = needm;
+            double e_l = 0.0;
+            while (jm) {
+              const int c = __builtin_popcountll(jm);
+              if (c > 6) run_jobs<8>(s, ldj, ldk, jm, v, e_l);
+              else if (c > 4) run_jobs<6>(s, ldj, ldk, jm, v, e_l);
+              else if (c > 2) run_jobs<4>(s, ldj, ldk, jm, v, e_l);
+              else run_jobs<2>(s, ldj, ldk, jm, v, e_l);
+            }
+            // each target takes the e of the last job at or before it (or the
+            // previous group's last e when its row continues from there)
+            const uint64_t upto = needm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
+            const double ej = __shfl(e_l, upto ? 63 - __builtin_clzll(upto) : 0);
+            e = row < 0 ? ck.W : upto ? ej : prev_e;
+          }
+        }
+        if (!left) {
+          if (t < L) {
+            V[t * mm + base] = v;
+            E[t * mm + base] = e;
+            R[t * mm + base] = row;
+          }
+          prev_row = __builtin_amdgcn_readlane(row, 63);
+          prev_e = readlane_dbl(e, 63);
+        }
+      }
+      if (left && lane == 0) leave_segment(td, word0 + (k >> 6), k & 63);
+    }
+    __syncthreads();   // the LDS is reused by the next item
   }
 }
 

@@ -304,7 +304,7 @@ struct BatchLayout {
   long long total_cols, total_z, total_out, total_ws, total_lam, total_pairs, total_tiles, total_words;
   size_t o_desc, o_colstart, o_zstart, o_ostart, o_tstart, o_wstart, o_lam, o_items, o_counter, o_xstart,
       meta_bytes;
-  size_t o_ci, o_smp, o_segflags, o_DZ, o_DZp, o_mask, o_V, o_E, o_R, o_Z, o_zflag, bytes;
+  size_t o_ci, o_smp, o_segflags, o_DZ, o_DZp, o_mask, o_todo, o_todolist, o_V, o_E, o_R, o_Z, o_zflag, bytes;
 };
 
 static void layout_sizes(BatchLayout &Ly) {
@@ -327,6 +327,8 @@ static void layout_sizes(BatchLayout &Ly) {
   Ly.o_DZ = take(2 * sizeof(double) * Ly.total_pairs);
   Ly.o_DZp = take(Ly.ss_split > 1 ? 2 * sizeof(double) * Ly.ss_split * (size_t)Ly.ss_per : 0);
   Ly.o_mask = take(sizeof(unsigned long long) * Ly.total_words);
+  Ly.o_todo = take(sizeof(unsigned long long) * Ly.total_words);
+  Ly.o_todolist = take(sizeof(int) * Ly.total_words);
   Ly.o_V = take(sizeof(double) * Ly.total_ws);
   Ly.o_E = take(sizeof(double) * Ly.total_ws);
   Ly.o_R = take(sizeof(int) * Ly.total_ws);
@@ -596,39 +598,23 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   int *dR = (int *)(d + Ly.o_R), *dzflag = (int *)(d + Ly.o_zflag);
   double2 *dDZ = (double2 *)(d + Ly.o_DZ), *dDZp = (double2 *)(d + Ly.o_DZp);
   unsigned long long *dmask = (unsigned long long *)(d + Ly.o_mask);
+  const TodoList todo{(unsigned long long *)(d + Ly.o_todo), (int *)(d + Ly.o_todolist), dcounter + 8};
   if (outp) *outp = BatchPtrs{dV, dR, dci};
   l1line_ctx pc = prof ? ctx : nullptr;
 
-  // window list capacity: the larger path list where the LDS allows it
-  // the dynamic LDS the segment kernels may request (about 154 KB of the
-  // CU's 160 KB): the path list's larger capacity is taken when it fits
-  const size_t lds_max = seg_lds_bytes(4 * SXJ_LDS_MAX, L1LINE_MAX_LAMBDAS, WIN_CAP);
   // column j goes to LDS up to SXJ_LDS_MAX rows; longer ones are read from
-  // global memory, which keeps room for more workgroups per CU.  The copy is
-  // also left out where that lets more workgroups share a CU (column j then
-  // comes from L2, where it stays across the item's k): the several-penalty
-  // kernel's 1024-entry lists leave room for two 2000-row workgroups per CU
-  // with the copy and three without (path L = 64 at 2000x2000: 66.8 -> 61.7
-  // ms).  At most four: the waves per SIMD the kernel's registers allow.
-  auto wg_per_cu = [](size_t bytes) {
-    const size_t b = (bytes + 16 + 511) / 512 * 512;   // + static LDS, 512-byte granules
-    return std::min<size_t>(4, (size_t)160 * 1024 / b);
-  };
-  int sxj_rows = Ly.nmax <= SXJ_LDS_MAX ? Ly.nmax : 0;
-  const int lcap = (Ly.Lmax > 1 && seg_lds_bytes(sxj_rows, Ly.Lmax, PATH_CAP) <= lds_max) ? PATH_CAP : WIN_CAP;
-  if (sxj_rows > 0 &&
-      wg_per_cu(seg_lds_bytes(0, Ly.Lmax, lcap)) > wg_per_cu(seg_lds_bytes(sxj_rows, Ly.Lmax, lcap)))
-    sxj_rows = 0;
-  const size_t lds = seg_lds_bytes(sxj_rows, Ly.Lmax, lcap);
+  // global memory, which keeps room for more workgroups per CU
+  const bool multi = Ly.Lmax > 1;
+  const int sxj_rows = Ly.nmax <= SXJ_LDS_MAX ? Ly.nmax : 0;
+  const size_t lds_fast = seg_sxj_bytes(sxj_rows) + SEG_WAVES * (multi ? sizeof(PathScratch) : sizeof(FastScratch));
+  // the exact kernel's list: the larger one for several penalties
+  const int lcap = multi ? PATH_CAP : WIN_CAP;
+  const size_t lds_rest = SEG_WAVES * rest_wave_bytes(Ly.Lmax, lcap);
   if (!ctx->attr_seg) {
-    HIP_TRY(hipFuncSetAttribute((const void *)k_seg_batch<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_max));
-    HIP_TRY(hipFuncSetAttribute((const void *)k_seg_batch<false, false>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max));
-    HIP_TRY(hipFuncSetAttribute((const void *)k_seg_batch<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_max));
-    HIP_TRY(hipFuncSetAttribute((const void *)k_seg_batch<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_max));
+    HIP_TRY(hipFuncSetAttribute((const void *)k_seg_rest, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(SEG_WAVES * rest_wave_bytes(L1LINE_MAX_LAMBDAS, PATH_CAP))));
+    HIP_TRY(hipFuncSetAttribute((const void *)k_seg_path<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(seg_sxj_bytes(SXJ_LDS_MAX) + SEG_WAVES * sizeof(PathScratch))));
     ctx->attr_seg = true;
   }
   const long long all_items = Ly.ksplit ? (long long)Ly.nitems * SEG_XCDS : (long long)Ly.nitems;
@@ -656,21 +642,22 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   {
     ProfScope ps(pc, ls, "zero_seg");
     hipLaunchKernelGGL(k_zero_segments, dim3((unsigned)((Ly.total_words + 3) / 4)), dim3(256), 0, ls, dP, dwst,
-                       (int)B, (int)Ly.total_words, dlam, dci, dDZ, dV, dE, dR, dmask,
+                       (int)B, (int)Ly.total_words, dlam, dci, dDZ, dV, dE, dR, dmask, todo.bits,
                        (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, Ly.ss_split, (const double2 *)dDZp,
                        Ly.ss_per);
   }
   if (t0) HIP_TRY(hipEventRecord(t0, ls));
   {
     ProfScope ps(pc, ls, "fit_seg");
-    // single-penalty problems take the instantiation tuned for one target
-    const bool multi = Ly.Lmax > 1;
-    auto kseg = sxj_rows > 0 ? (multi ? k_seg_batch<true, true> : k_seg_batch<true, false>)
-                             : (multi ? k_seg_batch<false, true> : k_seg_batch<false, false>);
-    hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * SEG_WAVES), lds, ls, dP, ditems,
-                       Ly.nitems, Ly.ksplit, dcounter, dxstart, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags, ro.cand,
-                       ro.ncand,
-                       ro.gate, ro.gate_on, dmask, lcap, sxj_rows);
+    const ItemQueue queue{ditems, Ly.nitems, Ly.ksplit, dcounter, dxstart};
+    auto kseg = sxj_rows > 0 ? (multi ? k_seg_path<true> : k_seg_fast<true>)
+                             : (multi ? k_seg_path<false> : k_seg_fast<false>);
+    hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * SEG_WAVES), lds_fast, ls, dP, queue, dlam, dci, dsmp,
+                       dDZ, dV, dE, dR, ro.cand, ro.ncand, ro.gate, ro.gate_on, dmask, todo, sxj_rows);
+    hipLaunchKernelGGL(k_seg_rest, dim3((unsigned)std::min<long long>(4ll * ctx->num_cu, (Ly.total_words + 3) / 4)),
+                       dim3(64 * SEG_WAVES), lds_rest, ls, dP, dwst, (int)B, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags,
+                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, todo.bits, todo.list, todo.count, dcounter + 9,
+                       Ly.Lmax, lcap);
   }
   if (t1) HIP_TRY(hipEventRecord(t1, ls));
   {

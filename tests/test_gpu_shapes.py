@@ -101,3 +101,68 @@ def test_column_statistics_forms(ctx, n, m):
     assert int(st[0]) == 0
     assert W.tobytes() == np.asarray(r[0]).tobytes()
     assert np.array_equal(zeros, (X == 0.0).sum(axis=0))
+
+
+# the division-free segment kernels at the edges of their row words (32 slots),
+# of the window list, of the probe cuts and of the LDS copy of column j
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 511, 513, 2047, 2048, 2049, 2177, 3000, 4096, 4097, 6200, 9000])
+@pytest.mark.parametrize("kind", ["sparse", "dense", "counts"])
+def test_segment_rows(ctx, n, kind):
+    from paper_2402_16712_amd import binding as B
+    m = 9 if n < 3000 else 5
+    print(f"case rows {n}x{m} {kind}", flush=True)
+    X = _data(3 * n + 1, n, m, kind)
+    big = max(wl.max_column_mass(X), 1.0)
+    Xd = B.device_matrix(X)
+    for lam in (0.0, 0.031 * big, 0.4 * big):
+        _fit_equal(_host(ctx.fit(Xd, lam)), O.fit(X, lam), (n, kind, lam))
+    lams = np.concatenate([big * 10.0 ** np.linspace(-4, 0, 9), [0.0]])
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, kind, "path"))
+
+
+# one to three values: a whole bin of equal ratios, divided again by row
+@pytest.mark.parametrize("n", [300, 2000, 4200, 9000])
+@pytest.mark.parametrize("span", [1, 2])
+def test_segment_ties(ctx, n, span):
+    from paper_2402_16712_amd import binding as B
+    print(f"case ties {n} span {span}", flush=True)
+    X = wl.random_small(n + span, n, 5, integer=True, span=span)
+    X[:, 4] = X[:, 0]                       # every ratio of a pair the same
+    X[:, 3] *= 2.0 ** -20
+    Xd = B.device_matrix(X)
+    for lam in (0.0, 1.5, 7.0, 0.1 * n):
+        _fit_equal(_host(ctx.fit(Xd, lam)), O.fit(X, lam), (n, span, lam))
+    lams = np.array([7.0, 0.0, 0.1 * n, 1.5, 3.0])
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, span, "path"))
+
+
+# penalties: one group of lanes, its last lane, a second group; unsorted; more
+# distinct solutions than one residual pass scores
+@pytest.mark.parametrize("L", [2, 5, 63, 64, 65, 128])
+@pytest.mark.parametrize("n", [700, 5000])
+def test_segment_penalties(ctx, L, n):
+    from paper_2402_16712_amd import binding as B
+    print(f"case penalties {L} rows {n}", flush=True)
+    m = 12 if n < 1000 else 4
+    X = _data(L + n, n, m, "sparse")
+    lams = np.random.default_rng(L).permutation(wl.log_lambdas(wl.max_column_mass(X), L, -4.0))
+    _path_equal(_host(ctx.fit_path(B.device_matrix(X), lams)), O.fit_path(X, lams), (L, n))
+
+
+# columns outside the division-free range next to columns inside it, signed
+# zeros, subnormals: the segments left to the exact kernel
+@pytest.mark.parametrize("n", [130, 2100, 5000])
+def test_segment_ranges(ctx, n):
+    from paper_2402_16712_amd import binding as B
+    print(f"case ranges {n}", flush=True)
+    X = _data(n + 7, n, 7, "sparse")
+    X[:, 1] *= 2.0 ** -420
+    X[:, 2] *= 2.0 ** 380
+    X[: n // 3, 3] = -0.0
+    X[::5, 4] = 0.0
+    X[:, 5] = np.sign(X[:, 5]) * 2.0 ** -300
+    Xd = B.device_matrix(X)
+    for lam in (0.0, 0.05 * wl.max_column_mass(X[:, :1]), 1e120):
+        _fit_equal(_host(ctx.fit(Xd, lam)), O.fit(X, lam), (n, lam))
+    lams = np.array([0.0, 1e-130, 1.0, 50.0, 1e115])
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, "path"))
