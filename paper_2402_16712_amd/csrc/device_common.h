@@ -522,5 +522,6 @@ __device__ __forceinline__ uint32_t hi32(double x) { return (uint32_t)((uint64_t
 // a, its sign flipped where d's sign bit is set
 __device__ __forceinline__ double flip_sign(double a, double d) {
   const uint64_t b = (uint64_t)__double_as_longlong(a);
-  return __longlong_as_double((long long)(((uint64_t)((uint32_t)(b >> 32) ^ (hi32(d) & 0x80000000u)) << 32) | (uint32_t)b));
+  const uint32_t h = (uint32_t)__builtin_amdgcn_bitop3_b32((int)(b >> 32), (int)hi32(d), (int)0x80000000u, 0x78);   // a ^ (d & c)
+  return __longlong_as_double((long long)(((uint64_t)h << 32) | (uint32_t)b));
 }

@@ -980,7 +980,8 @@ k_signsum_batch(const ProbDesc *__restrict__ P, const int *__restrict__ tstart, 
 //     the next k from an LDS counter.
 //  3. What the margin does not settle is left to k_seg_rest: exact 128-bit
 //     sums and general rounds.
-constexpr int SEG_WAVES = 4;
+constexpr int SEG_WAVES = 4;        // waves per workgroup (several penalties, exact)
+constexpr int FAST_WAVES = 4;
 constexpr int SXJ_LDS_MAX = 4096;   // longest column j copied to LDS (32 KB)
 constexpr int SEG_MASK_WORDS = 64;  // zero-segment mask words an item holds (one per lane: 4096 k)
 
@@ -1211,18 +1212,20 @@ __device__ __forceinline__ void for_row_pairs(const SegIO &s, LdJ ldj, LdK ldk, 
       }
     }
   };
-  double an[FB], bn[FB];
-  load(t0, an, bn);
-  for (int t = t0; t < t1; t += FB) {
-    double av[FB], bv[FB];
+  // (two buffers in turn: no copies)
+  double a0[FB], b0[FB], a1[FB], b1[FB];
+  load(t0, a0, b0);
+  for (int t = t0;; t += 2 * FB) {
+    const bool more = t + FB < t1;
+    if (more) load(t + FB, a1, b1);
 #pragma unroll
-    for (int r = 0; r < FB; ++r) {
-      av[r] = an[r];
-      bv[r] = bn[r];
-    }
-    if (t + FB < t1) load(t + FB, an, bn);
+    for (int r = 0; r < FB; ++r) f(a0[r], b0[r]);
+    if (!more) break;
+    const bool more2 = t + 2 * FB < t1;
+    if (more2) load(t + 2 * FB, a0, b0);
 #pragma unroll
-    for (int r = 0; r < FB; ++r) f(av[r], bv[r]);
+    for (int r = 0; r < FB; ++r) f(a1[r], b1[r]);
+    if (!more2) break;
   }
 }
 
@@ -1290,7 +1293,7 @@ __device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, in
   for (int level = 0; level < 8; ++level) {
     fs->bin[lane] = 0.0;
     wave_lds_sync();
-    constexpr int GB = 4;
+    constexpr int GB = 2;
     for (int e0 = 0; e0 < count; e0 += 64 * GB) {
       uint32_t x[GB];
       double av[GB], bv[GB];
@@ -1393,7 +1396,7 @@ __device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, in
 template <class LdJ, class LdK>
 __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool neg, double lam, double Wd,
                                          uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
-  constexpr double WDELTA = 0.08;
+  constexpr double WDELTA = 0.06;
   const double tol = 0x1p-38 * Wd;
   // sample values with low bits no simple fraction has: a ratio equal to a
   // bound cannot be settled here
@@ -1581,14 +1584,16 @@ __device__ __forceinline__ void wave_sort_u32(uint32_t (&x)[E]) {
 
 // The listed rows in (ratio, row) order: ps->list the rows, ps->val the
 // inclusive prefix weights, 64 E entries (the last repeated past count).
-// [blo, bhi]: the range the words divide.  false: two ratios share a word.
+// [blo, bhi]: the range the words divide.  Where the first sort leaves two
+// neighbours out of order, the rows are sorted by their numbers and then by
+// the ratios again, so that equal ratios sort by row; false if two different
+// ratios share a word.
 template <int E>
 __device__ __forceinline__ bool sort_listed(const SegIO &s, PathScratch *ps, int count, double blo, double bhi) {
   constexpr int N = 64 * E, IB = E == 1 ? 6 : E == 2 ? 7 : E == 4 ? 8 : 9;
   const int lane = s.lane;
   double scale = (double)(1u << (32 - IB)) / (bhi - blo);
   scale = bhi > blo && scale < 0x1p1000 ? scale : 0.0;
-  uint32_t x[E];
   {
     int rw[E];
     double av[E], bv[E];
@@ -1600,37 +1605,54 @@ __device__ __forceinline__ bool sort_listed(const SegIO &s, PathScratch *ps, int
       bv[q] = gld(s.xk + rw[q]);
     }
 #pragma unroll
+    for (int q = 0; q < E; ++q) ps->val[64 * q + lane] = bv[q] / av[q];
+  }
+  uint32_t rw[E];
+  double r[E];
+  bool bad = true;
+#pragma unroll 1
+  for (int phase = 0; phase < 3; ++phase) {
+    uint32_t x[E];
+#pragma unroll
     for (int q = 0; q < E; ++q) {
       const int e = 64 * q + lane;
-      const double r = bv[q] / av[q];
-      ps->val[e] = r;
-      const uint32_t w = min((uint32_t)fmax((r - blo) * scale, 0.0), (1u << (32 - IB)) - 1u);
+      const uint32_t w = phase == 1 ? ps->list[e]
+                                    : min((uint32_t)fmax((ps->val[e] - blo) * scale, 0.0), (1u << (32 - IB)) - 1u);
       x[q] = e < count ? (w << IB) | (uint32_t)e : ~0u;
     }
-  }
-  wave_sort_u32<E>(x);
-  wave_lds_sync();
-  // the entries E lane + q: rows, ratios and the next lane's first pair
-  uint32_t rw[E + 1];
-  double r[E + 1], w[E];
+    wave_sort_u32<E>(x);
+    wave_lds_sync();
+    // the entries E lane + q in this order
 #pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int id = E * lane + q < count ? (int)(x[q] & (N - 1)) : 0;
-    rw[q] = ps->list[id];
-    r[q] = ps->val[id];
-  }
-  {
-    const uint32_t nx = (uint32_t)__shfl_down((int)x[0], 1);
-    const int id = E * lane + E < count ? (int)(nx & (N - 1)) : 0;
-    rw[E] = ps->list[id];
-    r[E] = ps->val[id];
-  }
-  bool bad = false;
+    for (int q = 0; q < E; ++q) {
+      const int id = E * lane + q < count ? (int)(x[q] & (N - 1)) : 0;
+      rw[q] = ps->list[id];
+      r[q] = ps->val[id];
+    }
+    wave_lds_sync();
+    if (phase == 1) {
 #pragma unroll
-  for (int q = 0; q < E; ++q)
-    bad = bad || (E * lane + q + 1 < count && !(r[q] < r[q + 1] || (r[q] == r[q + 1] && rw[q] < rw[q + 1])));
+      for (int q = 0; q < E; ++q)
+        if (E * lane + q < count) {
+          ps->list[E * lane + q] = rw[q];
+          ps->val[E * lane + q] = r[q];
+        }
+      wave_lds_sync();
+      continue;
+    }
+    const double nr = __shfl_down(r[0], 1);
+    const uint32_t nw = (uint32_t)__shfl_down((int)rw[0], 1);
+    bad = false;
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      const double rn = q + 1 < E ? r[q + 1 < E ? q + 1 : 0] : nr;
+      const uint32_t wn = q + 1 < E ? rw[q + 1 < E ? q + 1 : 0] : nw;
+      bad = bad || (E * lane + q + 1 < count && !(r[q] < rn || (r[q] == rn && rw[q] < wn)));
+    }
+    if (__ballot(bad) == 0) break;
+  }
   if (__ballot(bad)) return false;
-  double tot = 0.0;
+  double w[E], tot = 0.0;
 #pragma unroll
   for (int q = 0; q < E; ++q) {
     const bool in = E * lane + q < count;
@@ -1655,7 +1677,7 @@ __device__ __forceinline__ bool sort_listed(const SegIO &s, PathScratch *ps, int
 template <class LdJ, class LdK>
 __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool neg, bool act, double lam, double Wd,
                                           uint32_t sa, uint32_t sb, double c, PathScratch *ps, double &v, int &row) {
-  constexpr double WDELTA = 0.08;
+  constexpr double WDELTA = 0.06;
   const int lane = s.lane;
   const double tol = 0x1p-38 * Wd;
   auto value = [&](int ix) {
@@ -1677,6 +1699,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
   int iend = min(max(wave_max_int_x(act ? cr : -1), neg ? -1 : lmin + 3), rmax);
   double lo = bound(il);
   int shrink = 0, start = il;
+  bool jump = true;
   for (int it = 0; it < 160 && pend; ++it) {
     // the next window: [lo, hi), hi at sample ir or (shrink) inside a gap
     int ir = min(il + step, max(iend, il + 1));
@@ -1688,7 +1711,8 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
         ir = il + ((ir - il) >> shrink);
         hi = bound(ir);
       } else {
-        if (shrink > 12 || il <= lmin || il + 1 >= rmax) return false;
+        // (not towards an open end)
+        if (shrink > 12 || (neg ? il <= lmin : il + 1 >= rmax)) return false;
         hi = lo + (bound(il + 1) - lo) * ldexp(1.0, -2 * shrink);
         ir = il;                                   // (the window ends inside the gap)
       }
@@ -1711,7 +1735,11 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
                       : count <= 128 ? sort_listed<2>(s, ps, count, blo, bhi)
                       : count <= 256 ? sort_listed<4>(s, ps, count, blo, bhi)
                                      : sort_listed<8>(s, ps, count, blo, bhi);
-      if (!ok) return false;
+      if (!ok) {
+        // (half the window divides the words twice as finely)
+        if (++shrink > 4) return false;
+        continue;
+      }
       // first entry whose prefix weight reaches D
       int p = 0;
       for (int h = count <= 64 ? 32 : count <= 128 ? 64 : count <= 256 ? 128 : 256; h; h >>= 1)
@@ -1735,17 +1763,19 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
     lo = hi;
     il = ir;
     if (pend == 0 && low) {
-      // targets below the first window: from further down, up to it
-      if (start <= lmin) return false;
+      // targets below the first window, or in a part passed over: again from
+      // further down, part by part
+      if (start <= lmin && !jump) return false;
       pend = low;
       low = 0;
-      iend = start;
+      jump = false;
+      iend = rmax;
       il = start = max(start - 13, lmin);
       lo = bound(il);
     } else if (pend) {
       // (nothing is expected before the pending targets' windows)
       const int nx = min(wave_min_int_x(((pend >> lane) & 1ull) ? cl : SAMPLE_ROWS), rmax - 1);
-      if (nx > il) {
+      if (jump && nx > il) {
         il = nx;
         lo = bound(il);
       }
@@ -2123,8 +2153,13 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
 }
 
 // The words of todo that hold an unsettled segment (listed by the
-// division-free kernels: todo_list[0, *todo_count)), one wave per word taken
-// from *next.  The count is final: it belongs to earlier kernels.
+// division-free kernels: todo_list[0, *todo_count)), REST_PER of a word's
+// segments per claim of a wave from *next: the first of every word, then the
+// next ones (whose claims most words leave empty).  Such segments cluster in a
+// few columns, so a whole word per wave was one long chain (2859 segments of
+// the 2000 x 2000 path 5.3 ms).  The count is final: it belongs to earlier
+// kernels.
+constexpr int REST_PER = 2;
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, const double *__restrict__ lam_all,
            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
@@ -2141,11 +2176,15 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
   unsigned short *lr = (unsigned short *)(lk + lcap);
   const int count = *todo_count;
   while (true) {
-    int e = 0;
-    if (lane == 0) e = atomicAdd(next, 1);
-    e = uni_int(e);
-    if (e >= count) break;
-    const int w = uni_int(todo_list[e]);
+    unsigned e = 0;
+    if (lane == 0) e = (unsigned)atomicAdd(next, 1);
+    e = (unsigned)uni_int((int)e);
+    if (e >= (unsigned)count * (64u / REST_PER)) break;
+    const int skip = (int)(e / (unsigned)count) * REST_PER;
+    const int w = uni_int(todo_list[e % (unsigned)count]);
+    uint64_t bits = todo[w];
+    if (__builtin_popcountll(bits) <= skip) continue;
+    for (int q = 0; q < skip; ++q) bits &= bits - 1;
     const int b = find_owner(wstart, B, w);
     const ProbDesc d = P[b];
     const int wpr = (d.m + 63) >> 6, wl = w - wstart[b], jj = wl / wpr, k0 = (wl - jj * wpr) * 64;
@@ -2158,7 +2197,7 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
     wave_lds_sync();
     for (int t = lane; t < d.L; t += 64) slam[t] = lambda_fixed(lam[t], cj.e0);
     wave_lds_sync();
-    for (uint64_t bits = todo[d.mask_off + wl]; bits; bits &= bits - 1) {
+    for (int q = 0; q < REST_PER && bits; ++q, bits &= bits - 1) {
       const int k = k0 + __builtin_ctzll(bits);
       const SegIO s{d.X + (long long)k * d.ld, d.X + (long long)j * d.ld, d.n, T, Tp, cj.e0, lane, false};
       seg_exact(s, cj, ci[d.col_off + k], smp + (long long)(d.col_off + j) * SAMPLE_ROWS, lam, d.L,
@@ -2287,7 +2326,7 @@ __device__ __forceinline__ void leave_segment(const TodoList &td, long long word
 // across the item's k).  gate (optional): the kernel does nothing unless
 // *gate == gate_on.
 template <bool kLdsJ>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(64 * FAST_WAVES) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
            double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, const int *__restrict__ cand, int ncand,

@@ -606,7 +606,8 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   // global memory, which keeps room for more workgroups per CU
   const bool multi = Ly.Lmax > 1;
   const int sxj_rows = Ly.nmax <= SXJ_LDS_MAX ? Ly.nmax : 0;
-  const size_t lds_fast = seg_sxj_bytes(sxj_rows) + SEG_WAVES * (multi ? sizeof(PathScratch) : sizeof(FastScratch));
+  const size_t lds_fast =
+      seg_sxj_bytes(sxj_rows) + (multi ? SEG_WAVES * sizeof(PathScratch) : FAST_WAVES * sizeof(FastScratch));
   // the exact kernel's list: the larger one for several penalties
   const int lcap = multi ? PATH_CAP : WIN_CAP;
   const size_t lds_rest = SEG_WAVES * rest_wave_bytes(Ly.Lmax, lcap);
@@ -652,7 +653,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
     const ItemQueue queue{ditems, Ly.nitems, Ly.ksplit, dcounter, dxstart};
     auto kseg = sxj_rows > 0 ? (multi ? k_seg_path<true> : k_seg_fast<true>)
                              : (multi ? k_seg_path<false> : k_seg_fast<false>);
-    hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * SEG_WAVES), lds_fast, ls, dP, queue, dlam, dci, dsmp,
+    hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * (multi ? SEG_WAVES : FAST_WAVES)), lds_fast, ls, dP, queue, dlam, dci, dsmp,
                        dDZ, dV, dE, dR, ro.cand, ro.ncand, ro.gate, ro.gate_on, dmask, todo, sxj_rows);
     hipLaunchKernelGGL(k_seg_rest, dim3((unsigned)std::min<long long>(4ll * ctx->num_cu, (Ly.total_words + 3) / 4)),
                        dim3(64 * SEG_WAVES), lds_rest, ls, dP, dwst, (int)B, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags,
