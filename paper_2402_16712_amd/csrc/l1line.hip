@@ -1988,9 +1988,10 @@ static int solution_path_impl(l1line_ctx ctx, const double *X, int64_t n, int64_
   }
   {
     ProfScope ps(ctx, s, "sp_bounds");
-    hipLaunchKernelGGL(k_sp_tiles, dim3(1), dim3(1024), 0, s, NE, (const double *)elam, (const PathScale *)sc, bnd,
-                       Tp);
-    hipLaunchKernelGGL(k_sp_slack, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, (int)n, (int)m,
+    // (the sorted sample in the tiles' upper bounds, which come later)
+    hipLaunchKernelGGL(k_sp_sample, dim3(SP_SAMPLES / 64), dim3(256), 0, s, NE, (const double *)elam, (uint64_t *)U);
+    hipLaunchKernelGGL(k_sp_tiles, dim3(1), dim3(1024), 0, s, (const uint64_t *)U, (const PathScale *)sc, bnd, Tp);
+    hipLaunchKernelGGL(k_sp_slack, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, (int)n, (int)m,
                        (const ColInfo *)bp.ci, (const double *)segv, (const PathScale *)sc, D);
     hipLaunchKernelGGL(k_sp_bounds, dim3(SP_TMAX), dim3(256), 0, s, (int)m, (const long long *)offsets,
                        (const uint64_t *)keyA, (const u128 *)stE, (const u128 *)stP, (const PathScale *)sc,

@@ -44,6 +44,7 @@
 constexpr int SP_TMAX = 4096;      // lambda tiles
 constexpr int SP_SAMPLES = 4096;   // breakpoints sampled to place them
 constexpr int SP_RG = 16;          // entries scored per pass over the rows
+constexpr int SP_CLAIM = 8;        // segments a wave of the residual kernel claims at a time
 
 struct PathScale {
   int sE, sP;        // units of E and P: 2^sE, 2^sP
@@ -335,15 +336,20 @@ k_sp_resid(const double *__restrict__ X, int n, int m, long long ld, const long 
   const int lane = threadIdx.x & 63;
   const XcdTiles tl(m, xcd_tile(n), blockDim.x >> 6);
   double we = 0.0, wv = 0.0, wl = 0.0;   // the wave's maxima, one atomic each at the end
-  for (;;) {
-    // the XCD's next tile slot from its own counter (next[x], zero at
-    // launch): the waves of an XCD stay on neighbouring slots, whose
-    // columns share its L2, however long their segments
-    int fi = 0;
-    if (lane == 0) fi = atomicAdd(next + tl.x, 1);
-    const long long f = __builtin_amdgcn_readfirstlane(__shfl(fi, 0));
+  for (int left = 0, fi = 0;; ++fi, --left) {
+    // the XCD's next tile slots from its own counter (next[x], zero at
+    // launch), SP_CLAIM at a time: the waves of an XCD stay on neighbouring
+    // slots, whose columns share its L2, however long their segments.  One
+    // counter takes an atomic every 0.1 us, which bound the kernel with one
+    // slot per claim (1000 x 501: 3.4 ms, now 1.6).
+    if (left == 0) {
+      int c = 0;
+      if (lane == 0) c = atomicAdd(next + tl.x, SP_CLAIM);
+      fi = __builtin_amdgcn_readfirstlane(c);
+      left = SP_CLAIM;
+    }
     long long g;
-    if (!tl.at(f, g)) break;
+    if (!tl.at(fi, g)) break;
     if (g < 0) continue;
     // the segment is the same for the whole wave: its values go to scalar
     // registers
@@ -655,56 +661,94 @@ k_sp_sort(int m, const long long *__restrict__ offsets, const double *__restrict
 // Tile boundaries b_0 = 0 < b_1 < ... < b_{T-1} = lambda_top at quantiles of
 // a strided sample of the breakpoints and on a uniform grid; tile i is
 // [b_i, b_{i+1}), the last [lambda_top, inf).  T = 1 when lambda_top is 0.
-__global__ void __launch_bounds__(1024)
-k_sp_tiles(long long NE, const double *__restrict__ elam, const PathScale *__restrict__ sc, double *__restrict__ bnd,
-           int *__restrict__ T) {
+// The breakpoint sample sorted: each of 64 blocks ranks 64 of the samples
+// against all of them (ties by place), four threads a sample.  (A bitonic
+// sort and a serial merge by one workgroup took 0.82 ms.)
+__global__ void __launch_bounds__(256)
+k_sp_sample(long long NE, const double *__restrict__ elam, uint64_t *__restrict__ sorted) {
   __shared__ uint64_t smp[SP_SAMPLES];
   const int tid = threadIdx.x;
-  for (int s = tid; s < SP_SAMPLES; s += 1024) {
+  for (int s = tid; s < SP_SAMPLES; s += 256) {
     const long long idx = NE > 0 ? ((long long)s * NE + NE / 2) / SP_SAMPLES : 0;
     smp[s] = NE > 0 ? dbits(elam[idx]) : 0;
   }
   __syncthreads();
-  for (int size = 2; size <= SP_SAMPLES; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = tid; t < SP_SAMPLES / 2; t += 1024) {
-        const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;
-        const bool up = (lo & size) == 0;
-        const uint64_t x = smp[lo], y = smp[hi];
-        if ((x > y) == up) {
-          smp[lo] = y;
-          smp[hi] = x;
-        }
-      }
-      __syncthreads();
-    }
+  const int me = blockIdx.x * 64 + (tid >> 2), part = tid & 3;
+  const uint64_t x = smp[me];
+  int rank = 0;
+#pragma unroll 8
+  for (int s = part; s < SP_SAMPLES; s += 4) {
+    const uint64_t y = smp[s];
+    rank += (y < x || (y == x && s < me)) ? 1 : 0;
   }
-  if (tid == 0) {
-    // half the boundaries at quantiles of the sample, half on a uniform grid
-    // over (0, lambda_top) (wide stretches with few breakpoints still get
-    // narrow tiles), merged in order without repeats
-    const double top = sc->lam_top;
-    constexpr int H = SP_TMAX / 2;
-    int c = 1;
-    bnd[0] = 0.0;
-    if (top > 0.0) {
-      int qa = 1, ua = 1;
-      while (qa < H || ua < H) {
-        const double xq = qa < H ? dofbits(smp[((long long)qa * SP_SAMPLES) / H]) : INFINITY;
-        const double xu = ua < H ? top * ((double)ua / (double)H) : INFINITY;
-        double x;
-        if (xq <= xu) {
-          x = xq;
-          ++qa;
-        } else {
-          x = xu;
-          ++ua;
-        }
-        if (x > bnd[c - 1] && x < top) bnd[c++] = x;
-      }
-      bnd[c++] = top;
+  rank += __shfl_xor(rank, 1);
+  rank += __shfl_xor(rank, 2);
+  if (part == 0) sorted[rank] = x;
+}
+
+// Tile bounds: half at quantiles of the sample, half on a uniform grid over
+// (0, lambda_top) (wide stretches with few breakpoints still get narrow
+// tiles), merged in order without repeats, from 0 to lambda_top.
+__global__ void __launch_bounds__(1024)
+k_sp_tiles(const uint64_t *__restrict__ sorted, const PathScale *__restrict__ sc, double *__restrict__ bnd,
+           int *__restrict__ T) {
+  constexpr int H = SP_TMAX / 2, M = 2 * (H - 1);
+  __shared__ double mg[SP_TMAX];
+  __shared__ int wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const double top = sc->lam_top;
+  if (!(top > 0.0)) {
+    if (tid == 0) {
+      bnd[0] = 0.0;
+      *T = 1;
     }
-    *T = c;
+    return;
+  }
+  auto quant = [&](int q) { return dofbits(sorted[((long long)q * SP_SAMPLES) / H]); };
+  auto grid = [&](int u) { return top * ((double)u / (double)H); };
+  // place in the merged order: a quantile goes before an equal grid point
+  for (int q = 1 + tid; q < H; q += 1024) {
+    const double x = quant(q);
+    int lo = 0, hi = H - 1;                        // grid points below x
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (grid(mid + 1) < x) lo = mid + 1; else hi = mid;
+    }
+    mg[q - 1 + lo] = x;
+    const double y = grid(q);
+    lo = 0;
+    hi = H - 1;                                    // quantiles at or below y
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (quant(mid + 1) <= y) lo = mid + 1; else hi = mid;
+    }
+    mg[q - 1 + lo] = y;
+  }
+  __syncthreads();
+  constexpr int PER = (M + 1023) / 1024;
+  bool keep[PER];
+  int cnt = 0;
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int i = tid * PER + r;
+    keep[r] = i < M && mg[i] > (i > 0 ? mg[i - 1] : 0.0) && mg[i] < top;
+    cnt += keep[r] ? 1 : 0;
+  }
+  const int incl = wave_scan_int(cnt);
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  int at = 1 + incl - cnt, all = 0;
+  for (int q = 0; q < 16; ++q) {
+    if (q < w) at += wsum[q];
+    all += wsum[q];
+  }
+#pragma unroll
+  for (int r = 0; r < PER; ++r)
+    if (keep[r]) bnd[at++] = mg[tid * PER + r];
+  if (tid == 0) {
+    bnd[0] = 0.0;
+    bnd[1 + all] = top;
+    *T = all + 2;
   }
 }
 
@@ -713,21 +757,24 @@ k_sp_tiles(long long NE, const double *__restrict__ elam, const PathScale *__res
 // residual terms, their R64 sum and of the ratios, plus ulp(lambda_top) V for
 // breakpoints rounded to doubles (V the largest |v| of the segment); 1.5 covers
 // the rounding of this sum.
-__global__ void k_sp_slack(int n, int m, const ColInfo *__restrict__ ci, const double *__restrict__ segv,
-                           const PathScale *__restrict__ sc, double *__restrict__ D) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// (one wave per j; the factor 1.5 covers the rounding of the sum in any order)
+__global__ void __launch_bounds__(256)
+k_sp_slack(int n, int m, const ColInfo *__restrict__ ci, const double *__restrict__ segv,
+           const PathScale *__restrict__ sc, double *__restrict__ D) {
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (j >= m) return;
   const double top = sc->lam_top;
   const double ulp = top > 0.0 ? ldexp(1.0, highest_bit_exp(top) - 52) : 0.0;
   const double u = ldexp(1.0, -53) * (double)(n + 4);
   const double Wj = ci[j].W;
   double s = 0.0;
-  for (int k = 0; k < m; ++k) {
+  for (int k = lane; k < m; k += 64) {
     if (k == j) continue;
     const double V = segv[(long long)j * m + k];
     s += u * (ci[k].W + V * Wj) + ulp * V;
   }
-  D[j] = 1.5 * s;
+  s = wave_total_dbl(s);
+  if (lane == 0) D[j] = 1.5 * s;
 }
 
 // Per tile i < T - 1 (one block): LB[i m + j] = lower bound of z_j on the tile,
@@ -849,7 +896,7 @@ struct PathOut {
 // Per tile: j at the start (after the entries at b_i), j at the end, the
 // records after the start point, and the entries of the start's j at b_i.
 struct TileInfo {
-  int jstart, jend, nstart, npoints;   // npoints: breakpoint values the sweep visited
+  int jstart, jend, nstart;
   long long ninner;
 };
 
@@ -900,8 +947,8 @@ __device__ void sp_batch(int m, int j, double lam, double p, const long long *__
   }
 }
 
-// records of coordinate j's sorted entries [s0, s1) (all at lambda p)
-__device__ void sp_events(int m, int j, double p, long long s0, long long s1, const long long *__restrict__ offsets,
+// records of coordinate j's sorted entries [s0, s1), each at its own lambda
+__device__ void sp_events(int m, int j, const uint64_t *__restrict__ key, long long s0, long long s1, const long long *__restrict__ offsets,
                           const uint32_t *__restrict__ id, const double *__restrict__ ev, const int *__restrict__ erow,
                           const u128 *__restrict__ stE, const u128 *__restrict__ stP, int sE, int sP,
                           const PathOut &o, long long at, long long cap, int lane) {
@@ -915,7 +962,7 @@ __device__ void sp_events(int m, int j, double p, long long s0, long long s1, co
     }
     const long long q = at + (s - s0);
     if (q < cap) {
-      o.lam[q] = p;
+      o.lam[q] = dofbits(key[s]);
       o.j[q] = j;
       o.k[q] = lo;
       o.v[q] = ev[e];
@@ -926,8 +973,58 @@ __device__ void sp_events(int m, int j, double p, long long s0, long long s1, co
   }
 }
 
-// One wave per tile.  emit = 0: fill info[i]; emit = 1: write the tile's
-// records from toff[i] (start-of-tile batch when swflag[i]).
+// The lowest of the lines (E, P) of the lanes with s >= 0 just right of p
+// (value, slope, then the smaller s), among the first `lanes` lanes (a power
+// of two; the result on every lane).
+__device__ __forceinline__ void sp_lowest(int &s, u128 &E, u128 &P, double p, int sE, int sP, int lanes, int lane) {
+  for (int d = 1; d < lanes; d <<= 1) {
+    const int os = __shfl_xor(s, d);
+    const u128 oE = shfl_u128(E, lane ^ d), oP = shfl_u128(P, lane ^ d);
+    bool take = false;
+    if (os >= 0) {
+      if (s < 0) take = true;
+      else {
+        const int cc = line_cmp_at(oE, oP, E, P, p, sE, sP);
+        take = cc < 0 || (cc == 0 && os < s);
+      }
+    }
+    if (take) {
+      s = os;
+      E = oE;
+      P = oP;
+    }
+  }
+  s = uni_int(s);
+  E = uni_u128(E);
+  P = uni_u128(P);
+}
+
+// The first of the crossings N / D (to slope P) of the lanes with s >= 0,
+// then the smallest slope, then the smaller s.
+__device__ __forceinline__ void sp_first_crossing(int &s, u128 &N, u128 &D, u128 &P, int lanes, int lane) {
+  for (int d = 1; d < lanes; d <<= 1) {
+    const int os = __shfl_xor(s, d);
+    const u128 oN = shfl_u128(N, lane ^ d), oD = shfl_u128(D, lane ^ d), oP = shfl_u128(P, lane ^ d);
+    bool take = false;
+    if (os >= 0) {
+      if (s < 0) take = true;
+      else {
+        const int cc = u256_cmp(u256_mul(oN, D), u256_mul(N, oD));
+        take = cc < 0 || (cc == 0 && (oP < P || (oP == P && os < s)));
+      }
+    }
+    if (take) {
+      s = os;
+      N = oN;
+      D = oD;
+      P = oP;
+    }
+  }
+  s = uni_int(s);
+  N = uni_u128(N);
+  D = uni_u128(D);
+}
+
 __global__ void __launch_bounds__(64)
 k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restrict__ elam,
            const double *__restrict__ ev, const int *__restrict__ erow, const uint64_t *__restrict__ key,
@@ -948,6 +1045,115 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
   const int sE = sc->sE, sP = sc->sP;
   const u128 one = fixed_of(1.0, sP);
   const double bl = bnd[i], br = i + 1 < T ? bnd[i + 1] : INFINITY;
+  if (c == 1) {
+    // one line all through the tile (nineteen tiles in twenty): its entries in
+    // [bl, br) in order, no crossings
+    const int j = L[0];
+    const long long a = offsets[(long long)j * m], N = offsets[(long long)j * m + m] - a;
+    const long long s0 = a + lower_bound_u64(key + a, N, dbits(bl)), s1 = a + upper_bound_u64(key + a, N, dbits(bl)),
+                    s2 = a + lower_bound_u64(key + a, N, dbits(br));
+    if (!emit) {
+      if (lane == 0) info[i] = TileInfo{j, j, (int)(s1 - s0), s2 - s1};
+      return;
+    }
+    long long to = toff[i];
+    if (swflag[i]) {
+      u128 E, P;
+      sp_line(stE, stP, a, s1, one, E, P);
+      sp_batch(m, j, bl, bl, offsets, elam, ev, erow, fixed_to_double(E, sE), fixed_to_double(P, sP), o, to, cap, lane);
+      to += m;
+    } else {
+      sp_events(m, j, key, s0, s1, offsets, id, ev, erow, stE, stP, sE, sP, o, to, cap, lane);
+      to += s1 - s0;
+    }
+    sp_events(m, j, key, s1, s2, offsets, id, ev, erow, stE, stP, sE, sP, o, to, cap, lane);
+    return;
+  }
+  if (c <= 64) {
+    // a lane per line, its place, next breakpoint and current line in
+    // registers: a breakpoint costs one trip to memory and as many comparison
+    // levels as the lines need
+    const int lanes = c <= 1 ? 1 : 1 << (32 - __builtin_clz((unsigned)(c - 1)));
+    const bool in = lane < c;
+    const int j = L[in ? lane : 0];
+    const long long a = offsets[(long long)j * m], b = offsets[(long long)j * m + m];
+    long long pos = a + lower_bound_u64(key + a, b - a, dbits(bl));
+    u128 E, P;
+    sp_line(stE, stP, a, pos, one, E, P);
+    uint64_t nk = in && pos < b ? key[pos] : ~0ull;
+    long long at = emit ? toff[i] : 0, ninner = 0;
+    int jstart = -1, nstart = 0, cur = -1;
+    double p = bl;
+    while (true) {
+      const uint64_t kp = dbits(p);
+      const long long pb = pos;
+      while (nk == kp) {
+        E = stE[pos];
+        P = stP[pos];
+        ++pos;
+        nk = pos < b ? key[pos] : ~0ull;
+      }
+      uint64_t qk = nk;
+      for (int d = 1; d < lanes; d <<= 1) {
+        const uint64_t x = shfl_xor_u64(qk, d);
+        qk = x < qk ? x : qk;
+      }
+      qk = uni_u64(qk);
+      const double q = qk == ~0ull ? br : fmin(dofbits(qk), br);
+      int bs = in ? lane : -1;
+      u128 bE = E, bP = P;
+      sp_lowest(bs, bE, bP, p, sE, sP, lanes, lane);
+      const int jn = __builtin_amdgcn_readlane(j, bs);
+      const long long s0 = (long long)uni_u64(shfl_u64((uint64_t)pb, bs)), s1 = (long long)uni_u64(shfl_u64((uint64_t)pos, bs));
+      const long long nev = s1 - s0;
+      const bool first = p == bl;
+      if (first) {
+        jstart = jn;
+        nstart = (int)nev;
+      }
+      const bool whole = first ? (emit && swflag[i]) : bs != cur;
+      if (!first) ninner += whole ? m : nev;
+      if (emit) {
+        if (whole) {
+          sp_batch(m, jn, p, p, offsets, elam, ev, erow, fixed_to_double(bE, sE), fixed_to_double(bP, sP), o, at, cap,
+                   lane);
+          at += m;
+        } else {
+          sp_events(m, jn, key, s0, s1, offsets, id, ev, erow, stE, stP, sE, sP, o, at, cap, lane);
+          at += nev;
+        }
+      }
+      cur = bs;
+      // crossings inside (p, q): the first line of smaller slope to meet the
+      // current one; among lines meeting it there, the smallest slope, then j
+      while (true) {
+        const u128 cE = readlane_u128(E, cur), cP = readlane_u128(P, cur);
+        int xs = in && P < cP && E > cE ? lane : -1;
+        u128 xN = E - cE, xD = cP - P, xP = P;
+        sp_first_crossing(xs, xN, xD, xP, lanes, lane);
+        if (xs < 0) break;
+        if (q < INFINITY) {
+          uint64_t Mq;
+          int Eq;
+          dbl_parts(q, Mq, Eq);
+          // crossing N/D 2^(sE - sP) at or beyond q: the entries at q decide
+          if (cmp_scaled(u256_of(xN), sE - sP, u256_mul(xD, (u128)Mq), Eq) >= 0) break;
+        }
+        cur = xs;
+        ninner += m;
+        if (emit) {
+          const u128 nE = readlane_u128(E, xs), nP = readlane_u128(P, xs);
+          sp_batch(m, __builtin_amdgcn_readlane(j, xs), ratio_to_double(xN, xD, sE - sP), p, offsets, elam, ev, erow,
+                   fixed_to_double(nE, sE), fixed_to_double(nP, sP), o, at, cap, lane);
+          at += m;
+        }
+      }
+      if (!(q < br)) break;
+      p = q;
+    }
+    if (!emit && lane == 0) info[i] = TileInfo{jstart, __builtin_amdgcn_readlane(j, cur), nstart, ninner};
+    return;
+  }
   for (int s = lane; s < c; s += 64) {
     const int j = L[s];
     const long long a = offsets[(long long)j * m], N = offsets[(long long)j * m + m] - a;
@@ -955,10 +1161,9 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
   }
   __syncthreads();
   long long at = emit ? toff[i] : 0, ninner = 0;
-  int jstart = -1, nstart = 0, cur = -1, npoints = 0;   // cur: survivor index of the lowest line
+  int jstart = -1, nstart = 0, cur = -1;   // cur: survivor index of the lowest line
   double p = bl;
   while (true) {
-    ++npoints;
     // apply the entries at p; the next breakpoint of any survivor
     const uint64_t kp = dbits(p);
     uint64_t qk = ~0ull;
@@ -987,26 +1192,7 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
         bP = P;
       }
     }
-    for (int d = 1; d < 64; d <<= 1) {
-      const int os = __shfl_xor(bs, d);
-      const u128 oE = shfl_u128(bE, lane ^ d), oP = shfl_u128(bP, lane ^ d);
-      bool take = false;
-      if (os >= 0) {
-        if (bs < 0) take = true;
-        else {
-          const int cc = line_cmp_at(oE, oP, bE, bP, p, sE, sP);
-          take = cc < 0 || (cc == 0 && os < bs);
-        }
-      }
-      if (take) {
-        bs = os;
-        bE = oE;
-        bP = oP;
-      }
-    }
-    bs = uni_int(bs);
-    bE = uni_u128(bE);
-    bP = uni_u128(bP);
+    sp_lowest(bs, bE, bP, p, sE, sP, 64, lane);
     const int jn = L[bs];
     const long long nev = POS[bs] - PB[bs];
     if (p == bl) {
@@ -1018,7 +1204,7 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
                    cap, lane);
           at += m;
         } else {
-          sp_events(m, jn, p, PB[bs], POS[bs], offsets, id, ev, erow, stE, stP, sE, sP, o, at, cap, lane);
+          sp_events(m, jn, key, PB[bs], POS[bs], offsets, id, ev, erow, stE, stP, sE, sP, o, at, cap, lane);
           at += nev;
         }
       }
@@ -1032,7 +1218,7 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
     } else {
       ninner += nev;
       if (emit) {
-        sp_events(m, jn, p, PB[bs], POS[bs], offsets, id, ev, erow, stE, stP, sE, sP, o, at, cap, lane);
+        sp_events(m, jn, key, PB[bs], POS[bs], offsets, id, ev, erow, stE, stP, sE, sP, o, at, cap, lane);
         at += nev;
       }
     }
@@ -1062,28 +1248,8 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
           xP = P;
         }
       }
-      for (int d = 1; d < 64; d <<= 1) {
-        const int os = __shfl_xor(xs, d);
-        const u128 oN = shfl_u128(xN, lane ^ d), oD = shfl_u128(xD, lane ^ d), oP = shfl_u128(xP, lane ^ d);
-        bool take = false;
-        if (os >= 0) {
-          if (xs < 0) take = true;
-          else {
-            const int cc = u256_cmp(u256_mul(oN, xD), u256_mul(xN, oD));
-            take = cc < 0 || (cc == 0 && (oP < xP || (oP == xP && os < xs)));
-          }
-        }
-        if (take) {
-          xs = os;
-          xN = oN;
-          xD = oD;
-          xP = oP;
-        }
-      }
-      xs = uni_int(xs);
+      sp_first_crossing(xs, xN, xD, xP, 64, lane);
       if (xs < 0) break;
-      xN = uni_u128(xN);
-      xD = uni_u128(xD);
       if (q < INFINITY) {
         uint64_t Mq;
         int Eq;
@@ -1110,7 +1276,6 @@ k_sp_sweep(int m, const long long *__restrict__ offsets, const double *__restric
     t.jstart = jstart;
     t.jend = L[cur];
     t.nstart = nstart;
-    t.npoints = npoints;
     t.ninner = ninner;
     info[i] = t;
   }
