@@ -980,8 +980,8 @@ k_signsum_batch(const ProbDesc *__restrict__ P, const int *__restrict__ tstart, 
 //     the next k from an LDS counter.
 //  3. What the margin does not settle is left to k_seg_rest: exact 128-bit
 //     sums and general rounds.
-constexpr int SEG_WAVES = 4;        // waves per workgroup (several penalties, exact)
-constexpr int FAST_WAVES = 4;
+constexpr int SEG_WAVES = 4;        // waves per workgroup of k_seg_rest
+constexpr int SEG_WAVES_MAX = 8;    // at most, of k_seg_fast and k_seg_path (4 or 8)
 constexpr int SXJ_LDS_MAX = 4096;   // longest column j copied to LDS (32 KB)
 constexpr int SEG_MASK_WORDS = 64;  // zero-segment mask words an item holds (one per lane: 4096 k)
 
@@ -1516,8 +1516,8 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
 // stage.  Neighbours in the sorted order are then checked against their exact
 // ratios and rows; where two ratios share a word the segment is left to
 // k_seg_rest.
-// 2000 x 2000 with 64 penalties 52.2 -> 27.6 ms (and 5.3 in k_seg_rest), 128
-// uneven matrices with 16 100 -> 62 (and 3.1).
+// 2000 x 2000 with 64 penalties 52.2 -> 22.5 ms, 128 uneven matrices with 16
+// 100 -> 40.
 struct PathScratch {
   double val[FAST_CAP];             // ratios in list order, then prefix weights in sorted order
   uint32_t list[FAST_CAP];          // rows in list order, then in sorted order
@@ -2326,7 +2326,7 @@ __device__ __forceinline__ void leave_segment(const TodoList &td, long long word
 // across the item's k).  gate (optional): the kernel does nothing unless
 // *gate == gate_on.
 template <bool kLdsJ>
-__global__ void __launch_bounds__(64 * FAST_WAVES) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(64 * SEG_WAVES_MAX) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
            double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, const int *__restrict__ cand, int ncand,
@@ -2481,7 +2481,7 @@ __device__ __forceinline__ void run_jobs(const SegIO &s, LdJ ldj, LdK ldk, uint6
 // Several penalties per problem: every live segment, one wave per segment, a
 // penalty per lane in groups of 64.
 template <bool kLdsJ>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(64 * SEG_WAVES_MAX) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
            double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, const int *__restrict__ cand, int ncand,

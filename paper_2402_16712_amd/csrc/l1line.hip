@@ -602,12 +602,22 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   if (outp) *outp = BatchPtrs{dV, dR, dci};
   l1line_ctx pc = prof ? ctx : nullptr;
 
-  // column j goes to LDS up to SXJ_LDS_MAX rows; longer ones are read from
-  // global memory, which keeps room for more workgroups per CU
+  // column j goes to LDS up to SXJ_LDS_MAX rows (2000 x 2000: 3.85 ms, from L2
+  // 6.24).  Four waves share it, or eight where that lets more waves share a
+  // CU (at most 16, what the kernels' registers allow: path 2000 x 2000 x 64
+  // 24.9 -> 22.5 ms, the batch of up to 4000 rows 59 -> 40); without the copy
+  // eight (20011 x 151 368 -> 314 us).
   const bool multi = Ly.Lmax > 1;
   const int sxj_rows = Ly.nmax <= SXJ_LDS_MAX ? Ly.nmax : 0;
-  const size_t lds_fast =
-      seg_sxj_bytes(sxj_rows) + (multi ? SEG_WAVES * sizeof(PathScratch) : FAST_WAVES * sizeof(FastScratch));
+  auto lds_of = [&](int waves) {
+    return seg_sxj_bytes(sxj_rows) + waves * (multi ? sizeof(PathScratch) : sizeof(FastScratch));
+  };
+  auto waves_per_cu = [&](int waves) {
+    const size_t granules = (lds_of(waves) + 16 + 511) / 512 * 512;   // + static LDS
+    return std::min<int>(16, waves * (int)((size_t)160 * 1024 / granules));
+  };
+  const int seg_waves = sxj_rows == 0 || waves_per_cu(8) > waves_per_cu(4) ? 8 : 4;
+  const size_t lds_fast = lds_of(seg_waves);
   // the exact kernel's list: the larger one for several penalties
   const int lcap = multi ? PATH_CAP : WIN_CAP;
   const size_t lds_rest = SEG_WAVES * rest_wave_bytes(Ly.Lmax, lcap);
@@ -615,7 +625,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
     HIP_TRY(hipFuncSetAttribute((const void *)k_seg_rest, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(SEG_WAVES * rest_wave_bytes(L1LINE_MAX_LAMBDAS, PATH_CAP))));
     HIP_TRY(hipFuncSetAttribute((const void *)k_seg_path<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(seg_sxj_bytes(SXJ_LDS_MAX) + SEG_WAVES * sizeof(PathScratch))));
+                                (int)(seg_sxj_bytes(SXJ_LDS_MAX) + 8 * sizeof(PathScratch))));
     ctx->attr_seg = true;
   }
   const long long all_items = Ly.ksplit ? (long long)Ly.nitems * SEG_XCDS : (long long)Ly.nitems;
@@ -653,7 +663,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
     const ItemQueue queue{ditems, Ly.nitems, Ly.ksplit, dcounter, dxstart};
     auto kseg = sxj_rows > 0 ? (multi ? k_seg_path<true> : k_seg_fast<true>)
                              : (multi ? k_seg_path<false> : k_seg_fast<false>);
-    hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * (multi ? SEG_WAVES : FAST_WAVES)), lds_fast, ls, dP, queue, dlam, dci, dsmp,
+    hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * seg_waves), lds_fast, ls, dP, queue, dlam, dci, dsmp,
                        dDZ, dV, dE, dR, ro.cand, ro.ncand, ro.gate, ro.gate_on, dmask, todo, sxj_rows);
     hipLaunchKernelGGL(k_seg_rest, dim3((unsigned)std::min<long long>(4ll * ctx->num_cu, (Ly.total_words + 3) / 4)),
                        dim3(64 * SEG_WAVES), lds_rest, ls, dP, dwst, (int)B, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags,
