@@ -1231,9 +1231,10 @@ __device__ __forceinline__ void for_row_pairs(const SegIO &s, LdJ ldj, LdK ldk, 
 
 template <class LdJ, class LdK>
 __device__ __forceinline__ void window_pass(const SegIO &s, LdJ ldj, LdK ldk, double lo, double hi, uint32_t *list,
-                                            int cap, double &Tsum, int &count) {
+                                            int cap, double &Tsum, int &count, int &listed) {
   double S = 0.0;
   int c = 0;
+  listed = 0;
   for (int t0 = 0; t0 < s.T; t0 += 32) {
     uint32_t m = 0;
     const int t1 = min(s.T, t0 + 32);
@@ -1246,8 +1247,12 @@ __device__ __forceinline__ void window_pass(const SegIO &s, LdJ ldj, LdK ldk, do
     m <<= 32 - ((t1 - t0 + 3) & ~3);
     const int pc = __builtin_popcount(m), incl = wave_scan_int(pc);
     const int tot = __builtin_amdgcn_readlane(incl, 63);
-    if (c + tot <= cap) {
+    if (c < cap) {
+      // (past the list's end nothing is written; the count goes on)
       int pos = c + incl - pc;
+      const uint64_t fit = __ballot(c + incl <= cap);   // (the lanes up to one)
+      listed = c + (fit ? __builtin_amdgcn_readlane(incl, __builtin_popcountll(fit) - 1) : 0);
+      m = c + incl <= cap ? m : 0;
       while (__ballot(m != 0)) {
         if (m) {
           const int i = __builtin_clz(m);
@@ -1273,6 +1278,67 @@ __device__ __forceinline__ void probe_pass(const SegIO &s, LdJ ldj, LdK ldk, con
   });
 #pragma unroll
   for (int q = 0; q < 3; ++q) T[q] = wave_total_dbl(S[q]);
+}
+
+// A window that overflows the list although its samples promised fewer rows
+// holds many equal ratios (whole numbers in long columns).  The most common
+// ratio of three of the listed rows, and bounds just around it.
+__device__ __forceinline__ bool tied_ratio(const SegIO &s, const uint32_t *list, int count, double &K, double &klo,
+                                           double &khi) {
+  if (count < 64) return false;                    // (too few were listed before the overflow)
+  const int r = (int)list[s.lane];
+  const double q = gld(s.xk + r) / sxj_at(s, r);
+  int best = -1;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const double x = readlane_dbl(q, 21 * c);
+    const int n = __builtin_popcountll(__ballot(q == x));
+    K = n > best ? x : K;
+    best = max(best, n);
+  }
+  klo = K - fabs(K) * 0x1p-44;
+  khi = K + fabs(K) * 0x1p-44;
+  return best > 1;
+}
+
+// The targets D (counted from klo, on the lanes of pend) among the rows
+// between klo and khi when every one of their ratios rounds to K: the order is
+// then the rows' order.  One pass finds each target's 64-row slot, a look at
+// that slot its row.  false: another ratio lies there, or too close to call.
+template <class LdJ, class LdK>
+__device__ __forceinline__ bool tie_rows(const SegIO &s, LdJ ldj, LdK ldk, double K, double klo, double khi,
+                                         uint64_t pend, double D, double tol, int &row) {
+  const bool mine = ((pend >> s.lane) & 1ull) != 0;
+  auto weight = [&](double a, double b, bool &bad) {
+    const bool in = ((hi32(fma(-klo, a, b)) ^ hi32(fma(-khi, a, b))) >> 31) != 0;
+    bad = bad || (in && b / a != K);
+    return in ? fabs(a) : 0.0;
+  };
+  double run = 0.0, base = 0.0;
+  int t = 0, slot = -1;
+  bool bad = false;
+  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
+    const double w = weight(a, b, bad);
+    if (__ballot(w != 0.0)) {
+      const double to = run + wave_total_dbl(w);
+      const bool here = mine && D > run && D <= to;
+      slot = here ? t : slot;
+      base = here ? run : base;
+      bad = bad || (mine && fabs(to - D) <= tol);
+      run = to;
+    }
+    ++t;
+  });
+  if (__ballot(bad || (mine && slot < 0))) return false;
+  for (; pend; pend &= pend - 1) {
+    const int l = __builtin_ctzll(pend), ts = __builtin_amdgcn_readlane(slot, l);
+    const double d = readlane_dbl(D, l) - readlane_dbl(base, l);
+    const double w = weight(ldj(s.lane + 64 * ts), ldk(s.lane + 64 * ts), bad), incl = wave_scan_dbl(w);
+    const uint64_t m = __ballot(w != 0.0 && incl >= d);
+    if (m == 0 || __ballot(w != 0.0 && fabs(incl - d) <= tol)) return false;
+    if (s.lane == l) row = 64 * ts + __builtin_ctzll(m);
+  }
+  return true;
 }
 
 enum : int { FAST_HIT, FAST_ABOVE, FAST_UNSURE };
@@ -1469,8 +1535,8 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
       continue;
     }
     double T;
-    int count;
-    window_pass(s, ldj, ldk, lo, hi, fs->list, FAST_CAP, T, count);
+    int count, listed;
+    window_pass(s, ldj, ldk, lo, hi, fs->list, FAST_CAP, T, count, listed);
     const double D = target(T);
     if (fabs(D) <= tol) return false;
     if (D < 0.0) {
@@ -1486,6 +1552,21 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
     }
     if (count > FAST_CAP) {
       est = count;
+      double t[3], Tq[3], K = 0.0;
+      if (tied_ratio(s, fs->list, listed, K, t[0], t[2]) && t[0] > lo && t[2] < hi) {
+        t[1] = t[2];
+        probe_pass(s, ldj, ldk, t, Tq);
+        const double dl = target(Tq[0]), dr = target(Tq[2]);
+        if (fabs(dl) <= tol || fabs(dr) <= tol) return false;
+        if (dl > 0.0 && dr < 0.0) {
+          v = K;
+          const bool ok = tie_rows(s, ldj, ldk, K, t[0], t[2], 1ull, dl, tol, row);
+          row = __builtin_amdgcn_readfirstlane(row);
+          return ok;
+        }
+        lo = dr > 0.0 ? t[2] : lo;
+        hi = dl < 0.0 ? t[0] : hi;
+      }
       continue;
     }
     const double blo = il <= lmin && neg ? value(0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1) : hi;
@@ -1718,13 +1799,36 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
       }
     }
     double T;
-    int count;
-    window_pass(s, ldj, ldk, lo, hi, ps->list, FAST_CAP, T, count);
+    int count, listed;
+    window_pass(s, ldj, ldk, lo, hi, ps->list, FAST_CAP, T, count, listed);
+    const bool mine = ((pend >> lane) & 1ull) != 0;
     if (count > FAST_CAP) {
       ++shrink;
+      double t[3], Tq[3], K = 0.0;
+      if (tied_ratio(s, ps->list, listed, K, t[0], t[2]) && t[0] > lo && t[2] < hi) {
+        // the targets among the equal ratios, now; the window then ends before them
+        t[1] = t[2];
+        probe_pass(s, ldj, ldk, t, Tq);
+        const double dl = 0.5 * (neg ? Tq[0] + lam : Tq[0] - lam), dr = 0.5 * (neg ? Tq[2] + lam : Tq[2] - lam);
+        if (__ballot(mine && (fabs(dl) <= tol || fabs(dr) <= tol))) return false;
+        const uint64_t tied = __ballot(mine && dl > 0.0 && dr < 0.0);
+        if (tied) {
+          int rr = 0;
+          if (!tie_rows(s, ldj, ldk, K, t[0], t[2], tied, dl, tol, rr)) return false;
+          if ((tied >> lane) & 1ull) {
+            v = K;
+            row = rr;
+          }
+          pend &= ~tied;
+        }
+        // nothing below the tie is wanted: go on above it
+        if (__ballot(((pend >> lane) & 1ull) && dl < 0.0) == 0) {
+          lo = t[2];
+          shrink = 0;
+        }
+      }
       continue;
     }
-    const bool mine = ((pend >> lane) & 1ull) != 0;
     const double D = 0.5 * (neg ? T + lam : T - lam);
     if (__ballot(mine && fabs(D) <= tol)) return false;
     low |= __ballot(mine && D < 0.0);
