@@ -1068,9 +1068,11 @@ __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInf
 // Segments settled by the sign sums alone.  One thread per pair (j, k), one
 // wave per 64 consecutive k of a preserved column: where every penalty of the
 // problem has 0 as a minimiser (sign_sum_side, the segment kernel's own test),
-// writes v_k = 0, e_jk = the R64 mass of column k, row -1 for every penalty
-// and sets bit k & 63 of mask word (jj, k >> 6); the segment kernel skips such
-// segments.  wstart[b] = first mask word of problem b (mj ceil(m / 64) words,
+// sets bit k & 63 of mask word (jj, k >> 6); the segment kernel skips such
+// segments.  They have v_k = 0, e_jk = the R64 mass of column k and row -1 for
+// every penalty: written here for a problem of one penalty (Algorithm 2 reads
+// them), taken from the mask by the kernels that follow for one of several
+// (2000 x 2000 with 64: 2.0 ms of scattered stores).  wstart[b] = first mask word of problem b (mj ceil(m / 64) words,
 // mj = ncand with a candidate list, problem 0 only, else m).
 __global__ void __launch_bounds__(256)
 k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, int total_words,
@@ -1110,13 +1112,11 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
       const double *lam = lam_all + d.lam_off;
       skip = true;
       for (int t = 0; t < d.L && skip; ++t) skip = sign_sum_side(dz, lam[t], cj.W, unc) == 0;
-      if (skip) {
-        const long long mm = (long long)d.m * d.m, base = d.ws_off + (long long)j * d.m + k;
-        for (int t = 0; t < d.L; ++t) {
-          V[base + t * mm] = 0.0;
-          E[base + t * mm] = ck.W;
-          R[base + t * mm] = -1;
-        }
+      if (skip && d.L == 1) {
+        const long long base = d.ws_off + (long long)j * d.m + k;
+        V[base] = 0.0;
+        E[base] = ck.W;
+        R[base] = -1;
       }
     }
   }
@@ -2279,14 +2279,18 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
   uint64_t *lk = (uint64_t *)(ws + 1);
   unsigned short *lr = (unsigned short *)(lk + lcap);
   const int count = *todo_count;
-  while (true) {
-    unsigned e = 0;
-    if (lane == 0) e = (unsigned)atomicAdd(next, 1);
-    e = (unsigned)uni_int((int)e);
-    if (e >= (unsigned)count * (64u / REST_PER)) break;
+  // the first claim is the wave's own number (an atomic of every wave on one
+  // counter took 50 us where nothing was left)
+  const unsigned waves = gridDim.x * 4u, claims = (unsigned)count * (64u / REST_PER);
+  for (unsigned e = blockIdx.x * 4u + wave; e < claims;) {
     const int skip = (int)(e / (unsigned)count) * REST_PER;
     const int w = uni_int(todo_list[e % (unsigned)count]);
     uint64_t bits = todo[w];
+    {
+      unsigned c = 0;
+      if (lane == 0) c = (unsigned)atomicAdd(next, 1);
+      e = waves + (unsigned)uni_int((int)c);
+    }
     if (__builtin_popcountll(bits) <= skip) continue;
     for (int q = 0; q < skip; ++q) bits &= bits - 1;
     const int b = find_owner(wstart, B, w);
@@ -2334,23 +2338,33 @@ struct ItemQueue {
 // The next item of the workgroup (every thread calls it): false when none is
 // left.  jj: the item's row in the masks.
 __device__ __forceinline__ bool next_item(const ItemQueue &q, const ProbDesc *__restrict__ P,
-                                          const int *__restrict__ cand, int ncand, int *s_item, int *s_tried,
-                                          WorkItem &it, int &jj) {
+                                          const int *__restrict__ cand, int ncand, int *s_item, WorkItem &it, int &jj) {
   while (true) {
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
+      // lanes 0 .. 7 look at the counters together (trying them one atomic
+      // after the other cost every workgroup about 6 us at its end); the
+      // nearest XCD at or after home with items left is tried
       int g = -1;
-      const int home = blockIdx.x % SEG_XCDS;
-      for (int tried = *s_tried; tried < SEG_XCDS; ++tried) {
-        const int x = (home + tried) % SEG_XCDS;
-        const int c = atomicAdd(q.counter + x, 1);
-        const int have = q.items ? q.xstart[x + 1] - q.xstart[x] : q.nitems;
-        if (c < have) {
-          g = q.items ? q.xstart[x] + c : x * q.nitems + c;
+      const int lane = threadIdx.x, x = (blockIdx.x + lane) % SEG_XCDS;
+      int begin = 0, have = 0;
+      if (lane < SEG_XCDS) {
+        begin = q.items ? q.xstart[x] : x * q.nitems;
+        have = q.items ? q.xstart[x + 1] - begin : q.nitems;
+      }
+      while (true) {
+        const int seen = lane < SEG_XCDS ? __hip_atomic_load(q.counter + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        const uint64_t open = __ballot(lane < SEG_XCDS && seen < have);
+        if (open == 0) break;
+        const int l = __builtin_ctzll(open);
+        int c = 0;
+        if (lane == l) c = atomicAdd(q.counter + x, 1);
+        c = __builtin_amdgcn_readlane(c, l);
+        if (c < __builtin_amdgcn_readlane(have, l)) {
+          g = __builtin_amdgcn_readlane(begin, l) + c;
           break;
         }
-        *s_tried = tried + 1;
       }
-      *s_item = g;
+      if (lane == 0) *s_item = g;
     }
     __syncthreads();
     const int g = uni_int(*s_item);
@@ -2437,15 +2451,14 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
            const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask, TodoList td,
            int sxj_rows) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_item, s_tried, knext;
+  __shared__ int s_item, knext;
   if (gate && *gate != gate_on) return;
-  if (threadIdx.x == 0) s_tried = 0;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double *sxj_lds = (double *)smem;
   FastScratch *fs = (FastScratch *)(smem + (kLdsJ ? seg_sxj_bytes(sxj_rows) : 0)) + wave;
   WorkItem it;
   int jj;
-  while (next_item(queue, P, cand, ncand, &s_item, &s_tried, it, jj)) {
+  while (next_item(queue, P, cand, ncand, &s_item, it, jj)) {
     const ProbDesc d = P[it.b];
     const int n = d.n, m = d.m, T = (n + 63) >> 6, j = it.j;
     const ColInfo *cis = ci + d.col_off;
@@ -2592,15 +2605,14 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
            const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask, TodoList td,
            int sxj_rows) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_item, s_tried, knext;
+  __shared__ int s_item, knext;
   if (gate && *gate != gate_on) return;
-  if (threadIdx.x == 0) s_tried = 0;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double *sxj_lds = (double *)smem;
   PathScratch *ps = (PathScratch *)(smem + (kLdsJ ? seg_sxj_bytes(sxj_rows) : 0)) + wave;
   WorkItem it;
   int jj;
-  while (next_item(queue, P, cand, ncand, &s_item, &s_tried, it, jj)) {
+  while (next_item(queue, P, cand, ncand, &s_item, it, jj)) {
     const ProbDesc d = P[it.b];
     const int n = d.n, m = d.m, L = d.L, T = (n + 63) >> 6, j = it.j;
     const ColInfo *cis = ci + d.col_off;
@@ -2706,7 +2718,8 @@ __global__ void __launch_bounds__(64)
 k_reduce_batch(const ProbDesc *__restrict__ P, const int *__restrict__ zstart, int B,
                const double *__restrict__ lam_all, const double *__restrict__ V, const double *__restrict__ E,
                double *__restrict__ Z, int *__restrict__ zflag, const int *__restrict__ jmask,
-               const int *__restrict__ gate, int gate_on) {
+               const int *__restrict__ gate, int gate_on, const unsigned long long *__restrict__ segmask,
+               const ColInfo *__restrict__ ci) {
   if (gate && *gate != gate_on) return;
   const long long g = blockIdx.x;
   const int lane = threadIdx.x;
@@ -2725,9 +2738,12 @@ k_reduce_batch(const ProbDesc *__restrict__ P, const int *__restrict__ zstart, i
   const long long off = d.ws_off + ((long long)t * d.m + j) * d.m;
   double pe = 0.0, pv = 0.0;
   int bad = 0;
+  // (several penalties: the segments of the mask are not in V and E)
+  const unsigned long long *zero = d.L > 1 ? segmask + d.mask_off + (long long)j * ((d.m + 63) >> 6) : nullptr;
   for (int k = lane; k < d.m; k += 64) {
-    pe = pe + E[off + k];
-    const double a = fabs(V[off + k]);
+    const bool z = zero && ((zero[k >> 6] >> lane) & 1ull);
+    pe = pe + (z ? ci[d.col_off + k].W : E[off + k]);
+    const double a = z ? 0.0 : fabs(V[off + k]);
     pv = pv + a;
     bad |= !isfinite(a);
   }
@@ -2751,7 +2767,8 @@ __global__ void __launch_bounds__(256)
 k_argmin_batch(const ProbDesc *__restrict__ P, const int *__restrict__ ostart, int B,
                const double *__restrict__ V, const int *__restrict__ R, const double *__restrict__ Z,
                const int *__restrict__ zflag, const ColInfo *__restrict__ ci, const int *__restrict__ segflags,
-               const int *__restrict__ jmask, const int *__restrict__ gate, int gate_on, int *__restrict__ sticky) {
+               const int *__restrict__ jmask, const int *__restrict__ gate, int gate_on, int *__restrict__ sticky,
+               const unsigned long long *__restrict__ segmask) {
   __shared__ double sz[256];
   __shared__ int sj[256];
   __shared__ int sflag[256];
@@ -2785,9 +2802,11 @@ k_argmin_batch(const ProbDesc *__restrict__ P, const int *__restrict__ ostart, i
   }
   const int js = sj[0];
   const long long src = d.ws_off + ((long long)t * m + js) * m;
+  const unsigned long long *zero = d.L > 1 ? segmask + d.mask_off + (long long)js * ((m + 63) >> 6) : nullptr;
   for (int k = tid; k < m; k += blockDim.x) {
-    d.Vout[(long long)t * m + k] = V[src + k];
-    if (d.ROWout) d.ROWout[(long long)t * m + k] = R[src + k];
+    const bool zk = zero && ((zero[k >> 6] >> (k & 63)) & 1ull);
+    d.Vout[(long long)t * m + k] = zk ? 0.0 : V[src + k];
+    if (d.ROWout) d.ROWout[(long long)t * m + k] = zk ? -1 : R[src + k];
     if (d.ZALLout) d.ZALLout[(long long)t * m + k] = z[k];
   }
   if (tid == 0) {

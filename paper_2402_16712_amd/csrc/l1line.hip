@@ -471,13 +471,13 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
   }
   // few sign-sum tiles (a narrow matrix, a candidate list): their rows are cut
   // into parts, summed apart and then added, so that every compute unit gets
-  // two workgroups; parts of at least 64 rows (four LDS stages), at most 32 of
+  // two workgroups; parts of at least 32 rows (two LDS stages), at most 32 of
   // them (each costs 16 bytes per pair written and read again).  From 2 tiles
   // per CU on one part is the faster form.  Never past the caller's limit on
   // the workspace.
   const long long want = 2ll * ctx->num_cu;
   long long sp = (want + Ly.total_tiles - 1) / std::max(1ll, Ly.total_tiles);
-  sp = std::min<long long>({sp, 32, Ly.nmax / 64});
+  sp = std::min<long long>({sp, 32, Ly.nmax / 32});
   Ly.ss_split = (int)std::max<long long>(1, sp);
   Ly.ss_per = (B == 1 && ro.cand) ? (long long)ro.ncand * probs[0].m : Ly.total_pairs;
   layout_sizes(Ly);
@@ -555,6 +555,37 @@ static void fill_meta(char *h, const BatchLayout &Ly, const l1line_problem *prob
   memcpy(h + Ly.o_xstart, Ly.xstart, sizeof Ly.xstart);
 }
 
+// Metadata of a one-problem call written by a kernel from its arguments: no
+// staging buffer, no copy and no event (which took about 10 us of a small
+// call), nothing for the next call to wait for.  Clears the counters too.
+struct LambdaArgs {
+  double v[L1LINE_MAX_LAMBDAS];
+};
+__global__ void __launch_bounds__(L1LINE_MAX_LAMBDAS) k_meta_single(ProbDesc pd, LambdaArgs lam, BatchLayout Ly, char *d) {
+  const int t = threadIdx.x;
+  if (t < pd.L) ((double *)(d + Ly.o_lam))[t] = lam.v[t];
+  if (t < 16) ((int *)(d + Ly.o_counter))[t] = 0;
+  if (t <= SEG_XCDS) ((int *)(d + Ly.o_xstart))[t] = Ly.xstart[t];
+  if (t != 0) return;
+  *(ProbDesc *)(d + Ly.o_desc) = pd;
+  auto pair = [&](size_t off, long long total) {
+    int *p = (int *)(d + off);
+    p[0] = 0;
+    p[1] = (int)total;
+  };
+  pair(Ly.o_colstart, Ly.total_cols);
+  pair(Ly.o_zstart, Ly.total_z);
+  pair(Ly.o_ostart, Ly.total_out);
+  pair(Ly.o_tstart, Ly.total_tiles);
+  pair(Ly.o_wstart, Ly.total_words);
+}
+static void launch_meta(hipStream_t s, const l1line_problem &p, const BatchLayout &Ly, char *d) {
+  const MetaCursor c0 = {0, 0, 0, 0, 0, 0, 0, 0};
+  LambdaArgs la;
+  for (int t = 0; t < L1LINE_MAX_LAMBDAS; ++t) la.v[t] = t < p.L ? p.lambdas[t] : 0.0;
+  hipLaunchKernelGGL(k_meta_single, dim3(1), dim3(L1LINE_MAX_LAMBDAS), 0, s, prob_desc(p, c0), la, Ly, d);
+}
+
 // The form of the column preparation for `cols` columns of up to n rows: four
 // waves per column with the column in LDS up to eight columns per CU (2000 x
 // 2000: 23 us, one wave 29), longer columns four waves up to four per CU (20011
@@ -576,10 +607,10 @@ static void launch_colprep(l1line_ctx ctx, hipStream_t s, const double *X, int64
 
 // The launch sequence of one batch call on stream ls, the workspace at d
 // (its metadata block already in place or written by an earlier kernel on
-// ls).  `prof`: bracket the kernels with the context's timing events;
+// ls).  `cleared`: the counters are zero already.  `prof`: bracket the kernels with the context's timing events;
 // t0 / t1 (optional): events recorded around the segment kernel.
 static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, char *d, int64_t B,
-                      const TuneParams &tp, const RunOpts &ro, bool prof, hipEvent_t t0, hipEvent_t t1,
+                      const TuneParams &tp, const RunOpts &ro, bool prof, bool cleared, hipEvent_t t0, hipEvent_t t1,
                       BatchPtrs *outp) {
   const ProbDesc *dP = (const ProbDesc *)(d + Ly.o_desc);
   const int *dcol = (const int *)(d + Ly.o_colstart), *dz = (const int *)(d + Ly.o_zstart),
@@ -632,7 +663,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   const int grid_seg = (int)std::max(1ll, std::min(all_items, (long long)tp.blocks_per_cu * ctx->num_cu));
   {
     ProfScope ps(pc, ls, "colprep");
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, ls, dcounter, 16ll, 0);
+    if (!cleared) hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, ls, dcounter, 16ll, 0);
     if (have_ci) {
       hipLaunchKernelGGL(k_fill_int, dim3((unsigned)((Ly.total_cols + 255) / 256)), dim3(256), 0, ls, dsegflags,
                          (long long)Ly.total_cols, 0);
@@ -674,12 +705,12 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   {
     ProfScope ps(pc, ls, "reduce");
     hipLaunchKernelGGL(k_reduce_batch, dim3((unsigned)Ly.total_z), dim3(64), 0, ls, dP, dz, (int)B, dlam, dV, dE,
-                       dZ, dzflag, ro.jmask, ro.gate, ro.gate_on);
+                       dZ, dzflag, ro.jmask, ro.gate, ro.gate_on, dmask, dci);
   }
   {
     ProfScope ps(pc, ls, "argmin");
     hipLaunchKernelGGL(k_argmin_batch, dim3((unsigned)Ly.total_out), dim3(256), 0, ls, dP, dout, (int)B, dV, dR,
-                       dZ, dzflag, dci, dsegflags, ro.jmask, ro.gate, ro.gate_on, ctx->sticky);
+                       dZ, dzflag, dci, dsegflags, ro.jmask, ro.gate, ro.gate_on, ctx->sticky, dmask);
   }
   return L1LINE_OK;
 }
@@ -693,47 +724,55 @@ static int run_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, int
   if (st) return st;
   st = ensure_ws(ctx, Ly.bytes, s);
   if (st) return st;
-  st = ensure_stage(ctx, Ly.meta_bytes);
-  if (st) return st;
-
-  // metadata into the pinned staging buffer
-  char *h = (char *)ctx->stage;
   char *d = (char *)ctx->ws;
-  fill_meta(h, Ly, probs, B, items, ro);
-
-  uint64_t key = fnv1a(h, Ly.meta_bytes, 1469598103934665603ull);
-  key = fnv1a(&tp, sizeof tp, key);
-  key = fnv1a(&ctx->ws, sizeof ctx->ws, key);
-  key = fnv1a(&ro, sizeof ro, key);
   const bool use_graph = (flags & L1LINE_BATCH_GRAPH) && !ctx->profiling && !only_seg_ms;
-  if (use_graph && ctx->graph && ctx->graph_key == key) {
-    // the device metadata of this layout is still in place: replay
-    if (outp) {
-      BatchPtrs bp{(double *)(d + Ly.o_V), (int *)(d + Ly.o_R), (ColInfo *)(d + Ly.o_ci)};
-      *outp = bp;
-    }
-    HIP_TRY(hipGraphLaunch(ctx->graph, s));
-    return L1LINE_OK;
-  }
-  drop_graph(ctx);
-  HIP_TRY(hipMemcpyAsync(d, h, Ly.meta_bytes, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipEventRecord(ctx->stage_done, s));
-  ctx->stage_pending = true;
-
+  const bool by_kernel = B == 1 && !use_graph;
   hipStream_t ls = s;
-  if (use_graph) {
-    // the metadata copy above must land before the captured kernels run on
-    // the capture stream's replay (replays go to `s`, after the copy)
-    HIP_TRY(hipStreamSynchronize(s));
-    HIP_TRY(hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
-    ls = ctx->cap_stream;
+  uint64_t new_key = 0;
+  if (by_kernel) {
+    drop_graph(ctx);
+    launch_meta(s, probs[0], Ly, d);
+  } else {
+    st = ensure_stage(ctx, Ly.meta_bytes);
+    if (st) return st;
+
+    // metadata into the pinned staging buffer
+    char *h = (char *)ctx->stage;
+    fill_meta(h, Ly, probs, B, items, ro);
+
+    uint64_t key = fnv1a(h, Ly.meta_bytes, 1469598103934665603ull);
+    key = fnv1a(&tp, sizeof tp, key);
+    key = fnv1a(&ctx->ws, sizeof ctx->ws, key);
+    key = fnv1a(&ro, sizeof ro, key);
+    if (use_graph && ctx->graph && ctx->graph_key == key) {
+      // the device metadata of this layout is still in place: replay
+      if (outp) {
+        BatchPtrs bp{(double *)(d + Ly.o_V), (int *)(d + Ly.o_R), (ColInfo *)(d + Ly.o_ci)};
+        *outp = bp;
+      }
+      HIP_TRY(hipGraphLaunch(ctx->graph, s));
+      return L1LINE_OK;
+    }
+    drop_graph(ctx);
+    HIP_TRY(hipMemcpyAsync(d, h, Ly.meta_bytes, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipEventRecord(ctx->stage_done, s));
+    ctx->stage_pending = true;
+
+    new_key = key;
+    if (use_graph) {
+      // the metadata copy above must land before the captured kernels run on
+      // the capture stream's replay (replays go to `s`, after the copy)
+      HIP_TRY(hipStreamSynchronize(s));
+      HIP_TRY(hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
+      ls = ctx->cap_stream;
+    }
   }
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (only_seg_ms) {
     HIP_TRY(hipEventCreate(&t0));
     HIP_TRY(hipEventCreate(&t1));
   }
-  st = launch_seq(ctx, ls, Ly, d, B, tp, ro, true, t0, t1, outp);
+  st = launch_seq(ctx, ls, Ly, d, B, tp, ro, true, by_kernel, t0, t1, outp);
   const hipError_t le = hipGetLastError();
   if (use_graph) {
     hipGraph_t g = nullptr;
@@ -747,7 +786,7 @@ static int run_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, int
     (void)hipGraphDestroy(g);
     if (ie != hipSuccess) return L1LINE_EHIP;
     ctx->graph = ex;
-    ctx->graph_key = key;
+    ctx->graph_key = new_key;
     HIP_TRY(hipGraphLaunch(ctx->graph, s));
     return L1LINE_OK;
   }
@@ -1118,29 +1157,6 @@ int l1line_fit(l1line_ctx ctx, const double *X, int64_t n, int64_t m, int64_t ld
   return note(ctx, fit_impl(ctx, X, n, m, ld, lambda, v, j, obj, median_row, z_all, status, stream));
 }
 
-// Metadata of a one-problem call written by a kernel from its arguments, so
-// that the no-alloc call needs no host staging buffer.  One thread.
-__global__ void k_meta_single(ProbDesc pd, double lam, long long tiles, BatchLayout Ly, char *d) {
-  if (threadIdx.x != 0) return;
-  *(ProbDesc *)(d + Ly.o_desc) = pd;
-  int *col = (int *)(d + Ly.o_colstart), *z = (int *)(d + Ly.o_zstart), *o = (int *)(d + Ly.o_ostart),
-      *t = (int *)(d + Ly.o_tstart);
-  col[0] = 0;
-  col[1] = pd.m;
-  z[0] = 0;
-  z[1] = pd.m;
-  o[0] = 0;
-  o[1] = 1;
-  t[0] = 0;
-  t[1] = (int)tiles;
-  int *ws = (int *)(d + Ly.o_wstart);
-  ws[0] = 0;
-  ws[1] = (int)Ly.total_words;
-  *(double *)(d + Ly.o_lam) = lam;
-  int *xs = (int *)(d + Ly.o_xstart);
-  for (int x = 0; x <= SEG_XCDS; ++x) xs[x] = Ly.xstart[x];
-}
-
 static int fit_noalloc_impl(l1line_ctx ctx, const double *X, int64_t n, int64_t m, int64_t ld, double lambda,
                             double *v, int64_t *j, double *obj, int32_t *median_row, double *z_all,
                             int32_t *status, void *stream) {
@@ -1160,12 +1176,9 @@ static int fit_noalloc_impl(l1line_ctx ctx, const double *X, int64_t n, int64_t 
   st = plan_batch(ctx, &p, 1, tp, kNoOpts, Ly, items, NOALLOC_BYTES);
   if (st) return st;
   if (Ly.bytes > NOALLOC_BYTES || !items.empty()) return L1LINE_ESIZE;
-  const MetaCursor c0 = {0, 0, 0, 0, 0, 0, 0, 0};
-  MetaCursor c1 = c0;
-  advance(c1, p, kNoOpts, 1);
   char *d = (char *)ctx->scratch;
-  hipLaunchKernelGGL(k_meta_single, dim3(1), dim3(64), 0, s, prob_desc(p, c0), lambda, c1.tiles, Ly, d);
-  st = launch_seq(ctx, s, Ly, d, 1, tp, kNoOpts, false, nullptr, nullptr, nullptr);
+  launch_meta(s, p, Ly, d);
+  st = launch_seq(ctx, s, Ly, d, 1, tp, kNoOpts, false, true, nullptr, nullptr, nullptr);
   if (st) return st;
   HIP_TRY(hipGetLastError());
   return L1LINE_OK;
