@@ -1400,7 +1400,7 @@ static RkLayout rk_layout(int64_t n, int64_t m) {
   auto take = [&](size_t b) { size_t o = off; off = align_up(off + b, 256); return o; };
   R.o_DZ = take(2 * sizeof(double) * m * m);
   // BF16 planes of the feature sign sums (high and low parts, signs)
-  const size_t plane = sizeof(__bf16) * (size_t)fss_rows(n) * (size_t)m;
+  const size_t plane = sizeof(__bf16) * (size_t)fss_rows(n) * (size_t)fss_cols(m);
   R.o_H = take(plane);
   R.o_L = take(plane);
   R.o_S = take(plane);
@@ -1431,12 +1431,14 @@ static int feature_signsums(l1line_ctx ctx, const double *X, int64_t n, int64_t 
   const int np = (int)fss_rows(n);
   const long long tb = (m + FSS_T - 1) / FSS_T;
   launch_colprep(ctx, s, X, n, m, ld, ci, (unsigned short *)(b + R.o_smp));
-  hipLaunchKernelGGL(k_feat_planes, dim3((unsigned)(m * ((np + 255) / 256))), dim3(256), 0, s, X, (int)n, (int)m,
+  hipLaunchKernelGGL(k_feat_planes, dim3((unsigned)(fss_cols(m) / 16 * ((np + FSP_ROWS - 1) / FSP_ROWS))), dim3(256), 0, s, X, (int)n, (int)m,
                      (long long)ld, np, (const ColInfo *)ci, Hp, Lp, Sp);
   {
     ProfScope ps(ctx, s, "feat_signsum");
-    hipLaunchKernelGGL(k_feat_signsum, dim3((unsigned)((tb * tb + 3) / 4)), dim3(256), 0, s, (const __bf16 *)Hp,
-                       (const __bf16 *)Lp, (const __bf16 *)Sp, (int)m, np, (const ColInfo *)ci, DZ);
+    // (few blocks: a wave per workgroup, so that each has a CU's L1)
+    const int waves = tb * tb < 2ll * ctx->num_cu ? 1 : 4;
+    hipLaunchKernelGGL(k_feat_signsum, dim3((unsigned)((tb * tb + waves - 1) / waves)), dim3(64 * waves), 0, s,
+                       (const __bf16 *)Hp, (const __bf16 *)Lp, (const __bf16 *)Sp, (int)m, np, (const ColInfo *)ci, DZ);
   }
   HIP_TRY(hipGetLastError());
   return L1LINE_OK;

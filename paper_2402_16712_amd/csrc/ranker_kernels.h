@@ -259,31 +259,55 @@ __global__ void k_mlp_adam(float *__restrict__ P, float *__restrict__ m1, float 
 //   Zr_jk = 2^E_j sum_i |h_ij| [x_ik = 0]              one product (terms >= 0:
 //                                                     relative error 2^-8)
 // with FP32 accumulation over the rows (error <= n 2^-24 of the sum of the
-// terms' magnitudes).  Planes: bf16 [m][np], np = n rounded up to 32, rows
-// past n zero in h and l (so they add nothing; their sign entries are +1).
+// terms' magnitudes).  Planes: np = n rounded up to 32 rows, m rounded up to
+// 64 columns, in fragment order: the 16 columns x 32 rows of one operand are
+// 1 KB, lane l's 16 bytes (column l & 15, rows 8 (l >> 4) ..) at 16 l, the
+// 32-row steps of 16 columns one after the other.  Rows past n and columns
+// past m are zero in h and l (they add nothing; their sign entries are +1).
+// With the columns stored one by one a fragment took half of sixteen cache
+// lines, and the other halves were gone from L1 when the next step wanted
+// them (10000 x 4000: products 1.46 ms, now 0.92; planes 0.13, now 0.10).
 constexpr int FSS_K = 32;            // rows per MFMA step
 constexpr int FSS_T = 64;            // output block (j and k) of one wave
 
 __host__ __device__ constexpr int64_t fss_rows(int64_t n) { return (n + FSS_K - 1) / FSS_K * FSS_K; }
+__host__ __device__ constexpr int64_t fss_cols(int64_t m) { return (m + FSS_T - 1) / FSS_T * FSS_T; }
 
 __device__ __forceinline__ int col_exp(const ColInfo &c) { return c.nnz > 0 ? c.bemax - 1023 : 0; }
 
+// One block: 16 columns x FSP_ROWS rows, through LDS (columns read along their
+// rows, fragments written along their lanes).
+constexpr int FSP_ROWS = 128;
 __global__ void __launch_bounds__(256)
 k_feat_planes(const double *__restrict__ X, int n, int m, long long ld, int np, const ColInfo *__restrict__ ci,
               __bf16 *__restrict__ H, __bf16 *__restrict__ Lo, __bf16 *__restrict__ S) {
-  // block b: column b / chunks, rows 256 (b % chunks) ...
-  const int chunks = (np + 255) >> 8;
-  const int j = blockIdx.x / chunks;
-  const int i = (blockIdx.x % chunks) * 256 + threadIdx.x;
-  if (j >= m || i >= np) return;
-  const double x = i < n ? X[(long long)j * ld + i] : 0.0;
-  const double xs = ldexp(x, -col_exp(ci[j]));
-  const __bf16 h = (__bf16)(float)xs;
-  const __bf16 l = (__bf16)(float)(xs - (double)(float)h);
-  const long long o = (long long)j * np + i;
-  H[o] = h;
-  Lo[o] = l;
-  S[o] = (__bf16)(i >= n ? 1.0f : (x > 0.0 ? 1.0f : (x < 0.0 ? -1.0f : 0.0f)));
+  __shared__ double tile[16][FSP_ROWS + 1];
+  const int tid = threadIdx.x, chunks = (np + FSP_ROWS - 1) / FSP_ROWS;
+  const int g = blockIdx.x / chunks, i0 = (blockIdx.x % chunks) * FSP_ROWS;
+  const int nch = np / FSS_K;
+  for (int e = tid; e < 16 * FSP_ROWS; e += 256) {
+    const int c = e / FSP_ROWS, i = e % FSP_ROWS, j = 16 * g + c;
+    tile[c][i] = (j < m && i0 + i < n) ? X[(long long)j * ld + i0 + i] : 0.0;
+  }
+  __syncthreads();
+  const int c = tid & 15, oct = tid >> 4, j = 16 * g + c;   // 8 rows of one column
+  if (i0 + 8 * oct >= np) return;
+  const int e = j < m ? -col_exp(ci[j]) : 0;
+  bf16x8 h, l, sg;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int i = i0 + 8 * oct + q;
+    const double x = tile[c][8 * oct + q];
+    const double xs = ldexp(x, e);
+    const __bf16 hv = (__bf16)(float)xs;
+    h[q] = hv;
+    l[q] = (__bf16)(float)(xs - (double)(float)hv);
+    sg[q] = (__bf16)((i >= n || j >= m) ? 1.0f : (x > 0.0 ? 1.0f : (x < 0.0 ? -1.0f : 0.0f)));
+  }
+  const long long o = (((long long)g * nch + (i0 >> 5) + (oct >> 2)) * 64 + c + 16 * (oct & 3)) * 8;
+  *(bf16x8 *)(H + o) = h;
+  *(bf16x8 *)(Lo + o) = l;
+  *(bf16x8 *)(S + o) = sg;
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -302,8 +326,8 @@ __device__ __forceinline__ bf16x8 zero_of_sign(bf16x8 v) {
 }
 
 // One wave per 64 x 64 block (j0, k0) of the m x m output; DZ[j m + k] =
-// (D_jk, Zr_jk) in FP64.  Fragments straight from the planes (each lane reads
-// 16 contiguous bytes of one column), the next step's prefetched.
+// (D_jk, Zr_jk) in FP64.  Fragments straight from the planes (1 KB each, in lane
+// order), the next step's prefetched.
 __global__ void __launch_bounds__(256)
 k_feat_signsum(const __bf16 *__restrict__ H, const __bf16 *__restrict__ Lo, const __bf16 *__restrict__ S, int m,
                int np, const ColInfo *__restrict__ ci, double2 *__restrict__ DZ) {
@@ -312,13 +336,14 @@ k_feat_signsum(const __bf16 *__restrict__ H, const __bf16 *__restrict__ Lo, cons
   const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (t >= tb * tb) return;
   const int j0 = (t / tb) * FSS_T, k0 = (t % tb) * FSS_T;
-  const int r = lane & 15, kq = 8 * (lane >> 4);
-  // columns past m read column m - 1 (their results are not stored)
+  const int r = lane & 15;
+  // (16 np elements per group of 16 columns; results of columns past m are
+  // not stored)
   long long oa[4], ob[4];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    oa[a] = (long long)min(j0 + 16 * a + r, m - 1) * np + kq;
-    ob[a] = (long long)min(k0 + 16 * a + r, m - 1) * np + kq;
+    oa[a] = (long long)(j0 + 16 * a) * np + 8 * lane;
+    ob[a] = (long long)(k0 + 16 * a) * np + 8 * lane;
   }
   f32x4 accD[4][4], accZ[4][4];
 #pragma unroll
@@ -346,9 +371,9 @@ k_feat_signsum(const __bf16 *__restrict__ H, const __bf16 *__restrict__ Lo, cons
     if (i0 + FSS_K < np) {
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        nh[a] = ld_frag(H + oa[a] + i0 + FSS_K);
-        nl[a] = ld_frag(Lo + oa[a] + i0 + FSS_K);
-        ns[a] = ld_frag(S + ob[a] + i0 + FSS_K);
+        nh[a] = ld_frag(H + oa[a] + 16 * (i0 + FSS_K));
+        nl[a] = ld_frag(Lo + oa[a] + 16 * (i0 + FSS_K));
+        ns[a] = ld_frag(S + ob[a] + 16 * (i0 + FSS_K));
       }
     }
 #pragma unroll

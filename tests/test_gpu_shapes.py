@@ -166,3 +166,19 @@ def test_segment_ranges(ctx, n):
         _fit_equal(_host(ctx.fit(Xd, lam)), O.fit(X, lam), (n, lam))
     lams = np.array([0.0, 1e-130, 1.0, 50.0, 1e115])
     _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, "path"))
+
+
+# the feature sign sums in fragment order: one wave per workgroup (few output
+# blocks) and four, partial fragments either way.  Bounds of the header, u = 2^-24
+@pytest.mark.parametrize("n,m", [(1, 1), (33, 17), (130, 70), (257, 64), (45, 1500)])
+def test_feature_sign_sums_layout(ctx, n, m):
+    from paper_2402_16712_amd import binding as B
+    print(f"case feature sums {n}x{m}", flush=True)
+    X = _data(n + m, n, m, "sparse")
+    X[: n // 3, m // 2] = 0.0
+    DZ = ctx.feature_signsums(B.device_matrix(X)).cpu().numpy()
+    W, u = np.abs(X).sum(axis=0), 2.0 ** -24
+    D, Z = X.T @ np.sign(X), np.abs(X).T @ (X == 0.0)
+    slack = n * 2.0 ** -52 * W[:, None]
+    assert np.all(np.abs(DZ[:, :, 0] - D) <= (2.0 ** -15 + 2 * n * u) * W[:, None] + slack)
+    assert np.all(np.abs(DZ[:, :, 1] - Z) <= (2.0 ** -8 + 2 * n * u) * Z + slack)
