@@ -561,8 +561,8 @@ static void fill_meta(char *h, const BatchLayout &Ly, const l1line_problem *prob
 struct LambdaArgs {
   double v[L1LINE_MAX_LAMBDAS];
 };
-__global__ void __launch_bounds__(L1LINE_MAX_LAMBDAS) k_meta_single(ProbDesc pd, LambdaArgs lam, BatchLayout Ly, char *d) {
-  const int t = threadIdx.x;
+__device__ __forceinline__ void write_meta(int t, const ProbDesc &pd, const LambdaArgs &lam, const BatchLayout &Ly,
+                                           char *d) {
   if (t < pd.L) ((double *)(d + Ly.o_lam))[t] = lam.v[t];
   if (t < 16) ((int *)(d + Ly.o_counter))[t] = 0;
   if (t <= SEG_XCDS) ((int *)(d + Ly.o_xstart))[t] = Ly.xstart[t];
@@ -579,13 +579,26 @@ __global__ void __launch_bounds__(L1LINE_MAX_LAMBDAS) k_meta_single(ProbDesc pd,
   pair(Ly.o_tstart, Ly.total_tiles);
   pair(Ly.o_wstart, Ly.total_words);
 }
-static void launch_meta(hipStream_t s, const l1line_problem &p, const BatchLayout &Ly, char *d) {
-  const MetaCursor c0 = {0, 0, 0, 0, 0, 0, 0, 0};
-  LambdaArgs la;
-  for (int t = 0; t < L1LINE_MAX_LAMBDAS; ++t) la.v[t] = t < p.L ? p.lambdas[t] : 0.0;
-  hipLaunchKernelGGL(k_meta_single, dim3(1), dim3(L1LINE_MAX_LAMBDAS), 0, s, prob_desc(p, c0), la, Ly, d);
+__global__ void __launch_bounds__(L1LINE_MAX_LAMBDAS)
+k_meta_single(ProbDesc pd, LambdaArgs lam, BatchLayout Ly, char *d) {
+  write_meta(threadIdx.x, pd, lam, Ly, d);
 }
 
+// One problem's columns, the first launch of its sequence: block 0 writes the
+// metadata for the launches that follow (a launch of its own for that took 4
+// of the 45 us of a 200 x 20 fit).
+template <int kW, bool kLds>
+__global__ void __launch_bounds__(64 * kW)
+k_colprep_first(ProbDesc pd, LambdaArgs lam, BatchLayout Ly, char *d) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ __attribute__((aligned(16))) PrepShared sh;
+  const int col = blockIdx.x;
+  if (col == 0)
+    for (int t = threadIdx.x; t < L1LINE_MAX_LAMBDAS; t += 64 * kW) write_meta(t, pd, lam, Ly, d);
+  colprep_block<kW, kLds>(pd.X + (long long)col * pd.ld, pd.n, (ColInfo *)(d + Ly.o_ci) + col,
+                          (unsigned short *)(d + Ly.o_smp) + (long long)col * SAMPLE_ROWS, sh, (double *)smem);
+  if (threadIdx.x == 0) ((int *)(d + Ly.o_segflags))[col] = 0;
+}
 // The form of the column preparation for `cols` columns of up to n rows: four
 // waves per column with the column in LDS up to eight columns per CU (2000 x
 // 2000: 23 us, one wave 29), longer columns four waves up to four per CU (20011
@@ -605,9 +618,28 @@ static void launch_colprep(l1line_ctx ctx, hipStream_t s, const double *X, int64
                      s, X, (int)n, (int)m, (long long)ld, ci, smp);
 }
 
+// `columns`: with the column preparation.  `prof`: as in launch_seq.
+static void launch_meta(l1line_ctx ctx, hipStream_t s, const l1line_problem &p, const BatchLayout &Ly, char *d,
+                        bool columns, bool prof) {
+  const MetaCursor c0 = {0, 0, 0, 0, 0, 0, 0, 0};
+  LambdaArgs la;
+  for (int t = 0; t < L1LINE_MAX_LAMBDAS; ++t) la.v[t] = t < p.L ? p.lambdas[t] : 0.0;
+  if (!columns) {
+    hipLaunchKernelGGL(k_meta_single, dim3(1), dim3(L1LINE_MAX_LAMBDAS), 0, s, prob_desc(p, c0), la, Ly, d);
+    return;
+  }
+  ProfScope ps(prof ? ctx : nullptr, s, "colprep");
+  const int f = prep_form(ctx, p.n, p.m);
+  auto k = f == PREP_ONE ? k_colprep_first<1, false>
+           : f == PREP_FOUR ? k_colprep_first<PREP_WAVES, false> : k_colprep_first<PREP_WAVES, true>;
+  hipLaunchKernelGGL(k, dim3((unsigned)p.m), dim3(f == PREP_ONE ? 64 : 64 * PREP_WAVES),
+                     f == PREP_LDS ? (size_t)p.n * 8 : 0, s, prob_desc(p, c0), la, Ly, d);
+}
+
 // The launch sequence of one batch call on stream ls, the workspace at d
 // (its metadata block already in place or written by an earlier kernel on
-// ls).  `cleared`: the counters are zero already.  `prof`: bracket the kernels with the context's timing events;
+// ls).  `cleared`: the counters are zero already, and without gate and earlier
+// column info the columns are prepared too.  `prof`: bracket the kernels with the context's timing events;
 // t0 / t1 (optional): events recorded around the segment kernel.
 static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, char *d, int64_t B,
                       const TuneParams &tp, const RunOpts &ro, bool prof, bool cleared, hipEvent_t t0, hipEvent_t t1,
@@ -661,7 +693,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   }
   const long long all_items = Ly.ksplit ? (long long)Ly.nitems * SEG_XCDS : (long long)Ly.nitems;
   const int grid_seg = (int)std::max(1ll, std::min(all_items, (long long)tp.blocks_per_cu * ctx->num_cu));
-  {
+  if (!cleared || ro.gate || ro.ci) {
     ProfScope ps(pc, ls, "colprep");
     if (!cleared) hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, ls, dcounter, 16ll, 0);
     if (have_ci) {
@@ -731,7 +763,8 @@ static int run_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, int
   uint64_t new_key = 0;
   if (by_kernel) {
     drop_graph(ctx);
-    launch_meta(s, probs[0], Ly, d);
+    // (a gated run and one with earlier column info prepare their columns below)
+    launch_meta(ctx, s, probs[0], Ly, d, !ro.gate && !ro.ci, true);
   } else {
     st = ensure_stage(ctx, Ly.meta_bytes);
     if (st) return st;
@@ -1177,7 +1210,7 @@ static int fit_noalloc_impl(l1line_ctx ctx, const double *X, int64_t n, int64_t 
   if (st) return st;
   if (Ly.bytes > NOALLOC_BYTES || !items.empty()) return L1LINE_ESIZE;
   char *d = (char *)ctx->scratch;
-  launch_meta(s, p, Ly, d);
+  launch_meta(ctx, s, p, Ly, d, true, false);
   st = launch_seq(ctx, s, Ly, d, 1, tp, kNoOpts, false, true, nullptr, nullptr, nullptr);
   if (st) return st;
   HIP_TRY(hipGetLastError());
