@@ -92,7 +92,7 @@ __device__ __forceinline__ bool pair_le(uint64_t key, int row, uint64_t hk, int 
 // counts[g] (int64, written to offsets + 1 + g) and lambda_max[g] of segment
 // g = j m + k; V0, R0: v_k and its row at lambda = 0 (m x m, row -1 for 0).
 // kList: also list each segment's entries (key, row), when there are at most
-// wcap (<= BP_LIST_MAX) of them, in row order at wkeys/wrows[g wcap ..]
+// wcap (<= BP_LIST_MAX) of them, in no order at wkeys/wrows[g wcap ..]
 // (staged in LDS, stored once per segment), and in wsb[g] the exact weight
 // of the negative ratios (negative minimiser) or of the negative and zero
 // ones (positive): the emit pass then takes its first window from there
@@ -134,55 +134,101 @@ k_bp_count(const double *__restrict__ X, int n, int m, long long ld, const ColIn
     const double v0 = V0[g];
     const uint64_t mkey = key_of(v0 + 0.0);
     const bool neg = v0 < 0.0;
-    // weights as FP64 sums of 37-bit chunks (exact, see weight_chunks);
-    // the columns are read one slot ahead
+    // weights as FP64 sums of 37-bit chunks (exact, see weight_chunks):
+    // negative ratios, zero ratios
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, z0 = 0.0, z1 = 0.0, z2 = 0.0;
-    int cnt = 0, nin = 0;
-    const __amdgpu_buffer_rsrc_t rj = col_rsrc(s.sxj, n), rk = col_rsrc(s.xk, n);
-    int off = lane * 8;
-    double an = col_ld(rj, off), bn = col_ld(rk, off);
-    for (int t = 0; t < T; ++t) {
-      const int i = lane + 64 * t;
-      const double a = an, b = bn;
-      off += 512;
-      an = col_ld(rj, off);
-      bn = col_ld(rk, off);
-      const uint64_t key = key_of_pair(i < n, a, b);
-      const bool valid = key != KEY_NONE;
-      const bool ng = key < KEY_ZERO, zr = key == KEY_ZERO;
-      double c0, c1, c2;
-      weight_chunks(a, s.e0, c0, c1, c2);
-      // masked adds as fma with a 0/1 factor: the same exact sums (whole
-      // numbers below 2^53; c 0 adds +0) in one op instead of select + add
-      const double fn = ng ? 1.0 : 0.0, fz = zr ? 1.0 : 0.0;
-      a0 = fma(c0, fn, a0);
-      a1 = fma(c1, fn, a1);
-      a2 = fma(c2, fn, a2);
-      z0 = fma(c0, fz, z0);
-      z1 = fma(c1, fz, z1);
-      z2 = fma(c2, fz, z2);
-      if (r0 >= 0 && valid) {
-        const bool in = neg ? (key < KEY_ZERO && pair_ge(key, i, mkey, r0))
-                            : (key > KEY_ZERO && pair_le(key, i, mkey, r0));
-        cnt += in ? 1 : 0;
+    int nin = 0;
+    const ColInfo ck = ci[k];
+    const bool quick = fast_columns(cj) && fast_columns(ck);
+    if (quick) {
+      // no division per row: the sign of b - t a is exact (see window_pass).
+      // a0.. sum the ratios below 0 (neg) or at or below it, the rows between
+      // 0 and the minimiser (moved out by 2^-50) are marked one bit each, and
+      // only they get their ratio and the exact test (1000 x 501: 0.77 ms with a
+      // division per row, now 0.56)
+      const __amdgpu_buffer_rsrc_t rj = col_rsrc(s.sxj, n), rk = col_rsrc(s.xk, n);
+      auto ldj = [&](int i) { return col_ld(rj, i * 8); };
+      auto ldk = [&](int i) { return col_ld(rk, i * 8); };
+      const double zb = neg ? -FAST_ZERO : FAST_ZERO, vb = r0 >= 0 ? v0 * (1.0 + 0x1p-50) : zb;
+      for (int t0 = 0; t0 < T; t0 += 32) {
+        const int t1 = min(T, t0 + 32);
+        uint32_t mask = 0;
+        for_row_pairs<4>(s, ldj, ldk, t0, t1, [&](double a, double b) {
+          const double dz = fma(-zb, a, b), dv = fma(-vb, a, b);
+          mask = __builtin_amdgcn_alignbit(mask, hi32(dz) ^ hi32(dv), 31);
+          double c0, c1, c2;
+          weight_chunks(a, s.e0, c0, c1, c2);
+          // masked adds as fma with a 0/1 factor: the same exact sums (whole
+          // numbers below 2^53; c 0 adds +0) in one op
+          const double f = ((hi32(dz) ^ hi32(a)) >> 31) ? 1.0 : 0.0;
+          a0 = fma(c0, f, a0);
+          a1 = fma(c1, f, a1);
+          a2 = fma(c2, f, a2);
+          if (__ballot(b == 0.0 && a != 0.0)) {
+            const double fz = b == 0.0 ? 1.0 : 0.0;
+            z0 = fma(c0, fz, z0);
+            z1 = fma(c1, fz, z1);
+            z2 = fma(c2, fz, z2);
+          }
+        });
+        mask <<= 32 - ((t1 - t0 + 3) & ~3);
+        while (__ballot(mask != 0)) {
+          const bool have = mask != 0;
+          const int q = have ? __builtin_clz(mask) : 0, i = lane + 64 * (t0 + q);
+          mask ^= have ? 0x80000000u >> q : 0u;
+          const double a = have ? gld(s.sxj + i) : 1.0, b = have ? gld(s.xk + i) : 0.0;
+          const uint64_t key = key_of_pair(have, a, b);
+          const bool in = have && (neg ? (key < KEY_ZERO && pair_ge(key, i, mkey, r0))
+                                       : (key > KEY_ZERO && pair_le(key, i, mkey, r0)));
+          const uint64_t im = __ballot(in);
+          const int pos = nin + lanes_below(im);
+          nin += __builtin_popcountll(im);
+          if (kList && in && pos < wcap) {
+            lk[pos] = key;
+            lr[pos] = (unsigned short)i;
+          }
+        }
       }
-      if constexpr (kList) {
-        // the emit pass's first window: the same elements, in row order
-        const bool inl = r0 >= 0 && valid &&
-                         (neg ? (key < KEY_ZERO && pair_ge(key, i, mkey, r0))
-                              : (key > KEY_ZERO && pair_le(key, i, mkey, r0)));
-        const uint64_t im = __ballot(inl);
+      nin = uni_int(nin);
+    } else {
+      // (the columns are read one slot ahead)
+      const __amdgpu_buffer_rsrc_t rj = col_rsrc(s.sxj, n), rk = col_rsrc(s.xk, n);
+      int off = lane * 8;
+      double an = col_ld(rj, off), bn = col_ld(rk, off);
+      for (int t = 0; t < T; ++t) {
+        const int i = lane + 64 * t;
+        const double a = an, b = bn;
+        off += 512;
+        an = col_ld(rj, off);
+        bn = col_ld(rk, off);
+        const uint64_t key = key_of_pair(i < n, a, b);
+        const bool valid = key != KEY_NONE;
+        const bool ng = key < KEY_ZERO, zr = key == KEY_ZERO;
+        double c0, c1, c2;
+        weight_chunks(a, s.e0, c0, c1, c2);
+        const double fn = ng ? 1.0 : 0.0, fz = zr ? 1.0 : 0.0;
+        a0 = fma(c0, fn, a0);
+        a1 = fma(c1, fn, a1);
+        a2 = fma(c2, fn, a2);
+        z0 = fma(c0, fz, z0);
+        z1 = fma(c1, fz, z1);
+        z2 = fma(c2, fz, z2);
+        const bool in = r0 >= 0 && valid &&
+                        (neg ? (key < KEY_ZERO && pair_ge(key, i, mkey, r0))
+                             : (key > KEY_ZERO && pair_le(key, i, mkey, r0)));
+        const uint64_t im = __ballot(in);
         const int pos = nin + lanes_below(im);
         nin += __builtin_popcountll(im);
-        if (inl && pos < wcap) {
+        if (kList && in && pos < wcap) {
           lk[pos] = key;
           lr[pos] = (unsigned short)i;
         }
       }
     }
-    const u128 A = chunks_to_u128(wave_sum_dbl(a0), wave_sum_dbl(a1), wave_sum_dbl(a2)),
-               B = A + chunks_to_u128(wave_sum_dbl(z0), wave_sum_dbl(z1), wave_sum_dbl(z2)), W = cj.wfix;
-    cnt = wave_sum_int(cnt);
+    const u128 S = chunks_to_u128(wave_total_dbl(a0), wave_total_dbl(a1), wave_total_dbl(a2)),
+               Zr = chunks_to_u128(wave_total_dbl(z0), wave_total_dbl(z1), wave_total_dbl(z2)), W = cj.wfix;
+    // (quick: the zero ratios are in S unless the minimiser is negative)
+    const u128 A = quick && !neg ? S - Zr : S, B = A + Zr;
     if constexpr (kList) {
       if (nin <= wcap) {
         wave_lds_sync();
@@ -198,7 +244,7 @@ k_bp_count(const double *__restrict__ X, int n, int m, long long ld, const ColIn
     if ((A << 1) > W) lm = (A << 1) - W;
     else if (W > (B << 1)) lm = W - (B << 1);
     if (lane == 0) {
-      counts[g] = (long long)((r0 >= 0 ? cnt : 0) + 1);
+      counts[g] = (long long)((r0 >= 0 ? nin : 0) + 1);
       lmax[g] = fixed_to_double(lm, cj.e0);
     }
   }

@@ -182,3 +182,31 @@ def test_feature_sign_sums_layout(ctx, n, m):
     slack = n * 2.0 ** -52 * W[:, None]
     assert np.all(np.abs(DZ[:, :, 0] - D) <= (2.0 ** -15 + 2 * n * u) * W[:, None] + slack)
     assert np.all(np.abs(DZ[:, :, 1] - Z) <= (2.0 ** -8 + 2 * n * u) * Z + slack)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 257, 2047, 2048, 2049, 2305])
+@pytest.mark.parametrize("kind", ["sparse", "counts", "scaled", "wide"])
+def test_breakpoint_counts(ctx, n, kind):
+    # one pass over slots of 32 x 64 rows; minimisers of both signs and at 0,
+    # columns whose magnitudes take the general branch ("scaled"), and a
+    # column that is refused for its span unless its first row is 0 ("wide")
+    from paper_2402_16712_amd import binding as B
+    X = _data(900 + n, n, 6, kind if kind == "counts" else "sparse")
+    X[:, 3] = -X[:, 2]
+    if kind == "wide":
+        X[:, 1] *= 2.0 ** -310
+        X[0, 4] *= 2.0 ** 305
+    if kind == "scaled":
+        X[:, 1] *= 2.0 ** -310
+        X[:, 4] *= 2.0 ** 305
+    X = np.asfortranarray(X)
+    print(f"case breakpoint counts n={n} {kind}", flush=True)
+    g, r = _host(ctx.breakpoints(B.device_matrix(X))), O.breakpoints(X)
+    if kind == "wide" and n > 1 and X[0, 4] != 0.0:
+        assert int(g["status"][0]) == B.EWIDE
+        return
+    assert int(g["status"][0]) == 0
+    assert np.array_equal(g["offsets"], r["offsets"])
+    for key in ("lambda_max", "lam", "v"):
+        assert g[key].tobytes() == r[key].tobytes(), key
+    assert np.array_equal(g["row"], r["row"])
