@@ -130,8 +130,9 @@ int l1line_fit(l1line_ctx ctx, const double *X, int64_t n, int64_t m,
  * workspace in a fixed device array of L1LINE_NOALLOC_SCRATCH_MB MiB that the
  * library holds on every GPU it runs on until the process ends.  The call
  * allocates nothing (no hipMalloc / hipFree, no pinned staging: its metadata
- * travels as kernel arguments).  The workspace needs about 36 m^2 + 64 m
- * bytes plus a few KB, so m <= L1LINE_NOALLOC_MAX_M (n up to L1LINE_MAX_N).
+ * travels as kernel arguments).  The workspace needs about 36 m^2 + 330 m
+ * bytes plus a few KB (what is left of the array holds the row parts of the
+ * sign sums), so m <= L1LINE_NOALLOC_MAX_M (n up to L1LINE_MAX_N).
  * Every call on one GPU, from any context, stream or thread, shares that
  * GPU's array and leaves its contents there; each call re-initialises what
  * it reads.  Calls that overlap in time on the same GPU race: the caller
@@ -211,8 +212,8 @@ int l1line_autotune(l1line_ctx ctx, const l1line_problem *probs, int64_t B,
 /* Read / set the context's default launch parameters, used for size
  * classes without a tuned entry (HOST [3]: workgroups per CU in [1, 16],
  * fewest k per item >= 1, items per CU in [1, 4096]; initially 4, 8, 24:
- * four 256-thread workgroups per CU fill the four wave slots per SIMD that
- * the segment kernel's registers allow wherever its LDS leaves room). */
+ * four workgroups per CU, of four or eight waves, fill the four wave slots
+ * per SIMD that the segment kernels' registers allow). */
 int l1line_tune_get(l1line_ctx ctx, int32_t *params);
 int l1line_tune_set(l1line_ctx ctx, const int32_t *params);
 

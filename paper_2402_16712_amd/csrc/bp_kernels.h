@@ -145,7 +145,7 @@ k_bp_count(const double *__restrict__ X, int n, int m, long long ld, const ColIn
       // a0.. sum the ratios below 0 (neg) or at or below it, the rows between
       // 0 and the minimiser (moved out by 2^-50) are marked one bit each, and
       // only they get their ratio and the exact test (1000 x 501: 0.77 ms with a
-      // division per row, now 0.56)
+      // division per row, now 0.56; 2000 x 2000 19.9, now 13.1)
       const __amdgpu_buffer_rsrc_t rj = col_rsrc(s.sxj, n), rk = col_rsrc(s.xk, n);
       auto ldj = [&](int i) { return col_ld(rj, i * 8); };
       auto ldk = [&](int i) { return col_ld(rk, i * 8); };

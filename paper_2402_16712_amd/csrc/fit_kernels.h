@@ -261,16 +261,20 @@ k_colprep(const double *__restrict__ X, int n, int m, long long ld, ColInfo *__r
 }
 
 // every column of every problem: colstart[b] = first column of problem b.
-// kLds: the launch has room for the longest problem's column.
+// kLds: the launch has room for the longest problem's column.  counters: the
+// call's SEG_COUNTERS counters, cleared here for the launches that follow (a
+// launch of its own took 4 of the 107 us of 4 matrices of up to 150 x 30).
+constexpr int SEG_COUNTERS = 16;
 template <int kW, bool kLds>
 __global__ void __launch_bounds__(64 * kW)
 k_colprep_batch(const ProbDesc *__restrict__ P, const int *__restrict__ colstart, int B,
                 ColInfo *__restrict__ ci, unsigned short *__restrict__ smp, int *__restrict__ segflags,
-                const int *__restrict__ gate, int gate_on) {
+                const int *__restrict__ gate, int gate_on, int *__restrict__ counters) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ __attribute__((aligned(16))) PrepShared sh;
   const int g = blockIdx.x;
   if (gate && *gate != gate_on) return;
+  if (g == 0 && threadIdx.x < SEG_COUNTERS) counters[threadIdx.x] = 0;
   const int b = find_owner(colstart, B, g);
   const ProbDesc d = P[b];
   const int col = g - colstart[b];
@@ -946,7 +950,9 @@ __device__ __forceinline__ void signsum_tile(const double *__restrict__ X, int i
 // One block takes about 2 us per 16-row stage when it has a CU to itself
 // (load latency and the FP64 matrix rate), so a matrix of few columns, whose
 // tiles leave most of the CUs idle, is bound by the length of its row loop:
-// 1003 x 517 (81 tiles) 123 us, 20011 x 151 (9 tiles) 2344 us in one part.
+// 1003 x 517 (81 tiles) 123 us in one part, the fit 742 -> 661 in several;
+// 20011 x 151 (9 tiles) 2344 us, the fit 5016 -> 2791.  2000 x 2000 (1024
+// tiles, one part) runs at 0.6 of the FP64 matrix rate, 0.56 ms.
 __global__ void __launch_bounds__(256)
 k_signsum_batch(const ProbDesc *__restrict__ P, const int *__restrict__ tstart, int B,
                 const int *__restrict__ cand, int ncand, double2 *__restrict__ DZ,
@@ -1072,8 +1078,9 @@ __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInf
 // segments.  They have v_k = 0, e_jk = the R64 mass of column k and row -1 for
 // every penalty: written here for a problem of one penalty (Algorithm 2 reads
 // them), taken from the mask by the kernels that follow for one of several
-// (2000 x 2000 with 64: 2.0 ms of scattered stores).  wstart[b] = first mask word of problem b (mj ceil(m / 64) words,
-// mj = ncand with a candidate list, problem 0 only, else m).
+// (2000 x 2000 with 64: 2.0 ms of scattered stores).  wstart[b] = first mask
+// word of problem b (mj ceil(m / 64) words, mj = ncand with a candidate list,
+// problem 0 only, else m).
 __global__ void __launch_bounds__(256)
 k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, int total_words,
                 const double *__restrict__ lam_all, const ColInfo *__restrict__ ci,
@@ -2336,14 +2343,15 @@ struct ItemQueue {
 };
 
 // The next item of the workgroup (every thread calls it): false when none is
-// left.  jj: the item's row in the masks.
+// left.  jj: the item's row in the masks; near: 0 before the first call.
 __device__ __forceinline__ bool next_item(const ItemQueue &q, const ProbDesc *__restrict__ P,
-                                          const int *__restrict__ cand, int ncand, int *s_item, WorkItem &it, int &jj) {
+                                          const int *__restrict__ cand, int ncand, int *s_item, WorkItem &it, int &jj, int &near) {
   while (true) {
     if (threadIdx.x < 64) {
-      // lanes 0 .. 7 look at the counters together (trying them one atomic
-      // after the other cost every workgroup about 6 us at its end); the
-      // nearest XCD at or after home with items left is tried
+      // the XCD of the last item (lane near's) is tried at once; when it has
+      // none left, lanes 0 .. 7 look at the counters together (trying them one
+      // atomic after the other cost every workgroup about 6 us at its end) and
+      // the nearest XCD at or after home with items left is tried
       int g = -1;
       const int lane = threadIdx.x, x = (blockIdx.x + lane) % SEG_XCDS;
       int begin = 0, have = 0;
@@ -2351,18 +2359,20 @@ __device__ __forceinline__ bool next_item(const ItemQueue &q, const ProbDesc *__
         begin = q.items ? q.xstart[x] : x * q.nitems;
         have = q.items ? q.xstart[x + 1] - begin : q.nitems;
       }
-      while (true) {
-        const int seen = lane < SEG_XCDS ? __hip_atomic_load(q.counter + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-        const uint64_t open = __ballot(lane < SEG_XCDS && seen < have);
-        if (open == 0) break;
+      uint64_t open = __ballot(have > 0);
+      open = (open >> near) & 1ull ? 1ull << near : open;
+      while (open != 0) {
         const int l = __builtin_ctzll(open);
         int c = 0;
         if (lane == l) c = atomicAdd(q.counter + x, 1);
         c = __builtin_amdgcn_readlane(c, l);
         if (c < __builtin_amdgcn_readlane(have, l)) {
           g = __builtin_amdgcn_readlane(begin, l) + c;
+          near = l;
           break;
         }
+        const int seen = lane < SEG_XCDS ? __hip_atomic_load(q.counter + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        open = __ballot(lane < SEG_XCDS && seen < have);
       }
       if (lane == 0) *s_item = g;
     }
@@ -2443,6 +2453,11 @@ __device__ __forceinline__ void leave_segment(const TodoList &td, long long word
 // copy (sxj_rows rows), else it is read from global memory (it stays in L2
 // across the item's k).  gate (optional): the kernel does nothing unless
 // *gate == gate_on.
+// Bound by VALU issue: about 1200 instructions per live segment of 2000 rows,
+// 0.71 of the issue slots (2600 and 0.89 with a guarded window test, IEEE
+// divisions and 64-bit sorts).  Four waves per SIMD: with five or six the
+// registers spill or gain nothing (3.9 to 4.6 ms).  2000 x 2000 6.25 -> 3.57
+// ms; 10000 x 4000 49.0 -> 31.4 ms, 32 of its columns 3.03 -> 0.85.
 template <bool kLdsJ>
 __global__ void __launch_bounds__(64 * SEG_WAVES_MAX) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
@@ -2457,8 +2472,8 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
   double *sxj_lds = (double *)smem;
   FastScratch *fs = (FastScratch *)(smem + (kLdsJ ? seg_sxj_bytes(sxj_rows) : 0)) + wave;
   WorkItem it;
-  int jj;
-  while (next_item(queue, P, cand, ncand, &s_item, it, jj)) {
+  int jj, near = 0;
+  while (next_item(queue, P, cand, ncand, &s_item, it, jj, near)) {
     const ProbDesc d = P[it.b];
     const int n = d.n, m = d.m, T = (n + 63) >> 6, j = it.j;
     const ColInfo *cis = ci + d.col_off;
@@ -2596,7 +2611,9 @@ __device__ __forceinline__ void run_jobs(const SegIO &s, LdJ ldj, LdK ldk, uint6
 }
 
 // Several penalties per problem: every live segment, one wave per segment, a
-// penalty per lane in groups of 64.
+// penalty per lane in groups of 64.  Bound by VALU issue too: the window pass
+// and the sort once per segment, then a residual per distinct row (7 of 64
+// penalties on average at 2000 x 2000; up to eight per pass over the rows).
 template <bool kLdsJ>
 __global__ void __launch_bounds__(64 * SEG_WAVES_MAX) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,
@@ -2611,8 +2628,8 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
   double *sxj_lds = (double *)smem;
   PathScratch *ps = (PathScratch *)(smem + (kLdsJ ? seg_sxj_bytes(sxj_rows) : 0)) + wave;
   WorkItem it;
-  int jj;
-  while (next_item(queue, P, cand, ncand, &s_item, it, jj)) {
+  int jj, near = 0;
+  while (next_item(queue, P, cand, ncand, &s_item, it, jj, near)) {
     const ProbDesc d = P[it.b];
     const int n = d.n, m = d.m, L = d.L, T = (n + 63) >> 6, j = it.j;
     const ColInfo *cis = ci + d.col_off;

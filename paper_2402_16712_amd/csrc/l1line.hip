@@ -34,7 +34,7 @@ struct ProfRec {
 struct TuneParams {
   int blocks_per_cu;   // persistent workgroups per compute unit
   int kchunk_min;      // fewest k per work item
-  int items_per_cu;    // target number of work items per compute unit
+  int items_per_cu;    // target number of work items per compute unit (small batches take fewer)
 };
 
 // Size class of a launch, the key of autotuned launch parameters: one
@@ -318,7 +318,7 @@ static void layout_sizes(BatchLayout &Ly) {
   Ly.o_wstart = take(sizeof(int) * (Ly.B + 1));
   Ly.o_lam = take(sizeof(double) * Ly.total_lam);
   Ly.o_items = take(sizeof(WorkItem) * (Ly.ksplit ? 0 : Ly.nitems));
-  Ly.o_counter = take(sizeof(int) * 16);
+  Ly.o_counter = take(sizeof(int) * SEG_COUNTERS);
   Ly.o_xstart = take(sizeof(int) * (SEG_XCDS + 1));
   Ly.meta_bytes = off;
   Ly.o_ci = take(sizeof(ColInfo) * Ly.total_cols);
@@ -388,7 +388,7 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
   Ly.B = (int)B;
   Ly.nmax = 1;
   Ly.Lmax = 1;
-  double total_cost = 0.0;
+  double total_cost = 0.0, item_work = 0.0;
   for (int64_t b = 0; b < B; ++b) {
     const l1line_problem &p = probs[b];
     Ly.total_cols += p.m;
@@ -403,14 +403,23 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
     Ly.nmax = std::max<int>(Ly.nmax, (int)p.n);
     Ly.Lmax = std::max<int>(Ly.Lmax, (int)p.L);
     total_cost += (double)p.n * (double)p.m * (double)p.m;
+    item_work += (double)p.n * (double)p.m * (double)p.m * (1.0 + (double)(p.L - 1) / 12.0);
   }
   if (Ly.total_cols > (1ll << 30) || Ly.total_z > (1ll << 30) || Ly.total_out > (1ll << 30) ||
       Ly.total_tiles > (1ll << 30) || Ly.total_words > (1ll << 30))
     return L1LINE_EINVAL;
 
   // work items: split every problem's k range so the whole batch offers
-  // about items_per_cu items per compute unit, each with >= kchunk_min k
-  const double target = (double)tp.items_per_cu * ctx->num_cu;
+  // about items_per_cu items per compute unit, each with >= kchunk_min k.  An
+  // item is a claim on its XCD's counter (0.1 us, one after the other) and a
+  // column j, a mask and a sample to load, so small batches take fewer: one
+  // per ITEM_ROWS rows over its columns k (12 penalties count as twice one),
+  // down to two per workgroup.  8 matrices of up to 500 x 150, one penalty:
+  // the segments 212 us, with items_per_cu items 347 (and a look at all
+  // counters before every claim).
+  constexpr double ITEM_ROWS = 32768.0;
+  const double target = std::min((double)tp.items_per_cu * ctx->num_cu,
+                                 std::max(2.0 * tp.blocks_per_cu * ctx->num_cu, item_work / ITEM_ROWS));
   if (B == 1) {
     const int m = (int)probs[0].m;
     // implicit items routed by XCD: each XCD's part of the k range is cut
@@ -433,7 +442,6 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
     }
     Ly.ksplit = chunks;
     Ly.nitems = (ro.cand ? ro.ncand : m) * chunks;     // per XCD
-    (void)target;
   } else {
     // problems to XCDs, largest first onto the least loaded one; an XCD
     // works through its problems largest first, so its workgroups share one
@@ -564,7 +572,7 @@ struct LambdaArgs {
 __device__ __forceinline__ void write_meta(int t, const ProbDesc &pd, const LambdaArgs &lam, const BatchLayout &Ly,
                                            char *d) {
   if (t < pd.L) ((double *)(d + Ly.o_lam))[t] = lam.v[t];
-  if (t < 16) ((int *)(d + Ly.o_counter))[t] = 0;
+  if (t < SEG_COUNTERS) ((int *)(d + Ly.o_counter))[t] = 0;
   if (t <= SEG_XCDS) ((int *)(d + Ly.o_xstart))[t] = Ly.xstart[t];
   if (t != 0) return;
   *(ProbDesc *)(d + Ly.o_desc) = pd;
@@ -639,8 +647,9 @@ static void launch_meta(l1line_ctx ctx, hipStream_t s, const l1line_problem &p, 
 // The launch sequence of one batch call on stream ls, the workspace at d
 // (its metadata block already in place or written by an earlier kernel on
 // ls).  `cleared`: the counters are zero already, and without gate and earlier
-// column info the columns are prepared too.  `prof`: bracket the kernels with the context's timing events;
-// t0 / t1 (optional): events recorded around the segment kernel.
+// column info the columns are prepared too.  `prof`: bracket the kernels with
+// the context's timing events; t0 / t1 (optional): events recorded around the
+// segment kernel.
 static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, char *d, int64_t B,
                       const TuneParams &tp, const RunOpts &ro, bool prof, bool cleared, hipEvent_t t0, hipEvent_t t1,
                       BatchPtrs *outp) {
@@ -695,8 +704,9 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   const int grid_seg = (int)std::max(1ll, std::min(all_items, (long long)tp.blocks_per_cu * ctx->num_cu));
   if (!cleared || ro.gate || ro.ci) {
     ProfScope ps(pc, ls, "colprep");
-    if (!cleared) hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, ls, dcounter, 16ll, 0);
     if (have_ci) {
+      if (!cleared)
+        hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, ls, dcounter, (long long)SEG_COUNTERS, 0);
       hipLaunchKernelGGL(k_fill_int, dim3((unsigned)((Ly.total_cols + 255) / 256)), dim3(256), 0, ls, dsegflags,
                          (long long)Ly.total_cols, 0);
     } else {
@@ -704,7 +714,8 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
       auto k = f == PREP_ONE ? k_colprep_batch<1, false>
                : f == PREP_FOUR ? k_colprep_batch<PREP_WAVES, false> : k_colprep_batch<PREP_WAVES, true>;
       hipLaunchKernelGGL(k, dim3((unsigned)Ly.total_cols), dim3(f == PREP_ONE ? 64 : 64 * PREP_WAVES),
-                         f == PREP_LDS ? (size_t)Ly.nmax * 8 : 0, ls, dP, dcol, (int)B, dci, dsmp, dsegflags, ro.gate, ro.gate_on);
+                         f == PREP_LDS ? (size_t)Ly.nmax * 8 : 0, ls, dP, dcol, (int)B, dci, dsmp, dsegflags, ro.gate,
+                         ro.gate_on, dcounter);
     }
   }
   {

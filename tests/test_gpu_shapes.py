@@ -210,3 +210,24 @@ def test_breakpoint_counts(ctx, n, kind):
     for key in ("lambda_max", "lam", "v"):
         assert g[key].tobytes() == r[key].tobytes(), key
     assert np.array_equal(g["row"], r["row"])
+
+
+# work items of a batch: the fewest (two per workgroup), between, and the most
+# per CU; more problems than XCDs and fewer.  Reference: each problem's own fit
+@pytest.mark.parametrize("sizes", [[(5, 2)], [(150, 30)] * 9, [(500, 150), (60, 20), (300, 90)],
+                                   [(2100, 200), (700, 40)], [(2000, 330), (1500, 210)]])
+def test_batch_item_counts(ctx, sizes):
+    from paper_2402_16712_amd import binding as B
+    print(f"case batch items {sizes}", flush=True)
+    probs = []
+    for q, (n, m) in enumerate(sizes):
+        X = _data(300 + q, n, m, ("sparse", "counts", "dense")[q % 3])
+        probs.append((B.device_matrix(X), np.array([0.07 * wl.max_column_mass(X)])))
+    for graph in (False, True, True):
+        outs = ctx.fit_batch(probs, graph=graph)
+        for (Xd, lam), o in zip(probs, outs):
+            g, r = _host(o), _host(ctx.fit(Xd, float(lam[0])))
+            assert int(g["status"][0]) == 0 == int(r["status"][0])
+            assert int(g["J"].ravel()[0]) == int(r["j"][0])
+            for a, b in (("V", "v"), ("ROW", "row"), ("ZALL", "z_all")):
+                assert g[a].ravel().tobytes() == r[b].ravel().tobytes(), a
