@@ -77,11 +77,15 @@ constexpr int SAMPLE_ROWS = 128;    // rows of column j drawn for the key window
 //   1 wave          many columns: the four-wave form's extra pass and
 //                   reductions cost more than they hide
 // (one wave per column and one load in flight before, and no sample: 2000 x
-// 2000 32 us, now 23; 20011 x 151 213 us, now 86; 10000 x 4000 215 us, now 159)
+// 2000 32 us, now 23; 20011 x 151 212 us, now 83; 10000 x 4000 213 us, now 146)
 // The sample's cumulative weight runs wave by wave and lane by lane (a lane's
 // rows in turn, from the scan of the lanes' masses): sample r is the row whose
-// weight interval holds (r + 1/2) step; one that no row took (rounding) is
-// the column's first nonzero row.  Any rows serve: they only place windows.
+// weight interval holds (r + 1/2) step.  A row stores itself at its first
+// sample only; the ones after it, and those that no row took (rounding), are
+// filled in at the end from the nearest sample before, else from the column's
+// first nonzero row (a store per sample was a serial loop where a few rows
+// hold most of the weight: counts of up to 150 rows 14.9 us, now 5.5).  Any rows serve:
+// they only place windows.
 template <int CB, class F>
 __device__ __forceinline__ void for_rows_batch(const double *__restrict__ x, int n, int i0, F f) {
   double v[CB];
@@ -188,15 +192,14 @@ __device__ __forceinline__ void colprep_block(const double *__restrict__ x, int 
   }
   const bool sample = smp != nullptr && flags == 0 && nnz > 0;
   if (wave == 0) {
-    const unsigned f = sample ? (unsigned)first : 0u;   // (without a sample no segment uses it)
-    ((unsigned *)sh.smp)[lane] = f | (f << 16);
+    ((unsigned *)sh.smp)[lane] = 0xFFFFFFFFu;
   }
   __syncthreads();
   u128 s = 0;
   if (!flags) {
     const bool chunks = n <= L1LINE_MAX_N;        // (chunk sums exact below 2^16 nonzeros)
     double c0s = 0.0, c1s = 0.0, c2s = 0.0;
-    const double step = total / SAMPLE_ROWS;
+    const double step = total / SAMPLE_ROWS, inv = SAMPLE_ROWS / total;
     double cum = before + (scan - mine);
     int r = sample ? max((int)ceil(cum / step - 0.5), 0) : SAMPLE_ROWS;
     double next = r < SAMPLE_ROWS ? (r + 0.5) * step : __builtin_inf();
@@ -213,7 +216,8 @@ __device__ __forceinline__ void colprep_block(const double *__restrict__ x, int 
       }
       cum = cum + a;
       if (cum > next && a != 0.0) {
-        for (; r < SAMPLE_ROWS && (r + 0.5) * step < cum; ++r) sh.smp[r] = (unsigned short)i;
+        sh.smp[r] = (unsigned short)i;
+        r = (int)fmin(fmax(ceil(cum * inv - 0.5), r + 1.0), (double)SAMPLE_ROWS);
         next = r < SAMPLE_ROWS ? (r + 0.5) * step : __builtin_inf();
       }
     });
@@ -230,7 +234,17 @@ __device__ __forceinline__ void colprep_block(const double *__restrict__ x, int 
   }
   __syncthreads();
   if (wave != 0) return;
-  if (smp) ((unsigned *)smp)[lane] = ((const unsigned *)sh.smp)[lane];
+  if (smp) {
+    const uint32_t two = ((const unsigned *)sh.smp)[lane];
+    const bool has0 = (two & 0xFFFFu) != 0xFFFFu, has1 = two >> 16 != 0xFFFFu;
+    // the lanes at or below that hold a sample, and each one's last
+    const uint64_t m = __ballot(has0 || has1), below = m & ((1ull << lane) - 1ull);
+    const uint32_t last = has1 ? two >> 16 : two & 0xFFFFu;
+    const uint32_t prev = (uint32_t)__shfl((int)last, below ? 63 - __builtin_clzll(below) : 0);
+    const uint32_t f = sample ? (uint32_t)first : 0u;   // (without a sample no segment uses it)
+    const uint32_t s0 = has0 ? two & 0xFFFFu : below ? prev : f, s1 = has1 ? two >> 16 : s0;
+    ((unsigned *)smp)[lane] = s0 | (s1 << 16);
+  }
   if (lane == 0) {
     ColInfo c;
     c.wfix = 0;
