@@ -146,8 +146,9 @@ def _pmc_per_dispatch(path, counter):
 
 
 def pmc_summary(fetch_csv, write_csv, copyf_csv, copyw_csv, sq_csv=None, lds_csv=None):
-    """The dominant kernel's counter record: HBM bytes per launch of
-    k_seg_batch from the FETCH_SIZE and WRITE_SIZE counters, each scaled by
+    """The dominant kernel's counter record: HBM bytes per launch of the
+    segment kernel that fetches most from the FETCH_SIZE and WRITE_SIZE
+    counters (k_seg_fast; k_seg_rest is next to it), each scaled by
     what the counter reads for a copy of exactly 512 MiB (bench.py
     --calibrate-copy), (optional) SQ_INSTS_VALU / SQ_INSTS_LDS per launch
     and (optional) SQ_LDS_IDX_ACTIVE / GRBM_GUI_ACTIVE per launch."""
@@ -157,7 +158,7 @@ def pmc_summary(fetch_csv, write_csv, copyf_csv, copyw_csv, sq_csv=None, lds_csv
     fs, ws = nbytes / cf, nbytes / cw
     f = _pmc_per_dispatch(fetch_csv, "FETCH_SIZE")
     w = _pmc_per_dispatch(write_csv, "WRITE_SIZE")
-    kern = "k_seg_batch"
+    kern = max((k for k in f if k.startswith("k_seg_")), key=f.get)
     fetch = f[kern] * 1024 * fs
     write = w[kern] * 1024 * ws
     rec = {"kernel": kern, "bytes_per_launch": fetch + write, "fetch_bytes": fetch, "write_bytes": write,
@@ -447,14 +448,15 @@ def main():
     z_gpu = out["z_all"].cpu().numpy()
     j_star = int(out["j"].item())
 
-    # roofline of the dominant kernel, k_seg_batch (one launch = the m(m-1)
-    # segments of one fit), against the method's algorithmic FP64 work
+    # roofline of the dominant kernel, k_seg_fast (one launch = the m(m-1)
+    # segments of one fit; the time is the launch's with the k_seg_rest after
+    # it), against the method's algorithmic FP64 work
     work = algorithmic_work(p.X)
     seg_s = kern["fit_seg"] / 1000.0
     achieved = work["flops"] / seg_s / 1e12
     peaks = ctx.measure_peaks()
     rec = _counters("seg_2000x2000")
-    roof = {"bound": "alu", "kernel": "k_seg_batch", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
+    roof = {"bound": "alu", "kernel": "k_seg_fast", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
             "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
             "traffic": rec.get("bytes_per_launch") if rec else None,
             "work": dict(work, basis="per fit: 2 flops per ratio element (IEEE divide, prefix-sum add), "
@@ -469,7 +471,7 @@ def main():
                          "valu_busy": busy,
                          "basis": "SQ_INSTS_VALU x 4 cycles / (1024 SIMDs x 2.4 GHz x launch time)"}
     if rec and rec.get("sq_insts_lds") and rec.get("sq_lds_idx_active") and rec.get("grbm_gui_active"):
-        # the window lists' sort and scan run through the LDS: its index
+        # column j and the window lists are read from the LDS: its index
         # unit's busy share of the launch (GRBM_GUI_ACTIVE sums the 8 XCDs'
         # cycles, SQ_LDS_IDX_ACTIVE the 256 CUs'), and the bytes moved if
         # every LDS instruction moves 8 bytes per lane, against the measured
@@ -481,7 +483,7 @@ def main():
                        "peak_measured_GBps": peaks["lds_GBps"],
                        "frac_est": lds_bytes / seg_s / 1e9 / peaks["lds_GBps"],
                        "basis": "busy = SQ_LDS_IDX_ACTIVE / (256 CUs x GRBM_GUI_ACTIVE / 8 XCDs); bytes = "
-                                "SQ_INSTS_LDS x 64 lanes x 8 B (the list keys and column j are 8-byte entries)"}
+                                "SQ_INSTS_LDS x 64 lanes x 8 B (column j is read 8 bytes per lane)"}
 
     # the sign-sum contraction on the FP64 matrix units: the MFMAs the
     # kernel issues (the Zr product only for 4 x 16 blocks holding a zero)

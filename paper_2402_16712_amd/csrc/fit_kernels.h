@@ -84,8 +84,8 @@ constexpr int SAMPLE_ROWS = 128;    // rows of column j drawn for the key window
 // sample only; the ones after it, and those that no row took (rounding), are
 // filled in at the end from the nearest sample before, else from the column's
 // first nonzero row (a store per sample was a serial loop where a few rows
-// hold most of the weight: counts of up to 150 rows 14.9 us, now 5.5).  Any rows serve:
-// they only place windows.
+// hold most of the weight: counts of up to 150 rows 14.9 us, now 5.5).  Any
+// rows serve: they only place windows.
 template <int CB, class F>
 __device__ __forceinline__ void for_rows_batch(const double *__restrict__ x, int n, int i0, F f) {
   double v[CB];
