@@ -1078,6 +1078,24 @@ __device__ __forceinline__ int sign_sum_side(double2 dz, double lam, double Wj, 
   return 3;
 }
 
+// 2^e0 when column j's weights and the penalty are whole multiples of it with
+// sums below 2^50 of them (whole numbers): then every FP64 sum of weights is
+// exact, and so is a comparison of one with the target; else 0.
+__device__ __forceinline__ double whole_unit(const ColInfo &cj, double lam) {
+  const double l = ldexp(lam, -cj.e0);
+  const bool ok = cj.bemin >= 1023 - 300 && cj.wfix < ((u128)1 << 50) && l < 0x1p50 && floor(l) == l;
+  return ok ? ldexp(1.0, cj.e0) : 0.0;
+}
+// sign_sum_side, and where its margin leaves the side open the exact sums'
+// answer if they are exact (count data tie at whole penalties: without it every
+// such segment took the exact kernel).
+__device__ __forceinline__ int sign_sum_side(const ColInfo &cj, double2 dz, double lam, bool unc) {
+  const int side = sign_sum_side(dz, lam, cj.W, unc);
+  if (side != 3 || unc || !(whole_unit(cj, lam) > 0.0)) return side;
+  const double d1 = lam + dz.y + dz.x, d2 = lam + dz.y - dz.x;
+  return d1 >= 0.0 && d2 >= 0.0 ? 0 : d1 < 0.0 ? 1 : 2;
+}
+
 // The sign sums cannot decide segment (j, k) when a ratio could underflow to
 // 0 (exponent fields more than 1000 apart) or a sum is not finite.
 __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInfo &ck, double2 dz) {
@@ -1132,7 +1150,7 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
       const bool unc = sign_sums_unsure(cj, ck, dz);
       const double *lam = lam_all + d.lam_off;
       skip = true;
-      for (int t = 0; t < d.L && skip; ++t) skip = sign_sum_side(dz, lam[t], cj.W, unc) == 0;
+      for (int t = 0; t < d.L && skip; ++t) skip = sign_sum_side(cj, dz, lam[t], unc) == 0;
       if (skip && d.L == 1) {
         const long long base = d.ws_off + (long long)j * d.m + k;
         V[base] = 0.0;
@@ -1482,9 +1500,13 @@ __device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, in
 // (from about 26000 rows) at quarters of its range.
 template <class LdJ, class LdK>
 __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool neg, double lam, double Wd,
-                                         uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
+                                         double unit, uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
   constexpr double WDELTA = 0.06;
-  const double tol = 0x1p-38 * Wd;
+  // unit > 0 (whole_unit): the prefix weights are multiples of it and the
+  // target of half of it, so a quarter of a unit settles a tie as the exact
+  // path does (negative side: the first prefix above the target; positive: the
+  // first at or above it) and leaves nothing closer than that
+  const double tol = unit > 0.0 ? 0.125 * unit : 0x1p-38 * Wd, shift = neg ? 0.25 * unit : -0.25 * unit;
   // sample values with low bits no simple fraction has: a ratio equal to a
   // bound cannot be settled here
   auto value = [&](int ix) {
@@ -1498,7 +1520,7 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
   auto bound = [&](int ix) {
     return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix);
   };
-  auto target = [&](double T) { return 0.5 * (neg ? T + lam : T - lam); };
+  auto target = [&](double T) { return 0.5 * (neg ? T + lam : T - lam) + shift; };
   double c = c0;
   int il = max((int)floor(c - WDELTA * SAMPLE_ROWS) - 1, lmin), ir = min((int)ceil(c + WDELTA * SAMPLE_ROWS), rmax);
   if (neg) il = max(min(il, rmax - 3), lmin);
@@ -2509,6 +2531,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     // the targets' places in the sample
     const double cneg = 0.5 * SAMPLE_ROWS * (Wd + lam) / Wd, cpos = 0.5 * SAMPLE_ROWS * (Wd - lam) / Wd;
     const bool fast_j = !cj.flags && fast_columns(cj);
+    const double unit = whole_unit(cj, lam);
     const double2 *DZj = DZ + d.pair_off + (long long)j * m;
     // claims are taken one segment ahead, and the next segment's sign sums and
     // sample are loaded before the current one's residual
@@ -2529,7 +2552,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
         v = k == j ? 1.0 : __longlong_as_double(0x7ff8000000000000ll);
         e = 0.0;
       } else {
-        const int side = sign_sum_side(dz, lam, Wd, sign_sums_unsure(cj, ck, dz));
+        const int side = sign_sum_side(cj, dz, lam, sign_sums_unsure(cj, ck, dz));
         left = side == 3 || (side != 0 && !(fast_j && fast_columns(ck)));
         if (side != 0 && !left) {
           const bool neg = side == 1;
@@ -2538,7 +2561,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
           const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, n), rj = col_rsrc(kLdsJ ? s.xk : s.sxj, n);
           auto ldj = [&](int i) { return sxj_pad(s, rj, i); };
           auto ldk = [&](int i) { return col_ld(rk, i * 8); };
-          left = !fast_one(s, ldj, ldk, neg, lam, Wd, sx[0], sx[1], neg ? cneg : cpos, fs, v, row);
+          left = !fast_one(s, ldj, ldk, neg, lam, Wd, unit, sx[0], sx[1], neg ? cneg : cpos, fs, v, row);
         }
       }
       const long long base = d.ws_off + (long long)j * m + k;

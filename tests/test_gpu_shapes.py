@@ -231,3 +231,20 @@ def test_batch_item_counts(ctx, sizes):
             assert int(g["J"].ravel()[0]) == int(r["j"][0])
             for a, b in (("V", "v"), ("ROW", "row"), ("ZALL", "z_all")):
                 assert g[a].ravel().tobytes() == r[b].ravel().tobytes(), a
+
+
+# whole numbers at whole penalties: targets that tie with prefix weights and
+# sides that tie, columns of few and many rows, a unit other than 1
+@pytest.mark.parametrize("n", [7, 64, 545, 2300, 5000])
+@pytest.mark.parametrize("unit", [1.0, 2.0 ** -20])
+def test_whole_penalties(ctx, n, unit):
+    from paper_2402_16712_amd import binding as B
+    print(f"case whole penalties n={n} unit={unit}", flush=True)
+    X = np.asfortranarray(_data(700 + n, n, 9, "counts") * unit)
+    Xd = B.device_matrix(X)
+    top = wl.max_column_mass(X) / unit
+    lams = unit * np.array([0.0, 1.0, 2.0, round(0.05 * top), round(0.05 * top) + 0.5, round(0.3 * top) + 1.0, top])
+    for lam in lams:
+        _fit_equal(_host(ctx.fit(Xd, float(lam))), O.fit(X, float(lam)), (n, lam))
+    lams = np.unique(lams)
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, "path"))
