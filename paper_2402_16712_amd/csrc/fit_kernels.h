@@ -1824,7 +1824,19 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
   double lo = bound(il);
   int shrink = 0, start = il;
   bool jump = true;
-  for (int it = 0; it < 160 && pend; ++it) {
+  for (int it = 0; it < 160 && (pend | low); ++it) {
+    if (pend == 0) {
+      // (after a listed window or a tie's rows) targets below the first window,
+      // or in a part passed over: again from further down, part by part
+      if (start <= lmin && !jump) return false;
+      pend = low;
+      low = 0;
+      jump = false;
+      iend = rmax;
+      il = start = max(start - 13, lmin);
+      lo = bound(il);
+      shrink = 0;
+    }
     // the next window: [lo, hi), hi at sample ir or (shrink) inside a gap
     int ir = min(il + step, max(iend, il + 1));
     ir = min(ir, rmax);
@@ -1909,17 +1921,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
     shrink = 0;
     lo = hi;
     il = ir;
-    if (pend == 0 && low) {
-      // targets below the first window, or in a part passed over: again from
-      // further down, part by part
-      if (start <= lmin && !jump) return false;
-      pend = low;
-      low = 0;
-      jump = false;
-      iend = rmax;
-      il = start = max(start - 13, lmin);
-      lo = bound(il);
-    } else if (pend) {
+    if (pend) {
       // (nothing is expected before the pending targets' windows)
       const int nx = min(wave_min_int_x(((pend >> lane) & 1ull) ? cl : SAMPLE_ROWS), rmax - 1);
       if (jump && nx > il) {
@@ -1929,7 +1931,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
       iend = max(iend, il + 12);
     }
   }
-  return pend == 0;
+  return (pend | low) == 0;
 }
 
 // ------------------------------------------------- segments left to the end

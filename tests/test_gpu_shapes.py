@@ -248,3 +248,27 @@ def test_whole_penalties(ctx, n, unit):
         _fit_equal(_host(ctx.fit(Xd, float(lam))), O.fit(X, float(lam)), (n, lam))
     lams = np.unique(lams)
     _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, "path"))
+
+
+def _correlated_counts(seed, n, m):
+    """Whole numbers <= 60 whose rows and columns share a scale: v_k != 0 for
+    most pairs, and hundreds to thousands of equal ratios."""
+    g = np.random.default_rng(seed)
+    scale = 0.6 * g.standard_normal(n)[:, None] + 0.6 * g.standard_normal(m)[None, :]
+    return np.asfortranarray(np.minimum(np.floor(np.exp(scale) * 2.0 * g.random((n, m))), 60.0))
+
+
+# several penalties: targets below the first window while the last of the others
+# lie among more equal ratios than the list holds (seeds whose segments do so)
+@pytest.mark.parametrize("n,L,seed", [(5000, 8, 2), (5000, 8, 3), (5000, 8, 4), (5000, 8, 6), (20000, 8, 5),
+                                      (20000, 8, 9), (20000, 33, 2), (20000, 33, 3)])
+def test_targets_below_a_tie(ctx, n, L, seed):
+    from paper_2402_16712_amd import binding as B
+    print(f"case below a tie {n} penalties {L} seed {seed}", flush=True)
+    X = _correlated_counts(seed, n, 6)
+    lams = wl.max_column_mass(X) * 10.0 ** (-3.0 + 3.0 * np.arange(L) / (L - 1))
+    Xd, r = B.device_matrix(X), O.fit_path(X, lams)
+    _path_equal(_host(ctx.fit_path(Xd, lams)), r, (n, L, seed))
+    got = ctx.fit_batch([(Xd, lams), (Xd, lams[:1])])
+    _path_equal(_host(got[0]), r, (n, L, seed, "batch"))
+    _path_equal(_host(got[1]), O.fit_path(X, lams[:1]), (n, L, seed, "batch"))
