@@ -2301,21 +2301,50 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
   }
 }
 
-// The words of todo that hold an unsettled segment (listed by the
-// division-free kernels: todo_list[0, *todo_count)), REST_PER of a word's
-// segments per claim of a wave from *next: the first of every word, then the
-// next ones (whose claims most words leave empty).  Such segments cluster in a
-// few columns, so a whole word per wave was one long chain (2859 segments of
-// the 2000 x 2000 path 5.3 ms).  The count is final: it belongs to earlier
-// kernels.
-constexpr int REST_PER = 2;
+// Where the division-free kernels leave what they cannot settle: a bit per
+// segment, and a list of the words' parts, which are what a wave of k_seg_rest
+// takes at a time: part p of a word is its left segments of rank
+// rest_rank(cut, p) to rest_rank(cut, p + 1) - 1.  A wave's parts are one chain
+// and should be short where there are few, but each costs an append to the list
+// and a claim of it, about 6 ns one after the other.  So the 64 segments of a
+// word go by 1, 2 or 4 (cut 0, 1, 2) as long as the call's words then give the
+// chip at most eight parts per wave (20000 x 40 has 40 words: by two and by eight
+// 8 whole penalties took 39 and 120 ms), and else (cut 3) by eight after a first
+// two, two and four: what is left clusters (the 2859 segments of the 2000 x 2000
+// path were close together in few columns; a word per wave took 5.3 ms).
+constexpr int REST_CUTS = 4;
+__host__ __device__ constexpr int rest_rank(int cut, int p) {
+  return cut < 3 ? p << cut : p < 3 ? 2 * p : 8 * (p - 2);
+}
+// parts of a word with `count` segments left
+__host__ __device__ constexpr int rest_parts(int cut, int count) {
+  return cut < 3 ? (count + (1 << cut) - 1) >> cut : count <= 4 ? (count + 1) / 2 : (count + 23) / 8;
+}
+struct TodoPart {
+  int word, part;
+};
+struct TodoList {
+  unsigned long long *bits;
+  TodoPart *list;
+  int *count;
+  int cut;
+};
+__device__ __forceinline__ void leave_segment(const TodoList &td, long long word, int bit) {
+  const int c = __builtin_popcountll(atomicOr(td.bits + word, 1ull << bit)), p = rest_parts(td.cut, c);
+  if (rest_parts(td.cut, c + 1) > p) td.list[atomicAdd(td.count, 1)] = TodoPart{(int)word, p};
+}
+
+// The parts that the division-free kernels listed, one per claim of a wave (or
+// several, of long lists) from *next; the first is the wave's own number (an
+// atomic of every wave on one counter took 50 us where nothing was left), and
+// the only one where there are no more parts than waves.  The count and the
+// words are final: they belong to earlier kernels.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, const double *__restrict__ lam_all,
            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
            double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, int *__restrict__ segflags,
            const int *__restrict__ cand, const int *__restrict__ gate, int gate_on,
-           const unsigned long long *__restrict__ todo, const int *__restrict__ todo_list,
-           const int *__restrict__ todo_count, int *__restrict__ next, int Lmax, int lcap) {
+           TodoList td, int *__restrict__ next, int Lmax, int lcap) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (gate && *gate != gate_on) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -2323,21 +2352,25 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
   WaveScratch *ws = (WaveScratch *)(slam + Lmax);
   uint64_t *lk = (uint64_t *)(ws + 1);
   unsigned short *lr = (unsigned short *)(lk + lcap);
-  const int count = *todo_count;
-  // the first claim is the wave's own number (an atomic of every wave on one
-  // counter took 50 us where nothing was left)
-  const unsigned waves = gridDim.x * 4u, claims = (unsigned)count * (64u / REST_PER);
-  for (unsigned e = blockIdx.x * 4u + wave; e < claims;) {
-    const int skip = (int)(e / (unsigned)count) * REST_PER;
-    const int w = uni_int(todo_list[e % (unsigned)count]);
-    uint64_t bits = todo[w];
-    {
-      unsigned c = 0;
-      if (lane == 0) c = (unsigned)atomicAdd(next, 1);
-      e = waves + (unsigned)uni_int((int)c);
+  const int count = *td.count, waves = (int)gridDim.x * SEG_WAVES;
+  const int per = max(1, count / (8 * waves));
+  int e = (blockIdx.x * SEG_WAVES + wave) * per, left = per;
+  while (e < count) {
+    const TodoPart part = td.list[e];
+    const int w = uni_int(part.word), p = uni_int(part.part);
+    uint64_t bits = td.bits[w];
+    ++e;
+    if (--left == 0) {
+      if (count <= waves) {
+        e = count;
+      } else {
+        int c = 0;
+        if (lane == 0) c = atomicAdd(next, per);
+        e = waves * per + uni_int(c);
+        left = per;
+      }
     }
-    if (__builtin_popcountll(bits) <= skip) continue;
-    for (int q = 0; q < skip; ++q) bits &= bits - 1;
+    for (int q = rest_rank(td.cut, p); q > 0; --q) bits &= bits - 1;
     const int b = find_owner(wstart, B, w);
     const ProbDesc d = P[b];
     const int wpr = (d.m + 63) >> 6, wl = w - wstart[b], jj = wl / wpr, k0 = (wl - jj * wpr) * 64;
@@ -2350,7 +2383,7 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
     wave_lds_sync();
     for (int t = lane; t < d.L; t += 64) slam[t] = lambda_fixed(lam[t], cj.e0);
     wave_lds_sync();
-    for (int q = 0; q < REST_PER && bits; ++q, bits &= bits - 1) {
+    for (int q = rest_rank(td.cut, p + 1) - rest_rank(td.cut, p); q > 0 && bits; --q, bits &= bits - 1) {
       const int k = k0 + __builtin_ctzll(bits);
       const SegIO s{d.X + (long long)k * d.ld, d.X + (long long)j * d.ld, d.n, T, Tp, cj.e0, lane, false};
       seg_exact(s, cj, ci[d.col_off + k], smp + (long long)(d.col_off + j) * SAMPLE_ROWS, lam, d.L,
@@ -2475,16 +2508,6 @@ struct LiveSegs {
     return 64 * (w0 + w) + __builtin_ctzll(__ballot(((lw >> lane) & 1ull) && lanes_below(lw) == r));
   }
 };
-
-// Where the division-free kernels leave what they cannot settle: a bit per
-// segment, and the words that have one listed once.
-struct TodoList {
-  unsigned long long *bits;
-  int *list, *count;
-};
-__device__ __forceinline__ void leave_segment(const TodoList &td, long long word, int bit) {
-  if (atomicOr(td.bits + word, 1ull << bit) == 0ull) td.list[atomicAdd(td.count, 1)] = (int)word;
-}
 
 // One penalty per problem: every live segment by the division-free path, one
 // wave per segment.  kLdsJ: every problem's column j fits the launch's LDS

@@ -300,6 +300,7 @@ struct BatchLayout {
   int B, nitems, ksplit, nmax, Lmax;
   int ss_split;               // row parts of the sign sums
   long long ss_per;           // pairs per part
+  int rest_cut;               // parts of the words left to the exact kernel
   int xstart[SEG_XCDS + 1];   // explicit items: XCD x owns [xstart[x], xstart[x + 1])
   long long total_cols, total_z, total_out, total_ws, total_lam, total_pairs, total_tiles, total_words;
   size_t o_desc, o_colstart, o_zstart, o_ostart, o_tstart, o_wstart, o_lam, o_items, o_counter, o_xstart,
@@ -328,7 +329,7 @@ static void layout_sizes(BatchLayout &Ly) {
   Ly.o_DZp = take(Ly.ss_split > 1 ? 2 * sizeof(double) * Ly.ss_split * (size_t)Ly.ss_per : 0);
   Ly.o_mask = take(sizeof(unsigned long long) * Ly.total_words);
   Ly.o_todo = take(sizeof(unsigned long long) * Ly.total_words);
-  Ly.o_todolist = take(sizeof(int) * Ly.total_words);
+  Ly.o_todolist = take(sizeof(TodoPart) * rest_parts(Ly.rest_cut, 64) * Ly.total_words);
   Ly.o_V = take(sizeof(double) * Ly.total_ws);
   Ly.o_E = take(sizeof(double) * Ly.total_ws);
   Ly.o_R = take(sizeof(int) * Ly.total_ws);
@@ -488,6 +489,8 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
   sp = std::min<long long>({sp, 32, Ly.nmax / 32});
   Ly.ss_split = (int)std::max<long long>(1, sp);
   Ly.ss_per = (B == 1 && ro.cand) ? (long long)ro.ncand * probs[0].m : Ly.total_pairs;
+  const long long rest_most = 8ll * 4 * SEG_WAVES * ctx->num_cu;
+  while (Ly.rest_cut < REST_CUTS - 1 && Ly.total_words * rest_parts(Ly.rest_cut, 64) > rest_most) ++Ly.rest_cut;
   layout_sizes(Ly);
   while (Ly.bytes > max_bytes && Ly.ss_split > 1) {
     Ly.ss_split /= 2;
@@ -670,7 +673,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   int *dR = (int *)(d + Ly.o_R), *dzflag = (int *)(d + Ly.o_zflag);
   double2 *dDZ = (double2 *)(d + Ly.o_DZ), *dDZp = (double2 *)(d + Ly.o_DZp);
   unsigned long long *dmask = (unsigned long long *)(d + Ly.o_mask);
-  const TodoList todo{(unsigned long long *)(d + Ly.o_todo), (int *)(d + Ly.o_todolist), dcounter + 8};
+  const TodoList todo{(unsigned long long *)(d + Ly.o_todo), (TodoPart *)(d + Ly.o_todolist), dcounter + 8, Ly.rest_cut};
   if (outp) *outp = BatchPtrs{dV, dR, dci};
   l1line_ctx pc = prof ? ctx : nullptr;
 
@@ -739,10 +742,12 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
                              : (multi ? k_seg_path<false> : k_seg_fast<false>);
     hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * seg_waves), lds_fast, ls, dP, queue, dlam, dci, dsmp,
                        dDZ, dV, dE, dR, ro.cand, ro.ncand, ro.gate, ro.gate_on, dmask, todo, sxj_rows);
-    hipLaunchKernelGGL(k_seg_rest, dim3((unsigned)std::min<long long>(4ll * ctx->num_cu, (Ly.total_words + 3) / 4)),
+    // (a wave per part that can be left, up to what the chip holds: a wave per
+    // word gave 20000 x 40 with 8 whole penalties 40 waves, 196 ms)
+    const long long rest_waves = Ly.total_words * rest_parts(Ly.rest_cut, 64);
+    hipLaunchKernelGGL(k_seg_rest, dim3((unsigned)std::min<long long>(4ll * ctx->num_cu, (rest_waves + 3) / 4)),
                        dim3(64 * SEG_WAVES), lds_rest, ls, dP, dwst, (int)B, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags,
-                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, todo.bits, todo.list, todo.count, dcounter + 9,
-                       Ly.Lmax, lcap);
+                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, todo, dcounter + 9, Ly.Lmax, lcap);
   }
   if (t1) HIP_TRY(hipEventRecord(t1, ls));
   {

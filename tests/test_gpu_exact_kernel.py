@@ -1,0 +1,93 @@
+"""The exact segment kernel (what the division-free kernels leave): parity with
+the CPU oracle in every form of its work list, and that its work spreads over
+the chip, by times of the same process in ratio to each other."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2402_16712_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2402_16712_amd import binding as B
+    c = B.Context(0)
+    yield c
+    c.close()
+
+
+def _host(out):
+    import torch
+    torch.cuda.synchronize()
+    return {k: (v.cpu().numpy() if v is not None else None) for k, v in out.items()}
+
+
+def _path_equal(g, r, tag):
+    assert int(g["status"][0]) == 0, (tag, g["status"])
+    assert np.array_equal(g["J"], r["J"]), tag
+    assert g["V"].tobytes() == r["V"].tobytes(), (tag, np.argwhere(g["V"] != r["V"])[:5])
+    assert np.array_equal(g["ROW"], r["ROW"]), tag
+    assert g["ZALL"].tobytes() == r["ZALL"].tobytes(), tag
+
+
+def _matrix(n, m, seed):
+    return wl.rank_one_matrix(n, m, max(1, m // 3), n // 10, 20.0, 0.01, (12, seed, n, m))
+
+
+def _segment_ms(ctx, call):
+    """Fastest of five runs of the segment kernels of one call."""
+    import torch
+    call()
+    best = np.inf
+    ctx.profile(True)
+    try:
+        for _ in range(5):
+            ctx.profile_read(None, reset=True)
+            call()
+            torch.cuda.synchronize()
+            best = min(best, ctx.profile_read("fit_seg", reset=True)[0])
+    finally:
+        ctx.profile(False)
+    return best
+
+
+# the columns at left are outside the division-free range: their segments are
+# left as row or as column of the pair.  Parts of one, two and four segments,
+# then the graded ones, words partly and wholly left, a last word of one segment
+@pytest.mark.parametrize("m,left", [(2, 2), (65, 65), (200, 200), (300, 7), (300, 300), (400, 3), (400, 50), (449, 449)])
+def test_work_list_forms(ctx, m, left):
+    from paper_2402_16712_amd import binding as B
+    print(f"case work list {m} left {left}", flush=True)
+    X = _matrix(70, m, left)
+    big = wl.max_column_mass(X)
+    X[:, np.random.default_rng(m).permutation(m)[:left]] *= 2.0 ** 320
+    Xd = B.device_matrix(X)
+    for lams in (np.array([0.05 * big]), np.array([0.0, 0.02 * big, 0.3 * big])):
+        r = O.fit_path(X, lams)
+        _path_equal(_host(ctx.fit_path(Xd, lams)), r, (m, left, len(lams)))
+        got = ctx.fit_batch([(Xd, lams), (Xd, lams[:1])])
+        _path_equal(_host(got[0]), r, (m, left, "batch"))
+
+
+# 552 segments are fewer than the chip's wave slots, so they take about as long
+# as the slowest of them alone, here of eight pairs of columns at the same
+# penalties (one after the other in 24 waves they took 23 times an average one;
+# four times leaves room for what they share)
+@pytest.mark.parametrize("L", [1, 8])
+def test_few_segments_run_at_once(ctx, L):
+    from paper_2402_16712_amd import binding as B
+    print(f"case at once penalties {L}", flush=True)
+    X = wl.accuracy_matrix(5000, 24, 3)[0] * 2.0 ** 320      # (dense direction: every v_k is nonzero)
+    lams = 0.02 * wl.max_column_mass(X) * (1.0 + 0.3 * np.arange(L))
+    Xd = B.device_matrix(X)
+    many, two = _segment_ms(ctx, lambda: ctx.fit_path(Xd, lams)), 0.0
+    for q in range(8):
+        Xq = B.device_matrix(X[:, 3 * q:3 * q + 2])
+        two = max(two, _segment_ms(ctx, lambda: ctx.fit_path(Xq, lams)))
+    print(f"  552 segments {1e3 * many:.1f} us, 2 segments {1e3 * two:.1f} us", flush=True)
+    assert many < 4.0 * two
