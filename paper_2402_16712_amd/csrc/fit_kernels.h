@@ -1934,6 +1934,78 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
   return (pend | low) == 0;
 }
 
+// RJ residuals in one pass over the rows (the sums of wave_residual, RJ at a
+// time); the lanes of the first RJ bits of jm (v_l: the lane's ratio) receive
+// theirs in e_l, and the bits are cleared.  The R64 trees are folded: at each
+// level two trees trade halves and go on as one, the lower one on the lower
+// lanes, so the adds and their pairing are those of RJ separate trees.
+__device__ __forceinline__ double fold32(double a, double b, bool wide) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  const auto l = wide ? __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false)
+                      : __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto h = wide ? __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false)
+                      : __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
+__device__ __forceinline__ double add_down(double p, int d) {
+  const uint64_t b = (uint64_t)__double_as_longlong(p);
+  return p + __longlong_as_double((long long)(((uint64_t)xdown32((uint32_t)(b >> 32), d) << 32) | xdown32((uint32_t)b, d)));
+}
+template <int RJ, class LdJ, class LdK>
+__device__ __forceinline__ void run_jobs(const SegIO &s, LdJ ldj, LdK ldk, uint64_t &jm, double v_l, double &e_l) {
+  const uint64_t all = jm;
+  double jv[RJ], p[RJ];
+#pragma unroll
+  for (int r = 0; r < RJ; ++r) {
+    jv[r] = jm ? readlane_dbl(v_l, __builtin_ctzll(jm)) : 0.0;
+    jm &= jm ? jm - 1 : 0;
+    p[r] = 0.0;
+  }
+  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
+#pragma unroll
+    for (int r = 0; r < RJ; ++r) {
+      const double prod = jv[r] * a;
+      const double d = b - prod;
+      p[r] = p[r] + fabs(d);
+    }
+  });
+  double x;
+  int src;                                         // where job i ends: its bits on lane bits 5, 4 (, 3)
+  const int i = lanes_below(all);
+  if constexpr (RJ > 4) {
+    auto at = [&](int r) { return r < RJ ? p[r] : 0.0; };
+    const double q0 = fold32(fold32(p[0], p[4], true), fold32(p[2], at(6), true), false);
+    const double q1 = fold32(fold32(p[1], at(5), true), fold32(p[3], at(7), true), false);
+    const bool up = (threadIdx.x & 8) != 0;
+    const double keep = up ? q1 : q0, send = up ? q0 : q1;
+    const uint64_t sb = (uint64_t)__double_as_longlong(send);
+    x = keep + __longlong_as_double((long long)(((uint64_t)xswap32((uint32_t)(sb >> 32), 8) << 32) | xswap32((uint32_t)sb, 8)));
+    src = ((i & 4) << 3) | ((i & 2) << 3) | ((i & 1) << 3);
+  } else if constexpr (RJ > 2) {
+    x = add_down(fold32(fold32(p[0], p[2], true), fold32(p[1], p[3], true), false), 8);
+    src = ((i & 2) << 4) | ((i & 1) << 4);
+  } else {
+    x = add_down(add_down(fold32(p[0], p[1], true), 16), 8);
+    src = (i & 1) << 5;
+  }
+  x = add_down(add_down(add_down(x, 4), 2), 1);
+  const double got = __shfl(x, src);
+  if (((all >> (threadIdx.x & 63)) & 1ull) && i < RJ) e_l = got;
+}
+
+// residuals of the lanes of jm (v_l finite), up to eight per pass over the rows
+template <class LdJ, class LdK>
+__device__ __forceinline__ void run_all_jobs(const SegIO &s, LdJ ldj, LdK ldk, uint64_t jm, double v_l, double &e_l) {
+  while (jm) {
+    const int c = __builtin_popcountll(jm);
+    if (c > 6) run_jobs<8>(s, ldj, ldk, jm, v_l, e_l);
+    else if (c > 4) run_jobs<6>(s, ldj, ldk, jm, v_l, e_l);
+    else if (c > 2) run_jobs<4>(s, ldj, ldk, jm, v_l, e_l);
+    else run_jobs<2>(s, ldj, ldk, jm, v_l, e_l);
+  }
+}
+
 // ------------------------------------------------- segments left to the end
 // One segment by one wave with exact 128-bit sums and the general rounds:
 // what the division-free kernels leave (columns outside their range, sums too
@@ -2260,8 +2332,10 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
     }
 
     // residuals, reused while the selected row repeats: the group's targets
-    // whose row differs from the previous target's are the jobs, scored up
-    // to RJ at a time in one pass over the rows
+    // whose row differs from the previous target's are the jobs, scored up to
+    // eight at a time in one pass over the rows (2000 x 1000
+    // outside 2^+-300 with 16 penalties 19.5 ms a pass each, now 17.1); one job,
+    // or an infinite ratio, takes a pass of its own
     const int tend = min(L, 64 * g + 64);
     const int cnt = tend - 64 * g;
     int orw_l = -1;
@@ -2275,7 +2349,13 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
     const bool need = lane < cnt && orw_l >= 0 && orw_l != prv;
     const uint64_t needm = __ballot(need);
     double e_l = 0.0;
-    for (uint64_t jm = needm; jm; jm &= jm - 1) {
+    uint64_t many = __ballot(need && __builtin_isfinite(v_l));
+    many = __builtin_popcountll(many) > 1 ? many : 0;
+    if (many) {
+      const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, n), rj = col_rsrc(s.sxj, n);
+      run_all_jobs(s, [&](int i) { return col_ld(rj, i * 8); }, [&](int i) { return col_ld(rk, i * 8); }, many, v_l, e_l);
+    }
+    for (uint64_t jm = needm & ~many; jm; jm &= jm - 1) {
       const int jl = __builtin_ctzll(jm);
       const double e1 = readlane_dbl(wave_residual(s, readlane_dbl(v_l, jl)), 0);
       if (lane == jl) e_l = e1;
@@ -2612,66 +2692,6 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
   }
 }
 
-// RJ residuals in one pass over the rows (the sums of wave_residual, RJ at a
-// time); the lanes of the first RJ bits of jm (v_l: the lane's ratio) receive
-// theirs in e_l, and the bits are cleared.  The R64 trees are folded: at each
-// level two trees trade halves and go on as one, the lower one on the lower
-// lanes, so the adds and their pairing are those of RJ separate trees.
-__device__ __forceinline__ double fold32(double a, double b, bool wide) {
-  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
-  const auto l = wide ? __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false)
-                      : __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
-  const auto h = wide ? __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false)
-                      : __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-  return __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0])) +
-         __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
-}
-__device__ __forceinline__ double add_down(double p, int d) {
-  const uint64_t b = (uint64_t)__double_as_longlong(p);
-  return p + __longlong_as_double((long long)(((uint64_t)xdown32((uint32_t)(b >> 32), d) << 32) | xdown32((uint32_t)b, d)));
-}
-template <int RJ, class LdJ, class LdK>
-__device__ __forceinline__ void run_jobs(const SegIO &s, LdJ ldj, LdK ldk, uint64_t &jm, double v_l, double &e_l) {
-  const uint64_t all = jm;
-  double jv[RJ], p[RJ];
-#pragma unroll
-  for (int r = 0; r < RJ; ++r) {
-    jv[r] = jm ? readlane_dbl(v_l, __builtin_ctzll(jm)) : 0.0;
-    jm &= jm ? jm - 1 : 0;
-    p[r] = 0.0;
-  }
-  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
-#pragma unroll
-    for (int r = 0; r < RJ; ++r) {
-      const double prod = jv[r] * a;
-      const double d = b - prod;
-      p[r] = p[r] + fabs(d);
-    }
-  });
-  double x;
-  int src;                                         // where job i ends: its bits on lane bits 5, 4 (, 3)
-  const int i = lanes_below(all);
-  if constexpr (RJ > 4) {
-    auto at = [&](int r) { return r < RJ ? p[r] : 0.0; };
-    const double q0 = fold32(fold32(p[0], p[4], true), fold32(p[2], at(6), true), false);
-    const double q1 = fold32(fold32(p[1], at(5), true), fold32(p[3], at(7), true), false);
-    const bool up = (threadIdx.x & 8) != 0;
-    const double keep = up ? q1 : q0, send = up ? q0 : q1;
-    const uint64_t sb = (uint64_t)__double_as_longlong(send);
-    x = keep + __longlong_as_double((long long)(((uint64_t)xswap32((uint32_t)(sb >> 32), 8) << 32) | xswap32((uint32_t)sb, 8)));
-    src = ((i & 4) << 3) | ((i & 2) << 3) | ((i & 1) << 3);
-  } else if constexpr (RJ > 2) {
-    x = add_down(fold32(fold32(p[0], p[2], true), fold32(p[1], p[3], true), false), 8);
-    src = ((i & 2) << 4) | ((i & 1) << 4);
-  } else {
-    x = add_down(add_down(fold32(p[0], p[1], true), 16), 8);
-    src = (i & 1) << 5;
-  }
-  x = add_down(add_down(add_down(x, 4), 2), 1);
-  const double got = __shfl(x, src);
-  if (((all >> (threadIdx.x & 63)) & 1ull) && i < RJ) e_l = got;
-}
-
 // Several penalties per problem: every live segment, one wave per segment, a
 // penalty per lane in groups of 64.  Bound by VALU issue too: the window pass
 // and the sort once per segment, then a residual per distinct row (7 of 64
@@ -2757,15 +2777,8 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
             int prv = __shfl_up(row, 1);
             if (lane == 0) prv = prev_row;
             const uint64_t needm = __ballot(row >= 0 && row != prv);
-            uint64_t jm = needm;
             double e_l = 0.0;
-            while (jm) {
-              const int c = __builtin_popcountll(jm);
-              if (c > 6) run_jobs<8>(s, ldj, ldk, jm, v, e_l);
-              else if (c > 4) run_jobs<6>(s, ldj, ldk, jm, v, e_l);
-              else if (c > 2) run_jobs<4>(s, ldj, ldk, jm, v, e_l);
-              else run_jobs<2>(s, ldj, ldk, jm, v, e_l);
-            }
+            run_all_jobs(s, ldj, ldk, needm, v, e_l);
             // each target takes the e of the last job at or before it (or the
             // previous group's last e when its row continues from there)
             const uint64_t upto = needm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));

@@ -74,6 +74,17 @@ def test_work_list_forms(ctx, m, left):
         _path_equal(_host(got[0]), r, (m, left, "batch"))
 
 
+# residuals of one to eight distinct solutions per pass over the rows, a second
+# pass, a second group of penalties
+@pytest.mark.parametrize("L", [2, 3, 5, 7, 9, 17, 64, 65, 128])
+def test_residuals_per_pass(ctx, L):
+    from paper_2402_16712_amd import binding as B
+    print(f"case residuals penalties {L}", flush=True)
+    X = wl.accuracy_matrix(333, 9, L)[0] * 2.0 ** 320
+    lams = wl.log_lambdas(wl.max_column_mass(X), L, -2.0)
+    _path_equal(_host(ctx.fit_path(B.device_matrix(X), lams)), O.fit_path(X, lams), L)
+
+
 # 552 segments are fewer than the chip's wave slots, so they take about as long
 # as the slowest of them alone, here of eight pairs of columns at the same
 # penalties (one after the other in 24 waves they took 23 times an average one;
