@@ -1061,14 +1061,32 @@ __device__ __forceinline__ bool window_midpoint(const uint64_t *smp, uint64_t pl
   return mid > plo;
 }
 
-// The side of the minimiser of segment (j, k) at penalty lam from the sign
-// sums dz = (D_jk, Zr_jk): 0 when 0 minimises g_jk, 1 negative, 2 positive,
-// 3 undecided (the exact pass decides).  Decision margin 2^-32 (W_j + lam):
-// far above the rounding error of the sign sums (at most ~n 2^-52 of W_j,
-// plus n 2^-1022 should the matrix unit flush subnormal terms: hence the
-// floor on the margin).  unc: the sums cannot be trusted for this segment.
-__device__ __forceinline__ int sign_sum_side(double2 dz, double lam, double Wj, bool unc) {
-  const double M = 0x1p-32 * (Wj + lam);
+// 2^e0 when column j's weights are whole multiples of it with a sum below 2^50
+// of them (whole numbers), else 0.  Every FP64 sum of such weights is exact, and
+// a weight sum compared with a penalty is an integer compared with a real: the
+// outcome is the one of the integer part, or of anything up to the next integer.
+__device__ __forceinline__ double whole_unit(const ColInfo &cj) {
+  return cj.bemin >= 1023 - 300 && cj.wfix < ((u128)1 << 50) ? ldexp(1.0, cj.e0) : 0.0;
+}
+// The penalty to compare with: of a column with a unit the middle between two
+// whole ones, a quarter of a unit from the target of every prefix weight and
+// half from the sides' sums, so that neither ties (count data at whole penalties
+// tie in most segments, which the exact kernel then had).  From 2^50 units on a
+// penalty is above every weight sum as it is.
+__device__ __forceinline__ double between_units(double lam, double unit, int e0) {
+  const double l = ldexp(lam, -e0);
+  return unit > 0.0 && l < 0x1p50 ? (floor(l) + 0.5) * unit : lam;
+}
+
+// The side of the minimiser of segment (j, k) at penalty lam (between_units)
+// from the sign sums dz = (D_jk, Zr_jk): 0 when 0 minimises g_jk, 1 negative, 2
+// positive, 3 undecided (the exact pass decides).  Decision margin 2^-32 (W_j +
+// lam): far above the rounding error of the sign sums (at most ~n 2^-52 of W_j,
+// plus n 2^-1022 should the matrix unit flush subnormal terms: hence the floor
+// on the margin); with a unit the sums are exact and an eighth of it will do.
+// unc: the sums cannot be trusted for this segment.
+__device__ __forceinline__ int sign_sum_side(double2 dz, double lam, double Wj, double unit, bool unc) {
+  const double M = unit > 0.0 ? 0.125 * unit : 0x1p-32 * (Wj + lam);
   const double d1 = lam + dz.y + dz.x;               // >= 0  <=>  2A <= W + lambda
   const double d2 = lam + dz.y - dz.x;               // >= 0  <=>  W <= 2B + lambda
   if (unc || !(M >= 0x1p-1000)) return 3;
@@ -1076,24 +1094,6 @@ __device__ __forceinline__ int sign_sum_side(double2 dz, double lam, double Wj, 
   if (d1 < -M) return 1;
   if (d2 < -M) return 2;
   return 3;
-}
-
-// 2^e0 when column j's weights and the penalty are whole multiples of it with
-// sums below 2^50 of them (whole numbers): then every FP64 sum of weights is
-// exact, and so is a comparison of one with the target; else 0.
-__device__ __forceinline__ double whole_unit(const ColInfo &cj, double lam) {
-  const double l = ldexp(lam, -cj.e0);
-  const bool ok = cj.bemin >= 1023 - 300 && cj.wfix < ((u128)1 << 50) && l < 0x1p50 && floor(l) == l;
-  return ok ? ldexp(1.0, cj.e0) : 0.0;
-}
-// sign_sum_side, and where its margin leaves the side open the exact sums'
-// answer if they are exact (count data tie at whole penalties: without it every
-// such segment took the exact kernel).
-__device__ __forceinline__ int sign_sum_side(const ColInfo &cj, double2 dz, double lam, bool unc) {
-  const int side = sign_sum_side(dz, lam, cj.W, unc);
-  if (side != 3 || unc || !(whole_unit(cj, lam) > 0.0)) return side;
-  const double d1 = lam + dz.y + dz.x, d2 = lam + dz.y - dz.x;
-  return d1 >= 0.0 && d2 >= 0.0 ? 0 : d1 < 0.0 ? 1 : 2;
 }
 
 // The sign sums cannot decide segment (j, k) when a ratio could underflow to
@@ -1105,7 +1105,7 @@ __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInf
 
 // Segments settled by the sign sums alone.  One thread per pair (j, k), one
 // wave per 64 consecutive k of a preserved column: where every penalty of the
-// problem has 0 as a minimiser (sign_sum_side, the segment kernel's own test),
+// problem has 0 as a minimiser (sign_sum_side, the segment kernels' own test),
 // sets bit k & 63 of mask word (jj, k >> 6); the segment kernel skips such
 // segments.  They have v_k = 0, e_jk = the R64 mass of column k and row -1 for
 // every penalty: written here for a problem of one penalty (Algorithm 2 reads
@@ -1149,8 +1149,10 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
     if (!cj.flags && !ck.flags) {
       const bool unc = sign_sums_unsure(cj, ck, dz);
       const double *lam = lam_all + d.lam_off;
+      const double unit = whole_unit(cj);
       skip = true;
-      for (int t = 0; t < d.L && skip; ++t) skip = sign_sum_side(cj, dz, lam[t], unc) == 0;
+      for (int t = 0; t < d.L && skip; ++t)
+        skip = sign_sum_side(dz, between_units(lam[t], unit, cj.e0), cj.W, unit, unc) == 0;
       if (skip && d.L == 1) {
         const long long base = d.ws_off + (long long)j * d.m + k;
         V[base] = 0.0;
@@ -1224,6 +1226,10 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 // else is unsettled leave the segment to k_seg_rest, which is exact.
 constexpr int FAST_CAP = 512;       // rows a window may list
 constexpr double FAST_ZERO = 0x1p-700, FAST_OPEN = 0x1p700;   // next to 0, beyond every ratio
+
+// what two weight sums of column j may be off in a comparison; with a unit all
+// are exact and differ from every target by a quarter of it at least
+__device__ __forceinline__ double segment_tol(double Wj, double unit) { return unit > 0.0 ? 0.125 * unit : 0x1p-38 * Wj; }
 
 struct FastScratch {
   uint32_t list[FAST_CAP];          // row, then row | bin << 16
@@ -1489,7 +1495,8 @@ __device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, in
   return FAST_UNSURE;
 }
 
-// The minimiser of segment s at one penalty, on side neg; sa, sb: the sorted
+// The minimiser of segment s at one penalty (between_units), on side neg; tol:
+// what a comparison of weight sums may be off (segment_tol); sa, sb: the sorted
 // sample (top 32 bits of the keys; index 2 l + c in lane l), c0 the target's
 // expected place in it.  false: unsettled.
 // The window starts WDELTA of the weight either side of the target's place
@@ -1500,13 +1507,8 @@ __device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, in
 // (from about 26000 rows) at quarters of its range.
 template <class LdJ, class LdK>
 __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool neg, double lam, double Wd,
-                                         double unit, uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
+                                         double tol, uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
   constexpr double WDELTA = 0.06;
-  // unit > 0 (whole_unit): the prefix weights are multiples of it and the
-  // target of half of it, so a quarter of a unit settles a tie as the exact
-  // path does (negative side: the first prefix above the target; positive: the
-  // first at or above it) and leaves nothing closer than that
-  const double tol = unit > 0.0 ? 0.125 * unit : 0x1p-38 * Wd, shift = neg ? 0.25 * unit : -0.25 * unit;
   // sample values with low bits no simple fraction has: a ratio equal to a
   // bound cannot be settled here
   auto value = [&](int ix) {
@@ -1520,7 +1522,7 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
   auto bound = [&](int ix) {
     return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix);
   };
-  auto target = [&](double T) { return 0.5 * (neg ? T + lam : T - lam) + shift; };
+  auto target = [&](double T) { return 0.5 * (neg ? T + lam : T - lam); };
   double c = c0;
   int il = max((int)floor(c - WDELTA * SAMPLE_ROWS) - 1, lmin), ir = min((int)ceil(c + WDELTA * SAMPLE_ROWS), rmax);
   if (neg) il = max(min(il, rmax - 3), lmin);
@@ -1796,14 +1798,14 @@ __device__ __forceinline__ bool sort_listed(const SegIO &s, PathScratch *ps, int
 }
 
 // The minimisers of segment s for the penalties of the lanes with act (lam the
-// lane's penalty, c its target's expected place in the sample sa, sb); v and
+// lane's penalty, between_units; tol as in fast_one; c its target's expected
+// place in the sample sa, sb); v and
 // row on those lanes.  false: some target is unsettled.
 template <class LdJ, class LdK>
-__device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool neg, bool act, double lam, double Wd,
+__device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool neg, bool act, double lam, const double &tol,
                                           uint32_t sa, uint32_t sb, double c, PathScratch *ps, double &v, int &row) {
   constexpr double WDELTA = 0.06;
   const int lane = s.lane;
-  const double tol = 0x1p-38 * Wd;
   auto value = [&](int ix) {
     const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1);
     return ratio_of_key(((uint64_t)p << 32) | 0x9E3779B1u);
@@ -2043,7 +2045,7 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
     const int t = g0 + lane;
     const bool in = t < L;
     int side = 0;
-    if (in) side = sign_sum_side(dz, lam[t], Wd, unc);
+    if (in) side = sign_sum_side(dz, lam[t], Wd, 0.0, unc);
     if (__ballot(side == 3)) {
       if (!have_exact) {
         ex = exact_sides(s);
@@ -2632,11 +2634,11 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     const unsigned short *sm = smp + (long long)(d.col_off + j) * SAMPLE_ROWS;
     const int sr0 = sm[lane], sr1 = sm[64 + lane];
     const double sv0 = __builtin_amdgcn_rcp(sxj[sr0]), sv1 = __builtin_amdgcn_rcp(sxj[sr1]);
-    const double lam = lam_all[d.lam_off], Wd = cj.W;
+    const double Wd = cj.W, unit = whole_unit(cj), tol = segment_tol(Wd, unit);
+    const double lam = between_units(lam_all[d.lam_off], unit, cj.e0);
     // the targets' places in the sample
     const double cneg = 0.5 * SAMPLE_ROWS * (Wd + lam) / Wd, cpos = 0.5 * SAMPLE_ROWS * (Wd - lam) / Wd;
     const bool fast_j = !cj.flags && fast_columns(cj);
-    const double unit = whole_unit(cj, lam);
     const double2 *DZj = DZ + d.pair_off + (long long)j * m;
     // claims are taken one segment ahead, and the next segment's sign sums and
     // sample are loaded before the current one's residual
@@ -2657,7 +2659,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
         v = k == j ? 1.0 : __longlong_as_double(0x7ff8000000000000ll);
         e = 0.0;
       } else {
-        const int side = sign_sum_side(cj, dz, lam, sign_sums_unsure(cj, ck, dz));
+        const int side = sign_sum_side(dz, lam, Wd, unit, sign_sums_unsure(cj, ck, dz));
         left = side == 3 || (side != 0 && !(fast_j && fast_columns(ck)));
         if (side != 0 && !left) {
           const bool neg = side == 1;
@@ -2666,7 +2668,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
           const __amdgpu_buffer_rsrc_t rk = col_rsrc(s.xk, n), rj = col_rsrc(kLdsJ ? s.xk : s.sxj, n);
           auto ldj = [&](int i) { return sxj_pad(s, rj, i); };
           auto ldk = [&](int i) { return col_ld(rk, i * 8); };
-          left = !fast_one(s, ldj, ldk, neg, lam, Wd, unit, sx[0], sx[1], neg ? cneg : cpos, fs, v, row);
+          left = !fast_one(s, ldj, ldk, neg, lam, Wd, tol, sx[0], sx[1], neg ? cneg : cpos, fs, v, row);
         }
       }
       const long long base = d.ws_off + (long long)j * m + k;
@@ -2705,6 +2707,7 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
            int sxj_rows) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ int s_item, knext;
+  __shared__ double s_unit, s_tol;
   if (gate && *gate != gate_on) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double *sxj_lds = (double *)smem;
@@ -2720,7 +2723,11 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     if constexpr (kLdsJ)
       for (int i = threadIdx.x; i < T * 64; i += blockDim.x) sxj_lds[i] = i < n ? xjg[i] : 0.0;
     const double *__restrict__ sxj = kLdsJ ? (const double *)sxj_lds : xjg;
-    if (threadIdx.x == 0) knext = 0;
+    if (threadIdx.x == 0) {
+      knext = 0;
+      s_unit = whole_unit(cj);
+      s_tol = segment_tol(cj.W, whole_unit(cj));
+    }
     __syncthreads();
     const long long word0 = d.mask_off + (long long)jj * ((m + 63) >> 6), mm = (long long)m * m;
     const LiveSegs segs(segmask + word0, it.kbeg, it.kend, lane);
@@ -2752,10 +2759,10 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
       auto ldk = [&](int i) { return col_ld(rk, i * 8); };
       for (int t0 = 0; t0 < L && !left; t0 += 64) {
         const int t = t0 + lane;
-        const double lam = t < L ? lams[t] : 0.0;
+        const double unit = s_unit, lam = between_units(t < L ? lams[t] : 0.0, unit, cj.e0);
         double v = plain ? (k == j ? 1.0 : __longlong_as_double(0x7ff8000000000000ll)) : 0.0, e = plain ? 0.0 : ck.W;
         int row = -1;
-        const int side = t < L && !plain ? sign_sum_side(dz, lam, Wd, unc) : 0;
+        const int side = t < L && !plain ? sign_sum_side(dz, lam, Wd, unit, unc) : 0;
         const uint64_t nz = __ballot(side != 0);
         left = __ballot(side == 3) != 0 || (nz && !(fast_j && fast_columns(ck)));
         if (nz && !left) {
@@ -2770,7 +2777,7 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
             sorted = true;
           }
           const double u = 0.5 * SAMPLE_ROWS * lam / Wd;
-          left = !fast_path(s, ldj, ldk, neg, side != 0, lam, Wd, sa, sb, 0.5 * SAMPLE_ROWS + (neg ? u : -u), ps, v, row);
+          left = !fast_path(s, ldj, ldk, neg, side != 0, lam, s_tol, sa, sb, 0.5 * SAMPLE_ROWS + (neg ? u : -u), ps, v, row);
           if (!left) {
             // residuals, reused while the selected row repeats: the targets whose
             // row differs from the previous target's are the jobs

@@ -688,7 +688,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
     return seg_sxj_bytes(sxj_rows) + waves * (multi ? sizeof(PathScratch) : sizeof(FastScratch));
   };
   auto waves_per_cu = [&](int waves) {
-    const size_t granules = (lds_of(waves) + 16 + 511) / 512 * 512;   // + static LDS
+    const size_t granules = (lds_of(waves) + 32 + 511) / 512 * 512;   // + static LDS
     return std::min<int>(16, waves * (int)((size_t)160 * 1024 / granules));
   };
   const int seg_waves = sxj_rows == 0 || waves_per_cu(8) > waves_per_cu(4) ? 8 : 4;

@@ -102,3 +102,52 @@ def test_few_segments_run_at_once(ctx, L):
         two = max(two, _segment_ms(ctx, lambda: ctx.fit_path(Xq, lams)))
     print(f"  552 segments {1e3 * many:.1f} us, 2 segments {1e3 * two:.1f} us", flush=True)
     assert many < 4.0 * two
+
+
+def _correlated_counts(n, m, seed):
+    g = np.random.default_rng(seed)
+    scale = 0.6 * g.standard_normal(n)[:, None] + 0.6 * g.standard_normal(m)[None, :]
+    return np.asfortranarray(np.minimum(np.floor(np.exp(scale) * 2.0 * g.random((n, m))), 60.0))
+
+
+# whole numbers at whole penalties, where most targets tie with a prefix weight,
+# take the route of the same numbers at penalties between whole ones (through
+# the exact kernel they took 6 and 90 times as long; twice is another target's row)
+@pytest.mark.parametrize("data", ["counts", "binary"])
+def test_ties_at_several_penalties(ctx, data):
+    from paper_2402_16712_amd import binding as B
+    print(f"case ties at penalties {data}", flush=True)
+    X = _correlated_counts(3000, 60, 5)
+    if data == "binary":
+        X = np.minimum(X, 1.0)
+    whole = np.unique(np.round(wl.log_lambdas(wl.max_column_mass(X), 8, -3.0)))
+    Xd = B.device_matrix(X)
+    a, b = (_segment_ms(ctx, lambda lam=lam: ctx.fit_path(Xd, lam)) for lam in (whole, whole + 0.375))
+    print(f"  8 whole penalties {1e3 * a:.1f} us, between them {1e3 * b:.1f} us", flush=True)
+    assert a < 2.0 * b
+    _path_equal(_host(ctx.fit_path(Xd, whole)), O.fit_path(X, whole), data)
+
+
+# the edges of the unit: column sums just below and above 2^50 of them, units far
+# from 1, penalties that vanish next to the unit, lie between two, or exceed all
+@pytest.mark.parametrize("top", [2.0 ** 3, 2.0 ** 38, 2.0 ** 42])
+@pytest.mark.parametrize("unit", [1.0, 2.0 ** -250, 2.0 ** 200])
+def test_unit_edges(ctx, top, unit):
+    from paper_2402_16712_amd import binding as B
+    print(f"case unit edges {top} {unit}", flush=True)
+    g = np.random.default_rng(int(np.log2(top)))
+    u = g.standard_normal(1100)
+    X = np.round((np.outer(u, g.standard_normal(8)) + 0.3 * g.standard_normal((1100, 8))) * top / 4.0)
+    X[:, 3] = X[:, 1]
+    X[::2, 3] += 1.0
+    X[:, 6] = np.sign(X[:, 6])
+    X[:, 7] = 0.0
+    X = np.asfortranarray(X * unit)
+    big = wl.max_column_mass(X)
+    lams = np.concatenate([unit * np.array([1e-300, 0.25, 0.5, 1.0, 1.75, 3.0, 300.0, 300.5]), [0.0, 1e-307, 1e300],
+                           unit * np.round(np.array([0.03, 0.2, 0.7]) * big / unit), [big]])
+    Xd = B.device_matrix(X)
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (top, unit))
+    for lam in lams:
+        got = ctx.fit_batch([(Xd, np.array([lam]))])
+        _path_equal(_host(got[0]), O.fit_path(X, [lam]), (top, unit, lam))
