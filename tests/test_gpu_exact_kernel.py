@@ -112,7 +112,7 @@ def _correlated_counts(n, m, seed):
 
 # whole numbers at whole penalties, where most targets tie with a prefix weight,
 # take the route of the same numbers at penalties between whole ones (through
-# the exact kernel they took 6 and 90 times as long; twice is another target's row)
+# the exact kernel they took 22 and 200 times as long)
 @pytest.mark.parametrize("data", ["counts", "binary"])
 def test_ties_at_several_penalties(ctx, data):
     from paper_2402_16712_amd import binding as B
@@ -151,3 +151,35 @@ def test_unit_edges(ctx, top, unit):
     for lam in lams:
         got = ctx.fit_batch([(Xd, np.array([lam]))])
         _path_equal(_host(got[0]), O.fit_path(X, [lam]), (top, unit, lam))
+
+
+def _decimals(n, m, seed, places=1):
+    return np.round(wl.accuracy_matrix(n, m, seed)[0], places)
+
+
+# decimal fractions: ratios that differ in the last bits only, and equal ones, in
+# lists of every length of the sort
+@pytest.mark.parametrize("n", [90, 300, 700, 1500, 3300, 6000])
+@pytest.mark.parametrize("places", [0, 1, 2])
+def test_ratios_that_nearly_tie(ctx, n, places):
+    from paper_2402_16712_amd import binding as B
+    print(f"case near ties {n} places {places}", flush=True)
+    X = _decimals(n, 10, n, places)
+    X[:, 4] = 0.7 * X[:, 2]
+    X[:, 8] = np.round(X[:, 2] / 3.0, places) * 3.0
+    lams = wl.log_lambdas(wl.max_column_mass(X), 12, -3.0)
+    lams[5] = np.round(lams[5])
+    _path_equal(_host(ctx.fit_path(B.device_matrix(X), lams)), O.fit_path(X, lams), (n, places))
+
+
+# rounded to one decimal, data take at most the five sorts more of their lists
+# (through the exact kernel they took 13 times as long as unrounded)
+def test_near_ties_stay_out_of_the_exact_kernel(ctx):
+    from paper_2402_16712_amd import binding as B
+    print("case near ties time", flush=True)
+    X = wl.accuracy_matrix(1000, 100, 6)[0]
+    lams = wl.log_lambdas(wl.max_column_mass(X), 16, -3.0)
+    Xr, Xd = B.device_matrix(np.round(X, 1)), B.device_matrix(X)
+    a, b = (_segment_ms(ctx, lambda A=A: ctx.fit_path(A, lams)) for A in (Xr, Xd))
+    print(f"  rounded {1e3 * a:.1f} us, unrounded {1e3 * b:.1f} us", flush=True)
+    assert a < 5.0 * b
