@@ -139,7 +139,7 @@ k_bp_count(const double *__restrict__ X, int n, int m, long long ld, const ColIn
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, z0 = 0.0, z1 = 0.0, z2 = 0.0;
     int nin = 0;
     const ColInfo ck = ci[k];
-    const bool quick = fast_columns(cj) && fast_columns(ck);
+    const bool quick = FastRange(cj, true).has(ck);
     if (quick) {
       // no division per row: the sign of b - t a is exact (see window_pass).
       // a0.. sum the ratios below 0 (neg) or at or below it, the rows between

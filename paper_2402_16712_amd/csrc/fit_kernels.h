@@ -1012,15 +1012,21 @@ __host__ __device__ constexpr size_t rest_wave_bytes(int L, int lcap) {
   return (size_t)L * 16 + sizeof(WaveScratch) + (size_t)lcap * (sizeof(uint64_t) + sizeof(unsigned short));
 }
 
-
-// The division-free path takes columns whose nonzero magnitudes all lie in
-// [2^-300, 2^300]: then the ratios and the products with a window bound stay
-// normal.
-constexpr int FAST_BEXP_LO = 1023 - 300, FAST_BEXP_HI = 1023 + 300;
-
-__device__ __forceinline__ bool fast_columns(const ColInfo &c) {
-  return c.nnz == 0 || (c.bemin >= FAST_BEXP_LO && c.bemax <= FAST_BEXP_HI);
-}
+// The division-free path takes the columns k whose nonzero magnitudes keep every
+// ratio to column j in 2^+-981 (normal, and between FAST_ZERO and FAST_OPEN);
+// column j in 2^+-901, so that its sums and 2^-38 of them are normal too.  The
+// exponents of column k that it takes with column j: none if !ok.
+constexpr int FAST_RATIO = 980, FAST_COLUMN = 900;
+struct FastRange {
+  int lo, hi;
+  __device__ __forceinline__ FastRange(const ColInfo &cj, bool ok) {
+    ok = ok && (cj.nnz == 0 || (cj.bemin >= 1023 - FAST_COLUMN && cj.bemax <= 1023 + FAST_COLUMN));
+    lo = ok ? max(1, cj.bemax - FAST_RATIO) : 1 << 20;
+    hi = cj.bemin + FAST_RATIO;
+  }
+  // (an empty column k: bemin 4096, bemax -1)
+  __device__ __forceinline__ bool has(const ColInfo &ck) const { return ck.bemin >= lo && ck.bemax <= hi; }
+};
 
 // Probe point of a window (plo, phi] that holds more elements than the
 // list: the middle one of the sample keys inside it, or with none inside the
@@ -1202,8 +1208,8 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 // ------------------------------------------------- division-free segments
 // One segment (j, k) at one penalty by one wave, without a division per row
 // and without a sort.  With a = x_ij, b = x_ik the sign of the fused d =
-// fma(-t, a, b) is the exact sign of b - t a (a and b zero or in [2^-300,
-// 2^300], |t| zero-like 2^-700 or more: no underflow), so it says on which
+// fma(-t, a, b) is the exact sign of b - t a (one rounding of the exact value,
+// which keeps its sign when it overflows or underflows), so it says on which
 // side of t the ratio b / a lies: below where d and a differ in sign.
 //  window_pass  over the rows: T = sum of |a| sgn(b/a - lo) (a with its sign
 //               flipped by d's: no comparison, no select), which is W - 2 S
@@ -1225,7 +1231,7 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 // rounded ratio meets the bound may be on either side of it) and whatever
 // else is unsettled leave the segment to k_seg_rest, which is exact.
 constexpr int FAST_CAP = 512;       // rows a window may list
-constexpr double FAST_ZERO = 0x1p-700, FAST_OPEN = 0x1p700;   // next to 0, beyond every ratio
+constexpr double FAST_ZERO = 0x1p-1000, FAST_OPEN = 0x1p1000;   // next to 0, beyond every ratio
 
 // what two weight sums of column j may be off in a comparison; with a unit all
 // are exact and differ from every target by a quarter of it at least
@@ -2334,7 +2340,7 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
     // residuals, reused while the selected row repeats: the group's targets
     // whose row differs from the previous target's are the jobs, scored up to
     // eight at a time in one pass over the rows (2000 x 1000
-    // outside 2^+-300 with 16 penalties 19.5 ms a pass each, now 17.1); one job,
+    // through this kernel with 16 penalties 19.5 ms a pass each, now 17.1); one job,
     // or an infinite ratio, takes a pass of its own
     const int tend = min(L, 64 * g + 64);
     const int cnt = tend - 64 * g;
@@ -2636,7 +2642,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     const double lam = between_units(lam_all[d.lam_off], unit, cj.e0);
     // the targets' places in the sample
     const double cneg = 0.5 * SAMPLE_ROWS * (Wd + lam) / Wd, cpos = 0.5 * SAMPLE_ROWS * (Wd - lam) / Wd;
-    const bool fast_j = !cj.flags && fast_columns(cj);
+    const FastRange fast(cj, !cj.flags);
     const double2 *DZj = DZ + d.pair_off + (long long)j * m;
     // claims are taken one segment ahead, and the next segment's sign sums and
     // sample are loaded before the current one's residual
@@ -2658,7 +2664,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
         e = 0.0;
       } else {
         const int side = sign_sum_side(dz, lam, Wd, unit, sign_sums_unsure(cj, ck, dz));
-        left = side == 3 || (side != 0 && !(fast_j && fast_columns(ck)));
+        left = side == 3 || (side != 0 && !fast.has(ck));
         if (side != 0 && !left) {
           const bool neg = side == 1;
           uint32_t sx[2] = {(uint32_t)(key_of(b0 * sv0 + 0.0) >> 32), (uint32_t)(key_of(b1 * sv1 + 0.0) >> 32)};
@@ -2734,7 +2740,7 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     const double sv0 = __builtin_amdgcn_rcp(sxj[sr0]), sv1 = __builtin_amdgcn_rcp(sxj[sr1]);
     const double *lams = lam_all + d.lam_off;
     const double Wd = cj.W;
-    const bool fast_j = !cj.flags && fast_columns(cj);
+    const FastRange fast(cj, !cj.flags);
     const double2 *DZj = DZ + d.pair_off + (long long)j * m;
     int claim = 0;
     if (lane == 0) claim = atomicAdd(&knext, 1);
@@ -2762,7 +2768,7 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
         int row = -1;
         const int side = t < L && !plain ? sign_sum_side(dz, lam, Wd, unit, unc) : 0;
         const uint64_t nz = __ballot(side != 0);
-        left = __ballot(side == 3) != 0 || (nz && !(fast_j && fast_columns(ck)));
+        left = __ballot(side == 3) != 0 || (nz && !fast.has(ck));
         if (nz && !left) {
           // (every penalty of a segment has the minimiser on the same side)
           const bool neg = __builtin_amdgcn_readlane(side, __builtin_ctzll(nz)) == 1;

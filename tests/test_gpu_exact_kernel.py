@@ -65,7 +65,7 @@ def test_work_list_forms(ctx, m, left):
     print(f"case work list {m} left {left}", flush=True)
     X = _matrix(70, m, left)
     big = wl.max_column_mass(X)
-    X[:, np.random.default_rng(m).permutation(m)[:left]] *= 2.0 ** 320
+    X[:, np.random.default_rng(m).permutation(m)[:left]] *= 2.0 ** 990
     Xd = B.device_matrix(X)
     for lams in (np.array([0.05 * big]), np.array([0.0, 0.02 * big, 0.3 * big])):
         r = O.fit_path(X, lams)
@@ -80,7 +80,7 @@ def test_work_list_forms(ctx, m, left):
 def test_residuals_per_pass(ctx, L):
     from paper_2402_16712_amd import binding as B
     print(f"case residuals penalties {L}", flush=True)
-    X = wl.accuracy_matrix(333, 9, L)[0] * 2.0 ** 320
+    X = wl.accuracy_matrix(333, 9, L)[0] * 2.0 ** 950
     lams = wl.log_lambdas(wl.max_column_mass(X), L, -2.0)
     _path_equal(_host(ctx.fit_path(B.device_matrix(X), lams)), O.fit_path(X, lams), L)
 
@@ -93,7 +93,7 @@ def test_residuals_per_pass(ctx, L):
 def test_few_segments_run_at_once(ctx, L):
     from paper_2402_16712_amd import binding as B
     print(f"case at once penalties {L}", flush=True)
-    X = wl.accuracy_matrix(5000, 24, 3)[0] * 2.0 ** 320      # (dense direction: every v_k is nonzero)
+    X = wl.accuracy_matrix(5000, 24, 3)[0] * 2.0 ** 950      # (dense direction: every v_k is nonzero)
     lams = 0.02 * wl.max_column_mass(X) * (1.0 + 0.3 * np.arange(L))
     Xd = B.device_matrix(X)
     many, two = _segment_ms(ctx, lambda: ctx.fit_path(Xd, lams)), 0.0
@@ -183,3 +183,71 @@ def test_near_ties_stay_out_of_the_exact_kernel(ctx):
     a, b = (_segment_ms(ctx, lambda A=A: ctx.fit_path(A, lams)) for A in (Xr, Xd))
     print(f"  rounded {1e3 * a:.1f} us, unrounded {1e3 * b:.1f} us", flush=True)
     assert a < 5.0 * b
+
+
+# columns up to the edges of the division-free range and past them, alone and
+# against each other: zeros of both signs, a column of one magnitude, subnormals
+@pytest.mark.parametrize("n", [70, 600, 4200])
+@pytest.mark.parametrize("scales", [(320, -420, 899, -880), (960, -960, 0, 500), (-885, -870, -200, -1040)])
+def test_column_ranges(ctx, n, scales):
+    from paper_2402_16712_amd import binding as B
+    print(f"case column ranges {n} {scales}", flush=True)
+    X = _matrix(n, 10, n)
+    X += np.outer(np.random.default_rng(n).standard_normal(n), np.linspace(-1.0, 1.0, 10))
+    X[:, 9] = np.sign(X[:, 9])
+    X[::4, 2] = 0.0
+    X[1::4, 2] = -0.0
+    X[::5, 6] = 0.0
+    for q, e in enumerate(scales):
+        X[:, 2 * q] = np.ldexp(X[:, 2 * q], e)
+        X[:, 2 * q + 1] = np.ldexp(X[:, 2 * q + 1], e)
+    X = np.asfortranarray(X)
+    Xd = B.device_matrix(X)
+    for lam in [0.0] + [0.03 * wl.max_column_mass(X[:, q:q + 1]) for q in (0, 3, 5, 9)]:
+        r = O.fit_path(X, [lam])
+        g = _host(ctx.fit_path(Xd, np.array([lam])))
+        if r["status"] != 0:                     # (a ratio that overflows is reported)
+            assert int(g["status"][0]) == r["status"]
+            continue
+        _path_equal(g, r, (n, scales, lam))
+    lams = np.sort([0.01 * wl.max_column_mass(X[:, q:q + 1]) for q in range(10)])
+    r, g = O.fit_path(X, lams), _host(ctx.fit_path(Xd, lams))
+    assert int(g["status"][0]) == r["status"]
+    if r["status"] == 0:
+        _path_equal(g, r, (n, scales, "path"))
+
+
+# a matrix scaled by a power of two has the same ratios and takes as long (by
+# the exact kernel, from 2^300 on, four to twenty times; twice leaves room for
+# the times' spread)
+@pytest.mark.parametrize("L", [1, 8])
+def test_scaled_matrix_takes_as_long(ctx, L):
+    from paper_2402_16712_amd import binding as B
+    print(f"case scaled penalties {L}", flush=True)
+    X = wl.accuracy_matrix(1500, 100, 8)[0]
+    lams = 0.02 * wl.max_column_mass(X) * (1.0 + 0.3 * np.arange(L))
+    X1, X2 = B.device_matrix(X), B.device_matrix(X * 2.0 ** 640)
+    a, b = _segment_ms(ctx, lambda: ctx.fit_path(X2, lams * 2.0 ** 640)), _segment_ms(ctx, lambda: ctx.fit_path(X1, lams))
+    print(f"  scaled {1e3 * a:.1f} us, unscaled {1e3 * b:.1f} us", flush=True)
+    assert a < 2.0 * b
+
+
+# breakpoint counts of pairs inside the division-free range and past it
+@pytest.mark.parametrize("n", [1, 65, 700, 2305])
+@pytest.mark.parametrize("e", [(320, -300), (490, -496), (950, 0), (-890, -905)])
+def test_breakpoint_ranges(ctx, n, e):
+    from paper_2402_16712_amd import binding as B
+    print(f"case breakpoint ranges {n} {e}", flush=True)
+    X = _matrix(n, 6, 40 + n)
+    X[:, 3] = -X[:, 2]
+    X[::7, 5] = 0.0
+    X[:, 1] = np.ldexp(X[:, 1], e[0])
+    X[:, 3] = np.ldexp(X[:, 3], e[0])
+    X[:, 4] = np.ldexp(X[:, 4], e[1])
+    X = np.asfortranarray(X)
+    g, r = _host(ctx.breakpoints(B.device_matrix(X))), O.breakpoints(X)
+    assert int(g["status"][0]) == 0
+    assert np.array_equal(g["offsets"], r["offsets"])
+    for key in ("lambda_max", "lam", "v"):
+        assert g[key].tobytes() == r[key].tobytes(), key
+    assert np.array_equal(g["row"], r["row"])
