@@ -1516,24 +1516,27 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
                                          double tol, uint32_t sa, uint32_t sb, double c0, FastScratch *fs, double &v, int &row) {
   constexpr double WDELTA = 0.06;
   // sample values with low bits no simple fraction has: a ratio equal to a
-  // bound cannot be settled here
-  auto value = [&](int ix) {
-    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1);
+  // bound cannot be settled here.  `out`: a step of the keys' top 32 bits, for
+  // bounds that have the sample's own row inside (a row that weighs more than
+  // the window lies between two equal samples: 434 x 291 of heavy tails took 4.7
+  // passes a segment, one now)
+  auto value = [&](int ix, int out) {
+    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1) + (uint32_t)out;
     return ratio_of_key(((uint64_t)p << 32) | 0x9E3779B1u);
   };
   // samples on the target's side: [first, last)
   const uint32_t kz = (uint32_t)(key_of(neg ? -FAST_ZERO : FAST_ZERO) >> 32);
   const int nb = __builtin_popcountll(__ballot(sa < kz)) + __builtin_popcountll(__ballot(sb < kz));
   const int lmin = neg ? -1 : nb - 1, rmax = neg ? nb : SAMPLE_ROWS;
-  auto bound = [&](int ix) {
-    return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix);
+  auto bound = [&](int ix, int out) {
+    return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix, out);
   };
   auto target = [&](double T) { return 0.5 * (neg ? T + lam : T - lam); };
   double c = c0;
   int il = max((int)floor(c - WDELTA * SAMPLE_ROWS) - 1, lmin), ir = min((int)ceil(c + WDELTA * SAMPLE_ROWS), rmax);
   if (neg) il = max(min(il, rmax - 3), lmin);
   else ir = min(max(ir, lmin + 3), rmax);
-  double lo = bound(il), hi = bound(ir);
+  double lo = bound(il, -1), hi = bound(ir, 1);
   double est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);   // rows the window may list
   for (int it = 0; it < 12; ++it) {
     if (est > 0.8 * FAST_CAP) {
@@ -1547,7 +1550,7 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
         ix[1] = mid;
         ix[2] = min(mid + h, ir - 1);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) t[q] = value(ix[q]);
+        for (int q = 0; q < 3; ++q) t[q] = value(ix[q], 0);
       } else {
 #pragma unroll
         for (int q = 0; q < 3; ++q) t[q] = lo + (hi - lo) * (0.25 * (q + 1));
@@ -1596,7 +1599,7 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
       hi = lo;
       ir = il;
       il = max(il - 12, lmin);
-      lo = bound(il);
+      lo = bound(il, -1);
       c = 0.5 * (il + ir);
       est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);
       continue;
@@ -1620,14 +1623,14 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
       }
       continue;
     }
-    const double blo = il <= lmin && neg ? value(0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1) : hi;
+    const double blo = il <= lmin && neg ? value(0, 0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1, 0) : hi;
     const int got = select_listed(s, fs, count, blo, bhi, D, tol, v, row);
     if (got == FAST_HIT) return v > lo && v < hi;
     if (got == FAST_UNSURE || ir >= rmax) return false;
     il = ir;
     lo = hi;
     ir = min(ir + 12, rmax);
-    hi = bound(ir);
+    hi = bound(ir, 1);
     c = 0.5 * (il + ir);
     est = (double)(ir - il) * s.n * (1.0 / SAMPLE_ROWS);
   }
@@ -1815,15 +1818,15 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
                                           uint32_t sa, uint32_t sb, double c, PathScratch *ps, double &v, int &row) {
   constexpr double WDELTA = 0.06;
   const int lane = s.lane;
-  auto value = [&](int ix) {
-    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1);
+  auto value = [&](int ix, int out) {
+    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)((ix & 1) ? sb : sa), ix >> 1) + (uint32_t)out;
     return ratio_of_key(((uint64_t)p << 32) | 0x9E3779B1u);
   };
   const uint32_t kz = (uint32_t)(key_of(neg ? -FAST_ZERO : FAST_ZERO) >> 32);
   const int nb = __builtin_popcountll(__ballot(sa < kz)) + __builtin_popcountll(__ballot(sb < kz));
   const int lmin = neg ? -1 : nb - 1, rmax = neg ? nb : SAMPLE_ROWS;
-  auto bound = [&](int ix) {
-    return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix);
+  auto bound = [&](int ix, int out) {
+    return ix <= lmin ? (neg ? -FAST_OPEN : FAST_ZERO) : ix >= rmax ? (neg ? -FAST_ZERO : FAST_OPEN) : value(ix, out);
   };
   const int cl = (int)floor(c - WDELTA * SAMPLE_ROWS) - 1, cr = (int)ceil(c + WDELTA * SAMPLE_ROWS);
   const double per = (double)s.n * (1.0 / SAMPLE_ROWS);   // rows a sample stands for
@@ -1832,7 +1835,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
   // [il, iend): what the pending targets' windows span
   int il = max(min(wave_min_int_x(act ? cl : SAMPLE_ROWS), neg ? rmax - 3 : SAMPLE_ROWS), lmin);
   int iend = min(max(wave_max_int_x(act ? cr : -1), neg ? -1 : lmin + 3), rmax);
-  double lo = bound(il);
+  double lo = bound(il, -1);
   int shrink = 0, start = il;
   bool jump = true;
   for (int it = 0; it < 160 && (pend | low); ++it) {
@@ -1845,22 +1848,22 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
       jump = false;
       iend = rmax;
       il = start = max(start - 13, lmin);
-      lo = bound(il);
+      lo = bound(il, -1);
       shrink = 0;
     }
     // the next window: [lo, hi), hi at sample ir or (shrink) inside a gap
     int ir = min(il + step, max(iend, il + 1));
     ir = min(ir, rmax);
     if (ir <= il) return false;
-    double hi = bound(ir);
+    double hi = bound(ir, 1);
     if (shrink > 0) {
       if ((ir - il) >> shrink) {
         ir = il + ((ir - il) >> shrink);
-        hi = bound(ir);
+        hi = bound(ir, 1);
       } else {
         // (not towards an open end)
         if (shrink > 12 || (neg ? il <= lmin : il + 1 >= rmax)) return false;
-        hi = lo + (bound(il + 1) - lo) * ldexp(1.0, -2 * shrink);
+        hi = lo + (bound(il + 1, 1) - lo) * ldexp(1.0, -2 * shrink);
         ir = il;                                   // (the window ends inside the gap)
       }
     }
@@ -1900,7 +1903,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
     low |= __ballot(mine && D < 0.0);
     pend &= ~low;
     if (pend && count > 0) {
-      const double blo = il <= lmin && neg ? value(0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1) : hi;
+      const double blo = il <= lmin && neg ? value(0, 0) : lo, bhi = ir >= rmax && !neg ? value(SAMPLE_ROWS - 1, 0) : hi;
       if (count <= 64) sort_listed<1>(s, ps, count, blo, bhi);
       else if (count <= 128) sort_listed<2>(s, ps, count, blo, bhi);
       else if (count <= 256) sort_listed<4>(s, ps, count, blo, bhi);
@@ -1932,7 +1935,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
       const int nx = min(wave_min_int_x(((pend >> lane) & 1ull) ? cl : SAMPLE_ROWS), rmax - 1);
       if (jump && nx > il) {
         il = nx;
-        lo = bound(il);
+        lo = bound(il, -1);
       }
       iend = max(iend, il + 12);
     }

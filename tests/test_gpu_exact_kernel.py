@@ -251,3 +251,22 @@ def test_breakpoint_ranges(ctx, n, e):
     for key in ("lambda_max", "lam", "v"):
         assert g[key].tobytes() == r[key].tobytes(), key
     assert np.array_equal(g["row"], r["row"])
+
+
+# a row that holds most of every column's weight is the solution of every segment
+# and lies between equal samples; a window that has it inside settles the segment
+# in one pass as any other (windows between the two samples missed it, and came
+# to it after several)
+@pytest.mark.parametrize("L", [1, 8])
+def test_heavy_row(ctx, L):
+    from paper_2402_16712_amd import binding as B
+    print(f"case heavy row penalties {L}", flush=True)
+    X = wl.accuracy_matrix(500, 200, 9)[0]
+    Y = X.copy()
+    Y[77] = 2.0 * np.abs(X).sum(axis=0) * np.where(X[77] < 0.0, -1.0, 1.0)
+    lx, ly = (0.02 * wl.max_column_mass(A) * (1.0 + 0.3 * np.arange(L)) for A in (X, Y))
+    Xd, Yd = B.device_matrix(X), B.device_matrix(Y)
+    a, b = _segment_ms(ctx, lambda: ctx.fit_path(Yd, ly)), _segment_ms(ctx, lambda: ctx.fit_path(Xd, lx))
+    print(f"  heavy {1e3 * a:.1f} us, without {1e3 * b:.1f} us", flush=True)
+    assert a < 1.5 * b
+    _path_equal(_host(ctx.fit_path(Yd, ly)), O.fit_path(Y, ly), L)
