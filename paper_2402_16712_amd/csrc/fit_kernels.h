@@ -1856,15 +1856,22 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
     ir = min(ir, rmax);
     if (ir <= il) return false;
     double hi = bound(ir, 1);
+    int again = 0;                                 // shrink of the next window if this one is listed
     if (shrink > 0) {
-      if ((ir - il) >> shrink) {
+      const int whole = 31 - __builtin_clz((unsigned)(ir - il));   // from here on one sample's gap
+      if (shrink <= whole) {
         ir = il + ((ir - il) >> shrink);
         hi = bound(ir, 1);
       } else {
-        // (not towards an open end)
-        if (shrink > 12 || (neg ? il <= lmin : il + 1 >= rmax)) return false;
-        hi = lo + (bound(il + 1, 1) - lo) * ldexp(1.0, -2 * shrink);
+        // a quarter of what is left of the gap, and so on (not towards an open
+        // end); the next window is the rest of it.  (A cut by what all shrinks
+        // had reached, and the shrinks again for each, settled 310 of 380
+        // segments of 5030 x 20 with 39 penalties in 24 passes each; now all
+        // in 5.6.)
+        if (shrink > whole + 12 || (neg ? il <= lmin : il + 1 >= rmax)) return false;
+        hi = lo + (bound(il + 1, 1) - lo) * ldexp(1.0, 2 * (whole - shrink));
         ir = il;                                   // (the window ends inside the gap)
+        again = whole;
       }
     }
     double T;
@@ -1927,7 +1934,7 @@ __device__ __forceinline__ bool fast_path(const SegIO &s, LdJ ldj, LdK ldk, bool
       pend &= ~__ballot(hit);
       wave_lds_sync();
     }
-    shrink = 0;
+    shrink = again;
     lo = hi;
     il = ir;
     if (pend) {

@@ -270,3 +270,27 @@ def test_heavy_row(ctx, L):
     print(f"  heavy {1e3 * a:.1f} us, without {1e3 * b:.1f} us", flush=True)
     assert a < 1.5 * b
     _path_equal(_host(ctx.fit_path(Yd, ly)), O.fit_path(Y, ly), L)
+
+
+# an outlier repeated in a tenth of the rows: most samples are equal, and most of
+# the other rows lie in the few gaps between them.  A gap's rows are listed in a
+# few parts, so the segments take a few times what they take with outliers that
+# differ (segments that ran out of windows took the exact kernel: 40 times)
+@pytest.mark.parametrize("L", [1, 16])
+def test_gaps_between_samples(ctx, L):
+    from paper_2402_16712_amd import binding as B
+    print(f"case gaps penalties {L}", flush=True)
+    n = 5030
+    g = np.random.default_rng(116)
+    X = 0.1 * g.laplace(size=(n, 24)) + np.outer(g.standard_normal(n), g.standard_normal(24) * (g.random(24) < 0.3))
+    rows = g.random(n) < 0.1
+    Y = X.copy()
+    X[rows] = 20.0 * g.standard_normal(24)
+    Y[rows] = 20.0 * g.standard_normal((rows.sum(), 24))
+    X, Y = np.asfortranarray(X), np.asfortranarray(Y)
+    lx, ly = (wl.max_column_mass(A) * (10.0 ** np.linspace(-4.0, -1.0, 16))[8 if L == 1 else 0:][:L] for A in (X, Y))
+    Xd, Yd = B.device_matrix(X), B.device_matrix(Y)
+    a, b = _segment_ms(ctx, lambda: ctx.fit_path(Xd, lx)), _segment_ms(ctx, lambda: ctx.fit_path(Yd, ly))
+    print(f"  1 outlier {1e3 * a:.1f} us, {rows.sum()} outliers {1e3 * b:.1f} us", flush=True)
+    assert a < 5.0 * b
+    _path_equal(_host(ctx.fit_path(Xd, lx)), O.fit_path(X, lx), L)
