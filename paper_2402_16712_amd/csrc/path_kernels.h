@@ -44,7 +44,7 @@
 constexpr int SP_TMAX = 4096;      // lambda tiles
 constexpr int SP_SAMPLES = 4096;   // breakpoints sampled to place them
 constexpr int SP_RG = 16;          // entries scored per pass over the rows
-constexpr int SP_CLAIM = 8;        // segments a wave of the residual kernel claims at a time
+constexpr int SP_CLAIM = 8;        // most segments a wave of the residual kernel claims at a time
 
 struct PathScale {
   int sE, sP;        // units of E and P: 2^sE, 2^sP
@@ -335,18 +335,22 @@ k_sp_resid(const double *__restrict__ X, int n, int m, long long ld, const long 
            double *__restrict__ segv, unsigned long long *__restrict__ gmax, int *__restrict__ next) {
   const int lane = threadIdx.x & 63;
   const XcdTiles tl(m, xcd_tile(n), blockDim.x >> 6);
+  const long long slots = min((tl.ntiles + 7) / 8 * tl.ts * tl.ts, (long long)m * m);   // of an XCD, at most
+  const int claim = (int)max(1ll, min((long long)SP_CLAIM, slots / (4 * tl.nwx)));
   double we = 0.0, wv = 0.0, wl = 0.0;   // the wave's maxima, one atomic each at the end
   for (int left = 0, fi = 0;; ++fi, --left) {
     // the XCD's next tile slots from its own counter (next[x], zero at
-    // launch), SP_CLAIM at a time: the waves of an XCD stay on neighbouring
+    // launch), up to SP_CLAIM at a time: the waves of an XCD stay on neighbouring
     // slots, whose columns share its L2, however long their segments.  One
     // counter takes an atomic every 0.1 us, which bound the kernel with one
-    // slot per claim (1000 x 501: 3.4 ms, now 1.6).
+    // slot per claim (1000 x 501: 3.4 ms, now 1.6).  Where the slots are fewer
+    // than four claims per wave, a claim takes less (a matrix of few columns left
+    // most waves without one: 2631 x 53 6.1 ms by eight, 4.1 by one).
     if (left == 0) {
       int c = 0;
-      if (lane == 0) c = atomicAdd(next + tl.x, SP_CLAIM);
+      if (lane == 0) c = atomicAdd(next + tl.x, claim);
       fi = __builtin_amdgcn_readfirstlane(c);
-      left = SP_CLAIM;
+      left = claim;
     }
     long long g;
     if (!tl.at(fi, g)) break;
