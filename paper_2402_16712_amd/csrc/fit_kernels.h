@@ -2404,10 +2404,11 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
 // and should be short where there are few, but each costs an append to the list
 // and a claim of it, about 6 ns one after the other.  So the 64 segments of a
 // word go by 1, 2 or 4 (cut 0, 1, 2) as long as the call's words then give the
-// chip at most eight parts per wave (20000 x 40 has 40 words: by two and by eight
-// 8 whole penalties took 39 and 120 ms), and else (cut 3) by eight after a first
-// two, two and four: what is left clusters (the 2859 segments of the 2000 x 2000
-// path were close together in few columns; a word per wave took 5.3 ms).
+// chip at most two parts per wave (20000 x 40 has 40 words: by two and by eight 8
+// penalties took 39 and 120 ms; with eight parts per wave 110 x 149 of ties took
+// 630 us, now 350), and else (cut 3) by eight after a first two, two and four:
+// what is left clusters (the 2859 segments of the 2000 x 2000 path were close
+// together in few columns; a word per wave took 5.3 ms).
 constexpr int REST_CUTS = 4;
 __host__ __device__ constexpr int rest_rank(int cut, int p) {
   return cut < 3 ? p << cut : p < 3 ? 2 * p : 8 * (p - 2);

@@ -489,7 +489,7 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
   sp = std::min<long long>({sp, 32, Ly.nmax / 32});
   Ly.ss_split = (int)std::max<long long>(1, sp);
   Ly.ss_per = (B == 1 && ro.cand) ? (long long)ro.ncand * probs[0].m : Ly.total_pairs;
-  const long long rest_most = 8ll * 4 * SEG_WAVES * ctx->num_cu;
+  const long long rest_most = 2ll * 4 * SEG_WAVES * ctx->num_cu;
   while (Ly.rest_cut < REST_CUTS - 1 && Ly.total_words * rest_parts(Ly.rest_cut, 64) > rest_most) ++Ly.rest_cut;
   layout_sizes(Ly);
   while (Ly.bytes > max_bytes && Ly.ss_split > 1) {
