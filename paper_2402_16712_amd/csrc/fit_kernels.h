@@ -24,6 +24,7 @@ struct ColInfo {
   int flags;    // COL_*
   int bemin;    // smallest biased exponent field over nonzero entries
   int bemax;    // largest biased exponent field over nonzero entries
+  double unit;  // the weights are whole multiples of it and their FP64 sums safe (column_unit), or 0
 };
 
 // One problem of a batch, as the kernels see it.  Workspace offsets are in
@@ -64,6 +65,17 @@ __device__ __forceinline__ int find_owner(const int *__restrict__ prefix, int co
 
 // ------------------------------------------------------------------ columns
 constexpr int SAMPLE_ROWS = 128;    // rows of column j drawn for the key windows
+
+// A unit of a column's weights in which sums of them come out near enough to
+// tell whole numbers apart: 2^e0 for weights with a sum below 2^50 of them (whole
+// numbers: every FP64 sum is exact), or the magnitude that all its nonzeros share
+// (two-valued data: a sum of n <= 65535 equal weights is off by less than 2^-20
+// of one); else 0.  amin, amax: least and largest nonzero magnitude.
+__device__ __forceinline__ double column_unit(u128 wfix, int e0, int nnz, double amin, double amax) {
+  if (nnz == 0) return 1.0;
+  if (amin >= 0x1p-300 && wfix < ((u128)1 << 50)) return ldexp(1.0, e0);
+  return amin == amax && amin >= 0x1p-900 && amax <= 0x1p900 ? amin : 0.0;
+}
 
 // One workgroup of kW waves per column: finiteness, counts, the fixed-point
 // exponent e0, the range check, the exact fixed-point mass, the R64 column
@@ -257,6 +269,7 @@ __device__ __forceinline__ void colprep_block(const double *__restrict__ x, int 
     c.flags = flags;
     c.bemin = nnz ? (int)((uint64_t)__double_as_longlong(amin) >> 52) : 4096;
     c.bemax = nnz ? (int)((uint64_t)__double_as_longlong(amax) >> 52) : -1;
+    c.unit = flags ? 0.0 : column_unit(c.wfix, e0, nnz, amin, amax);
     *out = c;
   }
 }
@@ -1067,21 +1080,19 @@ __device__ __forceinline__ bool window_midpoint(const uint64_t *smp, uint64_t pl
   return mid > plo;
 }
 
-// 2^e0 when column j's weights are whole multiples of it with a sum below 2^50
-// of them (whole numbers), else 0.  Every FP64 sum of such weights is exact, and
-// a weight sum compared with a penalty is an integer compared with a real: the
-// outcome is the one of the integer part, or of anything up to the next integer.
-__device__ __forceinline__ double whole_unit(const ColInfo &cj) {
-  return cj.bemin >= 1023 - 300 && cj.wfix < ((u128)1 << 50) ? ldexp(1.0, cj.e0) : 0.0;
-}
-// The penalty to compare with: of a column with a unit the middle between two
-// whole ones, a quarter of a unit from the target of every prefix weight and
-// half from the sides' sums, so that neither ties (count data at whole penalties
-// tie in most segments, which the exact kernel then had).  From 2^50 units on a
-// penalty is above every weight sum as it is.
-__device__ __forceinline__ double between_units(double lam, double unit, int e0) {
-  const double l = ldexp(lam, -e0);
-  return unit > 0.0 && l < 0x1p50 ? (floor(l) + 0.5) * unit : lam;
+// The penalty to compare with.  A weight sum of a column with a unit compared
+// with a penalty is an integer compared with a real: the outcome is the one of
+// the integer part, or of anything up to the next integer.  So it is taken in the
+// middle between two whole ones, a quarter of a unit from the target of every
+// prefix weight and half from the sides' sums, and neither ties (count data at
+// whole penalties tie in most segments, which the exact kernel then had).  From
+// 2^50 units on a penalty is above every weight sum as it is.
+__device__ __forceinline__ double between_units(double lam, double unit) {
+  const double l = lam * __builtin_amdgcn_rcp(unit);
+  double q = floor(l);                             // off by one at most
+  const double r = fma(-q, unit, lam);
+  q = r < 0.0 ? q - 1.0 : r >= unit ? q + 1.0 : q;
+  return unit > 0.0 && l < 0x1p50 ? (q + 0.5) * unit : lam;
 }
 
 // The side of the minimiser of segment (j, k) at penalty lam (between_units)
@@ -1089,7 +1100,7 @@ __device__ __forceinline__ double between_units(double lam, double unit, int e0)
 // positive, 3 undecided (the exact pass decides).  Decision margin 2^-32 (W_j +
 // lam): far above the rounding error of the sign sums (at most ~n 2^-52 of W_j,
 // plus n 2^-1022 should the matrix unit flush subnormal terms: hence the floor
-// on the margin); with a unit the sums are exact and an eighth of it will do.
+// on the margin); with a unit an eighth of it will do.
 // unc: the sums cannot be trusted for this segment.
 __device__ __forceinline__ int sign_sum_side(double2 dz, double lam, double Wj, double unit, bool unc) {
   const double M = unit > 0.0 ? 0.125 * unit : 0x1p-32 * (Wj + lam);
@@ -1155,10 +1166,10 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
     if (!cj.flags && !ck.flags) {
       const bool unc = sign_sums_unsure(cj, ck, dz);
       const double *lam = lam_all + d.lam_off;
-      const double unit = whole_unit(cj);
+      const double unit = cj.unit;
       skip = true;
       for (int t = 0; t < d.L && skip; ++t)
-        skip = sign_sum_side(dz, between_units(lam[t], unit, cj.e0), cj.W, unit, unc) == 0;
+        skip = sign_sum_side(dz, between_units(lam[t], unit), cj.W, unit, unc) == 0;
       if (skip && d.L == 1) {
         const long long base = d.ws_off + (long long)j * d.m + k;
         V[base] = 0.0;
@@ -1233,8 +1244,8 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 constexpr int FAST_CAP = 512;       // rows a window may list
 constexpr double FAST_ZERO = 0x1p-1000, FAST_OPEN = 0x1p1000;   // next to 0, beyond every ratio
 
-// what two weight sums of column j may be off in a comparison; with a unit all
-// are exact and differ from every target by a quarter of it at least
+// what two weight sums of column j may be off in a comparison; with a unit they
+// differ from every target by a quarter of it at least
 __device__ __forceinline__ double segment_tol(double Wj, double unit) { return unit > 0.0 ? 0.125 * unit : 0x1p-38 * Wj; }
 
 struct FastScratch {
@@ -2649,8 +2660,8 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     const unsigned short *sm = smp + (long long)(d.col_off + j) * SAMPLE_ROWS;
     const int sr0 = sm[lane], sr1 = sm[64 + lane];
     const double sv0 = __builtin_amdgcn_rcp(sxj[sr0]), sv1 = __builtin_amdgcn_rcp(sxj[sr1]);
-    const double Wd = cj.W, unit = whole_unit(cj), tol = segment_tol(Wd, unit);
-    const double lam = between_units(lam_all[d.lam_off], unit, cj.e0);
+    const double Wd = cj.W, unit = cj.unit, tol = segment_tol(Wd, unit);
+    const double lam = between_units(lam_all[d.lam_off], unit);
     // the targets' places in the sample
     const double cneg = 0.5 * SAMPLE_ROWS * (Wd + lam) / Wd, cpos = 0.5 * SAMPLE_ROWS * (Wd - lam) / Wd;
     const FastRange fast(cj, !cj.flags);
@@ -2740,8 +2751,8 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     const double *__restrict__ sxj = kLdsJ ? (const double *)sxj_lds : xjg;
     if (threadIdx.x == 0) {
       knext = 0;
-      s_unit = whole_unit(cj);
-      s_tol = segment_tol(cj.W, whole_unit(cj));
+      s_unit = cj.unit;
+      s_tol = segment_tol(cj.W, cj.unit);
     }
     __syncthreads();
     const long long word0 = d.mask_off + (long long)jj * ((m + 63) >> 6), mm = (long long)m * m;
@@ -2774,7 +2785,7 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
       auto ldk = [&](int i) { return col_ld(rk, i * 8); };
       for (int t0 = 0; t0 < L && !left; t0 += 64) {
         const int t = t0 + lane;
-        const double unit = s_unit, lam = between_units(t < L ? lams[t] : 0.0, unit, cj.e0);
+        const double unit = s_unit, lam = between_units(t < L ? lams[t] : 0.0, unit);
         double v = plain ? (k == j ? 1.0 : __longlong_as_double(0x7ff8000000000000ll)) : 0.0, e = plain ? 0.0 : ck.W;
         int row = -1;
         const int side = t < L && !plain ? sign_sum_side(dz, lam, Wd, unit, unc) : 0;

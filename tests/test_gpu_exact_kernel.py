@@ -294,3 +294,41 @@ def test_gaps_between_samples(ctx, L):
     print(f"  1 outlier {1e3 * a:.1f} us, {rows.sum()} outliers {1e3 * b:.1f} us", flush=True)
     assert a < 5.0 * b
     _path_equal(_host(ctx.fit_path(Xd, lx)), O.fit_path(X, lx), L)
+
+
+# columns of one magnitude that is no short binary fraction: sums of equal weights
+# tie as whole numbers do, though none of them is exact
+@pytest.mark.parametrize("n", [7, 64, 110, 1201, 5000])
+@pytest.mark.parametrize("c", [0.1, 1.0 / 3.0 * 2.0 ** 700, np.nextafter(2.0 ** -890, 1.0)])
+def test_columns_of_one_magnitude(ctx, n, c):
+    from paper_2402_16712_amd import binding as B
+    print(f"case one magnitude {n} {c}", flush=True)
+    g = np.random.default_rng(n)
+    u = g.standard_normal(n)
+    X = np.sign(np.outer(u, g.standard_normal(9)) + 0.7 * g.standard_normal((n, 9))) * c
+    X[:, 2] *= g.random(n) < 0.5
+    X[:, 5] *= 3.0
+    X[:, 6] = u * c                              # (all magnitudes, next to the others)
+    X[:, 7] = 0.0
+    X = np.asfortranarray(X)
+    Xd = B.device_matrix(X)
+    k = max(1, n // 20)
+    steps = [0.0, c, np.nextafter(c, 0.0), 2.0 * c, k * c, np.nextafter(k * c, np.inf), 0.4 * n * c, 3.0 * n * c]
+    for lam in steps:
+        _path_equal(_host(ctx.fit_path(Xd, np.array([lam]))), O.fit_path(X, [lam]), (n, c, lam))
+    lams = np.sort(np.array(steps))
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, c, "path"))
+
+
+# at penalty 0 half of the segments of two-valued data tie: no longer than at one
+# between two sums (twice leaves room for the times' spread; through the exact
+# kernel three to eight times)
+def test_one_magnitude_takes_as_long(ctx):
+    from paper_2402_16712_amd import binding as B
+    print("case one magnitude time", flush=True)
+    g = np.random.default_rng(3)
+    X = 0.1 * np.sign(np.outer(g.standard_normal(200), g.standard_normal(150)) + 0.5 * g.standard_normal((200, 150)))
+    Xd = B.device_matrix(X)
+    a, b = (_segment_ms(ctx, lambda lam=lam: ctx.fit(Xd, lam)) for lam in (0.0, 0.05))
+    print(f"  penalty 0 {1e3 * a:.1f} us, between {1e3 * b:.1f} us", flush=True)
+    assert a < 2.0 * b
