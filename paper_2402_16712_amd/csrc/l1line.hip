@@ -610,13 +610,16 @@ k_colprep_first(ProbDesc pd, LambdaArgs lam, BatchLayout Ly, char *d) {
                           (unsigned short *)(d + Ly.o_smp) + (long long)col * SAMPLE_ROWS, sh, (double *)smem);
   if (threadIdx.x == 0) ((int *)(d + Ly.o_segflags))[col] = 0;
 }
-// The form of the column preparation for `cols` columns of up to n rows: four
-// waves per column with the column in LDS up to eight columns per CU (2000 x
-// 2000: 23 us, one wave 29), longer columns four waves up to four per CU (20011
-// x 151: 83, one wave 176), else one wave per column (the batch's 32470 columns
-// of up to 4000 rows: 197, four waves with LDS 402; 10000 x 4000: 146, 280).
+// The form of the column preparation for `cols` columns of up to n rows: one
+// wave per column for up to two loads a lane (features of 77 x 957 50.1 us, four
+// waves 52.3), four waves per column with the
+// column in LDS up to eight columns per CU (2000 x 2000: 23 us, one wave 29),
+// longer columns four waves up to four per CU (20011 x 151: 83, one wave 176), else
+// one wave per column (the batch's 32470 columns of up to 4000 rows: 197, four
+// waves with LDS 402; 10000 x 4000: 146, 280).
 enum { PREP_ONE, PREP_FOUR, PREP_LDS };
 static int prep_form(l1line_ctx ctx, int64_t n, int64_t cols) {
+  if (n <= 128) return PREP_ONE;
   if (n <= PREP_LDS_MAX) return cols <= 8ll * ctx->num_cu ? PREP_LDS : PREP_ONE;
   return cols <= 4ll * ctx->num_cu ? PREP_FOUR : PREP_ONE;
 }
