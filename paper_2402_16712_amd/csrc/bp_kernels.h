@@ -111,8 +111,6 @@ k_bp_count(const double *__restrict__ X, int n, int m, long long ld, const ColIn
   unsigned short *lr = srows[(threadIdx.x >> 6) & 3];
   const int ts = xcd_tile(n);
   const int T = (n + 63) >> 6;
-  int Tp = 1;
-  while (Tp < T) Tp <<= 1;
   const XcdTiles tl(m, ts, blockDim.x >> 6);
   for (long long f = tl.wx;; f += tl.nwx) {
     long long g;
@@ -129,7 +127,7 @@ k_bp_count(const double *__restrict__ X, int n, int m, long long ld, const ColIn
       }
       continue;
     }
-    const SegIO s{X + (long long)k * ld, X + (long long)j * ld, n, T, Tp, cj.e0, lane, false};
+    const SegIO s{X + (long long)k * ld, X + (long long)j * ld, n, T, cj.e0, lane, false};
     const int r0 = R0[g];
     const double v0 = V0[g];
     const uint64_t mkey = key_of(v0 + 0.0);
@@ -351,8 +349,6 @@ k_bp_emit(const double *__restrict__ X, int n, int m, long long ld, const ColInf
   }
   const int ts = xcd_tile(n);
   const int T = (n + 63) >> 6;
-  int Tp = 1;
-  while (Tp < T) Tp <<= 1;
   const XcdTiles tl(m, ts, BP_WAVES);
   for (long long f = tl.wx;; f += tl.nwx) {
     long long g;
@@ -366,7 +362,7 @@ k_bp_emit(const double *__restrict__ X, int n, int m, long long ld, const ColInf
     const ColInfo cj = ci[j];
     const int r0 = R0[g];
     if (r0 >= 0) {
-      const SegIO s{X + (long long)k * ld, X + (long long)j * ld, n, T, Tp, cj.e0, lane, false};
+      const SegIO s{X + (long long)k * ld, X + (long long)j * ld, n, T, cj.e0, lane, false};
       const u128 W = cj.wfix;
       const bool neg = V0[g] < 0.0;
       long long emitted = 0;

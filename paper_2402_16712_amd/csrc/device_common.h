@@ -7,8 +7,6 @@
 
 typedef unsigned __int128 u128;
 
-#define L1_WAVE 64
-
 // Order-preserving map from a non-NaN double to uint64: a < b  <=>  key(a) < key(b).
 // Callers pass canonical zeros (+0.0), so every zero ratio has the same key.
 constexpr uint64_t KEY_ZERO = 0x8000000000000000ull;   // key(+0.0)
@@ -302,13 +300,6 @@ __device__ __forceinline__ void wave_sort_key_dbl(uint64_t &key, double &w, int 
     }
   }
 }
-
-// Keep the scheduler from hoisting every load of an unrolled slot loop (each
-// weight is 4 VGPRs): fence after every 4 slots.
-#define L1_SLOT_FENCE(t) \
-  do {                    \
-    if (((t) & 3) == 3) __builtin_amdgcn_sched_barrier(0); \
-  } while (0)
 
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");

@@ -318,7 +318,7 @@ k_colprep_batch(const ProbDesc *__restrict__ P, const int *__restrict__ colstart
 struct SegIO {
   const double *__restrict__ xk;   // column k (device memory)
   const double *__restrict__ sxj;  // column j (LDS when lds, else device memory)
-  int n, T, Tp, e0, lane;          // rows, slots, pow2 >= T, fixed-point exponent
+  int n, T, e0, lane;              // rows, slots, fixed-point exponent
   bool lds;                        // a compile-time constant at every construction
 };
 
@@ -2486,14 +2486,13 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
     const ColInfo cj = ci[d.col_off + j];
     const double *lam = lam_all + d.lam_off;
     const int T = (d.n + 63) >> 6;
-    int Tp = 1, err = 0;
-    while (Tp < T) Tp <<= 1;
+    int err = 0;
     wave_lds_sync();
     for (int t = lane; t < d.L; t += 64) slam[t] = lambda_fixed(lam[t], cj.e0);
     wave_lds_sync();
     for (int q = rest_rank(td.cut, p + 1) - rest_rank(td.cut, p); q > 0 && bits; --q, bits &= bits - 1) {
       const int k = k0 + __builtin_ctzll(bits);
-      const SegIO s{d.X + (long long)k * d.ld, d.X + (long long)j * d.ld, d.n, T, Tp, cj.e0, lane, false};
+      const SegIO s{d.X + (long long)k * d.ld, d.X + (long long)j * d.ld, d.n, T, cj.e0, lane, false};
       seg_exact(s, cj, ci[d.col_off + k], smp + (long long)(d.col_off + j) * SAMPLE_ROWS, lam, d.L,
                 DZ[d.pair_off + (long long)j * d.m + k], slam, ws, lk, lr, lcap, V + d.ws_off, E + d.ws_off,
                 R + d.ws_off, (long long)j * d.m + k, (long long)d.m * d.m, err);
@@ -2676,7 +2675,7 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
     double2 dz = DZj[k];
     double b0 = gld(d.X + (long long)k * d.ld + sr0), b1 = gld(d.X + (long long)k * d.ld + sr1);
     while (c < segs.nlive) {
-      const SegIO s{d.X + (long long)k * d.ld, sxj, n, T, 0, cj.e0, lane, kLdsJ};
+      const SegIO s{d.X + (long long)k * d.ld, sxj, n, T, cj.e0, lane, kLdsJ};
       const ColInfo ck = cis[k];
       double v = 0.0, e = ck.W;
       int row = -1;
@@ -2772,7 +2771,7 @@ k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
       if (lane == 0) claim = atomicAdd(&knext, 1);
       const int k = segs.at(cq, lane);
       const long long base = d.ws_off + (long long)j * m + k;
-      const SegIO s{d.X + (long long)k * d.ld, sxj, n, T, 0, cj.e0, lane, kLdsJ};
+      const SegIO s{d.X + (long long)k * d.ld, sxj, n, T, cj.e0, lane, kLdsJ};
       const ColInfo ck = cis[k];
       const double2 dz = DZj[k];
       const bool unc = sign_sums_unsure(cj, ck, dz), plain = k == j || cj.flags;
