@@ -1233,13 +1233,16 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 //               target's bin holds a few rows, ranked by counting.
 // The target, counted from lo, is D = (T + lambda) / 2 on the negative side and
 // (T - lambda) / 2 on the positive one (first prefix sum reaching D).  Sums
-// run in FP64: every value compared is a sum of nonnegative weights of
-// column j or a difference of such sums, at most W_j, off its exact value by
-// at most the terms a lane adds in turn plus 60 roundings of W_j (u = 2^-53),
-// less than 2^11 u W_j for 65535 rows.  A comparison whose operands differ by
-// more than tol = 2^-38 W_j (2^15 u W_j) therefore has the exact comparison's
-// outcome; closer ones, a selected ratio equal to lo or hi (a row whose
-// rounded ratio meets the bound may be on either side of it) and whatever
+// run in FP64: every value compared is a sum of nonnegative weights of column j
+// or a difference of such sums, at most W_j, and a rounding is at most u W_j (u =
+// 2^-53).  For 65535 rows T takes 1024 adds a lane and a scan, D two more: 1040.
+// The bins add up to 512 weights in turn, a scan and two for the new D, at up to
+// eight levels, and the ranking 64: 4240 (select_listed).  A tie's rows take 1024
+// slots' totals and scans: 1040 (tie_rows), a sorted list 30 (fast_path).  So two
+// sides of a comparison are off by less than 2^13 u W_j together, and one whose
+// operands differ by more than tol = 2^-38 W_j (2^15 u W_j) has the exact
+// comparison's outcome; closer ones, a selected ratio equal to lo or hi (a row
+// whose rounded ratio meets the bound may be on either side of it) and whatever
 // else is unsettled leave the segment to k_seg_rest, which is exact.
 constexpr int FAST_CAP = 512;       // rows a window may list
 constexpr double FAST_ZERO = 0x1p-1000, FAST_OPEN = 0x1p1000;   // next to 0, beyond every ratio
