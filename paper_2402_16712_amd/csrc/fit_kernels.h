@@ -1120,6 +1120,31 @@ __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInf
   return maybe_tiny || !isfinite(dz.x) || !isfinite(dz.y);
 }
 
+// Where the division-free kernels leave what they cannot settle: a bit per
+// segment, and a list of the words' parts: part p of a word is its left segments
+// of rank rest_rank(p) to rest_rank(p + 1) - 1.  An append to the list takes about
+// 6 ns, one after the other, so a full word has ten parts, not one per segment;
+// the first of a word are short, since what is left clusters (the 2859 segments
+// of the 2000 x 2000 path are close together in few columns; a word to a wave took
+// 5.3 ms).
+constexpr int REST_PARTS = 10;      // of a word, at most
+__host__ __device__ constexpr int rest_rank(int p) { return p < 3 ? 2 * p : 8 * (p - 2); }
+// parts of a word with `count` segments left
+__host__ __device__ constexpr int rest_parts(int count) { return count <= 4 ? (count + 1) / 2 : (count + 23) / 8; }
+struct TodoPart {
+  int word, part;
+};
+struct TodoList {
+  unsigned long long *bits;
+  TodoPart *list;
+  int *count;
+};
+__device__ __forceinline__ void leave_segment(const TodoList &td, long long word, int bit) {
+  const unsigned long long old = atomicOr(td.bits + word, 1ull << bit);
+  const int c = __builtin_popcountll(old), p = rest_parts(c);
+  if (!((old >> bit) & 1ull) && rest_parts(c + 1) > p) td.list[atomicAdd(td.count, 1)] = TodoPart{(int)word, p};
+}
+
 // Segments settled by the sign sums alone.  One thread per pair (j, k), one
 // wave per 64 consecutive k of a preserved column: where every penalty of the
 // problem has 0 as a minimiser (sign_sum_side, the segment kernels' own test),
@@ -1130,11 +1155,14 @@ __device__ __forceinline__ bool sign_sums_unsure(const ColInfo &cj, const ColInf
 // (2000 x 2000 with 64: 2.0 ms of scattered stores).  wstart[b] = first mask
 // word of problem b (mj ceil(m / 64) words, mj = ncand with a candidate list,
 // problem 0 only, else m).
+// Pairs outside the division-free range are left to the exact kernel here, a word
+// at a time (one by one by the segment kernels 49 x 438 subnormal data took 1390 us,
+// now 1060); `done` has them and the mask's bits: what the segment kernels skip.
 __global__ void __launch_bounds__(256)
 k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, int total_words,
                 const double *__restrict__ lam_all, const ColInfo *__restrict__ ci,
                 double2 *__restrict__ DZ, double *__restrict__ V, double *__restrict__ E,
-                int *__restrict__ R, unsigned long long *__restrict__ mask, unsigned long long *__restrict__ todo,
+                int *__restrict__ R, unsigned long long *__restrict__ mask, unsigned long long *__restrict__ done, TodoList td,
                 const int *__restrict__ cand, const int *__restrict__ gate, int gate_on, int split, const double2 *__restrict__ part,
                 long long per) {
   const int w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1146,7 +1174,7 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
   const int wl = w - wstart[b];
   const int jj = wl / wpr, k = (wl - jj * wpr) * 64 + lane;
   const int j = cand ? cand[jj] : jj;
-  bool skip = false;
+  bool skip = false, left = false;
   if (k < d.m && k != j) {
     const long long pair = d.pair_off + (long long)j * d.m + k;
     double2 dz;
@@ -1176,12 +1204,21 @@ k_zero_segments(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, 
         E[base] = ck.W;
         R[base] = -1;
       }
+      left = !skip && !FastRange(cj, true).has(ck);
     }
   }
-  const unsigned long long bits = __ballot(skip);
+  const unsigned long long bits = __ballot(skip), rest = __ballot(left);
   if (lane == 0) {
     mask[d.mask_off + wl] = bits;
-    todo[d.mask_off + wl] = 0ull;
+    done[d.mask_off + wl] = bits | rest;
+    td.bits[d.mask_off + wl] = rest;
+  }
+  if (rest) {
+    const int parts = rest_parts(__builtin_popcountll(rest));
+    int at = 0;
+    if (lane == 0) at = atomicAdd(td.count, parts);
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (lane < parts) td.list[at + lane] = TodoPart{(int)(d.mask_off + wl), lane};
   }
 }
 
@@ -2411,51 +2448,21 @@ __device__ __forceinline__ void seg_exact(const SegIO &s, const ColInfo &cj, con
   }
 }
 
-// Where the division-free kernels leave what they cannot settle: a bit per
-// segment, and a list of the words' parts, which are what a wave of k_seg_rest
-// takes at a time: part p of a word is its left segments of rank
-// rest_rank(cut, p) to rest_rank(cut, p + 1) - 1.  A wave's parts are one chain
-// and should be short where there are few, but each costs an append to the list
-// and a claim of it, about 6 ns one after the other.  So the 64 segments of a
-// word go by 1, 2 or 4 (cut 0, 1, 2) as long as the call's words then give the
-// chip at most two parts per wave (20000 x 40 has 40 words: by two and by eight 8
-// penalties took 39 and 120 ms; with eight parts per wave 110 x 149 of ties took
-// 630 us, now 350), and else (cut 3) by eight after a first two, two and four:
-// what is left clusters (the 2859 segments of the 2000 x 2000 path were close
-// together in few columns; a word per wave took 5.3 ms).
-constexpr int REST_CUTS = 4;
-__host__ __device__ constexpr int rest_rank(int cut, int p) {
-  return cut < 3 ? p << cut : p < 3 ? 2 * p : 8 * (p - 2);
-}
-// parts of a word with `count` segments left
-__host__ __device__ constexpr int rest_parts(int cut, int count) {
-  return cut < 3 ? (count + (1 << cut) - 1) >> cut : count <= 4 ? (count + 1) / 2 : (count + 23) / 8;
-}
-struct TodoPart {
-  int word, part;
-};
-struct TodoList {
-  unsigned long long *bits;
-  TodoPart *list;
-  int *count;
-  int cut;
-};
-__device__ __forceinline__ void leave_segment(const TodoList &td, long long word, int bit) {
-  const int c = __builtin_popcountll(atomicOr(td.bits + word, 1ull << bit)), p = rest_parts(td.cut, c);
-  if (rest_parts(td.cut, c + 1) > p) td.list[atomicAdd(td.count, 1)] = TodoPart{(int)word, p};
-}
-
-// The parts that the division-free kernels listed, one per claim of a wave (or
-// several, of long lists) from *next; the first is the wave's own number (an
-// atomic of every wave on one counter took 50 us where nothing was left), and
-// the only one where there are no more parts than waves.  The count and the
-// words are final: they belong to earlier kernels.
+// The parts that the division-free kernels listed, cut into 2^cut pieces (every
+// 2^cut-th segment) as long as four pieces per wave are not reached: few segments
+// go one to a wave (20000 x 40 with 8 penalties by two and by eight 39 and 120
+// ms), and the waves take the pieces in turn, since many are empty and a claim of
+// each, about 6 ns one after the other, costs more than it evens out (150 x 600
+// one-decimal data 1.00 ms, in turn 0.70).  Longer lists go part by part, by claims
+// from *next (49 x 438 of subnormals 0.89 ms, in turn 1.02), and so do the pieces of
+// long_segments (rows times penalties: 6727 x 133 of subnormals with 61 penalties
+// 342 ms, in turn 499).  The list is final: it belongs to earlier kernels.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B, const double *__restrict__ lam_all,
            const ColInfo *__restrict__ ci, const unsigned short *__restrict__ smp, const double2 *__restrict__ DZ,
            double *__restrict__ V, double *__restrict__ E, int *__restrict__ R, int *__restrict__ segflags,
            const int *__restrict__ cand, const int *__restrict__ gate, int gate_on,
-           TodoList td, int *__restrict__ next, int Lmax, int lcap) {
+           TodoList td, int *__restrict__ next, int Lmax, int lcap, bool long_segments) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (gate && *gate != gate_on) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -2464,24 +2471,23 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
   uint64_t *lk = (uint64_t *)(ws + 1);
   unsigned short *lr = (unsigned short *)(lk + lcap);
   const int count = *td.count, waves = (int)gridDim.x * SEG_WAVES;
-  const int per = max(1, count / (8 * waves));
-  int e = (blockIdx.x * SEG_WAVES + wave) * per, left = per;
-  while (e < count) {
-    const TodoPart part = td.list[e];
-    const int w = uni_int(part.word), p = uni_int(part.part);
+  int cut = 0;
+  while (cut < 3 && ((long long)count << cut) < 4ll * waves) ++cut;
+  const int pieces = count << cut;
+  const bool claims = (cut == 0 || long_segments) && pieces > waves;
+  for (int e = blockIdx.x * SEG_WAVES + wave, next_e; e < pieces; e = next_e) {
+    const TodoPart part = td.list[e % count];
+    const int w = uni_int(part.word), p = uni_int(part.part), piece = e / count;
     uint64_t bits = td.bits[w];
-    ++e;
-    if (--left == 0) {
-      if (count <= waves) {
-        e = count;
-      } else {
-        int c = 0;
-        if (lane == 0) c = atomicAdd(next, per);
-        e = waves * per + uni_int(c);
-        left = per;
-      }
+    next_e = e + waves;
+    if (claims) {
+      int c = 0;
+      if (lane == 0) c = atomicAdd(next, 1);
+      next_e = waves + uni_int(c);
     }
-    for (int q = rest_rank(td.cut, p); q > 0; --q) bits &= bits - 1;
+    for (int q = rest_rank(p); q > 0; --q) bits &= bits - 1;
+    int size = min(rest_rank(p + 1) - rest_rank(p), __builtin_popcountll(bits));
+    if (size <= piece) continue;
     const int b = find_owner(wstart, B, w);
     const ProbDesc d = P[b];
     const int wpr = (d.m + 63) >> 6, wl = w - wstart[b], jj = wl / wpr, k0 = (wl - jj * wpr) * 64;
@@ -2493,7 +2499,8 @@ k_seg_rest(const ProbDesc *__restrict__ P, const int *__restrict__ wstart, int B
     wave_lds_sync();
     for (int t = lane; t < d.L; t += 64) slam[t] = lambda_fixed(lam[t], cj.e0);
     wave_lds_sync();
-    for (int q = rest_rank(td.cut, p + 1) - rest_rank(td.cut, p); q > 0 && bits; --q, bits &= bits - 1) {
+    for (int q = 0; q < size; ++q, bits &= bits - 1) {
+      if ((q & ((1 << cut) - 1)) != piece) continue;
       const int k = k0 + __builtin_ctzll(bits);
       const SegIO s{d.X + (long long)k * d.ld, d.X + (long long)j * d.ld, d.n, T, cj.e0, lane, false};
       seg_exact(s, cj, ci[d.col_off + k], smp + (long long)(d.col_off + j) * SAMPLE_ROWS, lam, d.L,

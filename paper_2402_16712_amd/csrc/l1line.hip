@@ -300,12 +300,11 @@ struct BatchLayout {
   int B, nitems, ksplit, nmax, Lmax;
   int ss_split;               // row parts of the sign sums
   long long ss_per;           // pairs per part
-  int rest_cut;               // parts of the words left to the exact kernel
   int xstart[SEG_XCDS + 1];   // explicit items: XCD x owns [xstart[x], xstart[x + 1])
   long long total_cols, total_z, total_out, total_ws, total_lam, total_pairs, total_tiles, total_words;
   size_t o_desc, o_colstart, o_zstart, o_ostart, o_tstart, o_wstart, o_lam, o_items, o_counter, o_xstart,
       meta_bytes;
-  size_t o_ci, o_smp, o_segflags, o_DZ, o_DZp, o_mask, o_todo, o_todolist, o_V, o_E, o_R, o_Z, o_zflag, bytes;
+  size_t o_ci, o_smp, o_segflags, o_DZ, o_DZp, o_mask, o_done, o_todo, o_todolist, o_V, o_E, o_R, o_Z, o_zflag, bytes;
 };
 
 static void layout_sizes(BatchLayout &Ly) {
@@ -328,8 +327,9 @@ static void layout_sizes(BatchLayout &Ly) {
   Ly.o_DZ = take(2 * sizeof(double) * Ly.total_pairs);
   Ly.o_DZp = take(Ly.ss_split > 1 ? 2 * sizeof(double) * Ly.ss_split * (size_t)Ly.ss_per : 0);
   Ly.o_mask = take(sizeof(unsigned long long) * Ly.total_words);
+  Ly.o_done = take(sizeof(unsigned long long) * Ly.total_words);
   Ly.o_todo = take(sizeof(unsigned long long) * Ly.total_words);
-  Ly.o_todolist = take(sizeof(TodoPart) * rest_parts(Ly.rest_cut, 64) * Ly.total_words);
+  Ly.o_todolist = take(sizeof(TodoPart) * REST_PARTS * Ly.total_words);
   Ly.o_V = take(sizeof(double) * Ly.total_ws);
   Ly.o_E = take(sizeof(double) * Ly.total_ws);
   Ly.o_R = take(sizeof(int) * Ly.total_ws);
@@ -489,8 +489,6 @@ static int plan_batch(l1line_ctx ctx, const l1line_problem *probs, int64_t B, co
   sp = std::min<long long>({sp, 32, Ly.nmax / 32});
   Ly.ss_split = (int)std::max<long long>(1, sp);
   Ly.ss_per = (B == 1 && ro.cand) ? (long long)ro.ncand * probs[0].m : Ly.total_pairs;
-  const long long rest_most = 2ll * 4 * SEG_WAVES * ctx->num_cu;
-  while (Ly.rest_cut < REST_CUTS - 1 && Ly.total_words * rest_parts(Ly.rest_cut, 64) > rest_most) ++Ly.rest_cut;
   layout_sizes(Ly);
   while (Ly.bytes > max_bytes && Ly.ss_split > 1) {
     Ly.ss_split /= 2;
@@ -675,8 +673,8 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   double *dV = (double *)(d + Ly.o_V), *dE = (double *)(d + Ly.o_E), *dZ = (double *)(d + Ly.o_Z);
   int *dR = (int *)(d + Ly.o_R), *dzflag = (int *)(d + Ly.o_zflag);
   double2 *dDZ = (double2 *)(d + Ly.o_DZ), *dDZp = (double2 *)(d + Ly.o_DZp);
-  unsigned long long *dmask = (unsigned long long *)(d + Ly.o_mask);
-  const TodoList todo{(unsigned long long *)(d + Ly.o_todo), (TodoPart *)(d + Ly.o_todolist), dcounter + 8, Ly.rest_cut};
+  unsigned long long *dmask = (unsigned long long *)(d + Ly.o_mask), *ddone = (unsigned long long *)(d + Ly.o_done);
+  const TodoList todo{(unsigned long long *)(d + Ly.o_todo), (TodoPart *)(d + Ly.o_todolist), dcounter + 8};
   if (outp) *outp = BatchPtrs{dV, dR, dci};
   l1line_ctx pc = prof ? ctx : nullptr;
 
@@ -733,7 +731,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   {
     ProfScope ps(pc, ls, "zero_seg");
     hipLaunchKernelGGL(k_zero_segments, dim3((unsigned)((Ly.total_words + 3) / 4)), dim3(256), 0, ls, dP, dwst,
-                       (int)B, (int)Ly.total_words, dlam, dci, dDZ, dV, dE, dR, dmask, todo.bits,
+                       (int)B, (int)Ly.total_words, dlam, dci, dDZ, dV, dE, dR, dmask, ddone, todo,
                        (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, Ly.ss_split, (const double2 *)dDZp,
                        Ly.ss_per);
   }
@@ -744,13 +742,13 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
     auto kseg = sxj_rows > 0 ? (multi ? k_seg_path<true> : k_seg_fast<true>)
                              : (multi ? k_seg_path<false> : k_seg_fast<false>);
     hipLaunchKernelGGL(kseg, dim3((unsigned)grid_seg), dim3(64 * seg_waves), lds_fast, ls, dP, queue, dlam, dci, dsmp,
-                       dDZ, dV, dE, dR, ro.cand, ro.ncand, ro.gate, ro.gate_on, dmask, todo, sxj_rows);
-    // (a wave per part that can be left, up to what the chip holds: a wave per
+                       dDZ, dV, dE, dR, ro.cand, ro.ncand, ro.gate, ro.gate_on, ddone, todo, sxj_rows);
+    // (a wave per segment that can be left, up to what the chip holds: a wave per
     // word gave 20000 x 40 with 8 whole penalties 40 waves, 196 ms)
-    const long long rest_waves = Ly.total_words * rest_parts(Ly.rest_cut, 64);
+    const long long rest_waves = Ly.total_words * REST_PARTS * 8;
     hipLaunchKernelGGL(k_seg_rest, dim3((unsigned)std::min<long long>(4ll * ctx->num_cu, (rest_waves + 3) / 4)),
                        dim3(64 * SEG_WAVES), lds_rest, ls, dP, dwst, (int)B, dlam, dci, dsmp, dDZ, dV, dE, dR, dsegflags,
-                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, todo, dcounter + 9, Ly.Lmax, lcap);
+                       (B == 1) ? ro.cand : nullptr, ro.gate, ro.gate_on, todo, dcounter + 9, Ly.Lmax, lcap, (long long)Ly.nmax * Ly.Lmax >= 16384);
   }
   if (t1) HIP_TRY(hipEventRecord(t1, ls));
   {

@@ -57,8 +57,8 @@ def _segment_ms(ctx, call):
 
 
 # the columns at left are outside the division-free range: their segments are
-# left as row or as column of the pair.  Parts of one, two and four segments,
-# then the graded ones, words partly and wholly left, a last word of one segment
+# left as row or as column of the pair.  Words partly and wholly left, a last word
+# of one segment, lists cut into eight, four and two pieces and not at all
 @pytest.mark.parametrize("m,left", [(2, 2), (65, 65), (200, 200), (300, 7), (300, 300), (400, 3), (400, 50), (449, 449)])
 def test_work_list_forms(ctx, m, left):
     from paper_2402_16712_amd import binding as B
