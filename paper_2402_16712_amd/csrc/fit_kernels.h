@@ -1443,6 +1443,65 @@ __device__ __forceinline__ bool tie_rows(const SegIO &s, LdJ ldj, LdK ldk, doubl
   return true;
 }
 
+// lanes (as a 64-bit mask) that keep the larger word of a bitonic stage over
+// E words per lane: element E lane + q, partner lane ^ ls
+template <int E>
+constexpr uint64_t keep_max_mask(int size, int ls) {
+  uint64_t m = 0;
+  for (int l = 0; l < 64; ++l) {
+    const bool up = ((E * l) & size) == 0, lower = (l & ls) == 0;
+    if (up != lower) m |= 1ull << l;
+  }
+  return m;
+}
+__device__ __forceinline__ uint32_t pick(uint64_t keep_max, uint32_t x, uint32_t o) {
+  return ((o < x) != __builtin_amdgcn_inverse_ballot_w64(keep_max)) ? o : x;
+}
+// compare-exchange of x with lane ^ ls (equal words are interchangeable)
+__device__ __forceinline__ uint32_t cmpx_lane(uint32_t x, int ls, uint64_t keep_max) {
+  if (ls >= 16) {
+    // the swap leaves the pair's lower word in p[0] and its upper one in p[1]
+    // on both lanes
+    const auto p = ls == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                            : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return ((p[1] < p[0]) != __builtin_amdgcn_inverse_ballot_w64(keep_max)) ? p[1] : p[0];
+  }
+  return pick(keep_max, x, xswap32(x, ls));
+}
+
+// Bitonic sort of 64 E words, element E lane + q, ascending.
+template <int E>
+__device__ __forceinline__ void wave_sort_u32(uint32_t (&x)[E]) {
+#pragma unroll
+  for (int size = 2; size <= 64 * E; size <<= 1) {
+#pragma unroll
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      if (stride < E) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) {
+          if (q & stride) continue;
+          const uint32_t a = x[q], b = x[q | stride];
+          if (size < E) {
+            const bool up = (q & size) == 0;
+            x[q] = up ? min(a, b) : max(a, b);
+            x[q | stride] = up ? max(a, b) : min(a, b);
+            continue;
+          }
+          const uint64_t down = keep_max_mask<E>(size, 0);   // lanes whose block descends
+          const bool sw = (b < a) != __builtin_amdgcn_inverse_ballot_w64(down);
+          x[q] = sw ? b : a;
+          x[q | stride] = sw ? a : b;
+        }
+      } else {
+        const int ls = stride / E;
+        const uint64_t km = keep_max_mask<E>(size, ls);
+#pragma unroll
+        for (int q = 0; q < E; ++q) x[q] = cmpx_lane(x[q], ls, km);
+      }
+    }
+  }
+}
+
 enum : int { FAST_HIT, FAST_ABOVE, FAST_UNSURE };
 
 // The first listed row, in (ratio, row) order, whose prefix weight reaches D
@@ -1512,6 +1571,19 @@ __device__ __forceinline__ int select_listed(const SegIO &s, FastScratch *fs, in
     if (nc <= 64) {
       const int myrow = lane < nc ? (int)cr[lane] : 0;
       const double a = sxj_at(s, myrow), r = gld(s.xk + myrow) / a, wa = fabs(a);
+      if (nc > 24 && __ballot(lane < nc && r != readlane_dbl(r, 0)) == 0) {
+        // equal ratios: sorted by row (87 x 657 of two values 1531 us by counting
+        // among up to 64 rows, now 877)
+        uint32_t x[1] = {lane < nc ? ((uint32_t)myrow << 6) | (uint32_t)lane : ~0u};
+        wave_sort_u32<1>(x);
+        const double ws = __shfl(wa, (int)(x[0] & 63u)), sum = wave_scan_dbl(lane < nc ? ws : 0.0);
+        if (__ballot(lane < nc && fabs(sum - D) <= tol)) return FAST_UNSURE;
+        const uint64_t at = __ballot(lane < nc && sum >= D);
+        if (at == 0) return FAST_UNSURE;
+        v = readlane_dbl(r, 0);
+        row = (int)((uint32_t)__builtin_amdgcn_readlane((int)x[0], __builtin_ctzll(at)) >> 6);
+        return FAST_HIT;
+      }
       double run = 0.0;
       for (int i = 0; i < nc; ++i) {
         const double ri = readlane_dbl(r, i), wi = readlane_dbl(wa, i);
@@ -1708,65 +1780,6 @@ struct PathScratch {
   double val[FAST_CAP];             // ratios in list order, then prefix weights in sorted order
   uint32_t list[FAST_CAP];          // rows in list order, then in sorted order
 };
-
-// lanes (as a 64-bit mask) that keep the larger word of a bitonic stage over
-// E words per lane: element E lane + q, partner lane ^ ls
-template <int E>
-constexpr uint64_t keep_max_mask(int size, int ls) {
-  uint64_t m = 0;
-  for (int l = 0; l < 64; ++l) {
-    const bool up = ((E * l) & size) == 0, lower = (l & ls) == 0;
-    if (up != lower) m |= 1ull << l;
-  }
-  return m;
-}
-__device__ __forceinline__ uint32_t pick(uint64_t keep_max, uint32_t x, uint32_t o) {
-  return ((o < x) != __builtin_amdgcn_inverse_ballot_w64(keep_max)) ? o : x;
-}
-// compare-exchange of x with lane ^ ls (equal words are interchangeable)
-__device__ __forceinline__ uint32_t cmpx_lane(uint32_t x, int ls, uint64_t keep_max) {
-  if (ls >= 16) {
-    // the swap leaves the pair's lower word in p[0] and its upper one in p[1]
-    // on both lanes
-    const auto p = ls == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
-                            : __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    return ((p[1] < p[0]) != __builtin_amdgcn_inverse_ballot_w64(keep_max)) ? p[1] : p[0];
-  }
-  return pick(keep_max, x, xswap32(x, ls));
-}
-
-// Bitonic sort of 64 E words, element E lane + q, ascending.
-template <int E>
-__device__ __forceinline__ void wave_sort_u32(uint32_t (&x)[E]) {
-#pragma unroll
-  for (int size = 2; size <= 64 * E; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      if (stride < E) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) {
-          if (q & stride) continue;
-          const uint32_t a = x[q], b = x[q | stride];
-          if (size < E) {
-            const bool up = (q & size) == 0;
-            x[q] = up ? min(a, b) : max(a, b);
-            x[q | stride] = up ? max(a, b) : min(a, b);
-            continue;
-          }
-          const uint64_t down = keep_max_mask<E>(size, 0);   // lanes whose block descends
-          const bool sw = (b < a) != __builtin_amdgcn_inverse_ballot_w64(down);
-          x[q] = sw ? b : a;
-          x[q | stride] = sw ? a : b;
-        }
-      } else {
-        const int ls = stride / E;
-        const uint64_t km = keep_max_mask<E>(size, ls);
-#pragma unroll
-        for (int q = 0; q < E; ++q) x[q] = cmpx_lane(x[q], ls, km);
-      }
-    }
-  }
-}
 
 // The listed rows in (ratio, row) order: ps->list the rows, ps->val the
 // inclusive prefix weights, 64 E entries (the last repeated past count).

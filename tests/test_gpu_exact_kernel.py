@@ -332,3 +332,25 @@ def test_one_magnitude_takes_as_long(ctx):
     a, b = (_segment_ms(ctx, lambda lam=lam: ctx.fit(Xd, lam)) for lam in (0.0, 0.05))
     print(f"  penalty 0 {1e3 * a:.1f} us, between {1e3 * b:.1f} us", flush=True)
     assert a < 2.0 * b
+
+
+# all rows of a bin of one ratio: ranked by counting up to 24 rows, sorted up to
+# 64, divided again above; weights that differ, that tie and that are mixed
+@pytest.mark.parametrize("n", [23, 24, 25, 26, 48, 50, 63, 64, 65, 100, 128, 130])
+def test_equal_ratios(ctx, n):
+    from paper_2402_16712_amd import binding as B
+    print(f"case equal ratios {n}", flush=True)
+    g = np.random.default_rng(n)
+    X = g.standard_normal((n, 8))
+    X[:, 1] = 0.5 * X[:, 0]
+    X[:, 2] = -4.0 * X[:, 0]
+    X[:, 3] = np.where(g.random(n) < 0.8, X[:, 0], 2.0 * X[:, 0])
+    X[:, 4] = np.sign(X[:, 4])
+    X[:, 5] = 3.0 * X[:, 4]
+    X[:, 6] = np.where(g.random(n) < 0.7, X[:, 4], -X[:, 4])
+    X = np.asfortranarray(X)
+    Xd, big = B.device_matrix(X), wl.max_column_mass(X)
+    for lam in (0.0, 1.0, 0.01 * big, 0.1 * big, 0.4 * big):
+        _path_equal(_host(ctx.fit_batch([(Xd, np.array([lam]))])[0]), O.fit_path(X, [lam]), (n, lam))
+    lams = big * 10.0 ** np.linspace(-3.0, -0.3, 7)
+    _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, "path"))
