@@ -130,7 +130,7 @@ int l1line_fit(l1line_ctx ctx, const double *X, int64_t n, int64_t m,
  * workspace in a fixed device array of L1LINE_NOALLOC_SCRATCH_MB MiB that the
  * library holds on every GPU it runs on until the process ends.  The call
  * allocates nothing (no hipMalloc / hipFree, no pinned staging: its metadata
- * travels as kernel arguments).  The workspace needs about 36 m^2 + 330 m
+ * travels as kernel arguments).  The workspace needs about 38 m^2 + 350 m
  * bytes plus a few KB (what is left of the array holds the row parts of the
  * sign sums), so m <= L1LINE_NOALLOC_MAX_M (n up to L1LINE_MAX_N).
  * Every call on one GPU, from any context, stream or thread, shares that

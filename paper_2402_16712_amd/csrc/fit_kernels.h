@@ -1275,7 +1275,7 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 // 2^-53).  For 65535 rows T takes 1024 adds a lane and a scan, D two more: 1040.
 // The bins add up to 512 weights in turn, a scan and two for the new D, at up to
 // eight levels, and the ranking 64: 4240 (select_listed).  A tie's rows take 1024
-// slots' totals and scans: 1040 (tie_rows), a sorted list 30 (fast_path).  So two
+// slots' totals and scans, and as many for what lies below it: 2080 (tie_rows), a sorted list 30 (fast_path).  So two
 // sides of a comparison are off by less than 2^13 u W_j together, and one whose
 // operands differ by more than tol = 2^-38 W_j (2^15 u W_j) has the exact
 // comparison's outcome; closer ones, a selected ratio equal to lo or hi (a row
@@ -1404,38 +1404,54 @@ __device__ __forceinline__ bool tied_ratio(const SegIO &s, const uint32_t *list,
 }
 
 // The targets D (counted from klo, on the lanes of pend) among the rows
-// between klo and khi when every one of their ratios rounds to K: the order is
-// then the rows' order.  One pass finds each target's 64-row slot, a look at
-// that slot its row.  false: another ratio lies there, or too close to call.
+// between klo and khi whose ratio rounds to K: their order is the rows' order.
+// One pass finds each target's 64-row slot, a look at that slot its row; where
+// ratios next to K lie below it a second one, from their weight on (standardised
+// two-valued columns: the exact kernel took 4 ms for one such segment of 1387 rows
+// at 40 penalties).  false: a target among those or above, or too close to call.
 template <class LdJ, class LdK>
 __device__ __forceinline__ bool tie_rows(const SegIO &s, LdJ ldj, LdK ldk, double K, double klo, double khi,
                                          uint64_t pend, double D, double tol, int &row) {
   const bool mine = ((pend >> s.lane) & 1ull) != 0;
-  auto weight = [&](double a, double b, bool &bad) {
+  double under = 0.0;
+  auto weight = [&](double a, double b) {
     const bool in = ((hi32(fma(-klo, a, b)) ^ hi32(fma(-khi, a, b))) >> 31) != 0;
-    bad = bad || (in && b / a != K);
-    return in ? fabs(a) : 0.0;
+    const double r = b / a;
+    under = under + (in && r < K ? fabs(a) : 0.0);
+    return in && r == K ? fabs(a) : 0.0;
   };
-  double run = 0.0, base = 0.0;
-  int t = 0, slot = -1;
-  bool bad = false;
-  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
-    const double w = weight(a, b, bad);
-    if (__ballot(w != 0.0)) {
-      const double to = run + wave_total_dbl(w);
-      const bool here = mine && D > run && D <= to;
-      slot = here ? t : slot;
-      base = here ? run : base;
-      bad = bad || (mine && fabs(to - D) <= tol);
-      run = to;
+  double base = 0.0;
+  int slot = -1;
+  for (int pass = 0; pass < 2; ++pass) {
+    double run = 0.0;
+    int t = 0;
+    bool bad = false;
+    under = 0.0;
+    for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
+      const double w = weight(a, b);
+      if (__ballot(w != 0.0)) {
+        const double to = run + wave_total_dbl(w);
+        const bool here = mine && D > run && D <= to;
+        slot = here ? t : slot;
+        base = here ? run : base;
+        bad = bad || (mine && fabs(to - D) <= tol);
+        run = to;
+      }
+      ++t;
+    });
+    const double below = pass == 0 ? wave_total_dbl(under) : 0.0;
+    if (!(below > 0.0)) {
+      if (__ballot(bad || (mine && slot < 0))) return false;
+      break;
     }
-    ++t;
-  });
-  if (__ballot(bad || (mine && slot < 0))) return false;
+    D = D - below;
+    if (__ballot(mine && D <= tol)) return false;
+    slot = -1;
+  }
   for (; pend; pend &= pend - 1) {
     const int l = __builtin_ctzll(pend), ts = __builtin_amdgcn_readlane(slot, l);
     const double d = readlane_dbl(D, l) - readlane_dbl(base, l);
-    const double w = weight(ldj(s.lane + 64 * ts), ldk(s.lane + 64 * ts), bad), incl = wave_scan_dbl(w);
+    const double w = weight(ldj(s.lane + 64 * ts), ldk(s.lane + 64 * ts)), incl = wave_scan_dbl(w);
     const uint64_t m = __ballot(w != 0.0 && incl >= d);
     if (m == 0 || __ballot(w != 0.0 && fabs(incl - d) <= tol)) return false;
     if (s.lane == l) row = 64 * ts + __builtin_ctzll(m);
@@ -1774,7 +1790,7 @@ __device__ __forceinline__ bool fast_one(const SegIO &s, LdJ ldj, LdK ldk, bool 
 // stage.  Neighbours in the sorted order are then checked against their exact
 // ratios and rows; where they are out of order (equal ratios, or different ones
 // that share a word) the rows are sorted again by further words.
-// 2000 x 2000 with 64 penalties 52.2 -> 22.5 ms, 128 uneven matrices with 16
+// 2000 x 2000 with 64 penalties 52.2 -> 23.1 ms, 128 uneven matrices with 16
 // 100 -> 40.
 struct PathScratch {
   double val[FAST_CAP];             // ratios in list order, then prefix weights in sorted order
@@ -2088,8 +2104,8 @@ __device__ __forceinline__ void run_all_jobs(const SegIO &s, LdJ ldj, LdK ldk, u
 
 // ------------------------------------------------- segments left to the end
 // One segment by one wave with exact 128-bit sums and the general rounds:
-// what the division-free kernels leave (columns outside their range, sums too
-// close to call, ties, windows that missed).  Any number of penalties.
+// what the division-free kernels leave (pairs outside their range, sums too
+// close to call, windows that missed).  Any number of penalties.
 //  1. the sign sums dz decide the side of every penalty, the exact pass
 //     where they cannot;
 //  2. a key window from the row sample is listed with the exact weight below
@@ -2644,8 +2660,8 @@ struct LiveSegs {
 // copy (sxj_rows rows), else it is read from global memory (it stays in L2
 // across the item's k).  gate (optional): the kernel does nothing unless
 // *gate == gate_on.
-// Bound by VALU issue: about 1200 instructions per live segment of 2000 rows,
-// 0.71 of the issue slots (2600 and 0.89 with a guarded window test, IEEE
+// Bound by VALU issue: about 1150 instructions per live segment of 2000 rows,
+// 0.68 of the issue slots (2600 and 0.89 with a guarded window test, IEEE
 // divisions and 64-bit sorts).  Four waves per SIMD: with five or six the
 // registers spill or gain nothing (3.9 to 4.6 ms).  2000 x 2000 6.25 -> 3.57
 // ms; 10000 x 4000 49.0 -> 31.4 ms, 32 of its columns 3.03 -> 0.85.
@@ -2743,9 +2759,11 @@ k_seg_fast(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__rest
 }
 
 // Several penalties per problem: every live segment, one wave per segment, a
-// penalty per lane in groups of 64.  Bound by VALU issue too: the window pass
-// and the sort once per segment, then a residual per distinct row (7 of 64
-// penalties on average at 2000 x 2000; up to eight per pass over the rows).
+// penalty per lane in groups of 64: the window pass and the sort once per segment,
+// then a residual per distinct row (7 of 64 penalties on average at 2000 x 2000; up
+// to eight per pass over the rows).  There, with 64 penalties, it takes 0.63 of the
+// VALU issue slots (8.9e9 instructions, 23.1 ms) and moves 75 GB, 25 of them
+// stores: a segment's results lie 8 m^2 bytes apart, each in a line of its own.
 template <bool kLdsJ>
 __global__ void __launch_bounds__(64 * SEG_WAVES_MAX) __attribute__((amdgpu_waves_per_eu(4)))
 k_seg_path(const ProbDesc *__restrict__ P, ItemQueue queue, const double *__restrict__ lam_all,

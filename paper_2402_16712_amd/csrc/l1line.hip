@@ -681,7 +681,7 @@ static int launch_seq(l1line_ctx ctx, hipStream_t ls, const BatchLayout &Ly, cha
   // column j goes to LDS up to SXJ_LDS_MAX rows (2000 x 2000: 3.85 ms, from L2
   // 6.24).  Four waves share it, or eight where that lets more waves share a
   // CU (at most 16, what the kernels' registers allow: path 2000 x 2000 x 64
-  // 24.9 -> 22.5 ms, the batch of up to 4000 rows 59 -> 40); without the copy
+  // 24.9 -> 22.5 ms when taken, the batch of up to 4000 rows 59 -> 40); without the copy
   // eight (20011 x 151 368 -> 314 us).
   const bool multi = Ly.Lmax > 1;
   const int sxj_rows = Ly.nmax <= SXJ_LDS_MAX ? Ly.nmax : 0;
