@@ -1275,7 +1275,7 @@ __device__ __forceinline__ ExactSides exact_sides(const SegIO &s) {
 // 2^-53).  For 65535 rows T takes 1024 adds a lane and a scan, D two more: 1040.
 // The bins add up to 512 weights in turn, a scan and two for the new D, at up to
 // eight levels, and the ranking 64: 4240 (select_listed).  A tie's rows take 1024
-// slots' totals and scans, and as many for what lies below it: 2080 (tie_rows), a sorted list 30 (fast_path).  So two
+// slots' totals and scans: 1040 (tie_rows), a sorted list 30 (fast_path).  So two
 // sides of a comparison are off by less than 2^13 u W_j together, and one whose
 // operands differ by more than tol = 2^-38 W_j (2^15 u W_j) has the exact
 // comparison's outcome; closer ones, a selected ratio equal to lo or hi (a row
@@ -1404,54 +1404,38 @@ __device__ __forceinline__ bool tied_ratio(const SegIO &s, const uint32_t *list,
 }
 
 // The targets D (counted from klo, on the lanes of pend) among the rows
-// between klo and khi whose ratio rounds to K: their order is the rows' order.
-// One pass finds each target's 64-row slot, a look at that slot its row; where
-// ratios next to K lie below it a second one, from their weight on (standardised
-// two-valued columns: the exact kernel took 4 ms for one such segment of 1387 rows
-// at 40 penalties).  false: a target among those or above, or too close to call.
+// between klo and khi when every one of their ratios rounds to K: the order is
+// then the rows' order.  One pass finds each target's 64-row slot, a look at
+// that slot its row.  false: another ratio lies there, or too close to call.
 template <class LdJ, class LdK>
 __device__ __forceinline__ bool tie_rows(const SegIO &s, LdJ ldj, LdK ldk, double K, double klo, double khi,
                                          uint64_t pend, double D, double tol, int &row) {
   const bool mine = ((pend >> s.lane) & 1ull) != 0;
-  double under = 0.0;
-  auto weight = [&](double a, double b) {
+  auto weight = [&](double a, double b, bool &bad) {
     const bool in = ((hi32(fma(-klo, a, b)) ^ hi32(fma(-khi, a, b))) >> 31) != 0;
-    const double r = b / a;
-    under = under + (in && r < K ? fabs(a) : 0.0);
-    return in && r == K ? fabs(a) : 0.0;
+    bad = bad || (in && b / a != K);
+    return in ? fabs(a) : 0.0;
   };
-  double base = 0.0;
-  int slot = -1;
-  for (int pass = 0; pass < 2; ++pass) {
-    double run = 0.0;
-    int t = 0;
-    bool bad = false;
-    under = 0.0;
-    for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
-      const double w = weight(a, b);
-      if (__ballot(w != 0.0)) {
-        const double to = run + wave_total_dbl(w);
-        const bool here = mine && D > run && D <= to;
-        slot = here ? t : slot;
-        base = here ? run : base;
-        bad = bad || (mine && fabs(to - D) <= tol);
-        run = to;
-      }
-      ++t;
-    });
-    const double below = pass == 0 ? wave_total_dbl(under) : 0.0;
-    if (!(below > 0.0)) {
-      if (__ballot(bad || (mine && slot < 0))) return false;
-      break;
+  double run = 0.0, base = 0.0;
+  int t = 0, slot = -1;
+  bool bad = false;
+  for_row_pairs<4>(s, ldj, ldk, 0, s.T, [&](double a, double b) {
+    const double w = weight(a, b, bad);
+    if (__ballot(w != 0.0)) {
+      const double to = run + wave_total_dbl(w);
+      const bool here = mine && D > run && D <= to;
+      slot = here ? t : slot;
+      base = here ? run : base;
+      bad = bad || (mine && fabs(to - D) <= tol);
+      run = to;
     }
-    D = D - below;
-    if (__ballot(mine && D <= tol)) return false;
-    slot = -1;
-  }
+    ++t;
+  });
+  if (__ballot(bad || (mine && slot < 0))) return false;
   for (; pend; pend &= pend - 1) {
     const int l = __builtin_ctzll(pend), ts = __builtin_amdgcn_readlane(slot, l);
     const double d = readlane_dbl(D, l) - readlane_dbl(base, l);
-    const double w = weight(ldj(s.lane + 64 * ts), ldk(s.lane + 64 * ts)), incl = wave_scan_dbl(w);
+    const double w = weight(ldj(s.lane + 64 * ts), ldk(s.lane + 64 * ts), bad), incl = wave_scan_dbl(w);
     const uint64_t m = __ballot(w != 0.0 && incl >= d);
     if (m == 0 || __ballot(w != 0.0 && fabs(incl - d) <= tol)) return false;
     if (s.lane == l) row = 64 * ts + __builtin_ctzll(m);
