@@ -268,7 +268,7 @@ __device__ __forceinline__ void colprep_block(const double *__restrict__ x, int 
     c.zeros = n - nnz - nbad;
     c.flags = flags;
     c.bemin = nnz ? (int)((uint64_t)__double_as_longlong(amin) >> 52) : 4096;
-    c.bemax = nnz ? (int)((uint64_t)__double_as_longlong(amax) >> 52) : -1;
+    c.bemax = nbad ? 0x7ff : nnz ? (int)((uint64_t)__double_as_longlong(amax) >> 52) : -1;
     c.unit = flags ? 0.0 : column_unit(c.wfix, e0, nnz, amin, amax);
     *out = c;
   }
@@ -1035,9 +1035,10 @@ struct FastRange {
   __device__ __forceinline__ FastRange(const ColInfo &cj, bool ok) {
     ok = ok && (cj.nnz == 0 || (cj.bemin >= 1023 - FAST_COLUMN && cj.bemax <= 1023 + FAST_COLUMN));
     lo = ok ? max(1, cj.bemax - FAST_RATIO) : 1 << 20;
-    hi = cj.bemin + FAST_RATIO;
+    hi = min(cj.bemin + FAST_RATIO, 0x7fe);
   }
-  // (an empty column k: bemin 4096, bemax -1)
+  // (an empty column k: bemin 4096, bemax -1; one that is not finite: bemax 0x7ff,
+  // since a bound of its samples may be NaN, and padding rows would be listed)
   __device__ __forceinline__ bool has(const ColInfo &ck) const { return ck.bemin >= lo && ck.bemax <= hi; }
 };
 

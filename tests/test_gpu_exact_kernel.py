@@ -354,3 +354,34 @@ def test_equal_ratios(ctx, n):
         _path_equal(_host(ctx.fit_batch([(Xd, np.array([lam]))])[0]), O.fit_path(X, [lam]), (n, lam))
     lams = big * 10.0 ** np.linspace(-3.0, -0.3, 7)
     _path_equal(_host(ctx.fit_path(Xd, lams)), O.fit_path(X, lams), (n, "path"))
+
+
+# a column that is not finite: no route reads past the matrix (the padding below
+# each column, changed between two calls, changes nothing) or gives a row past it
+@pytest.mark.parametrize("n", [70, 130, 999, 4500])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_columns_not_finite(ctx, n, value):
+    import torch
+    print(f"case not finite {n} {value}", flush=True)
+    g = np.random.default_rng(n)
+    m, ld = 6, n + 320
+    X = np.outer(g.standard_normal(n), g.standard_normal(m)) + 0.3 * g.standard_normal((n, m))
+    X[:, 1] *= 2.0 ** 200
+    X[::2, m - 2] = value                  # half of the samples of every other column
+    X[int(np.argmax(np.abs(X[:, 0]))), m - 1] = value
+    outs = []
+    for fill in (0.0, 1.0, -1e30):
+        buf = torch.full((m, ld), fill, dtype=torch.float64, device="cuda:0")
+        buf[:, :n] = torch.from_numpy(np.ascontiguousarray(X.T)).cuda()
+        Xd = buf.t()[:n]
+        big = float(np.abs(X[:, 0]).sum())
+        lams = np.concatenate(([0.0], big * 10.0 ** np.linspace(-3.0, -0.1, 6)))
+        got = [_host(ctx.fit(Xd, lam)) for lam in lams] + [_host(ctx.fit_path(Xd, lams)), _host(ctx.breakpoints(Xd))]
+        for d in got:
+            assert int(d["status"].reshape(-1)[0]) != 0
+            for key in ("median_row", "ROW"):
+                if d.get(key) is not None:
+                    assert int(d[key].max(initial=-1)) < n, key
+        outs.append([{k: v.tobytes() for k, v in d.items() if v is not None and k in
+                      ("v", "j", "obj", "median_row", "z_all", "V", "J", "OBJ", "ROW", "ZALL", "offsets")} for d in got])
+    assert outs[0] == outs[1] == outs[2]
